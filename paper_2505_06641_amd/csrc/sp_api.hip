@@ -287,7 +287,7 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   s = (c->dtype == SP_BF16) ? upload_heads<uint16_t>(c, p) : upload_heads<float>(c, p);
   if (s != SP_OK) return s;
   if (c->H == 0 && c->dtype == SP_F32 && c->d <= 256) {
-    c->mfma_D = c->d <= 64 ? 64 : (c->d <= 128 ? 128 : 256);
+    c->mfma_D = std::max(64, (c->d + 31) / 32 * 32);
     if ((s = pack_mfma_blocks(c, p)) != SP_OK) return s;
   } else if (c->H > 0 && c->H <= kMlpH && c->dtype == SP_BF16 && (c->d % 8) == 0) {
     c->mlp_bf16 = true;
@@ -566,7 +566,11 @@ sp_status ensure_split_buffers(sp_ctx* c) {
 sp_status pack_mfma_blocks(sp_ctx* c, const sp_profile* p) {
   switch (c->mfma_D) {
     case 64: return pack_mfma_blocks_d<64>(c, p);
+    case 96: return pack_mfma_blocks_d<96>(c, p);
     case 128: return pack_mfma_blocks_d<128>(c, p);
+    case 160: return pack_mfma_blocks_d<160>(c, p);
+    case 192: return pack_mfma_blocks_d<192>(c, p);
+    case 224: return pack_mfma_blocks_d<224>(c, p);
     default: return pack_mfma_blocks_d<256>(c, p);
   }
 }
@@ -634,9 +638,15 @@ void launch_score(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, c
                            (const float*)x, ids, dw, sortkey, (const unsigned char*)c->blocks,                    \
                            (const int64_t*)c->block_off, (const float*)c->w_unscale, logits);                     \
     } while (0)
-    if (c->mfma_D == 64) SP_LAUNCH_MF(64);
-    else if (c->mfma_D == 128) SP_LAUNCH_MF(128);
-    else SP_LAUNCH_MF(256);
+    switch (c->mfma_D) {
+      case 64: SP_LAUNCH_MF(64); break;
+      case 96: SP_LAUNCH_MF(96); break;
+      case 128: SP_LAUNCH_MF(128); break;
+      case 160: SP_LAUNCH_MF(160); break;
+      case 192: SP_LAUNCH_MF(192); break;
+      case 224: SP_LAUNCH_MF(224); break;
+      default: SP_LAUNCH_MF(256); break;
+    }
 #undef SP_LAUNCH_MF
     return;
   }

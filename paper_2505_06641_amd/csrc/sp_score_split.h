@@ -67,12 +67,25 @@ struct SplitBlock {
   static constexpr int kBytes = kUnits * 16;
 };
 
-inline uint16_t host_f32_to_f16_bits(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }
+// Half-precision conversions on the host, rounding to nearest even, written out: without a target feature that the build
+// does not ask for the compiler calls a library routine for each, and a context converts every weight twice.
+inline uint16_t host_f32_to_f16_bits(float f) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, f), sign = (u >> 16) & 0x8000u, a = u & 0x7fffffffu;
+  if (a > 0x7f800000u) return (uint16_t)(sign | 0x7e00u);
+  if (a >= 0x47800000u) return (uint16_t)(sign | 0x7c00u);
+  if (a < 0x38800000u)                                    // below 2^-14: the adder rounds to multiples of 2^-24
+    return (uint16_t)(sign | (__builtin_bit_cast(uint32_t, __builtin_bit_cast(float, a) + 0.5f) - 0x3f000000u));
+  return (uint16_t)(sign | ((a - 0x38000000u + 0xfffu + ((a >> 13) & 1u)) >> 13));
+}
+inline float host_f16_bits_to_f32(uint16_t h) {
+  const uint32_t m = h & 0x7fffu;
+  const float v = m >= 0x7c00u ? (m == 0x7c00u ? HUGE_VALF : NAN) : m < 0x400u ? (float)m * 0x1p-24f : __builtin_bit_cast(float, (m << 13) + 0x38000000u);
+  return (h & 0x8000u) ? -v : v;
+}
 
 inline void host_split(float v, uint16_t& hi, uint16_t& lo) {
-  const _Float16 h = (_Float16)v;
-  hi = __builtin_bit_cast(uint16_t, h);
-  lo = __builtin_bit_cast(uint16_t, (_Float16)(v - (float)h));
+  hi = host_f32_to_f16_bits(v);
+  lo = host_f32_to_f16_bits(v - host_f16_bits_to_f32(hi));
 }
 
 // Power-of-two scale that brings |v| <= vmax into (-2^15, 2^15): returns the exponent ew (scale = 2^ew).
@@ -95,6 +108,16 @@ inline int split_k_index(int s, int g, int e) {
   return KMAP == kMapRows ? g * (D / 2) + 8 * s + e : 32 * (s / 2) + 8 * (2 * (s % 2) + e / 4) + 4 * g + e % 4;
 }
 
+// Features are read in pieces of 16 bytes (`per` of them); a piece that would pass the end of its row of d is read that
+// much further left, and one behind it repeats the row's last piece.  The weights say which of these inputs count: the
+// feature that slot k of the padded row holds, or -1 for one whose weight is zero.  (d >= per.)
+inline int row_slot_feature(int k, int d, int per) {
+  const int full = d / per * per;
+  if (k < full) return k;
+  const int f = d - per + k % per;
+  return (k / per == full / per && f >= full) ? f : -1;
+}
+
 // Host-side packing of one application's head (called at context creation).  Returns 2^-ew.
 template <int D, int KMAP>
 inline float pack_split_blocks(const float* W /*[d,C]*/, const float* b /*[C]*/, const float* acc /*[M,C]*/, int d,
@@ -112,8 +135,10 @@ inline float pack_split_blocks(const float* W /*[d,C]*/, const float* b /*[C]*/,
     for (int s = 0; s < D / 16; ++s)
       for (int lane = 0; lane < 64; ++lane)
         for (int e = 0; e < 8; ++e) {
-          const int k = split_k_index<D, KMAP>(s, lane / 32, e), cls = 32 * ct + lane % 32;
-          const float v = (k < d && cls < C) ? W[(size_t)k * C + cls] * ws : 0.f;
+          int k = split_k_index<D, KMAP>(s, lane / 32, e);
+          const int cls = 32 * ct + lane % 32;
+          if (KMAP == kMapRows && d >= 4) k = row_slot_feature(k, d, 4);
+          const float v = (k >= 0 && k < d && cls < C) ? W[(size_t)k * C + cls] * ws : 0.f;
           uint16_t hi, lo;
           host_split(v, hi, lo);
           wh[((size_t)(s * 2 + 0) * 64 + lane) * 8 + e] = hi;
@@ -271,22 +296,24 @@ __device__ __forceinline__ float other_half(float v, int g) {
 }
 
 // Softmax phase of one class tile (mostly vector ALU work): logits = acc * 2^-(ex+ew) + bias, online
-// softmax update, exponentials x table tile.
-template <int D, bool DUMP, bool SPLIT>
-__device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, float unscale, f32x4& ea_lo, f32x4& ea_hi,
-                                              float& ssum, float& m2, int ct, int C, int g, int lane, bool valid,
-                                              int64_t dump_row, float* __restrict__ logits_out, float& best_z,
-                                              int& best_c) {
-  using SB = SplitBlock<D>;
+// softmax update, exponentials x table tile.  tab, bias: the tile's table and bias units (layout: SplitBlock).
+// dump, split: constants, or uniform switches.
+// FINE: the exponent is formed without the scale of 2^14 that the exponentials are split at, which is then multiplied on.
+// An exponent near 0 has a smaller rounding error than one near 14 (3e-7 of the largest exponential); it costs one
+// instruction per logit, which kernels that the matrix or vector units bound do not spend.
+template <bool FINE = false>
+__device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bias, f32x16& acc, float unscale, f32x4& ea_lo,
+                                             f32x4& ea_hi, float& ssum, float& ssum_hi, float& m2, int ct, int C, int g, int lane, bool valid,
+                                             int64_t dump_row, float* __restrict__ logits_out, float& best_z, int& best_c,
+                                             const bool dump, const bool split) {
   // The other wavefront of this SIMD is, most of the time, streaming the MFMAs of its matrix phase and
   // always has the next one ready; without a higher priority the few MFMAs of this phase would wait
   // for that whole stream to end.
   __builtin_amdgcn_s_setprio(2);
   float4 bq[4];
   {
-    const float4* bp = blk + SB::kWUnits + SB::kTabUnits;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) bq[q] = bp[q * 2 + g];
+    for (int q = 0; q < 4; ++q) bq[q] = bias[q * 2 + g];
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -295,7 +322,7 @@ __device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, fl
     acc[4 * q + 2] = fmaf(acc[4 * q + 2], unscale, bq[q].z);
     acc[4 * q + 3] = fmaf(acc[4 * q + 3], unscale, bq[q].w);
   }
-  if (DUMP && valid) {
+  if (dump && valid) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int cls = 32 * ct + 8 * (v >> 2) + 4 * g + (v & 3);
@@ -306,7 +333,7 @@ __device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, fl
   float mt = acc[0];
 #pragma unroll
   for (int v = 1; v < 16; ++v) mt = fmaxf(mt, acc[v]);
-  if (SPLIT && __builtin_amdgcn_ballot_w64(mt > best_z) != 0ull) {
+  if (split && __builtin_amdgcn_ballot_w64(mt > best_z) != 0ull) {
     // subgroup label (Sec. 5.3.2): class of the largest logit seen by this lane so far; equal logits keep
     // the smallest class (v ascending is class ascending inside a lane)
     int vi = 15;
@@ -320,7 +347,7 @@ __device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, fl
   const float m2n = fmaxf(m2, mt * kLog2e);
   const float scale = __builtin_amdgcn_exp2f(m2 - m2n);
   m2 = m2n;
-  const float shift = kExpShift - m2n;
+  const float shift = FINE ? -m2n : kExpShift - m2n;
   // Exponentials x accuracy-table tile on 16x16x32 MFMAs (16 variants x 16 requests x 32 classes each):
   // ea_lo of lane (row q = lane/16, j = lane%16) holds variants 4q..4q+3 of request j, ea_hi those of
   // request 16 + j.  A lane's own request is lane%32, so in the odd rows ea_lo belongs to the neighbouring
@@ -336,6 +363,10 @@ __device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, fl
       ea_lo[v] *= sc_lo;
       ea_hi[v] *= sc_hi;
     }
+    if (FINE) {
+      ssum *= sc_lo;
+      ssum_hi *= sc_hi;
+    }
   }
   // the softmax denominator of this lane's 16 classes is a plain sum (two chains)
   float s0 = 0.f, s1 = 0.f;
@@ -344,17 +375,30 @@ __device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, fl
   for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
-      const float p0 = __builtin_amdgcn_exp2f(fmaf(acc[8 * ks + e], kLog2e, shift));       // in (0, 2^14]
-      const float p1 = __builtin_amdgcn_exp2f(fmaf(acc[8 * ks + e + 1], kLog2e, shift));
-      s0 += p0;
-      s1 += p1;
+      float p0 = __builtin_amdgcn_exp2f(fmaf(acc[8 * ks + e], kLog2e, shift));             // in (0, 2^14]
+      float p1 = __builtin_amdgcn_exp2f(fmaf(acc[8 * ks + e + 1], kLog2e, shift));
+      if (FINE) {
+        p0 *= 16384.0f;
+        p1 *= 16384.0f;
+      }
       f16x2 hi, lo;
-      split_f16x2(p0, p1, hi, lo);
+      if (FINE) {
+        constexpr float kGrid = 201326592.0f;               // 1.5 * 2^27: adding it rounds to a multiple of 16
+        const f32x2 vh = {(p0 + kGrid) - kGrid, (p1 + kGrid) - kGrid}, vl = {p0 - vh[0], p1 - vh[1]};
+        hi = __builtin_convertvector(vh, f16x2);
+        lo = __builtin_convertvector(vl, f16x2);
+      } else {
+        split_f16x2(p0, p1, hi, lo);
+      }
+      if (!FINE) {
+        s0 += p0;
+        s1 += p1;
+      }
       ph[ks][e] = hi[0]; ph[ks][e + 1] = hi[1];
       pl[ks][e] = lo[0]; pl[ks][e + 1] = lo[1];
     }
   }
-  ssum = fmaf(ssum, scale, s0 + s1);
+  if (!FINE) ssum = fmaf(ssum, scale, s0 + s1);
   // Row swap: a lane holds classes slice 0 (ph[0]) and slice 1 (ph[1]) of its own request.  Exchanging
   // slice 0 of the odd rows with slice 1 of the even rows leaves, in the first register set, requests
   // 0..15 with K slices (g, slice) = (0,0), (0,1), (1,0), (1,1) in rows 0..3, and in the second set the
@@ -375,9 +419,29 @@ __device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, fl
     bh_lo = __builtin_bit_cast(f16x8, a_h); bh_hi = __builtin_bit_cast(f16x8, b_h);
     bl_lo = __builtin_bit_cast(f16x8, a_l); bl_hi = __builtin_bit_cast(f16x8, b_l);
   }
-  const float4* tp = blk + SB::kWUnits + lane;
-  const f16x8 th = as_f16x8(tp[0]);
-  const f16x8 tl = as_f16x8(tp[64]);
+  const f16x8 th = as_f16x8(tab[lane]);
+  const f16x8 tl = as_f16x8(tab[lane + 64]);
+  if (FINE) {
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f16x8 one;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) one[e] = (_Float16)1.0f;
+    auto sum4 = [&](const f16x8& bh, const f16x8& bl, f32x4& ea, float& den) {
+      f32x4 t = __builtin_amdgcn_mfma_f32_16x16x32_f16(tl, bl, zero, 0, 0, 0);
+      f32x4 sl = __builtin_amdgcn_mfma_f32_16x16x32_f16(one, bl, zero, 0, 0, 0);
+      const f32x4 sh = __builtin_amdgcn_mfma_f32_16x16x32_f16(one, bh, zero, 0, 0, 0);
+      t = __builtin_amdgcn_mfma_f32_16x16x32_f16(tl, bh, t, 0, 0, 0);
+      const f32x4 u = __builtin_amdgcn_mfma_f32_16x16x32_f16(th, bh, zero, 0, 0, 0);
+      t = __builtin_amdgcn_mfma_f32_16x16x32_f16(th, bl, t, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ea[v] += u[v] + t[v];
+      den += sh[0] + sl[0];
+    };
+    sum4(bh_lo, bl_lo, ea_lo, ssum);
+    sum4(bh_hi, bl_hi, ea_hi, ssum_hi);
+    __builtin_amdgcn_s_setprio(0);
+    return;
+  }
   ea_lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(th, bh_lo, ea_lo, 0, 0, 0);
   ea_hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(th, bh_hi, ea_hi, 0, 0, 0);
   ea_lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(tl, bh_lo, ea_lo, 0, 0, 0);
@@ -386,18 +450,39 @@ __device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, fl
   ea_hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(th, bl_hi, ea_hi, 0, 0, 0);
   __builtin_amdgcn_s_setprio(0);
 }
+template <int D, bool DUMP, bool SPLIT>
+__device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, float unscale, f32x4& ea_lo, f32x4& ea_hi,
+                                              float& ssum, float& m2, int ct, int C, int g, int lane, bool valid,
+                                              int64_t dump_row, float* __restrict__ logits_out, float& best_z,
+                                              int& best_c) {
+  using SB = SplitBlock<D>;
+  softmax_tile(blk + SB::kWUnits, blk + SB::kWUnits + SB::kTabUnits, acc, unscale, ea_lo, ea_hi, ssum, ssum, m2, ct, C, g, lane, valid,
+               dump_row, logits_out, best_z, best_c, DUMP, SPLIT);
+}
 
 // After the last class tile: expected accuracies (eq. (9), with the prior's affine map), variance and key
 // (eq. (12)), the subgroup label, and the request's entries of the grouped arrays.
-template <bool SPLIT>
-__device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w, const f32x16& eacc, float m2,
-                                               float best_z, int best_c, int a, int M, int pos, int id, bool valid,
-                                               int r, int g, const float2* __restrict__ dw_g,
-                                               uint32_t* __restrict__ sortkey) {
+__device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w, const f32x4& ea_lo, const f32x4& ea_hi,
+                                               float lane_sum, float m2, float best_z, int best_c, int a, int M, int pos,
+                                               int id, bool valid, int lane, const float2* __restrict__ dw_g,
+                                               uint32_t* __restrict__ sortkey, const bool split) {
+  const int r = lane & 31, g = lane >> 5;
+  // Back to one request per lane pair for the epilogue: lane (r, g) takes variants 4g..4g+3 from row g and
+  // 8+4g..8+4g+3 from row 2+g, column r%16, out of ea_lo (r < 16) or ea_hi.
+  float eacc[8];
+  {
+    const int src_a = 16 * g + (r & 15), src_b = 16 * (2 + g) + (r & 15);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float a_lo = __shfl(ea_lo[v], src_a), a_hi = __shfl(ea_hi[v], src_a);
+      const float b_lo = __shfl(ea_lo[v], src_b), b_hi = __shfl(ea_hi[v], src_b);
+      eacc[v] = r < 16 ? a_lo : a_hi;
+      eacc[4 + v] = r < 16 ? b_lo : b_hi;
+    }
+  }
   // eacc[v] of lane (r, g) is table row 8*(v/4) + 4*g + v%4 for request r:
-  // v 0..3 -> variants 4g..4g+3, v 4..7 -> variants 8+4g..8+4g+3, v = 8 at g = 0 -> the sum of exponentials
-  const float ssum = __shfl(eacc[8], r);
-  const float inv = 1.0f / ssum;
+  // v 0..3 -> variants 4g..4g+3, v 4..7 -> variants 8+4g..8+4g+3; the sum of exponentials spans both lane halves
+  const float inv = 1.0f / (lane_sum + other_half(lane_sum, g));
   // prior of Sec. 4.2 eq. (10)-(11) as an affine map of the expected accuracies (gain 1, bias 0 without one)
   const float gain = tb.ea_gain[a];
   const float* biasp = tb.ea_bias + a * tb.Mmax;
@@ -425,7 +510,7 @@ __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w
     const int m = 8 * (v >> 2) + 4 * g + (v & 3);
     if (m < tb.Mmax) rowo[m] = ea[v];
   }
-  if (SPLIT) {
+  if (split) {
     // the lane halves' candidates meet; the largest posterior is exp(z_max - reference) / sum
     const float oz = other_half(best_z, g);
     const int oc = __float_as_int(other_half(__int_as_float(best_c), g));
@@ -461,7 +546,7 @@ __device__ __forceinline__ void class_tiles_and_finish(
     float* __restrict__ logits_out) {
   using SB = SplitBlock<D>;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 31, g = lane >> 5;
+  const int g = lane >> 5;
   __syncthreads();
 
   float m2 = kNegBig;                                    // running maximum, in units of log2
@@ -524,28 +609,22 @@ __device__ __forceinline__ void class_tiles_and_finish(
   }
 #undef SP_TILE
   if (DUMP) return;
-  // Back to one request per lane pair for the epilogue: lane (r, g) takes variants 4g..4g+3 from row g and
-  // 8+4g..8+4g+3 from row 2+g, column r%16, out of ea_lo (r < 16) or ea_hi; entry 8 is the denominator.
-  f32x16 eacc;
-  {
-    const int src_a = 16 * g + (r & 15), src_b = 16 * (2 + g) + (r & 15);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const float a_lo = __shfl(ea_lo[v], src_a), a_hi = __shfl(ea_hi[v], src_a);
-      const float b_lo = __shfl(ea_lo[v], src_b), b_hi = __shfl(ea_hi[v], src_b);
-      eacc[v] = r < 16 ? a_lo : a_hi;
-      eacc[4 + v] = r < 16 ? b_lo : b_hi;
-    }
-    eacc[8] = ssum + other_half(ssum, g);
-#pragma unroll
-    for (int v = 9; v < 16; ++v) eacc[v] = 0.f;
-  }
-  score_epilogue<SPLIT>(tb, w, eacc, m2, best_z, best_c, a, M, pos, id, valid, r, g, dw_g, sortkey);
+  score_epilogue(tb, w, ea_lo, ea_hi, ssum, m2, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, SPLIT);
+}
+
+// Four consecutive features of a row of d >= 4 from feature k0 on (see row_slot_feature); rows of any width, so the piece
+// may lie at any multiple of four bytes.
+typedef f32x4 f32x4_dw __attribute__((aligned(4)));
+__device__ __forceinline__ f32x4 row_piece(const float* __restrict__ row, int k0, int d) {
+  const f32x4_dw* p = reinterpret_cast<const f32x4_dw*>(row + min(k0, d - 4));
+  // a streaming load, unless pieces straddle cache lines: the second half would have to be fetched again
+  if ((d & 3) == 0) return __builtin_nontemporal_load(p);
+  return *p;
 }
 
 // This lane's half of its request's features, k = g*D/2 + [0, D/2): the row scaled by a power of two into
 // (-2^15, 2^15) and split into half-precision hi and lo parts.  Returns the factor that undoes the scaling
-// of row and weights.  `scratch` is 8 x 66 units of LDS private to the wavefront.
+// of row and weights.  `scratch` is 8 x (D/4 + 2) units of LDS private to the wavefront.
 template <int D>
 __device__ __forceinline__ float load_split_features(const float* __restrict__ x, int id, int d, float4* scratch,
                                                      int lane, float w_unscale_a, f16x8 (&xh)[D / 16],
@@ -553,25 +632,26 @@ __device__ __forceinline__ float load_split_features(const float* __restrict__ x
   const int r = lane & 31, g = lane >> 5;
     float xr[D / 2];
     const float* row = x + (int64_t)id * d;
-    if (D == 256 && (d & 3) == 0) {
-      // Coalesced: the wavefront reads whole rows (one 16-byte piece per lane, 1 KB per instruction),
-      // parks eight rows at a time in the block buffers that are still idle, and every lane then
-      // picks its own half row out of LDS.  Row stride 66 and half offset 33 (in 16-byte units) keep
-      // both the writes and the reads free of bank conflicts.
-      // (scratch: this wavefront's own 8 x 66 units of an idle block buffer)
+    if (d >= 4) {
+      // Coalesced: an instruction reads whole rows (one 16-byte piece per lane: one row of more than 128 features, two or
+      // four narrower ones), eight rows at a time are parked in the block buffers that are still idle, and every lane then
+      // picks its own half row out of LDS.  Row stride D/4 + 2 and half offset D/8 + 1 (in 16-byte units) keep both the
+      // writes and the reads free of bank conflicts for every D: the strides are odd multiples of 8 banks, the halves 4 off.
+      // (scratch: this wavefront's own 8 rows of an idle block buffer)
       // rows of pass ps+1 are already in flight while pass ps goes through LDS
-      float4 rows[2][8];
-      auto fetch_rows = [&](int ps, float4 (&dst)[8]) {
+      constexpr int kRows = D <= 64 ? 4 : (D <= 128 ? 2 : 1), kLanes = 64 / kRows, kLoads = 8 / kRows;
+      constexpr int kStride = D / 4 + 2, kHalf = D / 8 + 1;
+      const int piece = lane % kLanes, sub = lane / kLanes;
+      const int at = piece < D / 8 ? piece : kHalf + piece - D / 8;
+      float4 rows[2][kLoads];
+      auto fetch_rows = [&](int ps, float4 (&dst)[kLoads]) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int rid = __shfl(id, 8 * ps + i);
-          dst[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int i = 0; i < kLoads; ++i) {
+          const int rid = __shfl(id, 8 * ps + kRows * i + sub);
           // feature rows are read once: a streaming load, so that they do not push the packed blocks,
           // which every workgroup of the die reads again, out of its L2
-          if (4 * lane < d) {
-            const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(x + (int64_t)rid * d + 4 * lane));
-            dst[i] = make_float4(v[0], v[1], v[2], v[3]);
-          }
+          const f32x4 v = row_piece(x + (int64_t)rid * d, 4 * piece, d);
+          dst[i] = make_float4(v[0], v[1], v[2], v[3]);
         }
       };
       fetch_rows(0, rows[0]);
@@ -579,10 +659,12 @@ __device__ __forceinline__ float load_split_features(const float* __restrict__ x
       for (int ps = 0; ps < 4; ++ps) {
         if (ps + 1 < 4) fetch_rows(ps + 1, rows[(ps + 1) & 1]);
         __builtin_amdgcn_sched_barrier(0);
+        if (piece < D / 4) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) scratch[i * 66 + g * 33 + r] = rows[ps & 1][i];
+          for (int i = 0; i < kLoads; ++i) scratch[(kRows * i + sub) * kStride + at] = rows[ps & 1][i];
+        }
         if ((r >> 3) == ps) {
-          const float4* mine = scratch + (r & 7) * 66 + g * 33;
+          const float4* mine = scratch + (r & 7) * kStride + g * kHalf;
 #pragma unroll
           for (int q = 0; q < D / 8; ++q) {
             const float4 v = mine[q];
@@ -590,14 +672,6 @@ __device__ __forceinline__ float load_split_features(const float* __restrict__ x
           }
         }
         __builtin_amdgcn_sched_barrier(0);
-      }
-    } else if ((d & 3) == 0) {                           // rows are 16-byte aligned: whole float4 in or out of range
-#pragma unroll
-      for (int q = 0; q < D / 8; ++q) {
-        const int k0 = g * (D / 2) + 4 * q;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (k0 < d) v = *reinterpret_cast<const float4*>(row + k0);
-        xr[4 * q + 0] = v.x; xr[4 * q + 1] = v.y; xr[4 * q + 2] = v.z; xr[4 * q + 3] = v.w;
       }
     } else {
 #pragma unroll
@@ -666,7 +740,8 @@ __global__ __launch_bounds__(kMfThreads) void k_score_logistic_split(
   stage_block_dma<D>(src, buf_a, wave, lane);
 
   f16x8 xh[D / 16], xl[D / 16];
-  float4* scratch = (wave < kMfWaves / 2 ? buf_b : buf_c) + (wave % (kMfWaves / 2)) * (8 * 66);
+  float4* scratch = (wave < kMfWaves / 2 ? buf_b : buf_c) + (wave % (kMfWaves / 2)) * (8 * (D / 4 + 2));
+  static_assert((kMfWaves / 2) * 8 * (D / 4 + 2) <= SB::kUnits, "four wavefronts' rows must fit in a block buffer");
   const float unscale = load_split_features<D>(x, id, d, scratch, lane, w_unscale[a], xh, xl);
   class_tiles_and_finish<D, DUMP, SPLIT>(tb, w, buf_a, buf_b, buf_c, src, xh, xl, unscale, a, CT, C, M, pos, id, valid, dw_g,
                                   sortkey, logits_out);

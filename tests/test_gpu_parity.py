@@ -980,3 +980,12 @@ def test_optional_outputs_short_log_and_calls_after_the_end(gpu):
     assert rc == binding.SP_DONE
     ctx.close()
     ref["close"]()
+
+
+@pytest.mark.parametrize("d", [1, 3, 4, 7, 8, 63, 90, 95, 97, 150, 161, 191, 194, 223, 225, 255])
+def test_logistic_rows_that_end_inside_a_piece(gpu, d):
+    """Every padded width of the logistic kernel that walks the classes (64 to 256 in steps of 32), rows whose last
+    16-byte piece is partial or whose start is not aligned, rows shorter than a piece."""
+    w = wl.tiny(seed=8100 + d, n=700, classes=(140, 33, 5), models=(3, 16, 1), max_batch=5, feat_dim=d,
+                deadline=(5.0, 80.0), fractions=(0.5, 0.3, 0.2))
+    full_parity(gpu, w, max_rounds=10)
