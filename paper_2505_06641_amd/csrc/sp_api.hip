@@ -16,6 +16,7 @@
 #include "sp_score_generic.h"
 #include "sp_score_split.h"
 #include "sp_score_mlp.h"
+#include "sp_score_stream.h"
 #include "sp_rounds_persist.h"
 #include "sp_sort.h"
 #include "sp_probe.h"
@@ -56,6 +57,8 @@ struct sp_ctx {
   bool mlp_bf16 = false;             // bf16 MLP heads run on the matrix-core MLP kernel
   unsigned char* w1p = nullptr;      // packed layer-1 slices for that kernel
   int64_t* w1_off = nullptr;         // [A] byte offsets
+  int stream_nb = 0;                 // > 0: heads run on the streaming matrix-core kernel with this many blocks of 32 rows
+  StreamHeads stream{};
   // all rounds of a chunk in one launch, when every (application, variant) pair fits on the device at once
   bool persist = false;
   bool persist_split = false;        // ... and also with the per-wavefront windows that subgroups need in LDS
@@ -226,6 +229,7 @@ sp_status upload_heads(sp_ctx* c, const sp_profile* p) {
 
 sp_status pack_mfma_blocks(sp_ctx* c, const sp_profile* p);
 sp_status pack_mlp_blocks(sp_ctx* c, const sp_profile* p);
+sp_status pack_stream(sp_ctx* c, const sp_profile* p);
 sp_status setup_persist(sp_ctx* c, const sp_profile* p);
 sp_status ensure_split_buffers(sp_ctx* c);
 int score_tile(const sp_ctx* c);
@@ -284,14 +288,21 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
     if ((s = dev_upload(c, &c->d_swap, bias)) != SP_OK) return s;      // no swap-in costs
     tb.swap = c->d_swap;
   }
-  s = (c->dtype == SP_BF16) ? upload_heads<uint16_t>(c, p) : upload_heads<float>(c, p);
-  if (s != SP_OK) return s;
-  if (c->H == 0 && c->dtype == SP_F32 && c->d <= 256) {
+  if (c->H == 0 && c->dtype == SP_F32 && c->d <= 256 && (c->Cmax > kStreamClasses || c->d < 8)) {
     c->mfma_D = std::max(64, (c->d + 31) / 32 * 32);
     if ((s = pack_mfma_blocks(c, p)) != SP_OK) return s;
-  } else if (c->H > 0 && c->H <= kMlpH && c->dtype == SP_BF16 && (c->d % 8) == 0) {
+  } else if (c->H > 128 && c->H <= kMlpH && c->dtype == SP_BF16 && (c->d % 8) == 0) {
     c->mlp_bf16 = true;
     if ((s = pack_mlp_blocks(c, p)) != SP_OK) return s;
+  } else if (c->H <= kMlpH && c->d >= 8) {
+    // blocks of 32 first-layer rows (hidden units, or classes) a wavefront holds at a time
+    const int rows = c->H > 0 ? c->H : c->Cmax;
+    c->stream_nb = rows <= 32 ? 1 : (rows <= 64 ? 2 : (rows <= 128 ? 4 : 8));
+    if ((s = pack_stream(c, p)) != SP_OK) return s;
+  } else {
+    // what is left (hidden layers wider than 256, rows of a few features): plain matrices for the generic kernel
+    s = (c->dtype == SP_BF16) ? upload_heads<uint16_t>(c, p) : upload_heads<float>(c, p);
+    if (s != SP_OK) return s;
   }
 
   // window buffers
@@ -418,6 +429,112 @@ sp_status pack_mlp_blocks(sp_ctx* c, const sp_profile* p) {
   return SP_OK;
 }
 
+
+// Stages of the streaming kernel: per group of classes (or once) the first layer's slices, then the group's table and
+// bias (logistic heads), or the class tiles' packed blocks (one hidden layer).
+template <typename T, int NB, bool MLP>
+sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
+  using SG = StreamStage<NB, MLP>;
+  using I = StreamIn<T>;
+  using SB = SplitBlock<32 * NB>;
+  constexpr int kTab = SplitBlock<32>::kTabUnits, kBias = SplitBlock<32>::kBiasUnits;
+  const int A = p->n_apps, d = p->feat_dim, H = p->hidden_dim, nkc = (d + I::kChunk - 1) / I::kChunk;
+  std::vector<int64_t> off(A);
+  size_t total = 0;
+  for (int a = 0; a < A; ++a) {
+    off[a] = (int64_t)(total * SG::kUnits * 16);
+    const size_t CT = (size_t)(p->n_classes[a] + kClassTile - 1) / kClassTile;
+    total += MLP ? nkc + CT : (CT + NB - 1) / NB * (size_t)(nkc + 1);
+  }
+  std::vector<unsigned char> host(total * SG::kUnits * 16, 0), blocks;
+  std::vector<float> b1((size_t)(MLP ? A * 32 * NB : 1), 0.f), un1(A, 1.f), un2(A, 1.f), w2f;
+  for (int a = 0; a < A; ++a) {
+    const int C = p->n_classes[a], O = MLP ? H : C, CT = (C + kClassTile - 1) / kClassTile;
+    const T* W1 = (const T*)p->W1[a];
+    float scale = 1.f;
+    if (I::kF32) {
+      float wmax = 0.f;
+      for (size_t i = 0; i < (size_t)d * O; ++i) wmax = std::max(wmax, std::fabs((float)W1[i]));
+      const int ew = host_scale_exponent(wmax);
+      scale = std::ldexp(1.0f, ew);
+      un1[a] = std::ldexp(1.0f, -ew);
+    }
+    unsigned char* at = host.data() + off[a];
+    if constexpr (MLP) {
+      for (int kc = 0; kc < nkc; ++kc, at += (size_t)SG::kUnits * 16)
+        pack_stream_slice<T, NB>(W1, d, O, kc, 0, scale, reinterpret_cast<uint16_t*>(at));
+      std::memcpy(b1.data() + (size_t)a * 32 * NB, p->b1[a], (size_t)H * sizeof(float));
+      const float* w2 = (const float*)p->W2[a];
+      if (!I::kF32) {
+        w2f.resize((size_t)H * C);
+        for (size_t i = 0; i < w2f.size(); ++i) {
+          const uint32_t bits = (uint32_t)((const uint16_t*)p->W2[a])[i] << 16;
+          std::memcpy(&w2f[i], &bits, 4);
+        }
+        w2 = w2f.data();
+      }
+      blocks.resize((size_t)CT * SB::kBytes);
+      un2[a] = pack_split_blocks<32 * NB, kMapTile>(w2, p->b2[a], p->acc[a], H, C, p->n_models[a], blocks.data());
+      for (int ct = 0; ct < CT; ++ct, at += (size_t)SG::kUnits * 16) std::memcpy(at, blocks.data() + (size_t)ct * SB::kBytes, SB::kBytes);
+    } else {
+      // tables and biases in the layout of the class blocks: packed as blocks of a head without inputs
+      blocks.resize((size_t)CT * SplitBlock<32>::kBytes);
+      pack_split_blocks<32, kMapRows>(nullptr, p->b1[a], p->acc[a], 0, C, p->n_models[a], blocks.data());
+      for (int g0 = 0; g0 < CT; g0 += NB) {
+        for (int kc = 0; kc < nkc; ++kc, at += (size_t)SG::kUnits * 16)
+          pack_stream_slice<T, NB>(W1, d, O, kc, 32 * g0, scale, reinterpret_cast<uint16_t*>(at));
+        for (int hb = 0; hb < NB && g0 + hb < CT; ++hb) {
+          const unsigned char* from = blocks.data() + (size_t)(g0 + hb) * SplitBlock<32>::kBytes + (size_t)SplitBlock<32>::kWUnits * 16;
+          std::memcpy(at + (size_t)hb * kTab * 16, from, (size_t)kTab * 16);
+          std::memcpy(at + (size_t)(NB * kTab + hb * kBias) * 16, from + (size_t)kTab * 16, (size_t)kBias * 16);
+        }
+        at += (size_t)SG::kUnits * 16;
+      }
+    }
+  }
+  sp_status s;
+  unsigned char* d_st;
+  int64_t* d_off;
+  float *d_b1, *d_u1, *d_u2;
+  if ((s = dev_upload(c, &d_st, host)) != SP_OK) return s;
+  if ((s = dev_upload(c, &d_off, off)) != SP_OK) return s;
+  if ((s = dev_upload(c, &d_b1, b1)) != SP_OK) return s;
+  if ((s = dev_upload(c, &d_u1, un1)) != SP_OK) return s;
+  if ((s = dev_upload(c, &d_u2, un2)) != SP_OK) return s;
+  c->stream = StreamHeads{d_st, d_off, d_b1, d_u1, d_u2};
+  return SP_OK;
+}
+
+template <typename T, bool MLP>
+sp_status pack_stream_t(sp_ctx* c, const sp_profile* p) {
+  switch (c->stream_nb) {
+    case 1: return pack_stream_nb<T, 1, MLP>(c, p);
+    case 2: return pack_stream_nb<T, 2, MLP>(c, p);
+    case 4: return pack_stream_nb<T, 4, MLP>(c, p);
+    default: return pack_stream_nb<T, 8, MLP>(c, p);
+  }
+}
+
+sp_status pack_stream(sp_ctx* c, const sp_profile* p) {
+  if (c->dtype == SP_F32) return c->H > 0 ? pack_stream_t<float, true>(c, p) : pack_stream_t<float, false>(c, p);
+  return c->H > 0 ? pack_stream_t<uint16_t, true>(c, p) : pack_stream_t<uint16_t, false>(c, p);
+}
+
+template <typename T, bool MLP>
+void launch_score_stream(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, const float2* dw, uint32_t* sortkey,
+                         float* logits) {
+  const int tile = stream_tile(c->stream_nb);
+  const dim3 grid((unsigned)((c->n + tile - 1) / tile + c->A + kXcds)), blk(tile / 32 * kWave);   // see xcd_tile
+#define SP_LAUNCH_ST(NB) \
+  hipLaunchKernelGGL((k_score_stream<T, NB, MLP>), grid, blk, 0, s, c->tb, c->w, (const T*)x, ids, dw, sortkey, c->stream, logits)
+  switch (c->stream_nb) {
+    case 1: SP_LAUNCH_ST(1); break;
+    case 2: SP_LAUNCH_ST(2); break;
+    case 4: SP_LAUNCH_ST(4); break;
+    default: SP_LAUNCH_ST(8); break;
+  }
+#undef SP_LAUNCH_ST
+}
 
 // The one-launch rounds path needs every (application, variant) pair plus the commit workgroup resident at
 // once; contexts too large for that keep the two-kernels-per-round path.
@@ -587,7 +704,9 @@ void launch_score_generic(sp_ctx* c, hipStream_t s, int grid, const void* x, con
     hipLaunchKernelGGL((k_score_generic<T, 16>), dim3(grid), blk, c->score_lds, s, c->tb, c->w, (const T*)x, ids, dw, sortkey, logits);
 }
 
-int score_tile(const sp_ctx* c) { return (c->mfma_D > 0 || c->mlp_bf16) ? kMfTile : kScoreTile; }
+int score_tile(const sp_ctx* c) {
+  return (c->mfma_D > 0 || c->mlp_bf16) ? kMfTile : (c->stream_nb > 0 ? stream_tile(c->stream_nb) : kScoreTile);
+}
 
 // Address of the static scratch array on `device` (which must be current), looked up once per device.
 sp_status static_scratch_for(sp_ctx* c, int device, unsigned char** out) {
@@ -648,6 +767,16 @@ void launch_score(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, c
       default: SP_LAUNCH_MF(256); break;
     }
 #undef SP_LAUNCH_MF
+    return;
+  }
+  if (c->stream_nb > 0) {
+    if (c->dtype == SP_F32) {
+      if (c->H > 0) launch_score_stream<float, true>(c, s, x, ids, dw, sortkey, logits);
+      else launch_score_stream<float, false>(c, s, x, ids, dw, sortkey, logits);
+    } else {
+      if (c->H > 0) launch_score_stream<uint16_t, true>(c, s, x, ids, dw, sortkey, logits);
+      else launch_score_stream<uint16_t, false>(c, s, x, ids, dw, sortkey, logits);
+    }
     return;
   }
   const int grid = (c->n + kScoreTile - 1) / kScoreTile + c->A;

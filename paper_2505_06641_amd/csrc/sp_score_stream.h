@@ -1,0 +1,370 @@
+// Scoring kernel on the matrix cores for the heads that the two kernels with a fixed input width do not take:
+// logistic heads on bfloat16 features or on float32 features wider than 256, and one-hidden-layer heads (H <= 256)
+// on float32 features or on bfloat16 features that those kernels pad too much (Def. 4.1.1, 4.1.2; Sec. 4.1 eq. (9);
+// Sec. 5.1.1 eq. (12)).
+//
+// A wavefront owns 32 requests and keeps the whole transposed output tile of the first layer (32 NB rows: hidden
+// units, or classes) in NB float32 accumulators while it streams its requests' features from memory, kStBytes per
+// row and step; the matching weight slices, packed at context creation in the order the lanes read them, go through
+// two LDS buffers shared by the workgroup's four wavefronts.  Features never pass through LDS: the order of a slice's
+// channels is free as long as the weights are packed in the same one, so a lane takes 64 consecutive bytes of its
+// request's row.  A step costs memory more than matrix cores in all of these shapes, so features travel two steps ahead.
+//
+// bfloat16: products are exact, float32 accumulation.  float32: every operand is scaled by a power of two and split
+// into two half-precision numbers as in the logistic kernel (x.w = hi.hi + lo.hi + hi.lo).  A row's largest value is
+// not known before the row has been read, so the scale follows a running maximum: when a step brings a larger value,
+// the request's accumulators are rescaled by the exact power of two.
+//
+// Logistic heads then take the softmax and the table contraction straight from the accumulators; more than 32 NB
+// classes go in groups, each of which streams the rows again.  One-hidden-layer heads add bias, ReLU and split in
+// registers and walk the class tiles like the bfloat16 kernel; class blocks follow the slices through the same two
+// buffers.
+#pragma once
+#include "sp_common.h"
+#include "sp_score_split.h"
+#include "sp_score_mlp.h"
+
+namespace sp {
+
+// Wavefronts per workgroup: four, so that two or three workgroups share a CU and one's loads run beside another's
+// matrix work; eight where the accumulators leave two wavefronts per SIMD anyway (fewer units of a stage per thread).
+constexpr int stream_waves(int nb) { return nb == 8 ? 8 : 4; }
+constexpr int stream_tile(int nb) { return stream_waves(nb) * 32; }    // requests per workgroup
+// Logistic heads on up to 256 float32 features come here while no application has more classes than this: the scoring
+// kernel then takes 10-30% less time than the one that keeps a request's features in registers and walks the classes
+// (200,000 requests of 10 classes: 52 us against 65 with 256 features, 22 against 30 with 32; of 100 classes: 81 against
+// 93).  From 129 classes on it would hold eight blocks of rows and lose (130 classes: 110 us against 103, 52 against 50).
+constexpr int kStreamClasses = 128;
+constexpr int kStBytes = 128;                    // bytes of a feature row per step (one cache line)
+
+template <typename T>
+struct StreamIn {
+  static constexpr bool kF32 = sizeof(T) == 4;
+  static constexpr int kChunk = kStBytes / (int)sizeof(T);    // channels per step: 32 float32, 64 bfloat16
+  static constexpr int kSteps = kChunk / 16;                  // k-steps of 16 per slice
+  static constexpr int kParts = kF32 ? 2 : 1;                 // hi and lo, or the value itself
+};
+
+// What goes through the LDS buffers: a weight slice (256 NB units of 16 bytes), then per group of classes its table
+// and bias (logistic), or per class tile its packed block (one hidden layer).  All have one size, a multiple of the
+// workgroup, so that every stage is the same copy.
+template <int NB, bool MLP>
+struct StreamStage {
+  static constexpr int kThreads = stream_waves(NB) * kWave;
+  static constexpr int kSlice = 256 * NB;
+  static constexpr int kBlock = MLP ? SplitBlock<32 * NB>::kUnits : NB * (SplitBlock<32>::kTabUnits + SplitBlock<32>::kBiasUnits);
+  static constexpr int kMax = kSlice > kBlock ? kSlice : kBlock;
+  static constexpr int kPer = (kMax + kThreads - 1) / kThreads;    // units per thread
+  static constexpr int kUnits = kPer * kThreads;
+};
+
+// Channel (inside a slice) of lane half g, k-step s, element e: a lane's share of a row is contiguous.
+template <typename T>
+inline int stream_channel(int s, int g, int e) { return g * (StreamIn<T>::kChunk / 2) + 8 * s + e; }
+
+// One weight slice: unit ((hb * kSteps + s) * kParts + part) * 64 + lane, halves e = 0..7 hold (part of)
+// W[k = kChunk kc + channel(s, lane/32, e)][row0 + 32 hb + lane%32], zero beyond [d, O] (which input k is: row_slot_feature).
+template <typename T, int NB>
+inline void pack_stream_slice(const T* W /*[d, O]*/, int d, int O, int kc, int row0, float scale, uint16_t* out) {
+  using I = StreamIn<T>;
+  for (int hb = 0; hb < NB; ++hb)
+    for (int s = 0; s < I::kSteps; ++s)
+      for (int g = 0; g < 2; ++g)
+        for (int e = 0; e < 8; ++e) {
+          const int k = row_slot_feature(I::kChunk * kc + stream_channel<T>(s, g, e), d, 16 / (int)sizeof(T)), o0 = row0 + 32 * hb;
+          uint16_t* at = out + ((size_t)((hb * I::kSteps + s) * I::kParts) * 64 + 32 * g) * 8 + e;
+          const T* from = W + (size_t)std::max(k, 0) * O + o0;
+          for (int r = 0; r < 32 && k >= 0 && o0 + r < O; ++r) {      // (the buffer is zero to begin with)
+            if constexpr (I::kF32) host_split((float)from[r] * scale, at[r * 8], at[(64 + r) * 8]);
+            else at[r * 8] = (uint16_t)from[r];
+          }
+        }
+}
+
+struct StreamHeads {
+  const unsigned char* stages;    // per application: its stages, kUnits * 16 bytes each
+  const int64_t* off;             // [A] byte offsets
+  const float* b1;                // [A, 32 NB] first-layer bias of one-hidden-layer heads, padded with zeros
+  const float* unscale1;          // [A] undoes the first layer's weight scale (1 for bfloat16)
+  const float* unscale2;          // [A] undoes the second layer's
+};
+
+// 16 bytes of a feature row: rows start at any multiple of the element size
+typedef f32x4 f32x4_any __attribute__((aligned(2)));
+
+template <typename T, int NB, bool MLP>
+__global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
+    Tables tb, Window w, const T* __restrict__ x, const int32_t* __restrict__ ids, const float2* __restrict__ dw_g,
+    uint32_t* __restrict__ sortkey, StreamHeads hd, float* __restrict__ logits_out) {
+  using I = StreamIn<T>;
+  using SG = StreamStage<NB, MLP>;
+  constexpr int S = I::kSteps, CH = I::kChunk, D = 32 * NB;
+  __shared__ f32x4 buf[2][SG::kUnits];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 31, g = lane >> 5;
+  const int tile = xcd_tile(blockIdx.x, __builtin_amdgcn_readfirstlane(w.tile_start[tb.A]));
+  if (tile < 0) return;
+  const int4 desc = w.tile_desc[tile];
+  // (uniform, which the compiler cannot know of a load: tables and stages are then addressed from scalar registers)
+  const int a = __builtin_amdgcn_readfirstlane(desc.x), seg_e = __builtin_amdgcn_readfirstlane(desc.z);
+  const int pos = desc.y + wave * 32 + r;
+  const bool valid = pos < seg_e;
+  const int id = ids[valid ? pos : seg_e - 1];           // padding lanes recompute the last request, never store
+  const int d = tb.d, C = __builtin_amdgcn_readfirstlane(tb.n_classes[a]), M = __builtin_amdgcn_readfirstlane(tb.n_models[a]);
+  const int CT = (C + kClassTile - 1) / kClassTile;
+  const int nkc = (d + CH - 1) / CH;
+  const int n_groups = MLP ? 1 : (CT + NB - 1) / NB;
+  const int n_stages = MLP ? nkc + CT : n_groups * (nkc + 1);
+  const bool dump = logits_out != nullptr, split = tb.pol_split != 0;
+
+  // ---- stages: loaded into registers one ahead, stored into the idle buffer when the running one is done ----
+  const f32x4* src;
+  {
+    const int64_t o = hd.off[a];
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)o), hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)o >> 32));
+    src = reinterpret_cast<const f32x4*>(hd.stages + (int64_t)(((uint64_t)hi << 32) | lo));
+  }
+  f32x4 wst[SG::kPer];
+  auto fetch = [&](int st) {
+    const f32x4* p = src + (size_t)min(st, n_stages - 1) * SG::kUnits;
+#pragma unroll
+    for (int i = 0; i < SG::kPer; ++i) wst[i] = p[(uint32_t)(tid + i * SG::kThreads)];
+  };
+  auto park = [&](int st) {
+    f32x4* b = buf[st & 1] + tid;
+#pragma unroll
+    for (int i = 0; i < SG::kPer; ++i) b[i * SG::kThreads] = wst[i];
+  };
+
+  // ---- features: this lane's 64 bytes of a step ----
+  const unsigned char* row = reinterpret_cast<const unsigned char*>(x + (int64_t)id * d);
+  const int row_bytes = d * (int)sizeof(T);              // >= 16
+  auto load_x = [&](f32x4 (&xs)[4], int kc) {
+    const int at = kStBytes * kc + 64 * g;
+    if (kStBytes * (kc + 1) <= row_bytes) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (I::kF32) xs[q] = *reinterpret_cast<const f32x4_dw*>(row + at + 16 * q);
+        else xs[q] = *reinterpret_cast<const f32x4_any*>(row + at + 16 * q);
+      }
+    } else if (kc < nkc) {                               // the last, partial step (see row_slot_feature)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xs[q] = *reinterpret_cast<const f32x4_any*>(row + min(at + 16 * q, row_bytes - 16));
+    } else {                                             // past it
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xs[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+
+  float m2 = kNegBig, best_z = kNegBig, ssum = 0.f, ssum_hi = 0.f;
+  int best_c = 0x7fffffff;
+  f32x4 ea_lo = {0.f, 0.f, 0.f, 0.f}, ea_hi = {0.f, 0.f, 0.f, 0.f};
+  const int64_t dump_row = (int64_t)id * tb.Cmax;
+  f32x16 acc[NB];
+  int ex = 1000;                                         // float32: the row's running scale 2^ex (none yet)
+  bool infinite = false;                                 // float32: the row holds an infinity
+  const float un1 = I::kF32 ? hd.unscale1[a] : 1.f;
+
+  fetch(0);
+  park(0);
+  __syncthreads();
+
+  int st = 0;                                            // running stage
+  for (int grp = 0; grp < n_groups; ++grp) {
+    const int nbk = MLP ? NB : min(NB, CT - grp * NB);   // blocks of 32 rows that hold anything
+    f32x4 x0[4], x1[4];
+    int k0 = 0;
+    asm volatile("" : "+s"(k0));                         // (a zero that the compiler cannot see: it would keep every address of the
+    load_x(x0, k0);                                      // first steps in registers from one group to the next)
+    load_x(x1, k0 + 1);
+    ex = 1000;
+#pragma unroll
+    for (int hb = 0; hb < NB; ++hb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[hb][v] = 0.f;
+
+    // the running slice's weight fragments, kFrags per block of 32 rows, read one block ahead of the MFMAs that take
+    // them (not with eight blocks: the registers are needed for the accumulators)
+    constexpr int kFrags = S * I::kParts;
+    static_assert(kFrags == 4, "one block of a slice is four fragments for either type");
+    constexpr bool kAhead = NB < 8;
+    auto blocks = [&](auto mfmas) {
+      const f32x4* cur = buf[st & 1] + lane;
+      f32x4 wf[2][kFrags];
+      auto read = [&](int hb) {
+#pragma unroll
+        for (int i = 0; i < kFrags; ++i) wf[kAhead ? hb & 1 : 0][i] = cur[(hb * kFrags + i) * 64];
+      };
+      if (kAhead) read(0);
+#pragma unroll
+      for (int hb = 0; hb < NB; ++hb) {
+        if (!kAhead) read(hb);
+        else if (hb + 1 < NB) read(hb + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (hb < nbk) mfmas(hb, wf[kAhead ? hb & 1 : 0]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // one step: stage st + 1 and the features of step kc + 2 start, the MFMAs of step kc run, stage st + 1 is stored.
+    // The features of step kc are converted, or copied, first: that frees their registers for step kc + 2.
+    auto slice_f32 = [&](int kc, f32x4 (&xs)[4]) {
+      fetch(st + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      float amax = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) amax = fmaxf(amax, fabsf(xs[q][j]));
+      amax = fmaxf(amax, other_half(amax, g));
+      // amax = f 2^e with f in [0.5, 1): |x| 2^(15 - e) < 2^15; bounded so that scale and inverse stay normal numbers
+      const int e = (int)((__float_as_uint(amax) >> 23) & 0xffu) - 126;
+      const int want = min(max(kSplitExp - e, -113), 114);
+      infinite |= e > 128;
+      if (__builtin_amdgcn_ballot_w64(want < ex) != 0ull) {
+        // two bits of headroom, so that the maximum of a few more values rarely asks for another rescaling
+        const int nex = want < ex ? want - 2 : ex;
+        const float f = __builtin_amdgcn_ldexpf(1.0f, max(nex - ex, -1000));
+#pragma unroll
+        for (int hb = 0; hb < NB; ++hb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[hb][v] *= f;
+        ex = nex;
+      }
+      const float xsc = __builtin_amdgcn_ldexpf(1.0f, ex);
+      f16x8 xh[S], xl[S];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) {
+          f16x2 hi, lo;
+          split_f16x2(xs[q][j] * xsc, xs[q][j + 1] * xsc, hi, lo);
+          const int k = 4 * q + j;
+          xh[k >> 3][k & 7] = hi[0]; xh[k >> 3][(k & 7) + 1] = hi[1];
+          xl[k >> 3][k & 7] = lo[0]; xl[k >> 3][(k & 7) + 1] = lo[1];
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      load_x(xs, kc + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      blocks([&](int hb, const f32x4 (&wf)[kFrags]) {
+        f32x16 part;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[v] = 0.f;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const f16x8 wh = __builtin_bit_cast(f16x8, wf[(2 * s) % kFrags]), wl = __builtin_bit_cast(f16x8, wf[(2 * s + 1) % kFrags]);
+          part = __builtin_amdgcn_mfma_f32_32x32x16_f16(wl, xh[s], part, 0, 0, 0);
+          part = __builtin_amdgcn_mfma_f32_32x32x16_f16(wh, xl[s], part, 0, 0, 0);
+          part = __builtin_amdgcn_mfma_f32_32x32x16_f16(wh, xh[s], part, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[hb][v] += part[v];
+      });
+      park(st + 1);
+      __syncthreads();
+      ++st;
+    };
+    auto slice_bf16 = [&](int kc, f32x4 (&xs)[4]) {
+      fetch(st + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      bf16x8 xc[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xc[q] = as_bf16x8(xs[q]);
+      load_x(xs, kc + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      blocks([&](int hb, const f32x4 (&wf)[kFrags]) {
+        f32x16 part;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[v] = 0.f;
+#pragma unroll
+        for (int s = 0; s < kFrags; ++s)
+          part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(wf[s]), xc[s], part, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[hb][v] += part[v];
+      });
+      park(st + 1);
+      __syncthreads();
+      ++st;
+    };
+    for (int kc = k0;; kc += 2) {
+      if constexpr (I::kF32) slice_f32(kc, x0); else slice_bf16(kc, x0);
+      if (kc + 1 >= nkc) break;
+      if constexpr (I::kF32) slice_f32(kc + 1, x1); else slice_bf16(kc + 1, x1);
+      if (kc + 2 >= nkc) break;
+    }
+
+    const float un = I::kF32 ? __builtin_amdgcn_ldexpf(un1, -ex) : 1.f;
+    if constexpr (!MLP) {
+      // the group's table and bias are the running stage; the next group's first slice follows
+      const float4* tab = reinterpret_cast<const float4*>(buf[st & 1]);
+      fetch(st + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int hb = 0; hb < NB; ++hb) {
+        if (hb < nbk)
+          softmax_tile<true>(tab + hb * SplitBlock<32>::kTabUnits, tab + NB * SplitBlock<32>::kTabUnits + hb * SplitBlock<32>::kBiasUnits,
+                       acc[hb], un, ea_lo, ea_hi, ssum, ssum_hi, m2, grp * NB + hb, C, g, lane, valid, dump_row, logits_out, best_z, best_c,
+                       dump, split);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (grp + 1 < n_groups) {
+        park(st + 1);
+        __syncthreads();
+        ++st;
+      }
+    } else {
+      // bias, ReLU, per-request scale, split: acc[hb][v] of lane (r, g) is hidden unit 32 hb + 8 (v/4) + 4 g + v%4
+      const float4* b1p = reinterpret_cast<const float4*>(hd.b1 + (size_t)a * D);
+      float amax = 0.f;
+#pragma unroll
+      for (int hb = 0; hb < NB; ++hb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 bq = b1p[8 * hb + 2 * q + g];
+          const float bb[4] = {bq.x, bq.y, bq.z, bq.w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            acc[hb][4 * q + j] = fmaxf(fmaf(acc[hb][4 * q + j], un, bb[j]), 0.f);
+            amax = fmaxf(amax, acc[hb][4 * q + j]);
+          }
+        }
+      amax = fmaxf(amax, other_half(amax, g));
+      int hx = 0;
+      if (amax >= 1e-30f && amax <= 3e38f) hx = kSplitExp - (int)(((__float_as_uint(amax) >> 23) & 0xffu) - 126u);
+      const float hs = __uint_as_float((uint32_t)(127 + hx) << 23);
+      const float unscale = __uint_as_float((uint32_t)(127 - hx) << 23) * hd.unscale2[a];
+      f16x8 xh[D / 16], xl[D / 16];
+#pragma unroll
+      for (int hb = 0; hb < NB; ++hb)
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+          f16x2 hi, lo;
+          split_f16x2(acc[hb][v] * hs, acc[hb][v + 1] * hs, hi, lo);
+          xh[2 * hb + (v >> 3)][v & 7] = hi[0]; xh[2 * hb + (v >> 3)][(v & 7) + 1] = hi[1];
+          xl[2 * hb + (v >> 3)][v & 7] = lo[0]; xl[2 * hb + (v >> 3)][(v & 7) + 1] = lo[1];
+        }
+      for (int ct = 0; ct < CT; ++ct) {
+        const float4* blk = reinterpret_cast<const float4*>(buf[st & 1]);
+        if (ct + 1 < CT) fetch(st + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 z;
+        logits_phase<D>(blk, xh, xl, z, lane);
+        softmax_tile<true>(blk + SplitBlock<D>::kWUnits, blk + SplitBlock<D>::kWUnits + SplitBlock<D>::kTabUnits, z, unscale, ea_lo, ea_hi,
+                     ssum, ssum_hi, m2, ct, C, g, lane, valid, dump_row, logits_out, best_z, best_c, dump, split);
+        if (ct + 1 < CT) {
+          park(st + 1);
+          __syncthreads();
+        }
+        ++st;
+      }
+    }
+  }
+  if (dump) return;
+  // an infinite feature makes every expected accuracy NaN, as float32 arithmetic does (its halves would already be NaN
+  // in front of a ReLU, which turns them into zeros)
+  // (the denominators lie like the numerators and span both lane halves; the epilogue adds the halves' sums)
+  ssum = 0.5f * (r < 16 ? ssum : ssum_hi);
+  if (infinite) ssum = __builtin_nanf("");
+  score_epilogue(tb, w, ea_lo, ea_hi, ssum, m2, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, split);
+}
+
+}  // namespace sp

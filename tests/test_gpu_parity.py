@@ -989,3 +989,52 @@ def test_logistic_rows_that_end_inside_a_piece(gpu, d):
     w = wl.tiny(seed=8100 + d, n=700, classes=(140, 33, 5), models=(3, 16, 1), max_batch=5, feat_dim=d,
                 deadline=(5.0, 80.0), fractions=(0.5, 0.3, 0.2))
     full_parity(gpu, w, max_rounds=10)
+
+
+STREAM_SHAPES = [  # dtype, d, H, classes: rows held (1, 2, 4, 8 blocks of 32, at and next to their edges), steps of 32 or 64
+    (wl.F32, 8, 0, (32, 2)), (wl.F32, 9, 0, (33, 5)), (wl.F32, 257, 0, (64, 7)), (wl.F32, 300, 0, (65, 128)),
+    (wl.F32, 289, 0, (129, 300)), (wl.F32, 513, 0, (256, 257, 9)),
+    (wl.F32, 8, 1, (5, 40)), (wl.F32, 31, 32, (33, 3)), (wl.F32, 33, 33, (5, 64)), (wl.F32, 65, 64, (70, 2)),
+    (wl.F32, 128, 65, (10, 7, 2)), (wl.F32, 130, 128, (97, 4)), (wl.F32, 63, 129, (5, 9)), (wl.F32, 97, 256, (40, 3)),
+    (wl.BF16, 8, 0, (32, 2)), (wl.BF16, 9, 0, (33, 5)), (wl.BF16, 63, 0, (64, 7)), (wl.BF16, 65, 0, (128, 3)),
+    (wl.BF16, 129, 0, (129, 300)), (wl.BF16, 512, 0, (100, 31)),
+    (wl.BF16, 9, 5, (5, 40)), (wl.BF16, 64, 32, (33, 3)), (wl.BF16, 71, 64, (10, 70)), (wl.BF16, 200, 128, (100, 37)),
+    (wl.BF16, 127, 129, (9, 33)), (wl.BF16, 61, 255, (40, 3))]
+
+
+@pytest.mark.parametrize("shape", STREAM_SHAPES, ids=lambda s: f"{'bf16' if s[0] else 'f32'}-d{s[1]}-h{s[2]}-c{max(s[3])}")
+def test_heads_of_the_streaming_kernel(gpu, shape):
+    """The kernel that streams the features, at the edges of its tiles: one to nine steps with whole and partial last
+    steps, rows at any alignment, groups of classes, a workgroup with one request and one that is full."""
+    dtype, d, H, classes = shape
+    A = len(classes)
+    w = wl.tiny(seed=8200 + d + H, n=129 * A + 300, classes=classes, models=(3, 16, 1)[:A], max_batch=5, feat_dim=d, hidden_dim=H,
+                feat_dtype=dtype, deadline=(5.0, 80.0), fractions=(0.5, 0.3, 0.2)[:A] if A == 3 else (0.7, 0.3))
+    wl.attach_priors(w.profile, seed=8300 + d, kinds=(None, "weak"))
+    full_parity(gpu, w, max_rounds=10, ea_tol=2e-3 if dtype == wl.BF16 else None)
+
+
+@pytest.mark.parametrize("hidden", [0, 24])
+def test_streamed_rows_of_any_scale(gpu, hidden):
+    """float32 rows are scaled by a running maximum: rows whose large values come first, last, or not at all, rows of zeros,
+    and an infinity, which makes its own request's results NaN and no other's."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8400 + hidden, n=300, classes=(20, 6), models=(4, 3), feat_dim=300, hidden_dim=hidden)
+    x = w.requests.x
+    x[0::7] *= np.float32(1e-12)
+    x[1::7, 200:] *= np.float32(40.0)
+    x[2::7, :40] *= np.float32(30.0)
+    x[3::7] = 0.0
+    x[4::7] *= np.float32(1e-3)
+    x[4::7, 299] = 25.0
+    ref_ea, ref_key = orc.score_requests(w.profile, w.requests)
+    x[13, 150] = np.inf
+    ctx = binding.Context(w.profile, 300)
+    ea = torch.zeros((300, ctx.m_max), device="cuda:0")
+    ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
+    ea = ea.cpu().numpy()
+    ctx.close()
+    a = int(w.requests.app[13])
+    assert np.all(np.isnan(ea[13, :int(w.profile.n_models[a])]))
+    keep = np.arange(300) != 13
+    parity.assert_close("EA", ea[keep], ref_ea[keep], TOL)
