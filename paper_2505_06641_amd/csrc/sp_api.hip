@@ -35,12 +35,14 @@ struct sp_ctx {
   int64_t cap = 0;
   uint32_t* bufK[2] = {nullptr, nullptr};
   int32_t* bufV[3] = {nullptr, nullptr, nullptr};
-  // ordering: digit totals, per-tile published counts and tile descriptors of the radix passes
-  uint32_t* dtot_app = nullptr;      // [2 passes, 1 row, 256] pass(es) over the application ids (one segment)
+  // grouping: every tile's counts per application, or (more than 255 applications) the radix passes' digit totals and
+  // per-tile published counts
+  uint32_t* group_counts = nullptr;  // [tiles, 256]
+  uint32_t* dtot_app = nullptr;      // [2 passes, 1 row, 256] passes over the application ids (one segment)
   uint32_t* dtot_key = nullptr;      // [kMaxSortPasses, tiles_cap, 256] passes inside the applications' ranges
-  int64_t tiles_cap = 0;             // rows per pass slab of dtot_key, tiles of sort_state and sort_desc
+  int64_t tiles_cap = 0;             // rows per pass slab of dtot_key, tiles of sort_state
   unsigned long long* sort_state = nullptr;   // [tiles_cap, 256] generation-tagged words of the running pass
-  int4* sort_desc = nullptr;         // [tiles_cap]
+  int4* sort_desc = nullptr;         // descriptors of the runs that are sorted
   uint32_t sort_gen = 0;             // generations handed out so far
   int32_t* seg1 = nullptr;           // [2] the one-segment plan of the pass over the application ids
   float2* dw_g[2] = {nullptr, nullptr};   // [n] (deadline, weight) at each grouped position (two for two passes over the ids)
@@ -82,6 +84,7 @@ struct sp_ctx {
   int32_t* h_grp_n = nullptr;        // pinned [2]: number of groups of the scored window, most groups of one application
   hipEvent_t ev_groups = nullptr;    // recorded after the copy into h_grp_n
   int sub_passes = 0;                // 8-bit radix passes over the subgroup codes
+  uint32_t* bufL[2] = {nullptr, nullptr};   // subgroup codes in the order of the sort
   unsigned char* static_scratch = nullptr;   // this device's copy of the static scratch array (sp_greedy_round_static)
   std::string hip_err;
   // optional stage timing (benchmarks)
@@ -343,11 +346,16 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   if ((s = dev_alloc(c, &w.id_s, N)) != SP_OK) return s;
   if ((s = dev_alloc(c, &w.rec_g, N)) != SP_OK) return s;
   c->tiles_cap = (int64_t)(N / kSortTile) + A + 2;
+  {
+    int64_t rows = 1;                                    // the longest window of small tiles, or the capacity in large ones
+    for (const int64_t n : {std::min((int64_t)N, (int64_t)kGroupSmall), (int64_t)N}) rows = std::max(rows, (n + group_tile(n) - 1) / group_tile(n) + 1);
+    if ((s = dev_alloc(c, &c->group_counts, (size_t)rows * 256)) != SP_OK) return s;
+  }
   if ((s = dev_alloc(c, &c->dtot_app, 2 * 256)) != SP_OK) return s;
-  if ((s = dev_alloc(c, &c->dtot_key, (size_t)kMaxSortPasses * c->tiles_cap * 256)) != SP_OK) return s;
+  if (N > (size_t)kMergeMax && (s = dev_alloc(c, &c->dtot_key, (size_t)kMaxSortPasses * c->tiles_cap * 256)) != SP_OK) return s;
   if ((s = dev_alloc(c, &c->sort_state, (size_t)c->tiles_cap * 256)) != SP_OK) return s;
   SP_HIP(c, hipMemset(c->sort_state, 0, (size_t)c->tiles_cap * 256 * sizeof(unsigned long long)));
-  if ((s = dev_alloc(c, &c->sort_desc, (size_t)c->tiles_cap)) != SP_OK) return s;
+  if ((s = dev_alloc(c, &c->sort_desc, N / kRun + A + kXcds)) != SP_OK) return s;
   if ((s = dev_alloc(c, &c->seg1, 2)) != SP_OK) return s;
   for (int i = 0; i < (app_passes(A) > 1 ? 2 : 1); ++i)
     if ((s = dev_alloc(c, &c->dw_g[i], N)) != SP_OK) return s;
@@ -658,7 +666,8 @@ sp_status ensure_split_buffers(sp_ctx* c) {
   const size_t gcap = (size_t)std::max<int64_t>(A, std::min<int64_t>(slots, std::max<int64_t>(c->cap, 1)));
   Window& w = c->w;
   sp_status s;
-  if ((s = dev_alloc(c, &w.sub_g, (size_t)std::max<int64_t>(c->cap, 1))) != SP_OK) return s;
+  for (int i = 0; i < 2; ++i)
+    if ((s = dev_alloc(c, &c->bufL[i], (size_t)std::max<int64_t>(c->cap, 1))) != SP_OK) return s;
   if ((s = dev_upload(c, &c->slot_app, app_of)) != SP_OK) return s;
   if ((s = dev_upload(c, &c->slot_base, base)) != SP_OK) return s;
   if ((s = dev_alloc(c, &c->slot_beg, (size_t)slots)) != SP_OK) return s;
@@ -672,6 +681,7 @@ sp_status ensure_split_buffers(sp_ctx* c) {
   if ((s = dev_alloc(c, &w.cand_prio, gcap * c->Mmax)) != SP_OK) return s;
   if ((s = dev_alloc(c, &w.win_pos, gcap * c->B)) != SP_OK) return s;
   if ((s = dev_alloc(c, &w.win_n, gcap)) != SP_OK) return s;
+  if ((s = dev_alloc(c, &w.sub_g, (size_t)std::max<int64_t>(c->cap, 1))) != SP_OK) return s;
   w.gcap = (int32_t)gcap;
   SP_HIP(c, hipHostMalloc((void**)&c->h_grp_n, 2 * sizeof(int32_t), hipHostMallocDefault));
   c->h_grp_n[0] = A;
@@ -789,22 +799,149 @@ void launch_score(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, c
 // One stable radix pass over the tiles of `plan`; (keys, vals) -> (keys_out, vals_out).
 void radix_pass(sp_ctx* c, hipStream_t s, const SortPlan& plan, int tiles, const uint32_t* keys, const int32_t* vals,
                 int shift, int clamp_a, const uint32_t* dtot_pass, uint32_t* keys_out, int32_t* vals_out,
-                const SegArgs* fused_segments = nullptr, const SortCarry* carry = nullptr) {
+                const SortCarry* carry = nullptr) {
   if (c->sort_gen == 0xFFFFFFFFu) {                       // generation numbers about to wrap: start over
     hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)((c->tiles_cap * 256 + 255) / 256)), dim3(256), 0, s, c->sort_state,
                        (int64_t)c->tiles_cap * 256, 0ull);
     c->sort_gen = 0;
   }
   const uint32_t gen = ++c->sort_gen;
-  SegArgs sg{};                                            // seg == null: no segment bookkeeping in this launch
-  if (fused_segments) sg = *fused_segments;
   if (carry)
-    hipLaunchKernelGGL(k_radix_pass<true>, dim3(tiles + (fused_segments ? 1 : 0)), dim3(kSortThreads), 0, s, plan, keys, vals,
-                       shift, clamp_a, dtot_pass, c->sort_state, gen, c->sort_spin_limit, keys_out, vals_out, c->w.st, sg, c->w, *carry);
+    hipLaunchKernelGGL(k_radix_pass<true>, dim3(tiles), dim3(kSortThreads), 0, s, plan, keys, vals, shift, clamp_a, dtot_pass,
+                       c->sort_state, gen, c->sort_spin_limit, keys_out, vals_out, c->w.st, *carry);
   else
-    hipLaunchKernelGGL(k_radix_pass<false>, dim3(tiles + (fused_segments ? 1 : 0)), dim3(kSortThreads), 0, s, plan, keys, vals,
-                       shift, clamp_a, dtot_pass, c->sort_state, gen, c->sort_spin_limit, keys_out, vals_out, c->w.st, sg, c->w,
-                       SortCarry{});
+    hipLaunchKernelGGL(k_radix_pass<false>, dim3(tiles), dim3(kSortThreads), 0, s, plan, keys, vals, shift, clamp_a, dtot_pass,
+                       c->sort_state, gen, c->sort_spin_limit, keys_out, vals_out, c->w.st, SortCarry{});
+}
+
+// Requests grouped by application: ids, deadlines and weights at their grouped positions, segment starts, descriptors.
+// Returns the array that holds the ids.
+int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev, const float* deadline_ms_dev,
+                        const float* weight_dev) {
+  const int A = c->A;
+  Window& w = c->w;
+  SegArgs seg_args{n, A, nullptr, score_tile(c), n <= kMergeMax ? kRun : kSortTile, w.seg, w.tile_start, w.unit_start, w.tile_desc, c->sort_desc};
+  // a long window's ordering needs its digit totals cleared
+  uint32_t* zero = n > kMergeMax ? c->dtot_key : nullptr;
+  const int64_t zero_words = (int64_t)kMaxSortPasses * c->tiles_cap * 256;
+  // (a bound on the passes' look-back that a test has set asks for the passes that it bounds)
+  if (n > 0 && A <= kMaxGroupApps && c->sort_spin_limit == kSortSpinLimit) {
+    int nbits = 1;
+    while ((1 << nbits) <= A) ++nbits;
+    const int tile = group_tile(n), tiles = (n + tile - 1) / tile;
+#define SP_GROUP(ITEMS)                                                                                                 \
+    do {                                                                                                                \
+      hipLaunchKernelGGL(k_group_count<ITEMS>, dim3(tiles), dim3(kGroupThreads), 0, s, n, A, nbits, app_dev,            \
+                         c->group_counts, w.st, zero, zero_words);                                                      \
+      if (tiles > kGroupDirect)                                                                                         \
+        hipLaunchKernelGGL(k_group_scan, dim3(A + 1), dim3(1024), 0, s, c->group_counts, tiles);                        \
+      hipLaunchKernelGGL(k_group_place<ITEMS>, dim3((tiles + kXcds - 1) / kXcds * kXcds + 1), dim3(kGroupThreads), 0, s, n, A, nbits, app_dev, \
+                         deadline_ms_dev, weight_dev, (const uint32_t*)c->group_counts, tiles, c->bufV[0], c->dw_g[0],  \
+                         seg_args, w, w.st);                                                                            \
+    } while (0)
+    if (tile == 1024) SP_GROUP(2);
+    else SP_GROUP(4);
+#undef SP_GROUP
+    return c->bufV[0];
+  }
+  // stable passes over the application ids, read straight from the caller's array (ids outside [0, A) become A and raise
+  // the error flag); the segment starts then come from the sorted ids
+  hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(256), 0, s, w.st, n, c->seg1, c->dtot_app, 2 * 256);
+  uint32_t *curK = c->bufK[0], *altK = c->bufK[1];
+  int32_t *curV = c->bufV[0], *altV = c->bufV[1];
+  if (n > 0) {
+    const int n_app_passes = app_passes(A);
+    const int tiles = (n + kSortTile - 1) / kSortTile;
+    SortPlan whole{c->seg1, nullptr, 1, nullptr};
+    hipLaunchKernelGGL(k_digit_totals, dim3(tiles), dim3(kSortThreads), 0, s, whole, (const uint32_t*)app_dev, A, 0,
+                       n_app_passes, (int64_t)1, c->dtot_app, zero, zero_words, w.st);
+    const uint32_t* kin = (const uint32_t*)app_dev;
+    const int32_t* vin = nullptr;
+    for (int p = 0; p < n_app_passes; ++p) {
+      // every request's deadline and weight travel with it to its grouped position
+      const SortCarry cy = p == 0 ? SortCarry{deadline_ms_dev, weight_dev, nullptr, c->dw_g[n_app_passes - 1 - p]}
+                                  : SortCarry{nullptr, nullptr, c->dw_g[n_app_passes - p], c->dw_g[n_app_passes - 1 - p]};
+      radix_pass(c, s, whole, tiles, kin, vin, 8 * p, p == 0 ? A : 0, c->dtot_app + 256 * p, altK, altV, &cy);
+      std::swap(curK, altK);
+      std::swap(curV, altV);
+      kin = curK;
+      vin = curV;
+    }
+  }
+  seg_args.sorted_app = curK;
+  hipLaunchKernelGGL(k_segments, dim3(1), dim3(256), 0, s, seg_args, w);
+  if (curV != c->bufV[0]) std::swap(c->bufV[0], c->bufV[1]);
+  return c->bufV[0];
+}
+
+// Service order: inside each application by (key descending, id ascending), or with subgroups by (subgroup, key, id).  The
+// values that travel are positions of the grouped array, the grouped ids stay where they are.  Returns the subgroup codes
+// in service order (with subgroups).
+const uint32_t* order_requests(sp_ctx* c, hipStream_t s, int n, uint32_t* sortkey, uint32_t* spare_key) {
+  const int A = c->A, edf = c->tb.pol_edf | c->tb.pol_split;
+  const bool split = c->tb.pol_split != 0;
+  Window& w = c->w;
+  SortPlan plan{w.seg, w.unit_start, A, c->sort_desc};
+  auto stage_event = [&] { if (c->timing && c->timing_stages) (void)hipEventRecord(c->ev[6], s); };
+  if (n > kMergeMax) {
+    const int tiles = n / kSortTile + A;                      // upper bound on the tiles inside the applications' ranges
+    const int64_t slab = c->tiles_cap * 256;
+    uint32_t *k_in = sortkey, *k_out = spare_key;
+    const int32_t* v_in = nullptr;                            // the identity: positions of the grouped array
+    int32_t *v_out = c->bufV[1], *v_spare = c->bufV[2];
+    auto pass = [&](int shift, const uint32_t* totals) {
+      radix_pass(c, s, plan, tiles, k_in, v_in, shift, 0, totals, k_out, v_out);
+      std::swap(k_in, k_out);
+      v_in = v_out;
+      std::swap(v_out, v_spare);
+    };
+    auto totals = [&](int n_pass, uint32_t* at) {
+      hipLaunchKernelGGL(k_digit_totals, dim3(tiles), dim3(kSortThreads), 0, s, plan, (const uint32_t*)k_in, 0, 0, n_pass, c->tiles_cap,
+                         at, (uint32_t*)nullptr, (int64_t)0, w.st);
+    };
+    totals(4, c->dtot_key);
+    for (int p = 0; p < 4; ++p) pass(8 * p, c->dtot_key + slab * p);
+    if (split) {
+      // further stable passes over the subgroup codes make the order (subgroup, key)
+      hipLaunchKernelGGL(k_gather_sub_keys, dim3((n + 255) / 256), dim3(256), 0, s, A, (const int32_t*)w.seg, v_in, (const int32_t*)w.sub_g, k_in,
+                         (const State*)w.st);
+      totals(c->sub_passes, c->dtot_key + slab * 4);
+      for (int p = 0; p < c->sub_passes; ++p) pass(8 * p, c->dtot_key + slab * (4 + p));
+    }
+    stage_event();
+    hipLaunchKernelGGL(k_finish_order, dim3((n + kRunThreads - 1) / kRunThreads), dim3(kRunThreads), 0, s, n, A, (const int32_t*)w.seg, v_in,
+                       (const uint32_t*)k_in, w, edf);
+    return k_in;
+  }
+  const int grid = (n / kRun + A + kXcds - 1) / kXcds * kXcds;
+  int levels, ways;
+  merge_plan(n, levels, ways);
+  SortedRun from{sortkey, c->bufV[2], c->bufL[1]}, to{spare_key, c->bufV[1], c->bufL[0]};
+#define SP_RUNS(SPLIT, LAST)                                                                                     \
+  hipLaunchKernelGGL((k_sort_runs<SPLIT, LAST>), dim3(grid), dim3(kRunThreads), 0, s, plan, from, to,            \
+                     (const int32_t*)w.sub_g, c->sub_passes, n, w, edf)
+#define SP_MERGE(SPLIT, LAST)                                                                                    \
+  hipLaunchKernelGGL((k_merge_runs<SPLIT, LAST>), dim3(grid * kRunItems), dim3(kRunThreads), 0, s, plan, from, to, len, ways, n, w, edf)
+  bool last = levels == 0;
+  if (last) stage_event();
+  if (split && last) SP_RUNS(true, true);
+  else if (split) SP_RUNS(true, false);
+  else if (last) SP_RUNS(false, true);
+  else SP_RUNS(false, false);
+  int len = 1;                                            // chunks of kRun per sorted run
+  for (int l = 0; l < levels; ++l) {
+    std::swap(from, to);
+    last = l + 1 == levels;
+    if (last) stage_event();
+    if (split && last) SP_MERGE(true, true);
+    else if (split) SP_MERGE(true, false);
+    else if (last) SP_MERGE(false, true);
+    else SP_MERGE(false, false);
+    len *= ways;
+  }
+#undef SP_MERGE
+#undef SP_RUNS
+  return to.label;
 }
 
 // Number of groups of the scored window: the applications, or the non-empty (application, subgroup) pairs.
@@ -903,112 +1040,30 @@ sp_status sp_score(sp_ctx* c, int32_t n, const void* x_dev, const int32_t* app_d
   c->n = n;
   c->rounds_done = 0;
   c->done = false;
-  const int A = c->A;
-  hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(256), 0, s, w.st, n, c->seg1, c->dtot_app, 2 * 256);
+  w.ea_out = ea_out_dev;
+  w.key_out = key_out_dev;
   const bool tm = c->timing && n > 0;
   c->timed_score = false;
   c->timed_rounds = false;
   const bool tms = tm && c->timing_stages;
   if (tms) SP_HIP(c, hipEventRecord(c->ev[0], s));
-
-  uint32_t *curK = c->bufK[0], *altK = c->bufK[1];
-  int32_t *curV = c->bufV[0], *altV = c->bufV[1];
-  const int n_app_passes = app_passes(A);
-  const int tiles2 = n / kSortTile + A;                       // upper bound on the tiles inside the applications' ranges
-  const int64_t slab = c->tiles_cap * 256;                    // words per pass of dtot_key
-  // a single pass over the application ids: every application's count is one of its digit totals
-  // Applications whose whole range fits one workgroup's LDS are ordered by one kernel (k_sort_small) and get
-  // no tiles in the passes; not with subgroups (their passes over the labels need the tiles) and not with more
-  // applications than that kernel is worth a workgroup each.
-  const int small_cap = (!c->tb.pol_split && A <= 1024) ? kSmallSortCap : 0;
-  SegArgs seg_args{n, A, nullptr, c->dtot_app, score_tile(c), kSortTile, small_cap, w.seg, w.tile_start, w.unit_start,
-                   w.tile_desc, c->sort_desc};
-  if (n > 0) {
-    // requests grouped by application: stable pass(es) over the application id, read straight from the
-    // caller's array (ids outside [0, A) become A and raise the error flag)
-    SortPlan whole{c->seg1, nullptr, 1, nullptr};
-    const int tiles1 = (n + kSortTile - 1) / kSortTile;
-    hipLaunchKernelGGL(k_digit_totals, dim3(tiles1), dim3(kSortThreads), 0, s, whole, (const uint32_t*)app_dev, A, 0,
-                       n_app_passes, (int64_t)1, c->dtot_app, c->dtot_key, kMaxSortPasses, (int64_t)tiles2 + 1, c->tiles_cap,
-                       w.st);
-    const uint32_t* kin = (const uint32_t*)app_dev;
-    const int32_t* vin = nullptr;
-    for (int p = 0; p < n_app_passes; ++p) {
-      // a single pass: the segment bookkeeping (which needs only the ids' digit totals) rides along;
-      // every request's deadline and weight travel with it to its grouped position
-      const SortCarry cy = p == 0 ? SortCarry{deadline_ms_dev, weight_dev, nullptr, c->dw_g[n_app_passes - 1 - p]}
-                                  : SortCarry{nullptr, nullptr, c->dw_g[n_app_passes - p], c->dw_g[n_app_passes - 1 - p]};
-      radix_pass(c, s, whole, tiles1, kin, vin, 8 * p, p == 0 ? A : 0, c->dtot_app + 256 * p, altK, altV,
-                 n_app_passes == 1 ? &seg_args : nullptr, &cy);
-      std::swap(curK, altK);
-      std::swap(curV, altV);
-      kin = curK;
-      vin = curV;
-    }
-  }
-  if (n == 0 || n_app_passes > 1) {
-    // no pass to ride along with, or two passes (the segment starts then come from the sorted ids)
-    seg_args.sorted_app = curK;
-    seg_args.digit_tot = nullptr;
-    hipLaunchKernelGGL(k_segments, dim3(1), dim3(256), 0, s, seg_args, w);
-  }
+  const int32_t* ids = group_requests(c, s, n, app_dev, deadline_ms_dev, weight_dev);
   if (n > 0) {
     // posterior -> EA -> key, one pass over the features
-    uint32_t* sortkey = altK;
+    uint32_t* sortkey = c->bufK[0];
     if (tm) SP_HIP(c, hipEventRecord(c->ev[1], s));
-    launch_score(c, s, x_dev, curV, c->dw_g[0], sortkey, nullptr);
+    launch_score(c, s, x_dev, ids, c->dw_g[0], sortkey, nullptr);
     if (tm) SP_HIP(c, hipEventRecord(c->ev[2], s));
-    // service order: inside each application by (key descending, id ascending).  The passes carry
-    // positions of the grouped array (identity to start with), the grouped ids stay where they are.
-    SortPlan per_app{w.seg, w.unit_start, A, c->sort_desc};
-    // with n <= small_cap every application is small: the tiled passes have nothing to do and are not launched
-    const bool tiled = !(small_cap > 0 && n <= small_cap);
-    if (tiled)
-      hipLaunchKernelGGL(k_digit_totals, dim3(tiles2), dim3(kSortThreads), 0, s, per_app, (const uint32_t*)sortkey, 0, 0, 4,
-                         c->tiles_cap, c->dtot_key, (uint32_t*)nullptr, 0, (int64_t)0, (int64_t)0, w.st);
-    uint32_t *k_in = sortkey, *k_out = curK;
-    const int32_t* v_in = nullptr;
-    int32_t *v_out = altV, *v_spare = c->bufV[2];
-    for (int p = 0; p < 4; ++p) {
-      if (tiled) radix_pass(c, s, per_app, tiles2, k_in, v_in, 8 * p, 0, c->dtot_key + slab * p, k_out, v_out);
-      std::swap(k_in, k_out);
-      v_in = v_out;
-      std::swap(v_out, v_spare);
-    }
-    // the small applications, straight into the arrays the fourth pass has written (or would have)
-    if (small_cap > 0)
-      hipLaunchKernelGGL(k_sort_small, dim3(A), dim3(kSmallSortThreads), 0, s, (const int32_t*)w.seg, (const uint32_t*)sortkey,
-                         k_in, const_cast<int32_t*>(v_in));
-    if (c->tb.pol_split) {
-      // subgroups: further stable passes over the subgroup codes make the order (subgroup, key) inside
-      // every application; then the non-empty (application, subgroup) pairs become the rounds' groups
-      hipLaunchKernelGGL(k_gather_sub_keys, dim3((n + 255) / 256), dim3(256), 0, s, A, (const int32_t*)w.seg, v_in,
-                         (const int32_t*)w.sub_g, k_in);
-      hipLaunchKernelGGL(k_digit_totals, dim3(tiles2), dim3(kSortThreads), 0, s, per_app, (const uint32_t*)k_in, 0, 0,
-                         c->sub_passes, c->tiles_cap, c->dtot_key + slab * 4, (uint32_t*)nullptr, 0, (int64_t)0, (int64_t)0, w.st);
-      for (int p = 0; p < c->sub_passes; ++p) {
-        radix_pass(c, s, per_app, tiles2, k_in, v_in, 8 * p, 0, c->dtot_key + slab * (4 + p), k_out, v_out);
-        std::swap(k_in, k_out);
-        v_in = v_out;
-        std::swap(v_out, v_spare);
-      }
-    }
-    if (tms) SP_HIP(c, hipEventRecord(c->ev[6], s));
-    hipLaunchKernelGGL(k_finish_order, dim3((n + 255) / 256), dim3(256), 0, s, n, A, (const int32_t*)w.seg, v_in,
-                       (const uint32_t*)k_in, w, c->tb.pol_edf | c->tb.pol_split);
+    const uint32_t* labels = order_requests(c, s, n, sortkey, c->bufK[1]);
     if (c->tb.pol_split) {
       hipLaunchKernelGGL(k_slot_ranges, dim3((c->n_slots + 255) / 256), dim3(256), 0, s, c->n_slots,
                          (const int32_t*)c->slot_app, (const int32_t*)c->slot_base, (const int32_t*)w.seg,
-                         (const uint32_t*)k_in, c->slot_beg, c->slot_end);
+                         labels, c->slot_beg, c->slot_end);
       hipLaunchKernelGGL(k_groups_compact, dim3(1), dim3(1024), 0, s, c->n_slots, (const int32_t*)c->slot_app,
                          (const int32_t*)c->slot_beg, (const int32_t*)c->slot_end, w);
     }
     if (tms) SP_HIP(c, hipEventRecord(c->ev[3], s));
     if (tm) c->timed_score = true;
-    if (ea_out_dev)
-      SP_HIP(c, hipMemcpyAsync(ea_out_dev, w.ea, (size_t)n * c->Mmax * sizeof(float), hipMemcpyDeviceToDevice, s));
-    if (key_out_dev)
-      SP_HIP(c, hipMemcpyAsync(key_out_dev, w.key, (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, s));
   }
   if (c->tb.pol_split) {
     // the rounds' launch grids depend on the number of groups

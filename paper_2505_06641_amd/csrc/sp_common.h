@@ -81,6 +81,8 @@ struct Window {
   int32_t* unit_start;        // [A+1] prefix of sort units
   float* ea;                  // [n, Mmax]
   float* key;                 // [n]
+  float* ea_out;              // the caller's copies of the two, or null (set by every scoring call)
+  float* key_out;
   float4* rec_g;              // [n] (request id bits, deadline, weight, 0) at each position of the application-grouped (pre-order) array
   int32_t* id_s;              // [n] request id at each service position
   float* D_s;                 // [n]
@@ -109,6 +111,17 @@ struct Window {
   State* st;
   State* st_host;             // pinned host copy of *st that the two-kernel round path keeps current (device-visible address)
 };
+
+// Which tile a workgroup takes.  Consecutive workgroup ids go to the chip's eight accelerator dies (XCDs) in turn, each with
+// an L2 of its own; tiles are ordered by application, so giving every die one contiguous eighth of the tiles lets what the
+// tiles of an application share (packed weights, the cache lines their outputs meet in) live in one L2 instead of eight.
+// The launch must hold at least 8 * ceil(n_tiles / 8) workgroups; returns -1 for a workgroup without a tile.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int xcd_tile(int wg, int n_tiles) {
+  const int per = (n_tiles + kXcds - 1) / kXcds;
+  const int j = wg / kXcds, tile = (wg % kXcds) * per + j;
+  return (j < per && tile < n_tiles) ? tile : -1;
+}
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) {
   return __uint_as_float(((uint32_t)b) << 16);

@@ -390,16 +390,22 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Windo
   }
 }
 
-// Window state at the start of a window, and the one-segment plan of the pass over the application ids.
+// Window state at the start of a window.
+__device__ __forceinline__ void reset_state(State* st) {
+  st->t = 0.0; st->total_wu = 0.0; st->total_u = 0.0; st->total_viol = 0.0;
+  st->round = 0; st->next_order = 1; st->n_sched = 0; st->done = 0; st->err = 0u; st->pad = 0;
+  st->n_evals = 0ull;
+  st->last.app = -1; st->last.model = -1;        // nothing resident yet
+}
+
+// The same in a launch of its own, with the one-segment plan of the passes over the application ids and their digit totals
+// cleared: where those passes do the grouping.
 __global__ void k_reset_state(State* st, int n, int32_t* seg1, uint32_t* dtot_app, int dtot_words) {
-  for (int i = threadIdx.x; i < dtot_words; i += blockDim.x) dtot_app[i] = 0u;    // digit totals of the pass(es) over the application ids
+  for (int i = threadIdx.x; i < dtot_words; i += blockDim.x) dtot_app[i] = 0u;
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     seg1[0] = 0;
     seg1[1] = n;
-    st->t = 0.0; st->total_wu = 0.0; st->total_u = 0.0; st->total_viol = 0.0;
-    st->round = 0; st->next_order = 1; st->n_sched = 0; st->done = 0; st->err = 0u; st->pad = 0;
-    st->n_evals = 0ull;
-    st->last.app = -1; st->last.model = -1;      // nothing resident yet
+    reset_state(st);
   }
 }
 

@@ -15,16 +15,6 @@ constexpr int kScoreWaves = 4;
 constexpr int kScoreRW = 8;                          // requests per wavefront
 constexpr int kScoreTile = kScoreWaves * kScoreRW;   // requests per workgroup
 
-// Find s with start[s] <= v < start[s+1] (start has nseg+1 entries, non-decreasing).
-__device__ __forceinline__ int find_segment(const int32_t* start, int nseg, int v) {
-  int lo = 0, hi = nseg;
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (start[mid] <= v) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
@@ -68,6 +58,7 @@ __device__ __forceinline__ void finish_request(const Tables& tb, const Window& w
   if (err) atomicOr(&w.st->err, err);
   float key = fabsf(wi * (1.0f + var) * expf(-Di * tb.inv_timescale));   // a weight of -0 must not give the key -0: its bits would sort first
   w.key[id] = key;
+  if (w.key_out) w.key_out[id] = key;
   sortkey[pos] = tb.pol_edf ? __float_as_uint(Di) : ~__float_as_uint(key);   // ascending deadline, or descending key
   w.rec_g[pos] = make_float4(__int_as_float(id), Di, wi, 0.f);   // what the ordering needs of this request, in one piece
   float* row = w.ea + (int64_t)id * tb.Mmax;
@@ -76,6 +67,7 @@ __device__ __forceinline__ void finish_request(const Tables& tb, const Window& w
 #pragma unroll
     for (int q = 0; q < MT; ++q) v = (q == m && q < M) ? ea[q] : v;
     row[m] = v;
+    if (w.ea_out) w.ea_out[(int64_t)id * tb.Mmax + m] = v;
   }
 }
 

@@ -510,6 +510,14 @@ __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w
     const int m = 8 * (v >> 2) + 4 * g + (v & 3);
     if (m < tb.Mmax) rowo[m] = ea[v];
   }
+  if (w.ea_out != nullptr) {
+    float* out = w.ea_out + (int64_t)id * tb.Mmax;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+      const int m = 8 * (v >> 2) + 4 * g + (v & 3);
+      if (m < tb.Mmax) out[m] = ea[v];
+    }
+  }
   if (split) {
     // the lane halves' candidates meet; the largest posterior is exp(z_max - reference) / sum
     const float oz = other_half(best_z, g);
@@ -529,6 +537,7 @@ __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w
     if (err) atomicOr(&w.st->err, err);
     const float key = fabsf(wi * (1.0f + var) * expf(-Di * tb.inv_timescale));   // a weight of -0 must not give the key -0: its bits would sort first
     w.key[id] = key;
+    if (w.key_out != nullptr) w.key_out[id] = key;
     sortkey[pos] = tb.pol_edf ? __float_as_uint(Di) : ~__float_as_uint(key);   // ascending deadline, or descending key
     w.rec_g[pos] = make_float4(__int_as_float(id), Di, wi, 0.f);   // what the ordering needs of this request, in one piece
   }
@@ -697,17 +706,6 @@ __device__ __forceinline__ float load_split_features(const float* __restrict__ x
       xl[q >> 3][q & 7] = lo[0]; xl[q >> 3][(q & 7) + 1] = lo[1];
     }
   return unscale;
-}
-
-// Which scoring tile a workgroup takes.  Consecutive workgroup ids go to the chip's eight accelerator dies
-// (XCDs) in turn, each with an L2 of its own; tiles are ordered by application, so giving every die one
-// contiguous eighth of the tiles lets each application's packed blocks live in one L2 instead of eight.
-// The launch must hold at least 8 * ceil(n_tiles / 8) workgroups; returns -1 for a workgroup without a tile.
-constexpr int kXcds = 8;
-__device__ __forceinline__ int xcd_tile(int wg, int n_tiles) {
-  const int per = (n_tiles + kXcds - 1) / kXcds;
-  const int j = wg / kXcds, tile = (wg % kXcds) * per + j;
-  return (j < per && tile < n_tiles) ? tile : -1;
 }
 
 // DUMP: the launch only writes the logits (logits_out) and ends before the epilogue; dw_g and sortkey are

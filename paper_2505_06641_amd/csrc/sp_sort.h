@@ -1,33 +1,25 @@
-// Stable least-significant-digit radix passes (8-bit digits) over (key, value)
-// pairs, run independently inside each segment of the array.  Used twice per
-// window: once over the whole queue with the application id as the key (the
-// request groups of Alg. 1, "HashMap<app : request list>"), then four times
-// inside each application's range with the inverted bits of the priority key
-// (Alg. 1, "requests in g sorted by priority"; eq. (12)) or the bits of the
-// deadline (earliest deadline first), and, with data-aware subgroups
-// (Sec. 5.3.2), once or twice more with the subgroup label.
+// Grouping and ordering of a window's requests (Alg. 1 "HashMap<app : request list>" and "requests in g sorted by
+// priority"; eq. (12); Sec. 5.3.2 with subgroups).
 //
-// One kernel per pass.  The unit of work is a tile of kSortTile consecutive
-// elements of one segment, taken by one workgroup; tiles never straddle
-// segments.  A workgroup ranks its elements by digit (ballot matching inside
-// a wavefront, equal digits keep their order; per-wavefront digit counts in
-// LDS, scanned across the wavefronts), publishes its 256 digit counts, and
-// gets the counts of the tiles before it in its segment by looking back
-// through what they have published (a tile publishes first its own counts,
-// then the running prefix, so the walk ends at the first tile that already
-// knows its prefix).  The published words carry the generation number of the
-// pass, so a word is valid exactly when its generation matches: no clearing
-// between passes, no fences.  Where each digit of a segment starts follows
-// from the segment's digit totals, which one small kernel (k_digit_totals)
-// counts for all passes of a sort before the first pass.  The elements go
-// through LDS in sorted order, so that global writes are runs of consecutive
-// addresses per digit rather than single elements.
-// A tile waits only for tiles with a lower index, which the hardware starts
-// no later than itself; every wait is bounded all the same (kErrSortSync).
+// Grouping by application.  Up to 255 applications: one kernel counts the applications of every tile of the queue
+// (k_group_count), a second one places the requests (k_group_place): a tile reads the counts of all tiles, which are few
+// (tiles times applications words), so no tile waits for another.  More applications: two or three stable radix passes
+// over the ids (k_digit_totals, k_radix_pass), whose tiles learn the digit counts of the tiles before them by looking back
+// through published words.
+//
+// Ordering inside each application by the inverted bits of the priority key (or the deadline bits, or (subgroup, key)).
+// Up to kMergeMax requests: runs of kRun consecutive requests are sorted by one workgroup each in LDS (k_sort_runs); runs are
+// then merged several at a time (k_merge_runs): a workgroup takes consecutive elements of one run and finds the place of each
+// by counting, with binary searches in LDS, what precedes it in the sibling runs.  No workgroup waits for another, the number
+// of launches follows from the window's size alone (one for up to 1,024 requests, two for up to 16,384, three beyond), and
+// the last one writes the service order's arrays itself.  Longer windows: four radix passes inside the applications'
+// ranges and a gather, which read and write every element five times but do no searching.  Ordering took, merges against
+// passes: 20 us against 45 for 65,536 requests of 8 applications, 35 against 66 for 200,003 of 12; 58 against 70 for 300,000
+// of 12 but 97 against 79 for 300,000 of one, 133 against 82 for 600,000 of 8.
 #pragma once
+#include <type_traits>
 #include "sp_common.h"
 #include "sp_wave.h"
-#include "sp_score_generic.h"   // find_segment
 
 namespace sp {
 
@@ -36,15 +28,15 @@ constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kSortItems = 8;                         // elements per thread
 constexpr int kSortTile = kSortThreads * kSortItems;  // elements per tile
 constexpr int kSortSpinLimit = 1 << 20;               // polls before a look-back is given up
+constexpr int kMaxSortPasses = 6;                     // four key passes and up to two over subgroup labels
 constexpr uint32_t kSortCountMask = 0x3FFFFFFFu;      // a published word: generation << 32 | status << 30 | count
 constexpr int kLookBack = 8;                          // tiles whose published words are requested together
-constexpr int kMaxSortPasses = 6;                     // four key passes and up to two over subgroup labels
 
 struct SortPlan {
   const int32_t* seg;          // [nseg+1] segment starts
-  const int32_t* unit_start;   // [nseg+1] prefix of tiles per segment
+  const int32_t* unit_start;   // [nseg+1] prefix of runs per segment
   int32_t nseg;
-  const int4* desc;            // per tile: (segment, first element, end, first tile of the segment); null = one segment
+  const int4* desc;            // per run or tile: (start of the segment, first element, end of the segment, 0); null = one segment
 };
 
 // mask of lanes whose 8-bit digit equals mine
@@ -59,18 +51,21 @@ __device__ __forceinline__ unsigned long long match_digit(uint32_t digit, bool v
   return m;
 }
 
-// This workgroup's tile: segment s, elements [beg, end), first tile of s.  False for a workgroup without one.
-__device__ __forceinline__ bool sort_tile(const SortPlan& sp, int tile, int& s, int& beg, int& end, int& first) {
+// This workgroup's tile of a pass: elements [beg, end) of a segment that starts at s0 with tile `first`.  One segment
+// (desc == null), or the applications' ranges.  False for a workgroup without a tile.
+__device__ __forceinline__ bool sort_tile(const SortPlan& sp, int tile, int& s0, int& beg, int& end, int& first) {
   if (sp.desc == nullptr) {
     const int n = sp.seg[1];
-    s = 0; first = 0;
+    s0 = 0; first = 0;
     beg = tile * kSortTile;
     end = min(beg + kSortTile, n);
     return beg < n;
   }
   if (tile >= sp.unit_start[sp.nseg]) return false;
   const int4 d = sp.desc[tile];
-  s = d.x; beg = d.y; end = d.z; first = d.w;
+  s0 = d.x; beg = d.y;
+  end = min(beg + kSortTile, d.z);
+  first = tile - (beg - s0) / kSortTile;
   return true;
 }
 
@@ -103,14 +98,12 @@ __device__ __forceinline__ uint4 wave_digit_bases(const uint32_t* __restrict__ t
 // Segment starts from the application-sorted keys (values in [0, A], A =
 // invalid): seg[a] = first position with key >= a; then the prefixes of
 // scoring tiles and sort units per application and the scoring tiles' descriptors.  One workgroup.
-// digit_tot, when given, holds the count of every digit of a single radix pass over the application ids
-// (wavefront 0 turns them into the segment starts without any search).
+// digit_tot, when given, holds the count of every application id (256 words; wavefront 0 turns them into the segment
+// starts without any search).
 struct SegArgs {
   int32_t n, A;
-  const uint32_t* sorted_app;   // application-sorted keys (used when digit_tot is null)
-  const uint32_t* digit_tot;    // or: the count of every application id (one radix pass over the ids)
-  int32_t tile, unit;           // requests per scoring tile and per sort tile
-  int32_t small_cap;            // applications with at most this many requests get no sort tiles (k_sort_small orders them); 0: none
+  const uint32_t* sorted_app;   // application-sorted keys (not used where the counts of the ids are given)
+  int32_t tile, unit;           // requests per scoring tile and per sort run
   int32_t* seg;
   int32_t* tile_start;
   int32_t* unit_start;
@@ -119,10 +112,12 @@ struct SegArgs {
 };
 
 // Body of k_segments for the first 256 threads of a workgroup (any others only keep the barriers company).
-__device__ __forceinline__ void segments_body(const SegArgs& g, const Window& w) {
-  const int n = g.n, A = g.A, tile = g.tile, unit = g.unit;
+__device__ __forceinline__ void segments_body(const SegArgs& g, const Window& w, const uint32_t* digit_tot) {
+  // A look-back that ran out has left holes in the sorted ids: the window will be refused, and until then it has no
+  // requests, so that nothing reads what was never written.
+  const int n = digit_tot == nullptr && (w.st->err & kErrSortSync) ? 0 : g.n;
+  const int A = g.A, tile = g.tile, unit = g.unit;
   const uint32_t* __restrict__ sorted_app = g.sorted_app;
-  const uint32_t* __restrict__ digit_tot = g.digit_tot;
   int32_t *seg = g.seg, *tile_start = g.tile_start, *unit_start = g.unit_start;
   int4 *tile_desc = g.tile_desc, *sort_desc = g.sort_desc;
   const bool on = threadIdx.x < 256;
@@ -168,7 +163,7 @@ __device__ __forceinline__ void segments_body(const SegArgs& g, const Window& w)
   for (int a = a_lo; a < a_hi; ++a) {
     const int na = seg[a + 1] - seg[a];
     ts += (na + tile - 1) / tile;
-    us += na > g.small_cap ? (na + unit - 1) / unit : 0;
+    us += (na + unit - 1) / unit;
   }
   if (on) {
     run_t[tid] = ts;
@@ -199,7 +194,7 @@ __device__ __forceinline__ void segments_body(const SegArgs& g, const Window& w)
       s_seg[a] = sb;
     }
     ts += (na + tile - 1) / tile;
-    us += na > g.small_cap ? (na + unit - 1) / unit : 0;
+    us += (na + unit - 1) / unit;
   }
   if (on && tid == 255) {
     tile_start[A] = run_t[255];
@@ -223,7 +218,7 @@ __device__ __forceinline__ void segments_body(const SegArgs& g, const Window& w)
       }
       tile_desc[t] = make_int4(lo, s_seg[lo] + (t - s_tile[lo]) * tile, s_seg[lo + 1], 0);
     }
-    // and one per sort tile: (application, first element, end, first tile of the application)
+    // and one per run: (start of the application, first element, end of the application, 0)
     const int n_units = s_unit[A];
     for (int u = tid; on && u < n_units; u += 256) {
       int lo = 0, hi = A;
@@ -231,41 +226,40 @@ __device__ __forceinline__ void segments_body(const SegArgs& g, const Window& w)
         const int mid = (lo + hi) >> 1;
         if (s_unit[mid] <= u) lo = mid; else hi = mid;
       }
-      const int b0 = s_seg[lo] + (u - s_unit[lo]) * unit;
-      sort_desc[u] = make_int4(lo, b0, min(b0 + unit, s_seg[lo + 1]), s_unit[lo]);
+      sort_desc[u] = make_int4(s_seg[lo], s_seg[lo] + (u - s_unit[lo]) * unit, s_seg[lo + 1], 0);
     }
   } else {
     ts = ts0;
     us = us0;
     for (int a = a_lo; a < a_hi; ++a) {
-      const int sb = seg[a], se = seg[a + 1], nt = (se - sb + tile - 1) / tile, nu = se - sb > g.small_cap ? (se - sb + unit - 1) / unit : 0;
+      const int sb = seg[a], se = seg[a + 1], nt = (se - sb + tile - 1) / tile, nu = (se - sb + unit - 1) / unit;
       for (int t = 0; t < nt; ++t) tile_desc[ts + t] = make_int4(a, sb + t * tile, se, 0);
-      for (int u = 0; u < nu; ++u) sort_desc[us + u] = make_int4(a, sb + u * unit, min(sb + (u + 1) * unit, se), us);
+      for (int u = 0; u < nu; ++u) sort_desc[us + u] = make_int4(sb, sb + u * unit, se, 0);
       ts += nt;
       us += nu;
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) { segments_body(g, w); }
+__global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) { segments_body(g, w, nullptr); }
+
+__device__ __forceinline__ void clear_words(uint32_t* __restrict__ p, int64_t words) {
+  if (p == nullptr) return;
+  for (int64_t i = (int64_t)blockIdx.x * kSortThreads + threadIdx.x; i < words; i += (int64_t)gridDim.x * kSortThreads) p[i] = 0u;
+}
 
 // Digit totals of every segment for n_pass consecutive passes (digits at shift0, shift0 + 8, ...):
 // dtot[(p * tiles_cap + first tile of the segment) * 256 + digit], which must be zero beforehand.  Also
-// clears zero_rows rows of each of zero_passes pass slabs of another totals array (the next sort's).
+// clears zero_words words of the next sort's totals.
 __global__ __launch_bounds__(kSortThreads) void k_digit_totals(SortPlan sp, const uint32_t* __restrict__ keys,
                                                                int clamp_a, int shift0, int n_pass, int64_t tiles_cap,
                                                                uint32_t* __restrict__ dtot, uint32_t* __restrict__ zero_ptr,
-                                                               int zero_passes, int64_t zero_rows, int64_t zero_cap,
-                                                               State* st) {
+                                                               int64_t zero_words, State* st) {
   __shared__ uint32_t h[4][256];
   const int tid = threadIdx.x;
-  if (zero_ptr != nullptr) {
-    const int64_t per = zero_rows * 256, stride = (int64_t)gridDim.x * kSortThreads;
-    for (int p = 0; p < zero_passes; ++p)
-      for (int64_t i = (int64_t)blockIdx.x * kSortThreads + tid; i < per; i += stride) zero_ptr[p * zero_cap * 256 + i] = 0u;
-  }
-  int s, beg, end, first;
-  if (!sort_tile(sp, blockIdx.x, s, beg, end, first)) return;
+  clear_words(zero_ptr, zero_words);
+  int s0, beg, end, first;
+  if (!sort_tile(sp, blockIdx.x, s0, beg, end, first)) return;
   for (int i = tid; i < 4 * 256; i += kSortThreads) h[0][i] = 0u;
   __syncthreads();
   bool bad = false;
@@ -317,13 +311,7 @@ template <bool CARRY>
 __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
     SortPlan sp, const uint32_t* __restrict__ keys_in, const int32_t* __restrict__ vals_in, int shift, int clamp_a,
     const uint32_t* __restrict__ dtot_pass, unsigned long long* __restrict__ state, uint32_t gen, int spin_limit,
-    uint32_t* __restrict__ keys_out, int32_t* __restrict__ vals_out, State* st, SegArgs sg, Window sw, SortCarry cy) {
-  // One extra workgroup (sg.seg != null) does k_segments' job beside the pass over the application ids,
-  // which needs nothing but the ids' digit totals: a launch and its trips to memory less per window.
-  if (sg.seg != nullptr && (int)blockIdx.x == (int)gridDim.x - 1) {
-    segments_body(sg, sw);
-    return;
-  }
+    uint32_t* __restrict__ keys_out, int32_t* __restrict__ vals_out, State* st, SortCarry cy) {
   __shared__ uint32_t cnt[kSortWaves][256];      // digit counts per wavefront, then their exclusive prefix over the wavefronts
   __shared__ uint32_t lstart[256];               // where each digit starts inside the sorted tile
   __shared__ uint32_t dbase[256];                // global position of the digit's first element of this tile, minus lstart
@@ -332,8 +320,10 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
   __shared__ int32_t sval[kSortTile];
   __shared__ float2 spay[CARRY ? kSortTile : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int s, beg, end, first;
-  if (!sort_tile(sp, blockIdx.x, s, beg, end, first)) return;
+  // (an earlier pass whose look-back ran out has left holes: what is in them would not match the totals)
+  if ((vals_in != nullptr || sp.desc != nullptr) && (st->err & kErrSortSync)) return;
+  int s0, beg, end, first;
+  if (!sort_tile(sp, blockIdx.x, s0, beg, end, first)) return;
   const int tile = blockIdx.x;
   for (int i = tid; i < kSortWaves * 256; i += kSortThreads) cnt[0][i] = 0u;
   // a wavefront takes kSortItems chunks of 64 consecutive elements: all loads go out before the first is used
@@ -347,13 +337,11 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
     val[c] = i < end ? (vals_in ? vals_in[i] : i) : 0;
   }
   float2 pay[CARRY ? kSortItems : 1];
-  if (CARRY) {
 #pragma unroll
-    for (int c = 0; c < kSortItems; ++c) {
-      const int i = beg + (wave * kSortItems + c) * 64 + lane;
-      pay[c] = make_float2(0.f, 0.f);
-      if (i < end) pay[c] = cy.in01 ? cy.in01[i] : make_float2(cy.in0[i], cy.in1[i]);
-    }
+  for (int c = 0; c < (CARRY ? kSortItems : 0); ++c) {
+    const int i = beg + (wave * kSortItems + c) * 64 + lane;
+    pay[c] = make_float2(0.f, 0.f);
+    if (i < end) pay[c] = cy.in01 ? cy.in01[i] : make_float2(cy.in0[i], cy.in1[i]);
   }
   if (bad) atomicOr(&st->err, kErrApp);
   __syncthreads();
@@ -427,7 +415,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
   const uint32_t gs = scan256_excl(tot, wave_tot);
   if (tid < 256) {
     lstart[tid] = ls;
-    dbase[tid] = (uint32_t)sp.seg[s] + gs + excl - ls;
+    dbase[tid] = (uint32_t)s0 + gs + excl - ls;
   }
   __syncthreads();
   // into LDS in sorted order
@@ -454,106 +442,545 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
   }
 }
 
-// All four key passes of one application in one kernel, for applications whose whole range fits one
-// workgroup's LDS (at most kSmallSortCap requests; k_segments gives such applications no tiles in the passes
-// above).  A window of a few thousand requests is otherwise six dependent launches of a few microseconds each.
-// The elements live in registers between the passes (wavefront w holds elements [1024 w, 1024 (w + 1)) in
-// order, 64 per chunk); a pass ranks them like k_radix_pass, scans the counts over the wavefronts and the
-// digits, places the (key, value) pairs in LDS in sorted order and reads them back.  Values are grouped
-// positions, as in the passes above; the result goes to the same arrays the last of those passes writes.
-constexpr int kSmallSortThreads = 1024;
-constexpr int kSmallSortWaves = kSmallSortThreads / kWave;
-constexpr int kSmallSortItems = 16;
-constexpr int kSmallSortCap = kSmallSortThreads * kSmallSortItems;   // 16,384
+// ---- grouping by application, up to 255 of them ----
 
-__global__ __launch_bounds__(kSmallSortThreads) void k_sort_small(const int32_t* __restrict__ seg,
-                                                                  const uint32_t* keys_in /* may be keys_out */,
-                                                                  uint32_t* keys_out, int32_t* __restrict__ vals_out) {
-  __shared__ unsigned long long buf[kSmallSortCap];            // key << 32 | value, in sorted order
-  __shared__ uint32_t cnt[kSmallSortWaves][256];
-  __shared__ uint32_t lstart[256];
-  __shared__ uint32_t wave_tot[kSmallSortWaves];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b0 = seg[blockIdx.x], n = seg[blockIdx.x + 1] - b0;
-  if (n <= 0 || n > kSmallSortCap) return;                     // (uniform) empty, or sorted by the tiled passes
-  // wavefronts and chunks that hold elements (the ranking is the expensive part: nothing is spent on empty ones)
-  const int n_waves = (n + kSmallSortItems * 64 - 1) / (kSmallSortItems * 64);
-  const int my_chunks = min(kSmallSortItems, max(0, (n - wave * kSmallSortItems * 64 + 63) / 64));
-  uint32_t key[kSmallSortItems];
-  int32_t val[kSmallSortItems];
-#pragma unroll
-  for (int c = 0; c < kSmallSortItems; ++c) {
-    const int e = (wave * kSmallSortItems + c) * 64 + lane;
-    key[c] = e < n ? keys_in[b0 + e] : 0u;
-    val[c] = b0 + e;
+constexpr int kGroupThreads = 512;
+constexpr int kGroupWaves = kGroupThreads / kWave;
+constexpr int kMaxGroupApps = 255;
+// Requests per tile: small tiles spread a short queue over the chip; from kGroupSmall requests on, larger ones keep the
+// table of counts that every tile reads short.
+constexpr int kGroupSmall = 131072;
+constexpr int group_tile(int64_t n) { return n <= kGroupSmall ? 1024 : 2048; }
+
+// mask of lanes whose digit of nbits bits equals mine
+__device__ __forceinline__ unsigned long long match_bits(uint32_t digit, bool valid, int nbits) {
+  unsigned long long m = __ballot(valid);
+  for (int b = 0; b < nbits; ++b) {
+    const bool bit = (digit >> b) & 1u;
+    const unsigned long long vote = __ballot(bit);
+    m &= bit ? vote : ~vote;
   }
-  const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int shift = 0; shift < 32; shift += 8) {
-    for (int i = tid; i < n_waves * 256; i += kSmallSortThreads) cnt[0][i] = 0u;
-    __syncthreads();
-    uint32_t rank[kSmallSortItems];
+  return m;
+}
+
+// Requests of every application in every tile: counts[tile][a], a = A for ids outside [0, A).  The first kernel of a
+// window: its first workgroup also resets the window's state.
+template <int ITEMS>
+__global__ __launch_bounds__(kGroupThreads) void k_group_count(int n, int A, int nbits, const int32_t* __restrict__ app,
+                                                               uint32_t* __restrict__ counts, State* st,
+                                                               uint32_t* __restrict__ zero_ptr, int64_t zero_words) {
+  __shared__ uint32_t h[256];
+  clear_words(zero_ptr, zero_words);                   // the digit totals of a long window's ordering
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0 && tid == 0) reset_state(st);
+  if (tid < 256) h[tid] = 0u;
+  const int beg = blockIdx.x * (kGroupThreads * ITEMS);
+  uint32_t key[ITEMS];
+  bool bad = false;
 #pragma unroll
-    for (int c = 0; c < kSmallSortItems; ++c) {
-      rank[c] = 0;
-      if (c < my_chunks) {                                       // uniform over the wavefront
-        const int e = (wave * kSmallSortItems + c) * 64 + lane;
-        const bool valid = e < n;
-        const uint32_t dg = (key[c] >> shift) & 255u;
-        const unsigned long long same = match_digit(dg, valid);
-        const int leader = valid ? (__ffsll((long long)same) - 1) : lane;
-        uint32_t before = 0;
-        if (valid && lane == leader) before = atomicAdd(&cnt[wave][dg], (uint32_t)__popcll(same));
-        before = __shfl(before, leader);
-        rank[c] = before + (uint32_t)__popcll(same & lt);
-      }
-    }
+  for (int c = 0; c < ITEMS; ++c) {
+    const int i = beg + (wave * ITEMS + c) * 64 + lane;
+    key[c] = i < n ? sort_key_at((const uint32_t*)app, i, A, bad) : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const bool valid = beg + (wave * ITEMS + c) * 64 + lane < n;
+    const unsigned long long same = match_bits(key[c], valid, nbits);
+    if (valid && lane == __ffsll((long long)same) - 1) atomicAdd(&h[key[c]], (uint32_t)__popcll(same));
+  }
+  __syncthreads();
+  if (tid <= A) counts[(size_t)blockIdx.x * 256 + tid] = h[tid];
+}
+
+// Long windows: exclusive prefixes of every application's counts over the tiles, in place, and the totals (row n_tiles).  One
+// workgroup per application (and one for the invalid ids).  Up to kGroupDirect tiles, each tile adds the counts up itself.
+constexpr int kGroupDirect = 128;
+__global__ __launch_bounds__(1024) void k_group_scan(uint32_t* __restrict__ counts, int n_tiles) {
+  __shared__ uint32_t wave_tot[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, a = blockIdx.x;
+  uint32_t carry = 0;
+  for (int t0 = 0; t0 < n_tiles; t0 += 1024) {
+    const int t = t0 + tid;
+    const uint32_t c = t < n_tiles ? counts[(size_t)t * 256 + a] : 0u;
+    const uint32_t incl = wave_scan_incl(c);
+    if (lane == 63) wave_tot[wave] = incl;
     __syncthreads();
-    uint32_t mine = 0;
+    uint32_t before = carry, all = carry;
+    for (int v = 0; v < 16; ++v) {
+      before += v < wave ? wave_tot[v] : 0u;
+      all += wave_tot[v];
+    }
+    if (t < n_tiles) counts[(size_t)t * 256 + a] = before + incl - c;
+    carry = all;
+    __syncthreads();
+  }
+  if (tid == 0) counts[(size_t)n_tiles * 256 + a] = carry;
+}
+
+// Sums of the tiles' counts per application, over all tiles and over those before `tile`, into LDS (256 words each, zero
+// beyond A).  The whole workgroup takes part: the rows are dealt to as many groups of threads as there are.
+__device__ __forceinline__ void group_sums(const uint32_t* __restrict__ counts, int n_tiles, int tile, int A, int nbits,
+                                           uint32_t* before, uint32_t* total, uint32_t (*red)[2][64]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (n_tiles > kGroupDirect) {                                  // (uniform) k_group_scan has done it
     if (tid < 256) {
-      for (int w = 0; w < n_waves; ++w) {
-        const uint32_t c = cnt[w][tid];
-        cnt[w][tid] = mine;
-        mine += c;
-      }
-    }
-    const uint32_t ls = scan256_excl<kSmallSortWaves>(mine, wave_tot);
-    if (tid < 256) lstart[tid] = ls;
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < kSmallSortItems; ++c) {
-      const int e = (wave * kSmallSortItems + c) * 64 + lane;
-      if (e < n) {
-        const uint32_t dg = (key[c] >> shift) & 255u;
-        buf[lstart[dg] + cnt[wave][dg] + rank[c]] = ((unsigned long long)key[c] << 32) | (unsigned long long)(uint32_t)val[c];
-      }
+      before[tid] = tid <= A ? counts[(size_t)tile * 256 + tid] : 0u;
+      total[tid] = tid <= A ? counts[(size_t)n_tiles * 256 + tid] : 0u;
     }
     __syncthreads();
+    return;
+  }
+  const int nd = 1 << nbits, parts = kGroupThreads >> nbits;     // nd > A, at most 256
+  const int dg = tid & (nd - 1);
+  uint32_t b = 0, t = 0;
+  if (dg <= A) {
+#pragma unroll 8
+    for (int q = tid >> nbits; q < n_tiles; q += parts) {
+      const uint32_t c = counts[(size_t)q * 256 + dg];
+      t += c;
+      b += q < tile ? c : 0u;
+    }
+  }
+  for (int o = nd; o < 64; o <<= 1) {
+    b += __shfl_xor(b, o);
+    t += __shfl_xor(t, o);
+  }
+  red[wave][0][lane] = b;
+  red[wave][1][lane] = t;
+  __syncthreads();
+  if (tid < 256) {
+    uint32_t sb = 0, stt = 0;
+    if (tid <= A) {
+      const int per = nd > 64 ? nd >> 6 : 1;                     // wavefronts that hold the digits once between them
+      for (int v = tid >> 6; v < kGroupWaves; v += per) {
+        sb += red[v][0][tid & 63];
+        stt += red[v][1][tid & 63];
+      }
+    }
+    before[tid] = sb;
+    total[tid] = stt;
+  }
+  __syncthreads();
+}
+
+// Every request to its grouped position (applications in ascending order, request ids ascending inside), with its deadline
+// and weight (the scoring kernel then reads them in order instead of gathering by request id, 4 useful bytes per 64-byte
+// line).  One extra workgroup turns the counts into segment starts and descriptors.  Bound by three or four dependent
+// trips to memory (2 us each), not by its 28 bytes per request.
+template <int ITEMS>
+__global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int nbits, const int32_t* __restrict__ app,
+                                                               const float* __restrict__ D, const float* __restrict__ weight,
+                                                               const uint32_t* __restrict__ counts, int n_tiles,
+                                                               int32_t* __restrict__ ids_out, float2* __restrict__ dw_out,
+                                                               SegArgs sg, Window sw, State* st) {
+  constexpr int kTile = kGroupThreads * ITEMS;
+  __shared__ uint32_t before[256], total[256];
+  __shared__ uint32_t red[kGroupWaves][2][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0) {              // (the first: as the last it would wait for a place on a full chip)
+    group_sums(counts, n_tiles, 0, A, nbits, before, total, red);
+    if (tid == 0 && total[A] != 0u) atomicOr(&st->err, kErrApp);
+    segments_body(sg, sw, total);
+    return;
+  }
+  // neighbouring tiles write neighbouring runs of every application: on one die, so that the lines they meet in are whole
+  // when they leave its L2
+  const int tile = xcd_tile(blockIdx.x - 1, n_tiles);
+  if (tile < 0) return;
+  __shared__ uint32_t cnt[kGroupWaves][256];
+  __shared__ uint32_t lstart[256], dbase[256];
+  __shared__ uint32_t wave_tot[kGroupWaves];
+  __shared__ int32_t sval[kTile];
+  __shared__ float2 spay[kTile];
+  __shared__ uint8_t skey[kTile];
+  for (int i = tid; i < kGroupWaves * 256; i += kGroupThreads) cnt[0][i] = 0u;
+  const int beg = tile * kTile;
+  uint32_t key[ITEMS];
+  float2 pay[ITEMS];
+  bool bad = false;
 #pragma unroll
-    for (int c = 0; c < kSmallSortItems; ++c) {
-      const int e = (wave * kSmallSortItems + c) * 64 + lane;
-      if (e < n) {
+  for (int c = 0; c < ITEMS; ++c) {
+    const int i = beg + (wave * ITEMS + c) * 64 + lane;
+    key[c] = i < n ? sort_key_at((const uint32_t*)app, i, A, bad) : 0u;
+    pay[c] = i < n ? make_float2(D[i], weight[i]) : make_float2(0.f, 0.f);
+  }
+  group_sums(counts, n_tiles, tile, A, nbits, before, total, red);       // (its barriers cover the cleared counts)
+  // rank inside the wavefront: lanes with my application ahead of me in this chunk, plus the wavefront's earlier chunks
+  const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  uint32_t rank[ITEMS];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const bool valid = beg + (wave * ITEMS + c) * 64 + lane < n;
+    const unsigned long long same = match_bits(key[c], valid, nbits);
+    const int leader = valid ? (__ffsll((long long)same) - 1) : lane;
+    uint32_t ahead = 0;
+    if (valid && lane == leader) ahead = atomicAdd(&cnt[wave][key[c]], (uint32_t)__popcll(same));
+    ahead = __shfl(ahead, leader);
+    rank[c] = ahead + (uint32_t)__popcll(same & lt);
+  }
+  __syncthreads();
+  uint32_t mine = 0;
+  if (tid <= A) {
+#pragma unroll
+    for (int v = 0; v < kGroupWaves; ++v) {
+      const uint32_t c = cnt[v][tid];
+      cnt[v][tid] = mine;
+      mine += c;
+    }
+  }
+  const uint32_t ls = scan256_excl<kGroupWaves>(tid < 256 ? mine : 0u, wave_tot);
+  const uint32_t gs = scan256_excl<kGroupWaves>(tid < 256 ? total[tid] : 0u, wave_tot);
+  if (tid < 256) {
+    lstart[tid] = ls;
+    dbase[tid] = gs + before[tid] - ls;
+  }
+  __syncthreads();
+  // through LDS in sorted order, so that neighbouring threads write neighbouring elements
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const int i = beg + (wave * ITEMS + c) * 64 + lane;
+    if (i < n) {
+      const uint32_t p = lstart[key[c]] + cnt[wave][key[c]] + rank[c];
+      skey[p] = (uint8_t)key[c];
+      sval[p] = i;
+      spay[p] = pay[c];
+    }
+  }
+  __syncthreads();
+  const int n_tile = min(kTile, n - beg);
+  for (int j = tid; j < n_tile; j += kGroupThreads) {
+    const uint32_t dst = dbase[skey[j]] + (uint32_t)j;
+    ids_out[dst] = sval[j];
+    dw_out[dst] = spay[j];
+  }
+}
+
+// ---- ordering inside the applications ----
+
+// Requests per run.  Short runs spread even a small window over the chip: with 4,096 a run took 19 us to sort and the first
+// merge of two runs 10; with 1,024 sorting takes 6 and a merge of up to sixteen runs 6 to 8.
+constexpr int kRun = 1024;
+constexpr int kRunThreads = 256;
+constexpr int kRunWaves = kRunThreads / kWave;
+constexpr int kRunItems = kRun / kRunThreads;
+constexpr int kMergeWays = 16;                         // most runs merged at a time
+constexpr int kMergeMax = 262144;                      // longest window that is ordered this way (see the top of this file)
+
+// How many merge launches a window of n requests takes and how many runs each merges: the largest application may hold
+// every run.
+inline void merge_plan(int64_t n, int& levels, int& ways) {
+  const int64_t runs = (n + kRun - 1) / kRun;
+  levels = 0;
+  ways = 1;
+  if (runs <= 1) return;
+  for (int64_t c = 1; c < runs; c *= kMergeWays) ++levels;
+  for (ways = 2;; ++ways) {
+    int64_t c = 1;
+    for (int l = 0; l < levels; ++l) c *= ways;
+    if (c >= runs) return;
+  }
+}
+
+// This workgroup's run, or its share of one that PARTS workgroups take: elements [beg, end) of the segment [s0, se).  Runs are
+// dealt to the dies in contiguous eighths of the launch (see xcd_tile; the launch holds a multiple of 8 PARTS workgroups).
+template <int PARTS>
+__device__ __forceinline__ bool my_run(const SortPlan& sp, int& s0, int& beg, int& end, int& se) {
+  const int at = (blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds, unit = at / PARTS;
+  const int4 d = sp.desc[unit];                       // (the array covers the launch)
+  if (unit >= sp.unit_start[sp.nseg]) return false;
+  s0 = __builtin_amdgcn_readfirstlane(d.x);
+  beg = __builtin_amdgcn_readfirstlane(d.y) + at % PARTS * (kRun / PARTS);
+  se = __builtin_amdgcn_readfirstlane(d.z);
+  end = min(beg + kRun / PARTS, se);
+  return beg < end;
+}
+
+// What a launch of the ordering reads and writes: sort keys, positions of the application-grouped array, subgroup labels
+// (with subgroups).
+struct SortedRun {
+  uint32_t* key;
+  int32_t* pos;
+  uint32_t* label;
+};
+
+// A request at its final service position: id, deadline and weight come with one gather of the record the scoring kernel
+// left at the grouped position, the key straight from the sorted key bits.
+__device__ __forceinline__ void finish_position(const Window& w, int at, uint32_t key, int gpos, int edf) {
+  const float4 rc = w.rec_g[gpos];
+  const int id = __float_as_int(rc.x);
+  w.id_s[at] = id;
+  w.D_s[at] = rc.y;
+  w.w_s[at] = rc.z;
+  // sorted were the inverted key bits, or (earliest deadline first) the deadline bits
+  w.key_s[at] = edf ? w.key[id] : __uint_as_float(~key);
+  w.alive_s[at] = 1;
+}
+
+// The last launch also resets the per-request outputs (by request id) and what lies behind the valid requests.
+template <int ITEMS>
+__device__ __forceinline__ void finish_rest(const Window& w, int n, int n_valid_at, const int32_t* __restrict__ seg) {
+  const int nv = seg[n_valid_at];
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    const int i = (blockIdx.x * ITEMS + c) * kRunThreads + threadIdx.x;
+    if (i >= n) break;
+    if (i >= nv) w.alive_s[i] = 0;
+    w.model[i] = -1;
+    w.round_of[i] = -1;
+    w.order_of[i] = 0;
+    w.util[i] = 0.f;
+  }
+}
+
+// Mask of lanes whose 8-bit digit equals mine: per bit one vote and, on either half of the mask, one three-input operation.
+__device__ __forceinline__ void match_byte(uint32_t digit, bool valid, uint32_t& lo, uint32_t& hi) {
+  const unsigned long long m = __ballot(valid);
+  lo = (uint32_t)m;
+  hi = (uint32_t)(m >> 32);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const uint32_t mine = (uint32_t)((int32_t)(digit << (31 - b)) >> 31);      // all ones where my bit is set
+    const unsigned long long vote = __ballot(mine != 0u);
+    lo &= ~((uint32_t)vote ^ mine);
+    hi &= ~((uint32_t)(vote >> 32) ^ mine);
+  }
+}
+
+// Sorts one run in LDS: stable radix passes of 8 bits, elements in registers between the passes (a wavefront holds four
+// chunks of 64 consecutive elements), counts per wavefront scanned over wavefronts and digits by one thread per digit.
+// Bound by the latency of its four barriers and LDS round trips per pass.
+template <bool SPLIT, bool FINISH>
+__global__ __launch_bounds__(kRunThreads) void k_sort_runs(SortPlan sp, SortedRun in, SortedRun out, const int32_t* __restrict__ sub_g,
+                                                           int sub_passes, int n, Window w, int edf) {
+  static_assert(kRunThreads == 256 && kRunWaves == 4 && kRunItems == 4, "one thread per digit, four wavefronts of four chunks");
+  __shared__ unsigned long long buf[kRun];                     // key << 32 | element, in sorted order
+  __shared__ uint32_t lab[SPLIT ? kRun : 1];
+  __shared__ __align__(16) uint32_t cnt[kRunWaves][256];
+  __shared__ uint32_t wave_tot[kRunWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (FINISH) finish_rest<kRunItems>(w, n, sp.nseg, sp.seg);
+  int s0, beg, end, se;
+  if (!my_run<1>(sp, s0, beg, end, se)) return;
+  const int len = end - beg;
+  uint32_t key[kRunItems], lb[kRunItems];
+  int32_t val[kRunItems];
+#pragma unroll
+  for (int c = 0; c < kRunItems; ++c) {
+    const int e = (wave * kRunItems + c) * 64 + lane;
+    key[c] = e < len ? in.key[beg + e] : 0u;
+    lb[c] = SPLIT && e < len ? (uint32_t)sub_g[beg + e] : 0u;
+    val[c] = beg + e;
+  }
+  const int n_pass = 4 + (SPLIT ? sub_passes : 0);
+  for (int p = 0; p < n_pass; ++p) {
+    const int shift = 8 * (p & 3);
+    // (a wavefront's own row of counts, which its own LDS operations reach in order)
+    *reinterpret_cast<uint4*>(&cnt[wave][4 * lane]) = make_uint4(0u, 0u, 0u, 0u);
+    wave_sync();
+    uint32_t dg[kRunItems], lo[kRunItems], hi[kRunItems], ahead[kRunItems];
+#pragma unroll
+    for (int c = 0; c < kRunItems; ++c) {
+      const bool valid = (wave * kRunItems + c) * 64 + lane < len;
+      dg[c] = ((SPLIT && p >= 4 ? lb[c] : key[c]) >> shift) & 255u;
+      match_byte(dg[c], valid, lo[c], hi[c]);
+      const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi[c], __builtin_amdgcn_mbcnt_lo(lo[c], 0u));
+      ahead[c] = before;
+      if (valid && before == 0u) ahead[c] = atomicAdd(&cnt[wave][dg[c]], (uint32_t)(__popc(lo[c]) + __popc(hi[c])));
+    }
+#pragma unroll
+    for (int c = 0; c < kRunItems; ++c) {
+      // the first lane of each digit holds the wavefront's earlier elements of it
+      const int leader = lo[c] ? __ffs((int)lo[c]) - 1 : (hi[c] ? 31 + __ffs((int)hi[c]) : lane);
+      const uint32_t base = __shfl(ahead[c], leader);
+      ahead[c] = leader == lane ? base : base + ahead[c];
+    }
+    __syncthreads();
+    uint32_t c4[kRunWaves], all = 0;
+#pragma unroll
+    for (int v = 0; v < kRunWaves; ++v) {
+      c4[v] = all;
+      all += cnt[v][tid];
+    }
+    const uint32_t incl = wave_scan_incl(all);
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    uint32_t start = incl - all;
+#pragma unroll
+    for (int v = 0; v < kRunWaves; ++v) start += v < wave ? wave_tot[v] : 0u;
+#pragma unroll
+    for (int v = 0; v < kRunWaves; ++v) cnt[v][tid] = start + c4[v];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kRunItems; ++c) {
+      if ((wave * kRunItems + c) * 64 + lane < len) {
+        const uint32_t at = cnt[wave][dg[c]] + ahead[c];
+        buf[at] = ((unsigned long long)key[c] << 32) | (unsigned long long)(uint32_t)val[c];
+        if (SPLIT) lab[at] = lb[c];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kRunItems; ++c) {
+      const int e = (wave * kRunItems + c) * 64 + lane;
+      if (e < len) {
         const unsigned long long kv = buf[e];
         key[c] = (uint32_t)(kv >> 32);
         val[c] = (int32_t)(uint32_t)kv;
+        if (SPLIT) lb[c] = lab[e];
       }
     }
-    __syncthreads();
   }
 #pragma unroll
-  for (int c = 0; c < kSmallSortItems; ++c) {
-    const int e = (wave * kSmallSortItems + c) * 64 + lane;
-    if (e < n) {
-      keys_out[b0 + e] = key[c];
-      vals_out[b0 + e] = val[c];
+  for (int c = 0; c < kRunItems; ++c) {
+    const int e = (wave * kRunItems + c) * 64 + lane;
+    if (e < len) {
+      if (SPLIT) out.label[beg + e] = lb[c];
+      if (FINISH) {
+        finish_position(w, beg + e, key[c], val[c], edf);
+      } else {
+        out.key[beg + e] = key[c];
+        out.pos[beg + e] = val[c];
+      }
     }
   }
 }
 
+// Merges up to `ways` sorted runs of run_chunks * kRun elements of the same application.  A workgroup owns a quarter of a
+// chunk of one run, one element per thread; the place of an element is its place in its own run plus, for every sibling run, the
+// number of elements there that precede it (equal keys: the earlier run first, so the order is stable).  A sibling is looked
+// at in chunks of kRun: the chunks that lie wholly before or wholly behind the workgroup's own elements are settled by their
+// first and last key, the others (one to three per sibling, for keys in no particular order) are brought into LDS, kBatch of
+// them in one trip to memory, and searched.  Bound by three dependent
+// trips to memory and by the searches (four instructions for each of eleven steps, element and chunk), which a quarter of a
+// chunk per workgroup spreads over the chip: 15 us with whole chunks, 6.7 with quarters (65,536 requests of 8 applications).
+template <bool SPLIT, bool FINISH>
+__global__ __launch_bounds__(kRunThreads) void k_merge_runs(SortPlan sp, SortedRun in, SortedRun out, int run_chunks, int ways,
+                                                            int n, Window w, int edf) {
+  typedef typename std::conditional<SPLIT, unsigned long long, uint32_t>::type K;     // label << 32 | key, or the key
+  constexpr int kBatch = 8;                                    // chunks brought into LDS together
+  __shared__ K chunk[kBatch][kRun];
+  __shared__ int32_t active[kRunThreads];
+  __shared__ int n_active;
+  __shared__ uint32_t whole;                                   // elements of chunks that lie wholly before
+  const int tid = threadIdx.x;
+  if (FINISH) finish_rest<1>(w, n, sp.nseg, sp.seg);
+  int s0, beg, end, se;
+  if (!my_run<kRunItems>(sp, s0, beg, end, se)) return;
+  const int na = se - s0, len = end - beg, o = beg - s0;
+  // chunk numbers inside the application (a run starts at a multiple of kRun): the runs merged here are the chunks
+  // [c0, c1), this workgroup's own run the chunks [m0, m1)
+  const int n_chunks = (na + kRun - 1) / kRun, mine = o / kRun;
+  const int c0 = mine / (run_chunks * ways) * (run_chunks * ways), c1 = min(c0 + run_chunks * ways, n_chunks);
+  const int m0 = mine / run_chunks * run_chunks, m1 = min(m0 + run_chunks, n_chunks);
+  auto load_key = [&](int e) -> K {                            // e: element of the application
+    if constexpr (SPLIT) return ((unsigned long long)in.label[s0 + e] << 32) | in.key[s0 + e];
+    else return in.key[s0 + e];
+  };
+  const K key = tid < len ? load_key(o + tid) : ~K(0);
+  const int32_t val = tid < len ? in.pos[beg + tid] : 0;
+  uint32_t rank = (uint32_t)(o - m0 * kRun) + tid;
+  if (c1 - c0 > m1 - m0) {                                     // (uniform) there are siblings
+    const K first_key = load_key(o), last_key = load_key(o + len - 1);
+    for (int cb = c0; cb < c1; cb += kRunThreads) {
+      // (these keys travel with the elements' own: one trip to memory for both)
+      const int ch = cb + tid;
+      const bool sibling = ch < c1 && !(ch >= m0 && ch < m1);
+      K kf = 0, kl = 0;
+      if (sibling) {
+        kf = load_key(ch * kRun);
+        kl = load_key(min(ch * kRun + kRun, na) - 1);
+      }
+      if (tid == 0) {
+        n_active = 0;
+        whole = 0u;
+      }
+      __syncthreads();
+      if (sibling) {
+        const bool earlier = ch < m0;                          // an earlier run goes first among equal keys
+        if (earlier ? kl <= first_key : kl < first_key) atomicAdd(&whole, (uint32_t)(min(ch * kRun + kRun, na) - ch * kRun));
+        else if (earlier ? kf <= last_key : kf < last_key) active[atomicAdd(&n_active, 1)] = ch;
+      }
+      __syncthreads();
+      const int n_act = n_active;
+      const uint32_t n_whole = whole;
+      rank += n_whole;
+      for (int q0 = 0; q0 < n_act; q0 += kBatch) {
+        // all loads of the batch go out before the first is stored; what lies behind the last element or the last chunk
+        // sorts last and is not counted
+        K in_flight[kBatch][kRunItems];
+        int id_q[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) id_q[q] = q0 + q < n_act ? __builtin_amdgcn_readfirstlane(active[q0 + q]) : n_chunks;
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q)
+#pragma unroll
+          for (int c = 0; c < kRunItems; ++c) {
+            const int e = id_q[q] * kRun + c * kRunThreads + tid;
+            in_flight[q][c] = ~K(0);
+            if (e < na) in_flight[q][c] = load_key(e);
+          }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q)
+#pragma unroll
+          for (int c = 0; c < kRunItems; ++c) chunk[q][c * kRunThreads + tid] = in_flight[q][c];
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < kBatch; h += 4) {                  // the searches of four chunks side by side
+          if (q0 + h >= n_act) break;
+          uint32_t at[4];
+          K less[4];                                           // counted is what is less than this
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            at[q] = 0;
+            less[q] = id_q[h + q] < m0 ? key + 1 : key;
+          }
+#pragma unroll
+          for (int step = kRun / 2; step > 0; step >>= 1)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) at[q] += chunk[h + q][at[q] + step - 1] < less[q] ? step : 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const uint32_t clen = (uint32_t)max(0, min(kRun, na - id_q[h + q] * kRun));
+            at[q] += chunk[h + q][at[q]] < less[q] ? 1 : 0;
+            // (the largest key of all, in an earlier run: everything there goes first)
+            if (id_q[h + q] < m0 && key == ~K(0)) at[q] = clen;
+            rank += min(at[q], clen);
+          }
+        }
+        __syncthreads();
+      }
+      __syncthreads();                                         // n_active and whole are cleared for the next chunks
+    }
+  }
+  if (tid >= len) return;
+  const int at = s0 + c0 * kRun + (int)rank;
+  if constexpr (SPLIT) out.label[at] = (uint32_t)(key >> 32);
+  if (FINISH) {
+    finish_position(w, at, (uint32_t)key, val, edf);
+  } else {
+    out.key[at] = (uint32_t)key;
+    out.pos[at] = val;
+  }
+}
+
+// ---- the same for long windows: radix passes, then a gather ----
+
 // Subgroup codes as sort keys, in the current order of the passes' values (grouped positions).
 __global__ void k_gather_sub_keys(int n_valid_at, const int32_t* __restrict__ seg, const int32_t* __restrict__ grouped_pos,
-                                  const int32_t* __restrict__ sub_g, uint32_t* __restrict__ keys) {
+                                  const int32_t* __restrict__ sub_g, uint32_t* __restrict__ keys, const State* st) {
+  if (st->err & kErrSortSync) return;                  // (the passes have left positions unwritten)
   const int pos = blockIdx.x * blockDim.x + threadIdx.x;
   if (pos < seg[n_valid_at]) keys[pos] = (uint32_t)sub_g[grouped_pos[pos]];
+}
+
+// After the last pass: positions of the application-grouped array travelled as values.
+__global__ void k_finish_order(int n, int n_valid_at, const int32_t* __restrict__ seg, const int32_t* __restrict__ grouped_pos,
+                               const uint32_t* __restrict__ sorted_keys, Window w, int edf) {
+  finish_rest<1>(w, n, n_valid_at, seg);
+  if (w.st->err & kErrSortSync) return;                // (the passes have left positions unwritten)
+  const int pos = blockIdx.x * kRunThreads + threadIdx.x;
+  if (pos < seg[n_valid_at]) finish_position(w, pos, sorted_keys[pos], grouped_pos[pos], edf);
 }
 
 // Range of every possible (application, subgroup code) pair in the service order: two binary searches on
@@ -649,34 +1076,6 @@ __global__ void k_copy_outputs(int n, Window w, int32_t* __restrict__ model, int
   if (round_of) round_of[i] = w.round_of[i];
   if (order_of) order_of[i] = w.order_of[i];
   if (util) util[i] = w.util[i];
-}
-
-// After the last pass.  The passes carried positions of the application-grouped array as values and the
-// inverted key bits as keys, so per service position: id, deadline and weight come with one gather of the
-// record the scoring kernel left at the grouped position, the key straight from the sorted key bits.
-__global__ void k_finish_order(int n, int n_valid_at /*index into seg*/, const int32_t* __restrict__ seg,
-                               const int32_t* __restrict__ grouped_pos, const uint32_t* __restrict__ sorted_keys,
-                               Window w, int edf) {
-  const int pos = blockIdx.x * blockDim.x + threadIdx.x;
-  if (pos >= n) return;
-  const int nv = seg[n_valid_at];
-  if (pos < nv) {
-    const float4 rc = w.rec_g[grouped_pos[pos]];          // one 16-byte gather per request
-    const int id = __float_as_int(rc.x);
-    w.id_s[pos] = id;
-    w.D_s[pos] = rc.y;
-    w.w_s[pos] = rc.z;
-    // the passes sorted the inverted key bits, or (earliest deadline first) the deadline bits
-    w.key_s[pos] = edf ? w.key[id] : __uint_as_float(~sorted_keys[pos]);
-    w.alive_s[pos] = 1;
-  } else {
-    w.alive_s[pos] = 0;
-  }
-  // per-request outputs back to "not served" (indexed by request id: every id in [0, n) once)
-  w.model[pos] = -1;
-  w.round_of[pos] = -1;
-  w.order_of[pos] = 0;
-  w.util[pos] = 0.f;
 }
 
 }  // namespace sp

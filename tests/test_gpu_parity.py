@@ -1038,3 +1038,77 @@ def test_streamed_rows_of_any_scale(gpu, hidden):
     assert np.all(np.isnan(ea[13, :int(w.profile.n_models[a])]))
     keep = np.arange(300) != 13
     parity.assert_close("EA", ea[keep], ref_ea[keep], TOL)
+
+
+def _service_order(w, key, edf=False):
+    """Requests of each application by descending key (ascending deadline), equal ones by id: whole numbers, no tolerance."""
+    out = []
+    for a in range(int(w.profile.n_apps)):
+        ids = np.nonzero(w.requests.app == a)[0]
+        by = w.requests.deadline_rel_ms[ids] if edf else -key[ids].astype(np.float64)
+        out.append(ids[np.argsort(by, kind="stable")])
+    return np.concatenate(out)
+
+
+@pytest.mark.parametrize("policy", ["sneakpeek", "lo_edf"])
+@pytest.mark.parametrize("n,A,ties", [
+    (1, 1, 0), (255, 2, 0), (1023, 1, 0), (1024, 1, 0), (1025, 1, 0), (3000, 1, 3), (4097, 3, 0), (16384, 1, 0), (16385, 1, 2),
+    (17000, 40, 0), (131072, 5, 0), (131073, 200, 5), (262144, 1, 1), (262145, 2, 0), (300001, 255, 4), (5000, 256, 0), (5000, 700, 2)])
+def test_grouping_and_ordering_at_the_edges_of_their_plans(gpu, n, A, ties, policy):
+    """Window lengths at which the number of launches, the tiles or the method change, with the keys the library itself
+    computed: applications of very different sizes (one empty), many equal keys, zero weights (the largest sort key)."""
+    torch, binding = gpu
+    rng = np.random.default_rng(n + A)
+    frac = rng.pareto(1.0, A) + 0.01
+    if A > 2:
+        frac[1] = 0.0
+    w = wl.tiny(seed=8500 + A, n=n, classes=(2,) * A, models=(1,) * A, max_batch=2, feat_dim=8, fractions=tuple(frac / frac.sum()))
+    if ties:
+        w.requests.x[:] = 0.0
+        w.requests.deadline_rel_ms[:] = 10.0 + rng.integers(0, ties, n).astype(np.float32)
+        w.requests.weight[:] = rng.integers(0, 3, n).astype(np.float32)
+    ctx = binding.Context(w.profile, n, policy=wl.named_policy(policy))
+    key = torch.zeros(n, device="cuda:0")
+    order = torch.zeros(n, dtype=torch.int32, device="cuda:0")
+    x, app, D, wt = binding.to_device(w.requests)
+    for _ in range(2):                                  # the second window reuses every buffer
+        ctx.sp_score(x, app, D, wt, key_out=key)
+        ctx.sp_debug_dump(binding.SP_DUMP_ORDER, order)
+        assert np.array_equal(order.cpu().numpy(), _service_order(w, key.cpu().numpy(), edf=policy == "lo_edf"))
+    seg = torch.zeros(A + 1, dtype=torch.int32, device="cuda:0")
+    ctx.sp_debug_dump(binding.SP_DUMP_SEGMENTS, seg)
+    assert np.array_equal(seg.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(w.requests.app, minlength=A))]))
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [900, 5000, 20000, 270000])
+def test_ordering_by_subgroup_and_key(gpu, n):
+    """With data-aware subgroups the order inside an application is (subgroup, key, id) on every plan of the ordering."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8600, n=n, classes=(300, 3), models=(2, 1), max_batch=2, feat_dim=8, fractions=(0.8, 0.2))
+    for a in range(2):
+        w.profile.W1[a] = (w.profile.W1[a] * 12.0).astype(np.float32)          # confident heads: most requests in a subgroup
+    pol = wl.Policy(split_groups=1)
+    ctx = binding.Context(w.profile, n, policy=pol)
+    key = torch.zeros(n, device="cuda:0")
+    order = torch.zeros(n, dtype=torch.int32, device="cuda:0")
+    x, app, D, wt = binding.to_device(w.requests)
+    ctx.sp_score(x, app, D, wt, key_out=key)
+    ctx.sp_debug_dump(binding.SP_DUMP_ORDER, order)
+    z = torch.zeros((n, ctx.c_max), device="cuda:0")
+    ctx.sp_debug_dump(binding.SP_DUMP_LOGITS, z, x=x, app=app)
+    z, key, order = z.cpu().numpy().astype(np.float64), key.cpu().numpy(), order.cpu().numpy()
+    ctx.close()
+    at = 0
+    for a in range(2):
+        ids = np.nonzero(w.requests.app == a)[0]
+        th = orc.posterior(z[ids, :int(w.profile.n_classes[a])])
+        top = th.max(axis=1)
+        label = np.where(top > 0.5, 1 + th.argmax(axis=1), 0)
+        clear = np.abs(top - 0.5) > 1e-4                # (at the threshold either label is right)
+        got = order[at:at + ids.shape[0]]
+        at += ids.shape[0]
+        assert np.array_equal(np.sort(got), ids)
+        keep = np.isin(got, ids[clear])
+        want = ids[clear][np.lexsort((ids[clear], -key[ids[clear]].astype(np.float64), label[clear]))]
+        assert np.array_equal(got[keep], want)
