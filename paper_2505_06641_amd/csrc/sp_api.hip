@@ -69,6 +69,8 @@ struct sp_ctx {
   int32_t spin_limit = kSpinLimit;   // polls before a wait between resident workgroups is given up
   int32_t sort_spin_limit = kSortSpinLimit;   // polls before a radix pass's look-back is given up (< 0: at once)
   long long* h_ticks = nullptr;      // pinned mirror of ps.ticks
+  Decision* h_log = nullptr;         // pinned: the last launch's decisions, written by the rounds kernel
+  std::vector<Decision> log;         // the window's decisions as far as they have come to the host (rounds 0, 1, ...)
   double tick_ms = 0.0;              // milliseconds per timestamp tick
   std::vector<float> round_ms;       // per-round latencies of the last timed sp_schedule on that path
   int32_t rounds_in_call = 0;        // rounds the last sp_schedule call committed
@@ -594,6 +596,12 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
   SP_HIP(c, hipMemset(ps.dec, 0, kPersistRounds * 8));
   SP_HIP(c, hipMemset(ps.ticks, 0, (kPersistRounds + 1) * 8));
   SP_HIP(c, hipHostMalloc((void**)&c->h_ticks, (kPersistRounds + 1) * sizeof(long long), hipHostMallocDefault));
+  SP_HIP(c, hipHostMalloc((void**)&c->h_log, kPersistRounds * sizeof(Decision), hipHostMallocDefault));
+  {
+    void* dp = nullptr;
+    SP_HIP(c, hipHostGetDevicePointer(&dp, c->h_log, 0));
+    ps.log_host = (Decision*)dp;
+  }
   c->gen_base = 0;
   c->persist = true;
   return SP_OK;
@@ -957,8 +965,8 @@ void launch_round(sp_ctx* c, const Window& w, hipStream_t s, int32_t* ids_out, f
     hipLaunchKernelGGL(k_round_commit, dim3(1), dim3(kRoundThreads), 0, s, c->tb, w, ids_out);
 }
 
-// Brings the window state to the host.  mirrored: the last kernel on the stream was k_round_commit, which
-// has written the state into the pinned copy itself; otherwise it is copied here.
+// Brings the window state to the host.  mirrored: a round kernel is on the stream, whose commits write the state into the
+// pinned copy themselves; otherwise it is copied here.
 sp_status fetch_state(sp_ctx* c, hipStream_t s, bool mirrored = false) {
   if (!mirrored) SP_HIP(c, hipMemcpyAsync(c->h_state, c->w.st, sizeof(State), hipMemcpyDeviceToHost, s));
   SP_HIP(c, hipStreamSynchronize(s));
@@ -1019,6 +1027,7 @@ void sp_destroy(sp_ctx* c) {
   for (void* p : c->dev_allocs) (void)hipFree(p);
   if (c->h_state) (void)hipHostFree(c->h_state);
   if (c->h_ticks) (void)hipHostFree(c->h_ticks);
+  if (c->h_log) (void)hipHostFree(c->h_log);
   if (c->h_grp_n) (void)hipHostFree(c->h_grp_n);
   if (c->ev_groups) (void)hipEventDestroy(c->ev_groups);
   for (hipEvent_t e : c->ev)
@@ -1040,6 +1049,7 @@ sp_status sp_score(sp_ctx* c, int32_t n, const void* x_dev, const int32_t* app_d
   c->n = n;
   c->rounds_done = 0;
   c->done = false;
+  c->log.clear();
   w.ea_out = ea_out_dev;
   w.key_out = key_out_dev;
   const bool tm = c->timing && n > 0;
@@ -1086,6 +1096,7 @@ sp_status sp_greedy_round(sp_ctx* c, void* stream, sp_decision* out_host, int32_
   sp_status st = fetch_state(c, s, true);
   if (st != SP_OK) return st;
   if (c->rounds_done == before) return SP_DONE;
+  if ((int32_t)c->log.size() == before) c->log.push_back(c->h_state->last);
   if (out_host) std::memcpy(out_host, &c->h_state->last, sizeof(sp_decision));
   return SP_OK;
 }
@@ -1118,6 +1129,7 @@ sp_status sp_greedy_round_static(sp_ctx* c, void* stream, sp_decision* out_host,
   sp_status st = fetch_state(c, s, true);
   if (st != SP_OK) return st;
   if (c->rounds_done == before) return SP_DONE;
+  if ((int32_t)c->log.size() == before) c->log.push_back(c->h_state->last);
   if (out_host) std::memcpy(out_host, &c->h_state->last, sizeof(sp_decision));
   return SP_OK;
 }
@@ -1145,7 +1157,13 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
     if (max_rounds > 0) chunk = std::min(chunk, start + max_rounds - c->rounds_done);
     if (chunk <= 0) break;
     const int32_t before = c->rounds_done;
+    const Outputs outs{model_out_dev, round_out_dev, order_out_dev, util_out_dev};
+    const bool want_outputs = c->n > 0 && (model_out_dev || round_out_dev || order_out_dev || util_out_dev);
+    // the commit workgroup fills the caller's arrays itself where that is little next to the launch's rounds (not while the
+    // stages are timed: the copy then has a time of its own)
+    const bool outputs_inside = persist && want_outputs && !tm && c->rounds_done == 0 && (int64_t)c->n <= (int64_t)kOutputsPerRound * chunk;
     if (persist) {
+      c->ps.out = outputs_inside ? outs : Outputs{};
       if ((st = launch_rounds_persistent(c, s, chunk)) != SP_OK) return st;
       if (tm && c->timing_rounds)
         SP_HIP(c, hipMemcpyAsync(c->h_ticks, c->ps.ticks, (kPersistRounds + 1) * sizeof(long long), hipMemcpyDeviceToHost, s));
@@ -1156,22 +1174,22 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
       }
     }
     if (tm) SP_HIP(c, hipEventRecord(c->ev[5], s));
-    // the per-request outputs go out right behind the rounds, so that the one host synchronisation of
-    // fetch_state covers them too (a later chunk simply copies again)
-    if (c->n > 0 && (model_out_dev || round_out_dev || order_out_dev || util_out_dev)) {
+    // otherwise they go out right behind the rounds, so that the one host synchronisation of fetch_state covers them too (a
+    // later chunk simply copies again)
+    if (want_outputs && !outputs_inside) {
       const bool tc = tm && !outputs_copied;
       if (tc) SP_HIP(c, hipEventRecord(c->ev[7], s));
-      hipLaunchKernelGGL(k_copy_outputs, dim3((c->n + 255) / 256), dim3(256), 0, s, c->n, c->w, model_out_dev,
-                         round_out_dev, order_out_dev, util_out_dev);
+      hipLaunchKernelGGL(k_copy_outputs, dim3((c->n + 255) / 256), dim3(256), 0, s, c->n, c->w, outs);
       if (tc) {
         SP_HIP(c, hipEventRecord(c->ev[8], s));
         c->timed_copy = true;
       }
-      outputs_copied = true;
     }
-    st = fetch_state(c, s);          // tells how far the device got and whether the queue ran dry
+    outputs_copied = want_outputs;
+    st = fetch_state(c, s, true);    // tells how far the device got and whether the queue ran dry
     fetched = true;
     if (st != SP_OK) return st;
+    if (persist && (int32_t)c->log.size() == before) c->log.insert(c->log.end(), c->h_log, c->h_log + (c->rounds_done - before));
     if (persist && tm && c->timing_rounds)
       for (int i = 0; i < c->rounds_done - before; ++i)
         c->round_ms.push_back((float)((double)(c->h_ticks[i + 1] - c->h_ticks[i]) * c->tick_ms));
@@ -1181,12 +1199,14 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
   c->rounds_in_call = c->rounds_done - start;
   bool pending = false;
   if (c->n > 0 && !outputs_copied && (model_out_dev || round_out_dev || order_out_dev || util_out_dev)) {
-    hipLaunchKernelGGL(k_copy_outputs, dim3((c->n + 255) / 256), dim3(256), 0, s, c->n, c->w, model_out_dev,
-                       round_out_dev, order_out_dev, util_out_dev);
+    hipLaunchKernelGGL(k_copy_outputs, dim3((c->n + 255) / 256), dim3(256), 0, s, c->n, c->w,
+                       Outputs{model_out_dev, round_out_dev, order_out_dev, util_out_dev});
     pending = true;
   }
   const int32_t n_log = std::min(std::min(c->rounds_done, log_capacity), c->w.log_cap);
-  if (n_log > 0) {
+  if (n_log > 0 && (int32_t)c->log.size() == c->rounds_done) {
+    std::memcpy(round_log_host, c->log.data(), (size_t)n_log * sizeof(sp_decision));
+  } else if (n_log > 0) {
     SP_HIP(c, hipMemcpyAsync(round_log_host, c->w.log, (size_t)n_log * sizeof(sp_decision), hipMemcpyDeviceToHost, s));
     pending = true;
   }
@@ -1283,7 +1303,9 @@ sp_status sp_get_timing(sp_ctx* c, sp_timing* out) {
       SP_HIP(c, hipEventSynchronize(c->ev[8]));
       SP_HIP(c, hipEventElapsedTime(&t.copy_outputs_ms, c->ev[7], c->ev[8]));
     }
-    t.utility_evaluations = (int64_t)c->h_state->n_evals;
+    unsigned long long evals = 0;                        // (added up past the last commit: not in the pinned copy of the state)
+    SP_HIP(c, hipMemcpy(&evals, &c->w.st->n_evals, sizeof(evals), hipMemcpyDeviceToHost));
+    t.utility_evaluations = (int64_t)evals;
   }
   *out = t;
   return SP_OK;

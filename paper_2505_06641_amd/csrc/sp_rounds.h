@@ -41,6 +41,33 @@ __device__ __forceinline__ double block_sum_f64(double v, double* scratch, int n
   return scratch[0];
 }
 
+// Three sums over the members of a batch (one term per thread of the first kMaxBatch), in the order of the tree above: the
+// first two of its levels add zeros, the next three are taken by the first wavefront from LDS behind one barrier, the last
+// six in registers.  The results are valid on thread 0.  (A commit used to pass thirty barriers; it is what remains of a
+// launch after its last decision, and half of a round that is a call of its own.)
+__device__ __forceinline__ void batch_sums(double& a, double& b, double& c, double (*scratch)[kMaxBatch]) {
+  const int tid = threadIdx.x;
+  if (tid < kMaxBatch) {
+    scratch[0][tid] = a;
+    scratch[1][tid] = b;
+    scratch[2][tid] = c;
+  }
+  __syncthreads();
+  if (tid < kWave) {
+    double v[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double* s = scratch[k] + tid;
+      v[k] = (s[0] + s[128]) + (s[64] + s[192]);
+#pragma unroll
+      for (int o = kWave / 2; o > 0; o >>= 1) v[k] += __shfl_down(v[k], o);
+    }
+    a = v[0];
+    b = v[1];
+    c = v[2];
+  }
+}
+
 // When a batch on variant m of application a starts computing: now, plus the variant's swap-in cost
 // unless the previous batch of the window ran the same variant (Sec. 3.1 "context switch time";
 // Sec. 5.2 model locality).  prev.app is -1 before the first batch.
@@ -276,12 +303,18 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_score(Tables tb, Window
   if (tid == 0) w.cand[blockIdx.x] = best;
 }
 
+// The caller's per-request arrays (any of them may be null).
+struct Outputs {
+  int32_t *model, *round_of, *order_of;
+  float* util;
+};
+
 // Members of one batch: outputs, pending flags and the three sums.  pos_of(j) gives the service position
-// of the j-th member.  All threads of the workgroup call it; the sums come back on every thread.
+// of the j-th member.  All threads of the workgroup call it; the sums come back on thread 0.
 template <class PosFn>
-__device__ __forceinline__ void commit_members(const Tables& tb, const Window& w, int a, int m, int b, int r,
+__device__ __forceinline__ void commit_members(const Tables& tb, const Window& w, const Outputs& out, int a, int m, int b, int r,
                                                int next_order, double E, PosFn pos_of, int32_t* ids_out,
-                                               double* dsum, double& wu, double& su, double& viol) {
+                                               double (*dsum)[kMaxBatch], double& wu, double& su, double& viol) {
   const int kind = tb.penalty[a];
   wu = 0.0; su = 0.0; viol = 0.0;
   for (int j = threadIdx.x; j < b; j += kRoundThreads) {
@@ -293,6 +326,10 @@ __device__ __forceinline__ void commit_members(const Tables& tb, const Window& w
     w.round_of[id] = r;
     w.order_of[id] = next_order + j;
     w.util[id] = u;
+    if (out.model) out.model[id] = m;
+    if (out.round_of) out.round_of[id] = r;
+    if (out.order_of) out.order_of[id] = next_order + j;
+    if (out.util) out.util[id] = u;
     w.alive_s[pos] = 0;
     w.last_ids[j] = id;
     if (ids_out) ids_out[j] = id;
@@ -300,9 +337,7 @@ __device__ __forceinline__ void commit_members(const Tables& tb, const Window& w
     su += (double)u;
     viol += fmax(0.0, E - (double)D);
   }
-  wu = block_sum_f64(wu, dsum);
-  su = block_sum_f64(su, dsum);
-  viol = block_sum_f64(viol, dsum);
+  batch_sums(wu, su, viol, dsum);
 }
 
 // The window state as the host will read it after this kernel: written straight into pinned host memory by
@@ -318,7 +353,7 @@ __device__ __forceinline__ void mirror_state(const Window& w) {
 
 __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Window w, int32_t* __restrict__ ids_out) {
   __shared__ unsigned long long red[kRoundThreads / 64];
-  __shared__ double dsum[kRoundThreads];
+  __shared__ double dsum[3][kMaxBatch];
   State* st = w.st;
   const int tid = threadIdx.x;
   if (st->done || st->err) {
@@ -371,7 +406,7 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Windo
   const double E = start_time(tb, st->last, t, a, m) + (double)tb.lat[((int64_t)a * tb.Mmax + m) * B + (b - 1)];
   double wu, su, viol;
   const int32_t* row = w.win_pos + grp * B;
-  commit_members(tb, w, a, m, b, r, next_order, E, [&](int j) { return row[j]; }, ids_out, dsum, wu, su, viol);
+  commit_members(tb, w, Outputs{}, a, m, b, r, next_order, E, [&](int j) { return row[j]; }, ids_out, dsum, wu, su, viol);
   if (tid == 0) {
     Decision dc;
     dc.app = a; dc.model = m; dc.batch = b; dc.round = r;

@@ -49,8 +49,11 @@ constexpr int kSpinLimit = 1 << 20;             // polls before a wait is given 
 constexpr uint32_t kGenMask = 0x7FFFFFu;        // generation bits carried in a slot's first word
 constexpr int kMaxPairs = 1024;                 // (application, variant) pairs the reducer can hold
 constexpr int kSlotsPerThread = kMaxPairs / kRoundThreads;
+// Requests per round of a window's first launch up to which the commit workgroup also fills the caller's outputs (one CU writes
+// about 130 GB/s, beside rounds of 4 us and more that keep it busy for half of their time): a launch and its gap less per call.
+constexpr int kOutputsPerRound = 1024;
 constexpr int kMaxAppGroups = 64;               // groups of one application a resident pair can serve
-constexpr int kAllToAllPairs = 128;             // up to this many pairs, every pair polls every slot itself
+constexpr int kAllToAllPairs = 2 * kWave;       // up to this many pairs, every pair polls every slot itself (two per lane)
 static_assert(kWinCap <= kRoundThreads, "one window entry per thread");
 
 struct Persist {
@@ -66,6 +69,8 @@ struct Persist {
                                 //   << 32 | gen; swap-in cost bits << 32 | gen; unused
   unsigned long long* ring;     // [kPersistRounds, A, B]: generation << 32 | service position
   unsigned long long* dec;      // [kPersistRounds]: decision of each round, bit 63 set; zero once consumed
+  Outputs out;                  // the caller's arrays, when this launch starts a window and fills them (else null)
+  Decision* log_host;           // [kPersistRounds] pinned: the launch's decisions for the host
   long long* ticks;             // [kPersistRounds + 1]: constant-rate timestamps, launch start then each decision
 };
 
@@ -86,10 +91,42 @@ __device__ __forceinline__ unsigned long long slot_word0(float score, uint32_t g
          (valid ? 0x100ull : 0ull) | (unsigned long long)((b - 1) & 0xff);
 }
 
-__device__ void persist_commit_loop(const Tables& tb, const Window& w, const Persist& ps, double* dsum,
+__device__ __forceinline__ void copy_output(int i, const Window& w, const Outputs& out) {
+  if (out.model) out.model[i] = w.model[i];
+  if (out.round_of) out.round_of[i] = w.round_of[i];
+  if (out.order_of) out.order_of[i] = w.order_of[i];
+  if (out.util) out.util[i] = w.util[i];
+}
+
+// The four per-request outputs into the caller's arrays, in a launch of its own: for long windows.
+__global__ void k_copy_outputs(int n, Window w, Outputs out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) copy_output(i, w, out);
+}
+
+// One of the caller's arrays filled by one workgroup, 16 bytes per store (its start need not be aligned to them).
+__device__ __forceinline__ void fill_output(int32_t* out, int n, int32_t v) {
+  if (out == nullptr) return;
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+  for (int i = 4 * threadIdx.x; i + 4 <= n; i += 4 * kRoundThreads) *reinterpret_cast<i32x4*>(out + i) = i32x4{v, v, v, v};
+  if ((int)threadIdx.x < (n & 3)) out[(n & ~3) + threadIdx.x] = v;
+}
+
+__device__ void persist_commit_loop(const Tables& tb, const Window& w, const Persist& ps, double (*dsum)[kMaxBatch],
                                     unsigned long long* bcast) {
   State* st = w.st;
   const int tid = threadIdx.x;
+  // the caller's arrays as a window without rounds leaves them, before this workgroup's own commits go into both (it has
+  // nothing to do until the first decision, and is ahead of the rounds after it)
+  fill_output(ps.out.model, w.n, -1);
+  fill_output(ps.out.round_of, w.n, -1);
+  fill_output(ps.out.order_of, w.n, 0);
+  fill_output(reinterpret_cast<int32_t*>(ps.out.util), w.n, 0);
+  if (st->done || st->err) {
+    if (tid == 0) mirror_state(w);
+    return;
+  }
+  __syncthreads();
   int r = st->round, next_order = st->next_order, n_sched = st->n_sched;
   double t = st->t, twu = st->total_wu, tu = st->total_u, tv = st->total_viol;
   bool done = false, failed = false, any = false;
@@ -123,7 +160,7 @@ __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Per
     const unsigned long long* row = ps.ring + ((size_t)rl * tb.A + a) * B;
     bool lost = false;
     double wu, su, viol;
-    commit_members(tb, w, a, m, b, r, next_order, E,
+    commit_members(tb, w, ps.out, a, m, b, r, next_order, E,
                    [&](int j) {
                      unsigned long long e = 0ull;
                      for (int i = 0; i < ps.spin_limit; ++i) {
@@ -139,7 +176,10 @@ __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Per
     last.app = a; last.model = m; last.batch = b; last.round = r;
     last.t_start = t; last.t_end = E; last.score = score; last.batch_utility = (float)wu;
     any = true;
-    if (tid == 0 && r < w.log_cap) w.log[r] = last;
+    if (tid == 0) {
+      if (r < w.log_cap) w.log[r] = last;
+      ps.log_host[rl] = last;
+    }
     t = E; r += 1; next_order += b; n_sched += b;
     twu += wu; tu += su; tv += viol;
   }
@@ -149,12 +189,29 @@ __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Per
     if (any) st->last = last;
     if (done) st->done = 1;
     if (failed) atomicOr(&st->err, kErrSync);
+    mirror_state(w);                        // the host reads this copy: nothing is copied behind the kernel
   }
+}
+
+// The best of a set of candidates, with the latency and the swap-in cost that its pair has published.
+struct Best {
+  unsigned long long word;      // packed candidate, 0: none
+  float lat, swap;
+};
+// Over a wavefront (candidate ids are unique, so one lane holds the maximum).
+__device__ __forceinline__ Best wave_best(unsigned long long word, float lat, float swap) {
+  Best b;
+  b.word = wave_max_u64(word);
+  const unsigned long long who = __ballot(word == b.word);
+  const int lane = __builtin_amdgcn_readfirstlane(__ffsll((long long)who) - 1);
+  b.lat = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lat), lane));
+  b.swap = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(swap), lane));
+  return b;
 }
 
 // The reducing workgroup: maximum over the pairs' slots of every round, published as the decision.
 __device__ void persist_reduce_loop(const Tables& tb, const Window& w, const Persist& ps, unsigned long long* red,
-                                    float* lat_win, float* swap_win, int* timed_out) {
+                                    Best (*waves)[kRoundThreads / 64], int* timed_out) {
   const int tid = threadIdx.x;
   const int B = tb.B;
   if (ps.all_to_all) return;                      // every pair takes the maximum itself
@@ -219,27 +276,30 @@ __device__ void persist_reduce_loop(const Tables& tb, const Window& w, const Per
       if (a_star >= 0 && (int)(cid / (uint32_t)B) / tb.Mmax != a_star) continue;
       if (held[q] > mine) { mine = held[q]; mine_lat = held_lat[q]; mine_swap = held_swap[q]; }
     }
-    const unsigned long long all = block_max_u64(mine, red);
-    if (all != 0ull && mine == all) {                         // candidate ids are unique: one writer
-      *lat_win = mine_lat;
-      *swap_win = mine_swap;
+    // the wavefronts' maxima with what belongs to them, then one barrier; the array alternates between rounds
+    {
+      const Best b = wave_best(mine, mine_lat, mine_swap);
+      if ((tid & 63) == 0) waves[rl & 1][tid >> 6] = b;
     }
     __syncthreads();
     if (*timed_out) {
       if (tid == 0) atomicOr(&w.st->err, kErrSync);
       break;
     }
+    Best top1 = waves[rl & 1][0];
+    for (int i = 1; i < kRoundThreads / 64; ++i)
+      if (waves[rl & 1][i].word > top1.word) top1 = waves[rl & 1][i];
+    const unsigned long long all = top1.word;
     if (tid == 0) {
       unsigned long long* d = ps.decision + (size_t)(gen & 1u) * 4;
       const uint32_t cidp1 = all != 0ull ? (0xFFFFFFFFu - (uint32_t)(all & 0xFFFFFFFFull)) + 1u : 0u;
-      st_dev(d, ((unsigned long long)__float_as_uint(all != 0ull ? *lat_win : 0.f) << 32) | (unsigned long long)gen);
+      st_dev(d, ((unsigned long long)__float_as_uint(all != 0ull ? top1.lat : 0.f) << 32) | (unsigned long long)gen);
       st_dev(d + 1, ((unsigned long long)cidp1 << 32) | (unsigned long long)gen);
-      st_dev(d + 2, ((unsigned long long)__float_as_uint(all != 0ull ? *swap_win : 0.f) << 32) | (unsigned long long)gen);
+      st_dev(d + 2, ((unsigned long long)__float_as_uint(all != 0ull ? top1.swap : 0.f) << 32) | (unsigned long long)gen);
       st_dev(ps.dec + rl, all | (1ull << 63));
       ps.ticks[rl + 1] = wall_clock64();
     }
     if (all == 0ull) break;                                    // nothing live anywhere
-    __syncthreads();                                           // lat_win and swap_win are rewritten next round
   }
 }
 
@@ -288,19 +348,25 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
   __shared__ float lat_s[kMaxBatch];
   __shared__ int32_t wave_cnt[kRoundThreads / 64], keep_cnt[kRoundThreads / 64];
   __shared__ unsigned long long red[kRoundThreads / 64];
-  __shared__ double dsum[kRoundThreads];
-  __shared__ float lat_win, swap_win;
-  __shared__ uint32_t cid_win;
+  __shared__ unsigned long long cand_max[2][kRoundThreads / 64];   // a round's candidates per wavefront (alternating)
+  __shared__ Best waves[2][kRoundThreads / 64];
+  // block_sum_f64's scratch, or the commit workgroup's
+  __shared__ union { double one[kRoundThreads]; double three[3][kMaxBatch]; } dsum;
+  __shared__ struct { uint32_t cid; float lat, swap; } decided[2];   // a round's decision (alternating)
   __shared__ int timed_out;
+  __shared__ int32_t slot_model[kAllToAllPairs];                // variants behind the slots
   __shared__ int32_t head_s[kMaxAppGroups];                     // head pointer of each group of the application
   __shared__ unsigned long long sec_best[kRoundThreads / 64], sec_top[kRoundThreads / 64];   // per wavefront: its secondary groups' best
   __shared__ float sec_prio[kRoundThreads / 64];
   extern __shared__ __align__(16) unsigned char sec_lds[];      // with subgroups: per wavefront B window entries and B positions
   State* st = w.st;
+  if ((int)blockIdx.x == ps.n_pairs + 1) {
+    persist_commit_loop(tb, w, ps, dsum.three, red);
+    return;
+  }
   if (st->done || st->err) return;          // the state is rewritten only when the commit workgroup ends
-  if ((int)blockIdx.x >= ps.n_pairs) {
-    if ((int)blockIdx.x == ps.n_pairs) persist_reduce_loop(tb, w, ps, red, &lat_win, &swap_win, &timed_out);
-    if ((int)blockIdx.x == ps.n_pairs + 1) persist_commit_loop(tb, w, ps, dsum, red);
+  if ((int)blockIdx.x == ps.n_pairs) {
+    persist_reduce_loop(tb, w, ps, red, waves, &timed_out);
     return;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -352,7 +418,7 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
     timed_out = 0;
     if (ps.all_to_all && pair == 0) ps.ticks[0] = wall_clock64();
   }
-  const int slot_model = ps.all_to_all && tid < ps.n_pairs ? ps.pair_model[tid] : 0;   // variant behind the slot this thread polls
+  if (ps.all_to_all && tid < ps.n_pairs) slot_model[tid] = ps.pair_model[tid];
   float4* went = reinterpret_cast<float4*>(sec_lds) + (size_t)wave * B;
   int32_t* wpos = reinterpret_cast<int32_t*>(sec_lds + (size_t)(kRoundThreads / 64) * B * sizeof(float4)) + (size_t)wave * B;
   __syncthreads();
@@ -415,9 +481,9 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
         before += __popcll(bal & ((1ull << lane) - 1ull));
         if (keep) { win[before] = pos; ent[before] = e; om[before] = ov; }
         nb = total;
+        __syncthreads();
       }
       shift = 0;
-      __syncthreads();
     }
 
     // Walks on through the service order from scan_end and appends the live requests it meets, for at
@@ -491,7 +557,7 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
                            (uint32_t)((gprim * tb.Mmax + m) * B), nullptr, tb.pol_whole ? nbe : 0);
     float prio = 0.f;
     if (tb.pol_group_first) {          // eq. (14) over the window, the same fixed-order sum as in k_round_score
-      const double psum = block_sum_f64(tid < nbe ? (double)om[tid] : 0.0, dsum);
+      const double psum = block_sum_f64(tid < nbe ? (double)om[tid] : 0.0, dsum.one);
       prio = nbe > 0 ? (float)(psum / (double)nbe) : 0.f;
     }
     if (SPLIT && ng > 1 && lane == 0) {
@@ -499,10 +565,13 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
       sec_top[wave] = wtop;
       sec_prio[wave] = wprio;
     }
-    best = block_max_u64(best, red);     // (its barriers also make the wavefronts' secondary results visible)
+    best = wave_max_u64(best);
+    if (lane == 0) cand_max[rl & 1][wave] = best;
+    __syncthreads();                     // (also makes the wavefronts' secondary results visible)
 
     // ---- publish this pair's best candidate over its groups ----
     if (tid == 0) {
+      for (int i = 1; i < kRoundThreads / 64; ++i) best = cand_max[rl & 1][i] > best ? cand_max[rl & 1][i] : best;
       if (SPLIT && ng > 1) {
         if (tb.pol_group_first) {
           // first the group with the highest priority among those that have a candidate, then its candidate
@@ -530,83 +599,91 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
     // (three dependent trips to memory, about twice the exchange: only once less than two windows are left)
     if (nb < min(2 * Bw, cap) && scan_end < seg_e) walk(1, 4);
 
-    // ---- few pairs: the maximum over all pairs' slots, taken here (the reducer's rule on the same words) ----
-    if (ps.all_to_all) {
-      unsigned long long mine = 0ull, top = 0ull;
-      float mine_lat = 0.f, mine_swap = 0.f;
-      if (tid < ps.n_pairs) {
-        const unsigned long long* slot = ps.slots + ((size_t)(gen & 1u) * ps.n_pairs + tid) * 4;
-        unsigned long long v0 = 0ull, v1 = 0ull, v2 = 0ull, v3 = 0ull;
+    // ---- few pairs: the first wavefront takes the maximum over all pairs' slots (the reducer's rule on the same words), two
+    // slots per lane, and passes it on behind one barrier; else its first lane waits for the reducer's decision ----
+    if (wave == 0) {
+      if (ps.all_to_all) {
+        unsigned long long mine = 0ull, top = 0ull;
+        float mine_lat = 0.f, mine_swap = 0.f;
+        unsigned long long held[2] = {0ull, 0ull};
+        float held_lat[2] = {0.f, 0.f}, held_swap[2] = {0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int i = lane + q * kWave;
+          if (i >= ps.n_pairs) continue;
+          const unsigned long long* slot = ps.slots + ((size_t)(gen & 1u) * ps.n_pairs + i) * 4;
+          unsigned long long v0 = 0ull, v1 = 0ull, v2 = 0ull, v3 = 0ull;
+          bool ok = false;
+          for (int k = 0; k < ps.spin_limit; ++k) {
+            v0 = ld_dev(slot);
+            v1 = ld_dev(slot + 1);
+            v2 = ld_dev(slot + 2);
+            v3 = ld_dev(slot + 3);
+            ok = ((uint32_t)(v0 >> 9) & kGenMask) == (gen & kGenMask) && (uint32_t)(v1 & 0xFFFFull) == (gen & 0xFFFFu) &&
+                 (uint32_t)(v2 & 0xFFFFFFFFull) == gen && (uint32_t)(v3 & 0xFFFFFFFFull) == gen;
+            if (ok) break;
+            __builtin_amdgcn_s_sleep(1);
+          }
+          if (!ok) {
+            timed_out = 1;
+          } else if (v0 & 0x100ull) {
+            const int pg = (int)((uint32_t)(v1 >> 16) & 0xFFFFu);
+            const uint32_t c2 = (uint32_t)((pg * tb.Mmax + slot_model[i]) * B) + (uint32_t)(v0 & 0xffull);
+            held[q] = pack_candidate(__uint_as_float((uint32_t)(v0 >> 32)), c2);
+            held_lat[q] = __uint_as_float((uint32_t)(v1 >> 32));
+            held_swap[q] = __uint_as_float((uint32_t)(v2 >> 32));
+            const unsigned long long pt = ((unsigned long long)ordered_bits(__uint_as_float((uint32_t)(v3 >> 32))) << 32) |
+                                          (unsigned long long)(0xFFFFFFFFu - (uint32_t)pg);
+            top = pt > top ? pt : top;
+          }
+        }
+        int g_star = -1;                                         // -1: every group competes
+        if (tb.pol_group_first) {
+          top = wave_max_u64(top);
+          if (top != 0ull) g_star = (int)(0xFFFFFFFFu - (uint32_t)(top & 0xFFFFFFFFull));
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const uint32_t c2 = 0xFFFFFFFFu - (uint32_t)(held[q] & 0xFFFFFFFFull);
+          if (held[q] == 0ull || (g_star >= 0 && (int)(c2 / (uint32_t)B) / tb.Mmax != g_star)) continue;
+          if (held[q] > mine) { mine = held[q]; mine_lat = held_lat[q]; mine_swap = held_swap[q]; }
+        }
+        const Best all = wave_best(mine, mine_lat, mine_swap);
+        if (lane == 0) {
+          decided[rl & 1].cid = all.word != 0ull ? (0xFFFFFFFFu - (uint32_t)(all.word & 0xFFFFFFFFull)) + 1u : 0u;
+          decided[rl & 1].lat = all.lat;
+          decided[rl & 1].swap = all.swap;
+          if (pair == 0) {                                       // for the commit workgroup, and the round's timestamp
+            st_dev(ps.dec + rl, all.word | (1ull << 63));
+            ps.ticks[rl + 1] = wall_clock64();
+          }
+        }
+      } else if (lane == 0) {
+        const unsigned long long* d = ps.decision + (size_t)(gen & 1u) * 4;
+        unsigned long long v0 = 0ull, v1 = 0ull, v2 = 0ull;
         bool ok = false;
         for (int k = 0; k < ps.spin_limit; ++k) {
-          v0 = ld_dev(slot);
-          v1 = ld_dev(slot + 1);
-          v2 = ld_dev(slot + 2);
-          v3 = ld_dev(slot + 3);
-          ok = ((uint32_t)(v0 >> 9) & kGenMask) == (gen & kGenMask) && (uint32_t)(v1 & 0xFFFFull) == (gen & 0xFFFFu) &&
-               (uint32_t)(v2 & 0xFFFFFFFFull) == gen && (uint32_t)(v3 & 0xFFFFFFFFull) == gen;
+          v0 = ld_dev(d);
+          v1 = ld_dev(d + 1);
+          v2 = ld_dev(d + 2);
+          ok = (uint32_t)(v0 & 0xFFFFFFFFull) == gen && (uint32_t)(v1 & 0xFFFFFFFFull) == gen &&
+               (uint32_t)(v2 & 0xFFFFFFFFull) == gen;
           if (ok) break;
           __builtin_amdgcn_s_sleep(1);
         }
-        if (!ok) {
-          timed_out = 1;
-        } else if (v0 & 0x100ull) {
-          const int pg = (int)((uint32_t)(v1 >> 16) & 0xFFFFu);
-          const uint32_t c2 = (uint32_t)((pg * tb.Mmax + slot_model) * B) + (uint32_t)(v0 & 0xffull);
-          mine = pack_candidate(__uint_as_float((uint32_t)(v0 >> 32)), c2);
-          mine_lat = __uint_as_float((uint32_t)(v1 >> 32));
-          mine_swap = __uint_as_float((uint32_t)(v2 >> 32));
-          top = ((unsigned long long)ordered_bits(__uint_as_float((uint32_t)(v3 >> 32))) << 32) |
-                (unsigned long long)(0xFFFFFFFFu - (uint32_t)pg);
-        }
+        if (!ok) timed_out = 1;
+        decided[rl & 1].lat = __uint_as_float((uint32_t)(v0 >> 32));
+        decided[rl & 1].cid = (uint32_t)(v1 >> 32);
+        decided[rl & 1].swap = __uint_as_float((uint32_t)(v2 >> 32));
       }
-      if (tb.pol_group_first) {
-        top = block_max_u64(top, red);
-        if (top != 0ull && mine != 0ull) {
-          const int g_star = (int)(0xFFFFFFFFu - (uint32_t)(top & 0xFFFFFFFFull));
-          const uint32_t c2 = 0xFFFFFFFFu - (uint32_t)(mine & 0xFFFFFFFFull);
-          if ((int)(c2 / (uint32_t)B) / tb.Mmax != g_star) mine = 0ull;
-        }
-      }
-      const unsigned long long all = block_max_u64(mine, red);
-      if (all != 0ull && mine == all) {                          // candidate ids are unique: one writer
-        lat_win = mine_lat;
-        swap_win = mine_swap;
-      }
-      if (tid == 0) {
-        cid_win = all != 0ull ? (0xFFFFFFFFu - (uint32_t)(all & 0xFFFFFFFFull)) + 1u : 0u;
-        if (pair == 0) {                                         // for the commit workgroup, and the round's timestamp
-          st_dev(ps.dec + rl, all | (1ull << 63));
-          ps.ticks[rl + 1] = wall_clock64();
-        }
-      }
-    } else if (tid == 0) {
-      // ---- wait for the decision ----
-      const unsigned long long* d = ps.decision + (size_t)(gen & 1u) * 4;
-      unsigned long long v0 = 0ull, v1 = 0ull, v2 = 0ull;
-      bool ok = false;
-      for (int k = 0; k < ps.spin_limit; ++k) {
-        v0 = ld_dev(d);
-        v1 = ld_dev(d + 1);
-        v2 = ld_dev(d + 2);
-        ok = (uint32_t)(v0 & 0xFFFFFFFFull) == gen && (uint32_t)(v1 & 0xFFFFFFFFull) == gen &&
-             (uint32_t)(v2 & 0xFFFFFFFFull) == gen;
-        if (ok) break;
-        __builtin_amdgcn_s_sleep(1);
-      }
-      if (!ok) timed_out = 1;
-      lat_win = __uint_as_float((uint32_t)(v0 >> 32));
-      cid_win = (uint32_t)(v1 >> 32);
-      swap_win = __uint_as_float((uint32_t)(v2 >> 32));
     }
     __syncthreads();
     if (timed_out) {
       if (tid == 0) atomicOr(&st->err, kErrSync);
       break;
     }
-    const uint32_t cidp1 = cid_win;
-    const float lat_sel = lat_win, swap_sel = swap_win;
-    __syncthreads();                                         // both are rewritten next round
+    const uint32_t cidp1 = decided[rl & 1].cid;                // (written again two rounds from here)
+    const float lat_sel = decided[rl & 1].lat, swap_sel = decided[rl & 1].swap;
     if (cidp1 == 0u) break;                                  // nothing live anywhere
     const uint32_t cid = cidp1 - 1u;
     const int bsel = (int)(cid % (uint32_t)B) + 1;

@@ -1067,15 +1067,4 @@ __global__ __launch_bounds__(1024) void k_groups_compact(int n_slots, const int3
   }
 }
 
-// The four per-request outputs into the caller's arrays (any of them may be null), one launch.
-__global__ void k_copy_outputs(int n, Window w, int32_t* __restrict__ model, int32_t* __restrict__ round_of,
-                               int32_t* __restrict__ order_of, float* __restrict__ util) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (model) model[i] = w.model[i];
-  if (round_of) round_of[i] = w.round_of[i];
-  if (order_of) order_of[i] = w.order_of[i];
-  if (util) util[i] = w.util[i];
-}
-
 }  // namespace sp
