@@ -104,7 +104,7 @@ __device__ __forceinline__ unsigned long long triangle_best_kind(const float4* e
                                                                 int nthr, int tid) {
   static_assert(kPairLanes == 8 || kPairLanes == 16, "the sums below add over groups of 8 or 16 lanes");
   const int sub = tid % kPairLanes, grp = tid / kPairLanes;
-  const int n_pairs = (B + 1) / 2;
+  const int n_pairs = min((B + 1) / 2, nb);           // past nb the smaller of the two sizes is no candidate, nor is the larger
   unsigned long long best = 0ull;
   for (int p = grp; p < n_pairs; p += nthr / kPairLanes) {
     const int b1 = p + 1, b2 = B - p;                 // b1 <= b2; equal for the middle size of an odd B

@@ -338,6 +338,10 @@ __device__ __forceinline__ int wave_window(const Window& w, int kind, int head, 
   return min(found, Bw);
 }
 
+// Requests of small secondary groups that a resident pair keeps in LDS (512: ten KB beside the windows, so that three
+// workgroups still share a CU at batch sizes up to 128).
+constexpr int kCachedRequests = 512;
+
 // SPLIT: the window's groups are subgroups of the applications (tb.pol_split); the plain instantiation holds
 // none of the secondary-group code, so that it keeps its registers (three workgroups per CU must fit).
 template <bool SPLIT>
@@ -358,6 +362,11 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
   __shared__ int32_t head_s[kMaxAppGroups];                     // head pointer of each group of the application
   __shared__ unsigned long long sec_best[kRoundThreads / 64], sec_top[kRoundThreads / 64];   // per wavefront: its secondary groups' best
   __shared__ float sec_prio[kRoundThreads / 64];
+  // secondary groups of at most one request per lane, as far as they fit: read once, so that a round looks at them without
+  // a trip to memory (most subgroups are that small; a walk and its gathers are three trips for each)
+  __shared__ int32_t end_s[SPLIT ? kMaxAppGroups : 1], cache_at[SPLIT ? kMaxAppGroups : 1];   // first cached entry, or -1
+  __shared__ float4 cache_ent[SPLIT ? kCachedRequests : 1];
+  __shared__ int32_t cache_pos[SPLIT ? kCachedRequests : 1];    // service position, or -1: not pending
   extern __shared__ __align__(16) unsigned char sec_lds[];      // with subgroups: per wavefront B window entries and B positions
   State* st = w.st;
   if ((int)blockIdx.x == ps.n_pairs + 1) {
@@ -407,7 +416,10 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
     const int sz = w.grp_end[glo + i] - w.head[(r & 1) * w.gcap + glo + i];
     if (sz > prim_size) { prim_size = sz; prim = i; }
   }
-  for (int i = tid; i < ng; i += kRoundThreads) head_s[i] = w.head[(r & 1) * w.gcap + glo + i];
+  for (int i = tid; i < ng; i += kRoundThreads) {
+    head_s[i] = w.head[(r & 1) * w.gcap + glo + i];
+    if (SPLIT) end_s[i] = w.grp_end[glo + i];
+  }
   const int gprim = glo + prim;
   const int seg_e = ng > 0 ? w.grp_end[gprim] : 0;
   int scan_end = ng > 0 ? w.head[(r & 1) * w.gcap + gprim] : 0;   // everything before it is consumed or dead
@@ -422,6 +434,26 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
   float4* went = reinterpret_cast<float4*>(sec_lds) + (size_t)wave * B;
   int32_t* wpos = reinterpret_cast<int32_t*>(sec_lds + (size_t)(kRoundThreads / 64) * B * sizeof(float4)) + (size_t)wave * B;
   __syncthreads();
+  if (SPLIT && ng > 1) {
+    if (tid == 0) {
+      int used = 0;
+      for (int i = 0; i < ng; ++i) {
+        const int sz = end_s[i] - head_s[i];
+        const bool fits = i != prim && sz > 0 && sz <= kWave && used + sz <= kCachedRequests;
+        cache_at[i] = fits ? used : -1;
+        used += fits ? sz : 0;
+      }
+    }
+    __syncthreads();
+    for (int i = wave; i < ng; i += kRoundThreads / 64) {
+      const int at = cache_at[i], pos = head_s[i] + lane;
+      if (at < 0 || pos >= end_s[i]) continue;
+      const bool pending = w.alive_s[pos] != 0;
+      cache_pos[at + lane] = pending ? pos : -1;
+      cache_ent[at + lane] = window_entry(tb, w, pos, m);
+    }
+    __syncthreads();
+  }
 
   for (int rl = 0; rl < ps.n_rounds; ++rl) {
     const uint32_t gen = ps.gen_base + (uint32_t)rl + 1u;
@@ -434,11 +466,24 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
     if (SPLIT && ng > 1) {
       for (int i = wave; i < ng; i += kRoundThreads / 64) {
         if (i == prim) continue;
-        const int g = glo + i, se = w.grp_end[g];
-        const int nbs = wave_window(w, kind, head_s[i], se, E0, Bw, wpos, lane);
-        if (lane == 0) head_s[i] = nbs > 0 ? wpos[0] : se;       // what lies before has been consumed or has died
-        if (nbs == 0) continue;
-        for (int j = lane; j < nbs; j += kWave) went[j] = window_entry(tb, w, wpos[j], m);
+        const int g = glo + i, se = end_s[i], at = cache_at[i];
+        int nbs;
+        if (at >= 0) {
+          const bool has = lane < se - head_s[i];
+          const int pos = has ? cache_pos[at + lane] : -1;
+          const float4 e = cache_ent[has ? at + lane : at];
+          const bool live = pos >= 0 && !is_dead(kind, e.y, E0);
+          const unsigned long long m_live = __ballot(live);
+          const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m_live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m_live, 0u));
+          nbs = min(__popcll(m_live), Bw);
+          if (nbs == 0) continue;
+          if (live && rank < Bw) { wpos[rank] = pos; went[rank] = e; }
+        } else {
+          nbs = wave_window(w, kind, head_s[i], se, E0, Bw, wpos, lane);
+          if (lane == 0) head_s[i] = nbs > 0 ? wpos[0] : se;     // what lies before has been consumed or has died
+          if (nbs == 0) continue;
+          for (int j = lane; j < nbs; j += kWave) went[j] = window_entry(tb, w, wpos[j], m);
+        }
         wave_sync();
         if (lane == 0) evals += triangle_evals(nbs, tb.pol_whole);
         unsigned long long cand = triangle_best(scoring_penalty(tb, kind), went, lat_s, nbs, Bw, t + (double)swap_now,
@@ -697,7 +742,18 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
       // a secondary group was chosen: its window once more (same clock, nothing of it has changed since it was
       // scored), to move the head pointer past the batch and to hand the batch's positions to the commit workgroup
       const int isel = gsel - glo;
-      if (wave == 0) {
+      const int at = cache_at[isel];
+      if (wave == 0 && at >= 0) {
+        const bool has = lane < end_s[isel] - head_s[isel];
+        const int pos = has ? cache_pos[at + lane] : -1;
+        const bool live = pos >= 0 && !is_dead(kind, cache_ent[has ? at + lane : at].y, E0);
+        const unsigned long long m_live = __ballot(live);
+        const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m_live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m_live, 0u));
+        if (live && rank < bsel) {
+          if (m == 0) st_dev(ps.ring + ((size_t)rl * tb.A + a) * B + rank, ((unsigned long long)gen << 32) | (unsigned long long)(uint32_t)pos);
+          cache_pos[at + lane] = -1;
+        }
+      } else if (wave == 0) {
         const int nbs = wave_window(w, kind, head_s[isel], w.grp_end[gsel], E0, Bw, wpos, lane);
         if (m == 0)
           for (int j = lane; j < bsel && j < nbs; j += kWave)
