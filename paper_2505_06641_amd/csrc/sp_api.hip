@@ -84,7 +84,8 @@ struct sp_ctx {
   int32_t n_slots = 0;
   int32_t *slot_app = nullptr, *slot_base = nullptr, *slot_beg = nullptr, *slot_end = nullptr;
   int32_t* h_grp_n = nullptr;        // pinned [2]: number of groups of the scored window, most groups of one application
-  hipEvent_t ev_groups = nullptr;    // recorded after the copy into h_grp_n
+  int32_t* h_grp_n_dev = nullptr;    // its device-visible address
+  hipEvent_t ev_groups = nullptr;    // recorded after the kernel that writes h_grp_n
   int sub_passes = 0;                // 8-bit radix passes over the subgroup codes
   uint32_t* bufL[2] = {nullptr, nullptr};   // subgroup codes in the order of the sort
   unsigned char* static_scratch = nullptr;   // this device's copy of the static scratch array (sp_greedy_round_static)
@@ -625,6 +626,16 @@ bool rounds_in_one_launch(sp_ctx* c) {
   return c->h_grp_n[1] <= kMaxAppGroups;
 }
 
+// The same without waiting, for a caller that is about to launch the rounds: where the window's groups have not been counted
+// yet it says yes, and the kernel itself leaves the window alone if an application turns out to have too many.
+bool rounds_in_one_launch_so_far(sp_ctx* c) {
+  if (!c->persist || !c->tb.pol_split) return c->persist;
+  if (!c->persist_split) return false;
+  if (hipEventQuery(c->ev_groups) == hipSuccess) return c->h_grp_n[1] <= kMaxAppGroups;
+  (void)hipGetLastError();                             // (not ready yet)
+  return true;
+}
+
 void fill_u64(hipStream_t s, unsigned long long* p, size_t n) {
   hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, (int64_t)n, 0ull);
 }
@@ -694,6 +705,11 @@ sp_status ensure_split_buffers(sp_ctx* c) {
   SP_HIP(c, hipHostMalloc((void**)&c->h_grp_n, 2 * sizeof(int32_t), hipHostMallocDefault));
   c->h_grp_n[0] = A;
   c->h_grp_n[1] = 1;
+  {
+    void* dp = nullptr;
+    SP_HIP(c, hipHostGetDevicePointer(&dp, c->h_grp_n, 0));
+    c->h_grp_n_dev = (int32_t*)dp;
+  }
   SP_HIP(c, hipEventCreate(&c->ev_groups));
   return SP_OK;
 }
@@ -1070,14 +1086,14 @@ sp_status sp_score(sp_ctx* c, int32_t n, const void* x_dev, const int32_t* app_d
                          (const int32_t*)c->slot_app, (const int32_t*)c->slot_base, (const int32_t*)w.seg,
                          labels, c->slot_beg, c->slot_end);
       hipLaunchKernelGGL(k_groups_compact, dim3(1), dim3(1024), 0, s, c->n_slots, (const int32_t*)c->slot_app,
-                         (const int32_t*)c->slot_beg, (const int32_t*)c->slot_end, w);
+                         (const int32_t*)c->slot_beg, (const int32_t*)c->slot_end, w, c->h_grp_n_dev);
     }
     if (tms) SP_HIP(c, hipEventRecord(c->ev[3], s));
     if (tm) c->timed_score = true;
   }
   if (c->tb.pol_split) {
-    // the rounds' launch grids depend on the number of groups
-    SP_HIP(c, hipMemcpyAsync(c->h_grp_n, w.grp_n, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    // the two-kernel rounds' launch grids depend on the number of groups (k_groups_compact has written it to the host)
+    if (n == 0) { c->h_grp_n[0] = c->A; c->h_grp_n[1] = 1; }
     SP_HIP(c, hipEventRecord(c->ev_groups, s));
   }
   SP_HIP(c, hipGetLastError());
@@ -1152,7 +1168,7 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
   if (tm) SP_HIP(c, hipEventRecord(c->ev[4], s));
   c->round_ms.clear();
   while (!c->done) {
-    const bool persist = rounds_in_one_launch(c);
+    const bool persist = rounds_in_one_launch_so_far(c);
     int chunk = persist ? kPersistRounds : 64;
     if (max_rounds > 0) chunk = std::min(chunk, start + max_rounds - c->rounds_done);
     if (chunk <= 0) break;

@@ -369,6 +369,12 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
   __shared__ int32_t cache_pos[SPLIT ? kCachedRequests : 1];    // service position, or -1: not pending
   extern __shared__ __align__(16) unsigned char sec_lds[];      // with subgroups: per wavefront B window entries and B positions
   State* st = w.st;
+  // more groups than a pair serves: the window is left as it is, and the host, which has not waited for their number, sees
+  // no round done and takes two kernels per round
+  if (SPLIT && w.grp_n[1] > kMaxAppGroups) {
+    if ((int)blockIdx.x == ps.n_pairs + 1 && threadIdx.x == 0) mirror_state(w);
+    return;
+  }
   if ((int)blockIdx.x == ps.n_pairs + 1) {
     persist_commit_loop(tb, w, ps, dsum.three, red);
     return;
@@ -405,10 +411,6 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
       if (w.grp_app[mid] <= a) lo = mid + 1; else hi = mid;
     }
     ng = lo - glo;
-    if (ng > kMaxAppGroups) {                                // the host launches this kernel only when every application fits
-      if (tid == 0) atomicOr(&st->err, kErrSync);
-      ng = 0;
-    }
   }
   // the primary group (largest remaining range; ties: the first) keeps the LDS-resident window
   int prim = 0, prim_size = -1;

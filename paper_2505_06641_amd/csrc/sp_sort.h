@@ -1012,7 +1012,8 @@ __global__ void k_slot_ranges(int n_slots, const int32_t* __restrict__ slot_app,
 // The non-empty slots, in slot order, become the groups of the rounds.  One workgroup.
 __global__ __launch_bounds__(1024) void k_groups_compact(int n_slots, const int32_t* __restrict__ slot_app,
                                                          const int32_t* __restrict__ slot_beg,
-                                                         const int32_t* __restrict__ slot_end, Window w) {
+                                                         const int32_t* __restrict__ slot_end, Window w,
+                                                         int32_t* __restrict__ grp_n_host /*pinned [2]*/) {
   __shared__ int wave_cnt[16];
   __shared__ int base_s;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1064,6 +1065,8 @@ __global__ __launch_bounds__(1024) void k_groups_compact(int n_slots, const int3
   if (tid == 0) {
     w.grp_n[0] = G;
     w.grp_n[1] = max_run;
+    grp_n_host[0] = G;
+    grp_n_host[1] = max_run;
   }
 }
 
