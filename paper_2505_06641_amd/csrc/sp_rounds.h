@@ -199,6 +199,16 @@ __device__ __forceinline__ float4 window_entry(const Tables& tb, const Window& w
   return make_float4(wgt * w.ea[(int64_t)w.id_s[pos] * tb.Mmax + m], D, 1.0f / D, 2.0f * D);
 }
 
+// Groups of the window, and the application of one: the applications themselves unless the requests are split (no trip to the
+// group table then).
+__device__ __forceinline__ int n_groups(const Tables& tb, const Window& w) { return tb.pol_split ? *w.grp_n : tb.A; }
+__device__ __forceinline__ int group_app(const Tables& tb, const Window& w, int g) { return tb.pol_split ? w.grp_app[g] : g; }
+
+// Keeps a value's load where it stands: everything a kernel can ask for at its start then shares one trip to memory (about
+// 0.8 us), which the compiler would otherwise move behind the branches that come first.
+template <typename T>
+__device__ __forceinline__ void loaded_here(const T& v) { asm volatile("" : : "v"(v)); }
+
 __global__ __launch_bounds__(kRoundThreads) void k_round_score(Tables tb, Window w, float* __restrict__ cube_out) {
   __shared__ int32_t win[kMaxBatch];
   __shared__ float4 ent[kMaxBatch];
@@ -206,22 +216,23 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_score(Tables tb, Window
   __shared__ unsigned long long red[kRoundThreads / 64];
   __shared__ double dsum[kRoundThreads];
   State* st = w.st;
-  if (st->done || st->err) return;
   const int grp = blockIdx.x / tb.Mmax, m = blockIdx.x % tb.Mmax;   // group: an application, or one of its subgroups
-  if (grp >= *w.grp_n) return;
-  const int a = w.grp_app[grp];
+  if (tb.pol_split && grp >= *w.grp_n) return;
+  const int a = group_app(tb, w, grp);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int M = tb.n_models[a], B = tb.B, Bw = tb.Bcap;   // B: row stride of the tables; Bw: largest batch
+  const int r = st->round, kind = tb.penalty[a], seg_e = w.grp_end[grp];
+  const int head_even = w.head[grp], head_odd = w.head[w.gcap + grp];
+  const double t = st->t;
+  const float lmin = tb.lmin[a];
+  loaded_here(M); loaded_here(kind); loaded_here(seg_e); loaded_here(head_even); loaded_here(head_odd); loaded_here(lmin);
+  if (st->done || st->err) return;
   if (m >= M) {
     if (tid == 0) w.cand[blockIdx.x] = 0ull;
     return;
   }
-  const int r = st->round;
-  const double t = st->t;
-  const int kind = tb.penalty[a];
-  const double E0 = t + (double)tb.lmin[a];
-  const int seg_e = w.grp_end[grp];
-  const int head = w.head[(r & 1) * w.gcap + grp];
+  const double E0 = t + (double)lmin;
+  const int head = (r & 1) ? head_odd : head_even;
   // With the requests split into subgroups (Sec. 5.3.2) most groups hold a handful of requests: one
   // wavefront then does the whole workgroup's job and the others leave (a barrier counts only the
   // wavefronts that are still running).
@@ -356,13 +367,18 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Windo
   __shared__ double dsum[3][kMaxBatch];
   State* st = w.st;
   const int tid = threadIdx.x;
-  if (st->done || st->err) {
+  const int n_cand = n_groups(tb, w) * tb.Mmax;
+  State now = *st;
+  const unsigned long long mine = tid < n_cand ? w.cand[tid] : 0ull;
+  const float my_prio = tb.pol_group_first && tid < n_cand ? w.cand_prio[tid] : 0.f;
+  loaded_here(mine); loaded_here(my_prio); loaded_here(now.t); loaded_here(now.total_wu); loaded_here(now.total_u);
+  loaded_here(now.total_viol); loaded_here(now.round); loaded_here(now.next_order); loaded_here(now.n_sched); loaded_here(now.n_evals);
+  if (now.done || now.err) {
     if (tid == 0) mirror_state(w);
     return;
   }
-  unsigned long long best = 0ull;
-  const int n_cand = *w.grp_n * tb.Mmax;
-  for (int i = tid; i < n_cand; i += kRoundThreads) {
+  unsigned long long best = mine;
+  for (int i = tid + kRoundThreads; i < n_cand; i += kRoundThreads) {
     const unsigned long long c = w.cand[i];
     best = c > best ? c : best;
   }
@@ -377,20 +393,20 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Windo
   if (tb.pol_group_first) {
     // Alg. 1: first the application with the highest group priority (ties: the smallest application),
     // then the best candidate of that application alone
-    unsigned long long top = 0ull;
-    for (int i = tid; i < n_cand; i += kRoundThreads)
+    auto priority = [&](int i, float p) {
+      return ((unsigned long long)ordered_bits(p) << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)(i / tb.Mmax));
+    };
+    unsigned long long top = mine != 0ull ? priority(tid, my_prio) : 0ull;
+    for (int i = tid + kRoundThreads; i < n_cand; i += kRoundThreads)
       if (w.cand[i] != 0ull) {
-        const unsigned long long pk = ((unsigned long long)ordered_bits(w.cand_prio[i]) << 32) |
-                                      (unsigned long long)(0xFFFFFFFFu - (uint32_t)(i / tb.Mmax));
+        const unsigned long long pk = priority(i, w.cand_prio[i]);
         top = pk > top ? pk : top;
       }
     top = block_max_u64(top, red);
     const int g_star = (int)(0xFFFFFFFFu - (uint32_t)(top & 0xFFFFFFFFull));
-    best = 0ull;
-    for (int i = g_star * tb.Mmax + tid; i < (g_star + 1) * tb.Mmax; i += kRoundThreads) {
-      const unsigned long long c = w.cand[i];
-      best = c > best ? c : best;
-    }
+    best = tid / tb.Mmax == g_star ? mine : 0ull;
+    for (int i = g_star * tb.Mmax + tid; i < (g_star + 1) * tb.Mmax; i += kRoundThreads)
+      if (i >= kRoundThreads) best = w.cand[i] > best ? w.cand[i] : best;
     best = block_max_u64(best, red);
   }
   const uint32_t cid = 0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull);
@@ -399,11 +415,9 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Windo
   const int b = (int)(cid % (uint32_t)B) + 1;
   const int am = (int)(cid / (uint32_t)B);
   const int m = am % tb.Mmax, grp = am / tb.Mmax;
-  const int a = w.grp_app[grp];
-  const int r = st->round;
-  const double t = st->t;
-  const int next_order = st->next_order;
-  const double E = start_time(tb, st->last, t, a, m) + (double)tb.lat[((int64_t)a * tb.Mmax + m) * B + (b - 1)];
+  const int a = group_app(tb, w, grp), r = now.round, next_order = now.next_order;
+  const double t = now.t;
+  const double E = start_time(tb, now.last, t, a, m) + (double)tb.lat[((int64_t)a * tb.Mmax + m) * B + (b - 1)];
   double wu, su, viol;
   const int32_t* row = w.win_pos + grp * B;
   commit_members(tb, w, Outputs{}, a, m, b, r, next_order, E, [&](int j) { return row[j]; }, ids_out, dsum, wu, su, viol);
@@ -413,15 +427,16 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Windo
     dc.t_start = t; dc.t_end = E;
     dc.score = score; dc.batch_utility = (float)wu;
     if (r < w.log_cap) w.log[r] = dc;
-    st->last = dc;
-    st->t = E;
-    st->round = r + 1;
-    st->next_order = next_order + b;
-    st->n_sched += b;
-    st->total_wu += wu;
-    st->total_u += su;
-    st->total_viol += viol;
-    mirror_state(w);
+    now.last = dc;
+    now.t = E;
+    now.round = r + 1;
+    now.next_order = next_order + b;
+    now.n_sched += b;
+    now.total_wu += wu;
+    now.total_u += su;
+    now.total_viol += viol;
+    *st = now;                        // (nobody else writes the state while this kernel runs)
+    if (w.st_host != nullptr) *w.st_host = now;
   }
 }
 

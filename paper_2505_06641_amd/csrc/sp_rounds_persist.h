@@ -155,7 +155,7 @@ __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Per
     const int b = (int)(cid % (uint32_t)B) + 1;
     const int am = (int)(cid / (uint32_t)B);
     const int m = am % tb.Mmax, grp = am / tb.Mmax;
-    const int a = w.grp_app[grp];                     // group = application unless the requests are split into subgroups
+    const int a = group_app(tb, w, grp);              // group = application unless the requests are split into subgroups
     const double E = start_time(tb, last, t, a, m) + (double)tb.lat[((int64_t)a * tb.Mmax + m) * B + (b - 1)];
     const unsigned long long* row = ps.ring + ((size_t)rl * tb.A + a) * B;
     bool lost = false;
