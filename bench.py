@@ -35,7 +35,7 @@ PEAK_VALU_F32_TFLOPS = 157.3
 #   scoring_kernel_traffic <workload> fetch_bytes=<f> write_bytes=<w> kernel_sources_sha256=<sha>
 # which is read here; a figure is only reported while the kernel sources it was taken on are unchanged
 # (sha256 over the files below), otherwise traffic is null.
-KERNEL_SOURCES = ["sp_common.h", "sp_score_generic.h", "sp_score_split.h", "sp_score_mlp.h"]
+KERNEL_SOURCES = ["sp_common.h", "sp_score_generic.h", "sp_score_split.h", "sp_score_mlp.h", "sp_score_stream.h"]
 PROFILE_FILES = {w: os.path.join("profiles", f"hot_path_{w}_kernel_stats_and_hbm_traffic.md") for w in ("cfg4", "cfg5")}
 
 
@@ -230,16 +230,18 @@ def main():
     tflops = flops / (k_avg * 1e-3) / 1e12
     gbs = k_bytes / (k_avg * 1e-3) / 1e9
     ai = flops / k_bytes
-    split = p.feat_dtype == wl.F32 and int(p.hidden_dim) == 0 and int(p.feat_dim) <= 256
-    mlp_mfma = p.feat_dtype == wl.BF16 and 0 < int(p.hidden_dim) <= 256 and int(p.feat_dim) % 8 == 0
-    if mlp_mfma:
-        # layer 1 is one bf16 MFMA per product; layer 2 and the table contraction take three fp16 MFMAs per
-        # product (float32 hidden activations as hi + lo halves): the ceiling is the flop-weighted mix
-        f1 = float(sum(int(counts[a]) * 2 * int(p.feat_dim) * int(p.hidden_dim) for a in range(A)))
+    # which arithmetic the library's scoring kernels use: float32 heads in three fp16 MFMAs per product, bf16 ones in one per
+    # product of the first layer; only hidden layers wider than 256 (and rows of a few features) stay on the vector units
+    d, H = int(p.feat_dim), int(p.hidden_dim)
+    on_mfma = H <= 256 and d >= 8
+    split = p.feat_dtype == wl.F32 and (on_mfma or H == 0)
+    bf16_mfma = p.feat_dtype == wl.BF16 and on_mfma
+    if bf16_mfma:
+        # the products with the features are one bf16 MFMA each; a second layer and the table contraction take
+        # three fp16 MFMAs per product (float32 values as hi + lo halves): the ceiling is the flop-weighted mix
+        f1 = float(sum(int(counts[a]) * 2 * d * (H or int(p.n_classes[a])) for a in range(A)))
         peak_c = flops / (f1 / PEAK_MFMA_BF16_TFLOPS + (flops - f1) / (PEAK_MFMA_F16_TFLOPS / 3.0))
-        peak_note = "bf16 dense MFMA peak for layer 1, fp16 peak / 3 for layer 2 and the table, weighted by flops"
-    elif p.feat_dtype == wl.BF16:
-        peak_c, peak_note = PEAK_VALU_F32_TFLOPS, "float32 vector peak (generic kernel)"
+        peak_note = "bf16 dense MFMA peak for the products with the features, fp16 peak / 3 for a second layer and the table, weighted by flops"
     elif split:
         # the kernel forms every float32 product from three fp16 MFMAs (hi.hi + lo.hi + hi.lo), so its
         # ceiling for float32 flops is a third of the fp16 MFMA peak
@@ -248,10 +250,10 @@ def main():
         peak_c, peak_note = PEAK_VALU_F32_TFLOPS, "float32 vector peak (generic kernel)"
     ridge = peak_c * 1e12 / (PEAK_HBM_GBS * 1e9)
     if ai >= ridge:
-        roof = {"bound": "mfma" if (split or mlp_mfma) else "alu", "achieved": tflops, "peak": peak_c, "unit": "TFLOP/s", "frac": tflops / peak_c}
+        roof = {"bound": "mfma" if (split or bf16_mfma) else "alu", "achieved": tflops, "peak": peak_c, "unit": "TFLOP/s", "frac": tflops / peak_c}
     else:
         roof = {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS}
-    if split or mlp_mfma:
+    if split or bf16_mfma:
         # what the matrix cores sustain on this device, measured now: the bare half-precision MFMA loop on
         # constant operands and on operands with random bits (the clock drops with the toggle rate, so the
         # second figure is the ceiling for real data); the kernel's ceiling scaled by sustained / published
@@ -313,14 +315,15 @@ def main():
         gbs_ = nbytes / (ms * 1e-3) / 1e9 if ms > 0 else None
         return {"name": name, "algorithmic_bytes": nbytes, "ms": ms, "gbs": gbs_,
                 "frac_of_hbm_peak": gbs_ / PEAK_HBM_GBS if gbs_ else None, "what": note}
-    # applications that fit one workgroup's LDS are ordered by one kernel that reads and writes each (key,
-    # position) pair once; longer ones take four radix passes over tiles (Sec. 5.2, eq. 12 ordering)
-    in_lds = (not args.split_groups) and A <= 1024 and int(np.max(counts)) <= 16384
-    order_b = 16 if in_lds else 68
-    order_note = ("one kernel per application: (key, position) read (8 B) and written (8 B) once, four passes in LDS" if in_lds
+    # windows of up to 262,144 requests: runs of 1,024 sorted in LDS, then merged (up to sixteen runs a time); the last launch
+    # is counted as finish_order.  Longer ones: digit totals and four radix passes, then a gather.
+    launches = 1 + (0 if n <= 1024 else 1 if n <= 16384 else 2)
+    merged = n <= 262144
+    order_b = 16 * (launches - 1) if merged else 68
+    order_note = (f"{launches - 1} of the {launches} launches that sort and merge runs: (key, position) read (8 B) and written (8 B)" if merged
                   else "digit totals of the keys (4 B) + four radix passes (8 B read, 8 B written each)")
     out["kernels"] = [
-        stream("group_by_app", 32 * N, g_ms, "digit totals of the application ids (4 B read per request) + one radix pass (id 4 B, deadline and weight 8 B read; id, position 8 B and deadline, weight 8 B written)"),
+        stream("group_by_app", 28 * N, g_ms, "application counts per tile (4 B read per request), then every request placed (id 4 B, deadline and weight 8 B read; position 4 B and deadline, weight 8 B written)"),
         stream("order_by_key_passes", order_b * N, o_ms - f_ms, order_note),
         stream("finish_order", 57 * N, f_ms, "position, 16-byte record and key read; id, deadline, weight, key, pending flag written; outputs reset"),
         stream("copy_outputs", 32 * N, c_ms, "four per-request outputs read and written"),
@@ -328,7 +331,7 @@ def main():
     out["hbm_copy_measured_gbs"] = binding.sp_debug_copy_rate(1 << 28)
     # the whole step against the scoring kernel's ceilings: its algorithmic flops and the algorithmic bytes of
     # every stage over the step's wall time (the rounds work on LDS-resident windows: no bytes counted for them)
-    step_bytes = k_bytes + (32 + order_b + 57 + 32) * N
+    step_bytes = k_bytes + (28 + order_b + 57 + 32) * N
     out["whole_step_roofline"] = {"algorithmic_flops": flops, "algorithmic_bytes": step_bytes,
                                   "tflops": flops / (ms_per_step * 1e-3) / 1e12,
                                   "frac_of_scoring_kernel_ceiling": flops / (ms_per_step * 1e-3) / 1e12 / peak_c,

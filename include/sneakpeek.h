@@ -122,10 +122,13 @@ typedef struct {
   float order_ms;          /* per-application ordering by key                                  */
   float rounds_ms;         /* all rounds of the last sp_schedule call                          */
   int32_t n_rounds_timed;  /* rounds with an individual time (see sp_get_round_times)          */
-  float finish_order_ms;   /* within order_ms: the kernel that gathers id, deadline, weight and
-                              key per service position after the last radix pass              */
+  float finish_order_ms;   /* within order_ms: its last kernel, which gathers id, deadline, weight
+                              and key per service position (windows of up to 262,144 requests:
+                              and sorts or merges)                                            */
   float copy_outputs_ms;   /* the kernel that copies the four per-request outputs to the
-                              caller's arrays (first chunk of the last sp_schedule call)      */
+                              caller's arrays (first chunk of the last sp_schedule call; while
+                              no stage is timed, short windows' outputs are written by the
+                              rounds kernel instead)                                          */
   int64_t utility_evaluations;  /* terms key * EA * (1 - penalty) summed by the rounds of the
                               window so far: per round and (group, variant), nb (nb + 1) / 2
                               for a candidate window of nb requests (nb under SP_BATCH_WHOLE) */
@@ -345,7 +348,8 @@ sp_status sp_debug_set_spin_limit(sp_ctx* ctx, int32_t polls);
  * is bounded, and a look-back that runs out raises an error that the next sp_greedy_round / sp_schedule
  * reports as SP_EDEVICE (the window has to be scored again; the context stays usable).  polls > 0 sets the
  * bound, polls < 0 makes every look-back give up at once (a test's way into that path with every kernel
- * still ending normally), 0 restores the default (2^20).  SP_EINVAL: ctx NULL.
+ * still ending normally), 0 restores the default (2^20).  While a bound is set, requests are grouped by radix
+ * passes whatever the number of applications (otherwise only beyond 255).  SP_EINVAL: ctx NULL.
  */
 sp_status sp_debug_set_sort_spin_limit(sp_ctx* ctx, int32_t polls);
 

@@ -14,7 +14,7 @@
 //   * the arg max over all pairs goes through one slot per pair and a reducing workgroup: every pair
 //     publishes its best candidate, the reducer polls the slots (one per thread), takes the maximum and
 //     publishes the decision, which one thread of every pair polls.  With few pairs (kAllToAllPairs) there
-//     is no reducer: every pair polls all slots itself and takes the maximum, which halves the trips
+//     is no reducer: every pair's first wavefront polls all slots itself and takes the maximum, which halves the trips
 //     through the fabric between a round's last candidate and its decision (the decisions are the same:
 //     every pair applies the reducer's rule to the same words; pair 0 passes the decision on to the commit
 //     workgroup).  Slots and the decision are pairs of
@@ -28,9 +28,9 @@
 //     batch through a ring of generation-tagged window positions written by the chosen application's
 //     first pair, so the commits (outputs, totals, decision log) run beside the next round's scoring.
 // With data-aware subgroups (Sec. 5.3.2) a pair serves every group of its application: the largest one
-// (the "primary") keeps the LDS-resident window described above; the others are walked afresh every round,
-// one wavefront per group (they are small: a handful of requests behind a head pointer kept in LDS), before
-// the primary's block-wide work; the pair publishes the best candidate over its groups together with the
+// (the "primary") keeps the LDS-resident window described above; the others take one wavefront each before
+// the primary's block-wide work: groups of at most 64 requests are kept in LDS for the whole launch, larger ones are
+// walked afresh every round; the pair publishes the best candidate over its groups together with the
 // group's index.  The chosen batch's positions reach the commit workgroup after the decision: the chosen
 // application's first pair writes them into the ring (from the primary's window, or from one more walk of
 // the chosen secondary group, which every pair of that application does anyway to move its head pointer).

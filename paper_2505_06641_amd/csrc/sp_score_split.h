@@ -1,5 +1,5 @@
-// Scoring kernel for logistic heads with float32 features on the matrix cores,
-// d <= 256, M <= 16: float32 products emulated by three half-precision MFMAs.
+// Scoring kernel for logistic heads of more than 128 classes with float32 features on the matrix cores,
+// d <= 256 (padded to a multiple of 32), M <= 16: float32 products emulated by three half-precision MFMAs.
 //
 // Every float32 operand v is scaled by a power of two (per request row for the
 // features, per application for the weights; exact) into (-2^15, 2^15) and

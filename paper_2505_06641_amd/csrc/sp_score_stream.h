@@ -15,10 +15,20 @@
 // not known before the row has been read, so the scale follows a running maximum: when a step brings a larger value,
 // the request's accumulators are rescaled by the exact power of two.
 //
+// Partial sums of a step are added to the accumulators in float32 registers, and the exponentials are split on a fixed grid:
+// the matrix cores cut off the bits of a term that lie far below the largest one of an instruction, which in a chain of
+// hundreds of them shows as a bias of 5e-8.
+//
 // Logistic heads then take the softmax and the table contraction straight from the accumulators; more than 32 NB
 // classes go in groups, each of which streams the rows again.  One-hidden-layer heads add bias, ReLU and split in
 // registers and walk the class tiles like the bfloat16 kernel; class blocks follow the slices through the same two
 // buffers.
+//
+//
+// Measured (rocprofv3, median us, before -> now): 32,768 rows of 768 floats, 100 classes 1543 -> 39.8 (2.5 TB/s of rows);
+// 65,536 rows of 512 bfloat16, 100 classes 1273 -> 26.5 (2.5 TB/s); 100,000 requests of 128-64-10/7/2 float32 heads 185 -> 26.4
+// (1.9 TB/s), all three from the generic kernel; 30,011 of 384-128-100/37/10 bfloat16 heads 29 -> 20.4 (1.1 TB/s), from the
+// kernel that pads the hidden layer to 256.  A large copy reaches 5.2 TB/s on this card (read and written).
 #pragma once
 #include "sp_common.h"
 #include "sp_score_split.h"
