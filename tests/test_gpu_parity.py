@@ -1112,3 +1112,31 @@ def test_ordering_by_subgroup_and_key(gpu, n):
         keep = np.isin(got, ids[clear])
         want = ids[clear][np.lexsort((ids[clear], -key[ids[clear]].astype(np.float64), label[clear]))]
         assert np.array_equal(got[keep], want)
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 3100])
+@pytest.mark.parametrize("rounds", [1, 3])
+def test_outputs_of_unserved_requests_at_the_fill_edges(gpu, n, rounds):
+    """The workgroup that commits the rounds fills the outputs of requests that no round serves, 1,024 per round: windows
+    it covers exactly, by one request too few and by more than the rounds allow (those are written behind the rounds)."""
+    w = wl.tiny(seed=8700, n=n, classes=(5, 3), models=(3, 2), max_batch=7, feat_dim=16, deadline=(6.0, 150.0), fractions=(0.7, 0.3))
+    full_parity(gpu, w, max_rounds=rounds)
+
+
+@pytest.mark.parametrize("big", [63, 64, 65])
+def test_subgroups_at_the_edge_of_the_lds_copy(gpu, big):
+    """Subgroups of up to 64 requests are kept in LDS, 512 requests in all: sizes at that edge, one that is larger, and
+    more small ones than fit."""
+    sizes = [150, big, 1, 64, 65, 63] + [64] * 8
+    C = len(sizes)
+    n = sum(sizes)
+    w = wl.tiny(seed=8710, n=n, classes=(C,), models=(3,), max_batch=9, feat_dim=16, deadline=(6.0, 400.0), fractions=(1.0,))
+    lab = np.random.default_rng(8711).permutation(np.repeat(np.arange(C), sizes))
+    w.requests.x[:] = 0.0
+    w.requests.x[np.arange(n), lab] = 1.0
+    w.profile.W1[0] = np.zeros((16, C), dtype=np.float32)
+    w.profile.W1[0][np.arange(C), np.arange(C)] = 6.0              # class posterior 0.97: every request in its class's subgroup
+    policy = wl.named_policy("sneakpeek")
+    policy.split_groups = 1
+    got, stats = full_parity(gpu, w, max_rounds=0, policy=policy)
+    assert got["summary"]["done"] == 1 and stats["rounds"] > 10
