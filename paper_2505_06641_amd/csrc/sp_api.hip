@@ -1093,7 +1093,7 @@ sp_status sp_score(sp_ctx* c, int32_t n, const void* x_dev, const int32_t* app_d
   }
   if (c->tb.pol_split) {
     // the two-kernel rounds' launch grids depend on the number of groups (k_groups_compact has written it to the host)
-    if (n == 0) { c->h_grp_n[0] = c->A; c->h_grp_n[1] = 1; }
+    if (n == 0) hipLaunchKernelGGL(k_groups_publish, dim3(1), dim3(kWave), 0, s, w, c->h_grp_n_dev);
     SP_HIP(c, hipEventRecord(c->ev_groups, s));
   }
   SP_HIP(c, hipGetLastError());

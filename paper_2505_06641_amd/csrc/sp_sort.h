@@ -1070,4 +1070,10 @@ __global__ __launch_bounds__(1024) void k_groups_compact(int n_slots, const int3
   }
 }
 
+// The same two numbers of an empty window for the host, in the order of the stream: an earlier window's k_groups_compact may
+// still be on its way there.
+__global__ void k_groups_publish(Window w, int32_t* __restrict__ grp_n_host /*pinned [2]*/) {
+  if (threadIdx.x < 2) grp_n_host[threadIdx.x] = w.grp_n[threadIdx.x];
+}
+
 }  // namespace sp

@@ -1140,3 +1140,30 @@ def test_subgroups_at_the_edge_of_the_lds_copy(gpu, big):
     policy.split_groups = 1
     got, stats = full_parity(gpu, w, max_rounds=0, policy=policy)
     assert got["summary"]["done"] == 1 and stats["rounds"] > 10
+
+
+def test_empty_window_right_behind_a_split_one(gpu):
+    """The number of groups reaches the host in stream order: an empty window scored while a split window of a single group
+    is still on the stream has its own number of groups (every application), and nothing to serve."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8720, n=30000, classes=(3,) * 12, models=(2,) * 12, max_batch=4, feat_dim=64)
+    w.requests.app[:] = 0
+    w.requests.x[:] = 0.0
+    w.profile.b1[0][:] = np.array([9.0, 0.0, 0.0], np.float32)           # one subgroup of one application
+    ctx = binding.Context(w.profile, 30000, policy=wl.Policy(split_groups=1))
+    args = binding.to_device(w.requests)
+    none = tuple(t[:0] for t in args)
+    for one_launch in (True, False):
+        for _ in range(3):
+            ctx.sp_score(*args)
+            ctx.sp_score(*none)
+            if one_launch:
+                rc, summ, _ = ctx.sp_schedule(4)
+                assert rc == binding.SP_DONE and summ["n_rounds"] == 0
+            else:
+                rc, dec = ctx.sp_greedy_round()
+                assert rc == binding.SP_DONE and dec is None
+            cube = torch.zeros((12, ctx.m_max, 4), device="cuda:0")
+            ctx.sp_debug_dump(binding.SP_DUMP_SCORE_CUBE, cube)          # one slab per group of the empty window
+            assert torch.all(cube == -1.0)
+    ctx.close()
