@@ -72,8 +72,24 @@ struct StreamStage {
 template <typename T>
 inline int stream_channel(int s, int g, int e) { return g * (StreamIn<T>::kChunk / 2) + 8 * s + e; }
 
+// Which feature slot k of the padded row holds (-1: zero), and the part of its weight that counts there.  A piece of 16 bytes
+// (`per` features) that would pass the row's end is read that much further left; the features that it repeats count by half
+// in either place (exact in both types).  With the whole weight in one place and zero in the other an infinite feature would
+// make NaNs, which a hidden layer's ReLU turns into zeros.  Pieces behind the row's end are zero.
+inline uint16_t host_bf16_half(uint16_t v) {
+  return (uint16_t)(__builtin_bit_cast(uint32_t, __builtin_bit_cast(float, (uint32_t)v << 16) * 0.5f) >> 16);
+}
+struct StreamSlot { int feature; float part; };
+inline StreamSlot stream_slot(int k, int d, int per) {
+  const int full = d / per * per;
+  if (k < full) return {k, k >= d - per && full < d ? 0.5f : 1.0f};
+  if (k / per != full / per || full == d) return {-1, 0.f};
+  const int f = d - per + k % per;
+  return {f, f < full ? 0.5f : 1.0f};
+}
+
 // One weight slice: unit ((hb * kSteps + s) * kParts + part) * 64 + lane, halves e = 0..7 hold (part of)
-// W[k = kChunk kc + channel(s, lane/32, e)][row0 + 32 hb + lane%32], zero beyond [d, O] (which input k is: row_slot_feature).
+// W[k = kChunk kc + channel(s, lane/32, e)][row0 + 32 hb + lane%32], zero beyond [d, O] (which input k is: stream_slot).
 template <typename T, int NB>
 inline void pack_stream_slice(const T* W /*[d, O]*/, int d, int O, int kc, int row0, float scale, uint16_t* out) {
   using I = StreamIn<T>;
@@ -81,12 +97,13 @@ inline void pack_stream_slice(const T* W /*[d, O]*/, int d, int O, int kc, int r
     for (int s = 0; s < I::kSteps; ++s)
       for (int g = 0; g < 2; ++g)
         for (int e = 0; e < 8; ++e) {
-          const int k = row_slot_feature(I::kChunk * kc + stream_channel<T>(s, g, e), d, 16 / (int)sizeof(T)), o0 = row0 + 32 * hb;
+          const StreamSlot slot = stream_slot(I::kChunk * kc + stream_channel<T>(s, g, e), d, 16 / (int)sizeof(T));
+          const int k = slot.feature, o0 = row0 + 32 * hb;
           uint16_t* at = out + ((size_t)((hb * I::kSteps + s) * I::kParts) * 64 + 32 * g) * 8 + e;
           const T* from = W + (size_t)std::max(k, 0) * O + o0;
           for (int r = 0; r < 32 && k >= 0 && o0 + r < O; ++r) {      // (the buffer is zero to begin with)
-            if constexpr (I::kF32) host_split((float)from[r] * scale, at[r * 8], at[(64 + r) * 8]);
-            else at[r * 8] = (uint16_t)from[r];
+            if constexpr (I::kF32) host_split((float)from[r] * (scale * slot.part), at[r * 8], at[(64 + r) * 8]);
+            else at[r * 8] = slot.part == 1.0f ? (uint16_t)from[r] : host_bf16_half((uint16_t)from[r]);
           }
         }
 }
@@ -98,6 +115,8 @@ struct StreamHeads {
   const float* unscale1;          // [A] undoes the first layer's weight scale (1 for bfloat16)
   const float* unscale2;          // [A] undoes the second layer's
 };
+
+static __device__ f32x4 stream_zeros;            // what lies behind a row's end
 
 // 16 bytes of a feature row: rows start at any multiple of the element size
 typedef f32x4 f32x4_any __attribute__((aligned(2)));
@@ -157,9 +176,12 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
         if constexpr (I::kF32) xs[q] = *reinterpret_cast<const f32x4_dw*>(row + at + 16 * q);
         else xs[q] = *reinterpret_cast<const f32x4_any*>(row + at + 16 * q);
       }
-    } else if (kc < nkc) {                               // the last, partial step (see row_slot_feature)
+    } else if (kc < nkc) {                               // the last, partial step (see stream_slot)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) xs[q] = *reinterpret_cast<const f32x4_any*>(row + min(at + 16 * q, row_bytes - 16));
+      for (int q = 0; q < 4; ++q) {
+        const unsigned char* p = row + min(at + 16 * q, row_bytes - 16);
+        xs[q] = *reinterpret_cast<const f32x4_any*>(at + 16 * q < row_bytes ? p : reinterpret_cast<const unsigned char*>(&stream_zeros));
+      }
     } else {                                             // past it
 #pragma unroll
       for (int q = 0; q < 4; ++q) xs[q] = f32x4{0.f, 0.f, 0.f, 0.f};

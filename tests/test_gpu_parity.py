@@ -1167,3 +1167,33 @@ def test_empty_window_right_behind_a_split_one(gpu):
             ctx.sp_debug_dump(binding.SP_DUMP_SCORE_CUBE, cube)          # one slab per group of the empty window
             assert torch.all(cube == -1.0)
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16], ids=["bf16"])
+@pytest.mark.parametrize("d,at", [(72, 71), (71, 64), (9, 8), (100, 95), (128, 120), (300, 299)])
+def test_infinite_feature_in_front_of_a_hidden_layer(gpu, dtype, d, at):
+    """An infinite feature, also among the last ones of a row that ends inside a step, acts as in plain arithmetic: hidden units
+    it drives to +inf make the request's expected accuracies NaN, units it drives to -inf are zero and leave the head's
+    output bias.  No other request notices."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8730 + d, n=200, classes=(9, 4), models=(3, 2), feat_dim=d, hidden_dim=20, feat_dtype=dtype)
+    inf = np.uint16(0x7f80) if dtype == wl.BF16 else np.float32(np.inf)
+    sign = np.uint16(0x8000)
+    for a in range(2):                                   # every unit's weight of that feature is negative
+        row = w.profile.W1[a][at]
+        row[:] = (row | sign) if dtype == wl.BF16 else -np.abs(row)
+    ref_ea, _ = orc.score_requests(w.profile, w.requests)
+    w.requests.x[7, at] = inf                            # +inf: every unit at -inf
+    w.requests.x[90, at] = -inf if dtype == wl.F32 else inf | sign      # -inf: every unit at +inf
+    ctx = binding.Context(w.profile, 200)
+    ea = torch.zeros((200, ctx.m_max), device="cuda:0")
+    ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
+    ea = ea.cpu().numpy()
+    ctx.close()
+    M = [int(w.profile.n_models[int(a)]) for a in w.requests.app]
+    assert np.all(np.isnan(ea[90, :M[90]]))
+    a = int(w.requests.app[7])
+    z = w.profile.b2[a].astype(np.float64)
+    parity.assert_close("EA without hidden units", ea[7, :M[7]], w.profile.acc[a].astype(np.float64) @ orc.posterior(z[None])[0], TOL)
+    keep = ~np.isin(np.arange(200), (7, 90))
+    parity.assert_close("EA", ea[keep], ref_ea[keep], 2e-3 if dtype == wl.BF16 else TOL)
