@@ -194,7 +194,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
   const int64_t dump_row = (int64_t)id * tb.Cmax;
   f32x16 acc[NB];
   int ex = 1000;                                         // float32: the row's running scale 2^ex (none yet)
-  bool infinite = false;                                 // float32: the row holds an infinity
+  bool infinite = false;                                 // float32, hidden layer: the row holds an infinity
   const float un1 = I::kF32 ? hd.unscale1[a] : 1.f;
 
   fetch(0);
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
       // amax = f 2^e with f in [0.5, 1): |x| 2^(15 - e) < 2^15; bounded so that scale and inverse stay normal numbers
       const int e = (int)((__float_as_uint(amax) >> 23) & 0xffu) - 126;
       const int want = min(max(kSplitExp - e, -113), 114);
-      infinite |= e > 128;
+      if (MLP) infinite |= e > 128;
       if (__builtin_amdgcn_ballot_w64(want < ex) != 0ull) {
         // two bits of headroom, so that the maximum of a few more values rarely asks for another rescaling
         const int nex = want < ex ? want - 2 : ex;
@@ -344,6 +344,30 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
         ++st;
       }
     } else {
+      // Rows with an infinity (their halves are NaN): every hidden unit by the features that are not finite, as float32
+      // arithmetic has it; infinities swallow the finite products.  The weights come out of the packed slices.
+      if (I::kF32 && __builtin_amdgcn_ballot_w64(infinite) != 0ull) {
+#pragma unroll
+        for (int hb = 0; hb < NB; ++hb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[hb][v] = infinite ? 0.f : acc[hb][v];
+        const int full = d & ~3;
+        for (int k = 0; k < d; ++k) {
+          const float xv = static_cast<float>(x[(int64_t)id * d + k]);
+          const bool odd = infinite && !(fabsf(xv) < __builtin_inff());
+          if (__builtin_amdgcn_ballot_w64(odd) == 0ull) continue;
+          const int slot = k < full ? k : full + k - (d - 4), in = slot % CH, gk = in / (CH / 2), e = in % (CH / 2);   // (see stream_slot)
+          const _Float16* wk = reinterpret_cast<const _Float16*>(src + (size_t)(slot / CH) * SG::kUnits + (e >> 3) * 128 + 32 * gk) + (e & 7);
+#pragma unroll
+          for (int hb = 0; hb < NB; ++hb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              const int at = hb * S * 128 + 8 * (v >> 2) + 4 * g + (v & 3);       // units of 8 halves
+              const float wv = (float)wk[at * 8] + (float)wk[(at + 64) * 8];
+              acc[hb][v] = odd ? acc[hb][v] + xv * wv : acc[hb][v];
+            }
+        }
+      }
       // bias, ReLU, per-request scale, split: acc[hb][v] of lane (r, g) is hidden unit 32 hb + 8 (v/4) + 4 g + v%4
       const float4* b1p = reinterpret_cast<const float4*>(hd.b1 + (size_t)a * D);
       float amax = 0.f;
@@ -391,11 +415,8 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
     }
   }
   if (dump) return;
-  // an infinite feature makes every expected accuracy NaN, as float32 arithmetic does (its halves would already be NaN
-  // in front of a ReLU, which turns them into zeros)
   // (the denominators lie like the numerators and span both lane halves; the epilogue adds the halves' sums)
   ssum = 0.5f * (r < 16 ? ssum : ssum_hi);
-  if (infinite) ssum = __builtin_nanf("");
   score_epilogue(tb, w, ea_lo, ea_hi, ssum, m2, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, split);
 }
 

@@ -1169,7 +1169,7 @@ def test_empty_window_right_behind_a_split_one(gpu):
     ctx.close()
 
 
-@pytest.mark.parametrize("dtype", [wl.BF16], ids=["bf16"])
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32], ids=["bf16", "f32"])
 @pytest.mark.parametrize("d,at", [(72, 71), (71, 64), (9, 8), (100, 95), (128, 120), (300, 299)])
 def test_infinite_feature_in_front_of_a_hidden_layer(gpu, dtype, d, at):
     """An infinite feature, also among the last ones of a row that ends inside a step, acts as in plain arithmetic: hidden units
