@@ -70,6 +70,7 @@ struct sp_ctx {
   int32_t sort_spin_limit = kSortSpinLimit;   // polls before a radix pass's look-back is given up (< 0: at once)
   long long* h_ticks = nullptr;      // pinned mirror of ps.ticks
   Decision* h_log = nullptr;         // pinned: the last launch's decisions, written by the rounds kernel
+  int32_t* h_lost = nullptr;         // pinned: a workgroup of the last launch has given up waiting
   std::vector<Decision> log;         // the window's decisions as far as they have come to the host (rounds 0, 1, ...)
   double tick_ms = 0.0;              // milliseconds per timestamp tick
   std::vector<float> round_ms;       // per-round latencies of the last timed sp_schedule on that path
@@ -602,6 +603,10 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
     void* dp = nullptr;
     SP_HIP(c, hipHostGetDevicePointer(&dp, c->h_log, 0));
     ps.log_host = (Decision*)dp;
+    SP_HIP(c, hipHostMalloc((void**)&c->h_lost, sizeof(int32_t), hipHostMallocDefault));
+    *c->h_lost = 0;
+    SP_HIP(c, hipHostGetDevicePointer(&dp, c->h_lost, 0));
+    ps.lost_host = (int32_t*)dp;
   }
   c->gen_base = 0;
   c->persist = true;
@@ -655,6 +660,7 @@ sp_status launch_rounds_persistent(sp_ctx* c, hipStream_t s, int n_rounds) {
   ps.spin_limit = c->spin_limit;
   ps.gen_base = c->gen_base;
   c->gen_base += (uint32_t)n_rounds;
+  *c->h_lost = 0;                                                // (the launch before has been waited for)
   if (c->tb.pol_split)
     hipLaunchKernelGGL(k_rounds_persistent<true>, dim3(ps.n_pairs + 2), dim3(kRoundThreads), persist_dynamic_lds(c), s, c->tb, c->w, ps);
   else
@@ -994,12 +1000,13 @@ sp_status fetch_state(sp_ctx* c, hipStream_t s, bool mirrored = false) {
     c->scored = false;
     return SP_EDEVICE;
   }
-  if (c->h_state->err & kErrSync) {
+  if ((c->h_state->err & kErrSync) || (c->h_lost && *c->h_lost)) {
     // resident workgroups lost each other: leave the exchange buffers clean and stop using that path
     c->hip_err = "rounds kernel: a wait between workgroups ran out";
     fill_u64(s, c->ps.slots, 8 * (size_t)c->ps.n_pairs);
     fill_u64(s, c->ps.dec, kPersistRounds);
     (void)hipStreamSynchronize(s);
+    *c->h_lost = 0;
     c->persist = false;
     c->scored = false;                 // the window's state is not trustworthy any more: score it again
     return SP_EDEVICE;
@@ -1044,6 +1051,7 @@ void sp_destroy(sp_ctx* c) {
   if (c->h_state) (void)hipHostFree(c->h_state);
   if (c->h_ticks) (void)hipHostFree(c->h_ticks);
   if (c->h_log) (void)hipHostFree(c->h_log);
+  if (c->h_lost) (void)hipHostFree(c->h_lost);
   if (c->h_grp_n) (void)hipHostFree(c->h_grp_n);
   if (c->ev_groups) (void)hipEventDestroy(c->ev_groups);
   for (hipEvent_t e : c->ev)

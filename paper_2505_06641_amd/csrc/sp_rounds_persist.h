@@ -71,6 +71,7 @@ struct Persist {
   unsigned long long* dec;      // [kPersistRounds]: decision of each round, bit 63 set; zero once consumed
   Outputs out;                  // the caller's arrays, when this launch starts a window and fills them (else null)
   Decision* log_host;           // [kPersistRounds] pinned: the launch's decisions for the host
+  int32_t* lost_host;           // pinned: set by any workgroup whose wait has run out
   long long* ticks;             // [kPersistRounds + 1]: constant-rate timestamps, launch start then each decision
 };
 
@@ -89,6 +90,13 @@ __device__ __forceinline__ void st_dev(unsigned long long* p, unsigned long long
 __device__ __forceinline__ unsigned long long slot_word0(float score, uint32_t gen, bool valid, int b) {
   return ((unsigned long long)__float_as_uint(score) << 32) | ((unsigned long long)(gen & kGenMask) << 9) |
          (valid ? 0x100ull : 0ull) | (unsigned long long)((b - 1) & 0xff);
+}
+
+// A wait has run out.  The commit workgroup mirrors the state for the host when its own work ends, which may be before another
+// workgroup gives up: each of them tells the host itself.
+__device__ __forceinline__ void raise_lost(State* st, const Persist& ps) {
+  atomicOr(&st->err, kErrSync);
+  *ps.lost_host = 1;
 }
 
 __device__ __forceinline__ void copy_output(int i, const Window& w, const Outputs& out) {
@@ -188,7 +196,7 @@ __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Per
     st->total_wu = twu; st->total_u = tu; st->total_viol = tv;
     if (any) st->last = last;
     if (done) st->done = 1;
-    if (failed) atomicOr(&st->err, kErrSync);
+    if (failed) raise_lost(st, ps);
     mirror_state(w);                        // the host reads this copy: nothing is copied behind the kernel
   }
 }
@@ -283,7 +291,7 @@ __device__ void persist_reduce_loop(const Tables& tb, const Window& w, const Per
     }
     __syncthreads();
     if (*timed_out) {
-      if (tid == 0) atomicOr(&w.st->err, kErrSync);
+      if (tid == 0) raise_lost(w.st, ps);
       break;
     }
     Best top1 = waves[rl & 1][0];
@@ -726,7 +734,7 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
     }
     __syncthreads();
     if (timed_out) {
-      if (tid == 0) atomicOr(&st->err, kErrSync);
+      if (tid == 0) raise_lost(st, ps);
       break;
     }
     const uint32_t cidp1 = decided[rl & 1].cid;                // (written again two rounds from here)
