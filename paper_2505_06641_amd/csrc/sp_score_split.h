@@ -48,11 +48,14 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1e30f;
 constexpr int kSplitExp = 15;               // operands are scaled into (-2^15, 2^15)
 constexpr float kExpShift = 14.0f;          // exponentials are scaled into (0, 2^14]
+// Accuracies are scaled by this in the packed tables: their halves then keep 22 bits down to 2^-18, and what lies below is off by
+// 2^-40 at most.  (Unscaled, half precision ends at 2^-24: expected accuracies near 0.001 would be off by 3e-5 of themselves.)
+constexpr float kTableScale = 32768.0f;
 
 // Packed block of one (application, class tile), in 16-byte units (8 halves or 4 floats each):
 //   W     [D/16][2][64]  unit ((s*2 + part)*64 + lane): halves e = 0..7 hold part (0 = hi, 1 = lo) of
 //                        W'[k = (lane/32)*D/2 + 8 s + e][class = 32 ct + lane%32], W' = W * 2^ew
-//   table [2][64]        unit (part*64 + lane): halves e hold part of Acc[m = lane%16][class] (0 for m >= M),
+//   table [2][64]        unit (part*64 + lane): halves e hold part of 2^15 Acc[m = lane%16][class] (0 for m >= M),
 //                        class = 32 ct + 16 s + 8 (e/4) + 4 g + e%4 with g = lane/32, s = (lane/16)%2: the
 //                        A operand of a 16x16x32 MFMA whose K index 8 (lane/16) + e runs over the classes
 //                        in the order the exponentials sit in the lanes after the row swap (softmax_phase)
@@ -149,7 +152,7 @@ inline float pack_split_blocks(const float* W /*[d,C]*/, const float* b /*[C]*/,
       for (int e = 0; e < 8; ++e) {
         const int m = lane % 16, g = lane / 32, sl = (lane / 16) % 2;
         const int cls = 32 * ct + 16 * sl + 8 * (e / 4) + 4 * g + e % 4;
-        const float v = (cls < C && m < M) ? acc[(size_t)m * C + cls] : 0.f;
+        const float v = (cls < C && m < M) ? acc[(size_t)m * C + cls] * kTableScale : 0.f;
         uint16_t hi, lo;
         host_split(v, hi, lo);
         tab[((size_t)0 * 64 + lane) * 8 + e] = hi;
@@ -482,7 +485,7 @@ __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w
   }
   // eacc[v] of lane (r, g) is table row 8*(v/4) + 4*g + v%4 for request r:
   // v 0..3 -> variants 4g..4g+3, v 4..7 -> variants 8+4g..8+4g+3; the sum of exponentials spans both lane halves
-  const float inv = 1.0f / (lane_sum + other_half(lane_sum, g));
+  const float inv = 1.0f / (lane_sum + other_half(lane_sum, g)), inv_ea = inv * (1.0f / kTableScale);
   // prior of Sec. 4.2 eq. (10)-(11) as an affine map of the expected accuracies (gain 1, bias 0 without one)
   const float gain = tb.ea_gain[a];
   const float* biasp = tb.ea_bias + a * tb.Mmax;
@@ -491,7 +494,7 @@ __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w
 #pragma unroll
   for (int v = 0; v < 8; ++v) {
     const int m = 8 * (v >> 2) + 4 * g + (v & 3);
-    ea[v] = (m < M) ? fmaf(gain, eacc[v] * inv, biasp[m]) : 0.f;
+    ea[v] = (m < M) ? fmaf(gain, eacc[v] * inv_ea, biasp[m]) : 0.f;
     part += ea[v];
   }
   const float mean = (part + __shfl_xor(part, 32)) / (float)M;

@@ -1232,3 +1232,22 @@ def test_a_wait_that_runs_out_is_reported_by_its_own_call(gpu):
             assert rc == binding.SP_OK and summ["n_rounds"] == 2
         ctx.close()
     assert lost > 0
+
+
+@pytest.mark.parametrize("dtype,d,H,C", [(wl.F32, 300, 0, 100), (wl.F32, 40, 24, 30), (wl.F32, 40, 0, 150), (wl.BF16, 64, 0, 100), (wl.BF16, 72, 40, 20),
+                                         (wl.BF16, 64, 200, 20)])
+def test_small_accuracies_keep_their_bits(gpu, dtype, d, H, C):
+    """Accuracy tables with values down to 1e-6, whole variants of small ones among them: expected accuracies relative to
+    themselves, at the general float32 tolerance (the halves hold 22 bits: 2.4e-7 each)."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8750 + d, n=300, classes=(C, 7), models=(8, 3), feat_dim=d, hidden_dim=H, feat_dtype=dtype)
+    rng = np.random.default_rng(8751)
+    for a in range(2):
+        M, Ca = w.profile.acc[a].shape
+        w.profile.acc[a] = (w.profile.acc[a] * 10.0 ** -np.linspace(0.0, 6.0, M)[:, None] * 10.0 ** rng.uniform(-0.3, 0.0, (M, Ca))).astype(np.float32)
+    ref_ea, _ = orc.score_requests(w.profile, w.requests)
+    ctx = binding.Context(w.profile, 300)
+    ea = torch.zeros((300, ctx.m_max), device="cuda:0")
+    ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
+    parity.assert_close("EA", ea.cpu().numpy(), ref_ea, TOL, floor=1e-12)
+    ctx.close()
