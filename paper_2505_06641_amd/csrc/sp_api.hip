@@ -2,6 +2,8 @@
 // upload, window buffers, kernel launch order, status codes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -60,6 +62,7 @@ struct sp_ctx {
   unsigned char* w1p = nullptr;      // packed layer-1 slices for that kernel
   int64_t* w1_off = nullptr;         // [A] byte offsets
   int stream_nb = 0;                 // > 0: heads run on the streaming matrix-core kernel with this many blocks of 32 rows
+  bool stream_cols = false;          // ... which multiplies features of very different ranges by a factor each
   StreamHeads stream{};
   // all rounds of a chunk in one launch, when every (application, variant) pair fits on the device at once
   bool persist = false;
@@ -252,7 +255,8 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   }
   c->Mmax = Mmax; c->Cmax = Cmax;
   c->score_lds = (size_t)kScoreWaves * kScoreRW * (size_t)(c->d + c->H) * sizeof(float);
-  if (c->score_lds > 160 * 1024) return SP_ECAPACITY;
+  if (c->score_lds > 160 * 1024) return SP_ECAPACITY;            // (d + H <= 1,280)
+  static_assert((size_t)kScoreWaves * kScoreRW * kStreamMaxD * sizeof(float) == 160 * 1024, "the streaming kernel's longest row");
 
   Tables& tb = c->tb;
   tb.A = A; tb.d = c->d; tb.H = c->H; tb.B = B; tb.Mmax = Mmax; tb.Cmax = Cmax; tb.dtype = c->dtype;
@@ -460,13 +464,36 @@ sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
   }
   std::vector<unsigned char> host(total * SG::kUnits * 16, 0), blocks;
   std::vector<float> b1((size_t)(MLP ? A * 32 * NB : 1), 0.f), un1(A, 1.f), un2(A, 1.f), w2f;
+  std::vector<float> cols(I::kF32 ? (size_t)A * nkc * I::kChunk : 1, 1.f);
+  std::vector<T> w1;
   for (int a = 0; a < A; ++a) {
     const int C = p->n_classes[a], O = MLP ? H : C, CT = (C + kClassTile - 1) / kClassTile;
     const T* W1 = (const T*)p->W1[a];
+    const auto spread = [](const std::vector<int>& e) { return std::any_of(e.begin(), e.end(), [](int v) { return v != 0; }); };
+    // hidden units, then features, of very different ranges (see equalizing_exponents)
+    const std::vector<int> eh = MLP ? equalizing_exponents((const T*)p->W2[a], H, C) : std::vector<int>();
+    if (spread(eh)) {
+      w1.assign(W1, W1 + (size_t)d * O);
+      for (size_t i = 0; i < w1.size(); ++i) w1[i] = host_times_2(w1[i], eh[i % O]);
+      W1 = w1.data();
+    }
+    if (I::kF32) {
+      const std::vector<int> ef = equalizing_exponents(W1, d, O);
+      if (spread(ef)) {
+        if (W1 != w1.data()) w1.assign(W1, W1 + (size_t)d * O);
+        for (size_t i = 0; i < w1.size(); ++i) w1[i] = host_times_2(w1[i], -ef[i / O]);
+        W1 = w1.data();
+        for (int k = 0; k < nkc * I::kChunk; ++k) {
+          const int f = stream_slot(k, d, 16 / (int)sizeof(T)).feature;
+          if (f >= 0) cols[(size_t)a * nkc * I::kChunk + k] = std::ldexp(1.0f, ef[f]);
+        }
+        c->stream_cols = true;
+      }
+    }
     float scale = 1.f;
     if (I::kF32) {
       float wmax = 0.f;
-      for (size_t i = 0; i < (size_t)d * O; ++i) wmax = std::max(wmax, std::fabs((float)W1[i]));
+      for (size_t i = 0; i < (size_t)d * O; ++i) wmax = std::max(wmax, std::fabs(host_value(W1[i])));
       const int ew = host_scale_exponent(wmax);
       scale = std::ldexp(1.0f, ew);
       un1[a] = std::ldexp(1.0f, -ew);
@@ -475,18 +502,13 @@ sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
     if constexpr (MLP) {
       for (int kc = 0; kc < nkc; ++kc, at += (size_t)SG::kUnits * 16)
         pack_stream_slice<T, NB>(W1, d, O, kc, 0, scale, reinterpret_cast<uint16_t*>(at));
-      std::memcpy(b1.data() + (size_t)a * 32 * NB, p->b1[a], (size_t)H * sizeof(float));
-      const float* w2 = (const float*)p->W2[a];
-      if (!I::kF32) {
-        w2f.resize((size_t)H * C);
-        for (size_t i = 0; i < w2f.size(); ++i) {
-          const uint32_t bits = (uint32_t)((const uint16_t*)p->W2[a])[i] << 16;
-          std::memcpy(&w2f[i], &bits, 4);
-        }
-        w2 = w2f.data();
+      w2f.resize((size_t)H * C);
+      for (int j = 0; j < H; ++j) {
+        b1[(size_t)a * 32 * NB + j] = std::ldexp(p->b1[a][j], eh[j]);
+        for (int cl = 0; cl < C; ++cl) w2f[(size_t)j * C + cl] = std::ldexp(host_value(((const T*)p->W2[a])[(size_t)j * C + cl]), -eh[j]);
       }
       blocks.resize((size_t)CT * SB::kBytes);
-      un2[a] = pack_split_blocks<32 * NB, kMapTile>(w2, p->b2[a], p->acc[a], H, C, p->n_models[a], blocks.data());
+      un2[a] = pack_split_blocks<32 * NB, kMapTile>(w2f.data(), p->b2[a], p->acc[a], H, C, p->n_models[a], blocks.data());
       for (int ct = 0; ct < CT; ++ct, at += (size_t)SG::kUnits * 16) std::memcpy(at, blocks.data() + (size_t)ct * SB::kBytes, SB::kBytes);
     } else {
       // tables and biases in the layout of the class blocks: packed as blocks of a head without inputs
@@ -507,13 +529,14 @@ sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
   sp_status s;
   unsigned char* d_st;
   int64_t* d_off;
-  float *d_b1, *d_u1, *d_u2;
+  float *d_b1, *d_u1, *d_u2, *d_cols;
   if ((s = dev_upload(c, &d_st, host)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_off, off)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_b1, b1)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_u1, un1)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_u2, un2)) != SP_OK) return s;
-  c->stream = StreamHeads{d_st, d_off, d_b1, d_u1, d_u2};
+  if ((s = dev_upload(c, &d_cols, cols)) != SP_OK) return s;
+  c->stream = StreamHeads{d_st, d_off, d_b1, d_u1, d_u2, d_cols};
   return SP_OK;
 }
 
@@ -532,13 +555,13 @@ sp_status pack_stream(sp_ctx* c, const sp_profile* p) {
   return c->H > 0 ? pack_stream_t<uint16_t, true>(c, p) : pack_stream_t<uint16_t, false>(c, p);
 }
 
-template <typename T, bool MLP>
+template <typename T, bool MLP, bool COLS = false>
 void launch_score_stream(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, const float2* dw, uint32_t* sortkey,
                          float* logits) {
   const int tile = stream_tile(c->stream_nb);
   const dim3 grid((unsigned)((c->n + tile - 1) / tile + c->A + kXcds)), blk(tile / 32 * kWave);   // see xcd_tile
 #define SP_LAUNCH_ST(NB) \
-  hipLaunchKernelGGL((k_score_stream<T, NB, MLP>), grid, blk, 0, s, c->tb, c->w, (const T*)x, ids, dw, sortkey, c->stream, logits)
+  hipLaunchKernelGGL((k_score_stream<T, NB, MLP, COLS>), grid, blk, 0, s, c->tb, c->w, (const T*)x, ids, dw, sortkey, c->stream, logits)
   switch (c->stream_nb) {
     case 1: SP_LAUNCH_ST(1); break;
     case 2: SP_LAUNCH_ST(2); break;
@@ -811,7 +834,9 @@ void launch_score(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, c
   }
   if (c->stream_nb > 0) {
     if (c->dtype == SP_F32) {
-      if (c->H > 0) launch_score_stream<float, true>(c, s, x, ids, dw, sortkey, logits);
+      if (c->H > 0 && c->stream_cols) launch_score_stream<float, true, true>(c, s, x, ids, dw, sortkey, logits);
+      else if (c->H > 0) launch_score_stream<float, true>(c, s, x, ids, dw, sortkey, logits);
+      else if (c->stream_cols) launch_score_stream<float, false, true>(c, s, x, ids, dw, sortkey, logits);
       else launch_score_stream<float, false>(c, s, x, ids, dw, sortkey, logits);
     } else {
       if (c->H > 0) launch_score_stream<uint16_t, true>(c, s, x, ids, dw, sortkey, logits);

@@ -76,9 +76,12 @@ inline int stream_channel(int s, int g, int e) { return g * (StreamIn<T>::kChunk
 // (`per` features) that would pass the row's end is read that much further left; the features that it repeats count by half
 // in either place (exact in both types).  With the whole weight in one place and zero in the other an infinite feature would
 // make NaNs, which a hidden layer's ReLU turns into zeros.  Pieces behind the row's end are zero.
-inline uint16_t host_bf16_half(uint16_t v) {
-  return (uint16_t)(__builtin_bit_cast(uint32_t, __builtin_bit_cast(float, (uint32_t)v << 16) * 0.5f) >> 16);
+inline float host_times_2(float v, int e) { return std::ldexp(v, e); }
+inline uint16_t host_times_2(uint16_t v, int e) {       // (bfloat16 bits)
+  return (uint16_t)(__builtin_bit_cast(uint32_t, std::ldexp(__builtin_bit_cast(float, (uint32_t)v << 16), e)) >> 16);
 }
+inline float host_value(float v) { return v; }
+inline float host_value(uint16_t v) { return __builtin_bit_cast(float, (uint32_t)v << 16); }
 struct StreamSlot { int feature; float part; };
 inline StreamSlot stream_slot(int k, int d, int per) {
   const int full = d / per * per;
@@ -103,10 +106,42 @@ inline void pack_stream_slice(const T* W /*[d, O]*/, int d, int O, int kc, int r
           const T* from = W + (size_t)std::max(k, 0) * O + o0;
           for (int r = 0; r < 32 && k >= 0 && o0 + r < O; ++r) {      // (the buffer is zero to begin with)
             if constexpr (I::kF32) host_split((float)from[r] * (scale * slot.part), at[r * 8], at[(64 + r) * 8]);
-            else at[r * 8] = slot.part == 1.0f ? (uint16_t)from[r] : host_bf16_half((uint16_t)from[r]);
+            else at[r * 8] = slot.part == 1.0f ? (uint16_t)from[r] : host_times_2((uint16_t)from[r], -1);
           }
         }
 }
+
+// Inputs of very different ranges.  Halves that share one scale hold an input (or a weight) to 22 bits only down to 2^-18 of the
+// largest, so an input that is small next to the others but has large weights to make up for it would lose bits that a
+// float32 product keeps: with column scales of 10^+-4 expected accuracies were off by 1e-4.  What counts is an input's share in the sums,
+// so inputs are multiplied by 2^e and their weights by 2^-e, e such that every input's largest weight has the same exponent.
+// In front of a hidden layer's outputs this is exact and free (the ReLU commutes with it: it goes into the first layer's
+// weights and biases); features are multiplied in the kernel (COLS), which only heads with a spread of more than kStreamSpread take:
+// below it what is lost is less than 2^-28 of the largest product.  It costs 2 us of 41 (32,768 rows of 768, 100 classes) and of
+// 29 (100,000 of a 128-64-10 head), but registers with wide hidden layers: 36 -> 47 us (128-128-20), 42 -> 124 (60,000 of 200-256-40,
+// which take 912 on the generic kernel).
+constexpr int kStreamSpread = 10, kStreamShiftMax = 60;
+// Exponents e (<= 0) of the rows of W [rows, cols], all zero where the rows' ranges are alike.  Rows of zeros get the smallest:
+// such an input must not set the scale for the others.
+template <typename T>
+inline std::vector<int> equalizing_exponents(const T* W, int rows, int cols) {
+  std::vector<int> e(rows, 0);
+  int top = INT_MIN, low = INT_MAX;
+  for (int k = 0; k < rows; ++k) {
+    float m = 0.f;
+    for (int j = 0; j < cols; ++j) m = std::max(m, std::fabs(host_value(W[(size_t)k * cols + j])));
+    if (!std::isfinite(m)) return std::vector<int>(rows, 0);
+    if (m > 0.f) (void)std::frexp(m, &e[k]);
+    else e[k] = INT_MIN;
+    if (m > 0.f) top = std::max(top, e[k]);
+    low = std::min(low, e[k]);
+  }
+  if (top == INT_MIN || (low != INT_MIN && top - low <= kStreamSpread)) return std::vector<int>(rows, 0);
+  for (int k = 0; k < rows; ++k) e[k] = e[k] == INT_MIN ? -kStreamShiftMax : std::max(e[k] - top, -kStreamShiftMax);
+  return e;
+}
+
+constexpr int kStreamMaxD = 1280;                // longest row: the context's limit on d + H (its generic kernel's LDS)
 
 struct StreamHeads {
   const unsigned char* stages;    // per application: its stages, kUnits * 16 bytes each
@@ -114,6 +149,7 @@ struct StreamHeads {
   const float* b1;                // [A, 32 NB] first-layer bias of one-hidden-layer heads, padded with zeros
   const float* unscale1;          // [A] undoes the first layer's weight scale (1 for bfloat16)
   const float* unscale2;          // [A] undoes the second layer's
+  const float* cols;              // [A, steps * channels] factor of every slot of a row (COLS), see equalizing_exponents
 };
 
 static __device__ f32x4 stream_zeros;            // what lies behind a row's end
@@ -121,14 +157,16 @@ static __device__ f32x4 stream_zeros;            // what lies behind a row's end
 // 16 bytes of a feature row: rows start at any multiple of the element size
 typedef f32x4 f32x4_any __attribute__((aligned(2)));
 
-template <typename T, int NB, bool MLP>
+template <typename T, int NB, bool MLP, bool COLS = false>
 __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
     Tables tb, Window w, const T* __restrict__ x, const int32_t* __restrict__ ids, const float2* __restrict__ dw_g,
     uint32_t* __restrict__ sortkey, StreamHeads hd, float* __restrict__ logits_out) {
   using I = StreamIn<T>;
   using SG = StreamStage<NB, MLP>;
   constexpr int S = I::kSteps, CH = I::kChunk, D = 32 * NB;
+  static_assert(!COLS || I::kF32, "bfloat16 features are not scaled");
   __shared__ f32x4 buf[2][SG::kUnits];
+  __shared__ f32x4 cols[COLS ? kStreamMaxD / 4 : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
   const int tile = xcd_tile(blockIdx.x, __builtin_amdgcn_readfirstlane(w.tile_start[tb.A]));
@@ -199,6 +237,8 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
 
   fetch(0);
   park(0);
+  if (COLS)
+    for (int i = tid; i < nkc * (CH / 4); i += SG::kThreads) cols[i] = reinterpret_cast<const f32x4*>(hd.cols)[(size_t)a * nkc * (CH / 4) + i];
   __syncthreads();
 
   int st = 0;                                            // running stage
@@ -242,11 +282,14 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
     auto slice_f32 = [&](int kc, f32x4 (&xs)[4]) {
       fetch(st + 1);
       __builtin_amdgcn_sched_barrier(0);
+      f32x4 xv[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xv[q] = COLS ? xs[q] * cols[kc * (CH / 4) + 4 * g + q] : xs[q];
       float amax = 0.f;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) amax = fmaxf(amax, fabsf(xs[q][j]));
+        for (int j = 0; j < 4; ++j) amax = fmaxf(amax, fabsf(xv[q][j]));
       amax = fmaxf(amax, other_half(amax, g));
       // amax = f 2^e with f in [0.5, 1): |x| 2^(15 - e) < 2^15; bounded so that scale and inverse stay normal numbers
       const int e = (int)((__float_as_uint(amax) >> 23) & 0xffu) - 126;
@@ -269,7 +312,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
 #pragma unroll
         for (int j = 0; j < 4; j += 2) {
           f16x2 hi, lo;
-          split_f16x2(xs[q][j] * xsc, xs[q][j + 1] * xsc, hi, lo);
+          split_f16x2(xv[q][j] * xsc, xv[q][j + 1] * xsc, hi, lo);
           const int k = 4 * q + j;
           xh[k >> 3][k & 7] = hi[0]; xh[k >> 3][(k & 7) + 1] = hi[1];
           xl[k >> 3][k & 7] = lo[0]; xl[k >> 3][(k & 7) + 1] = lo[1];

@@ -1251,3 +1251,33 @@ def test_small_accuracies_keep_their_bits(gpu, dtype, d, H, C):
     ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
     parity.assert_close("EA", ea.cpu().numpy(), ref_ea, TOL, floor=1e-12)
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,d,H,C", [(wl.F32, 300, 0, 20), (wl.F32, 770, 0, 100), (wl.F32, 289, 0, 300), (wl.F32, 40, 0, 50), (wl.F32, 130, 24, 30),
+                                         (wl.F32, 33, 60, 5), (wl.F32, 150, 128, 40), (wl.F32, 97, 256, 40), (wl.BF16, 70, 40, 20), (wl.BF16, 64, 128, 9)])
+def test_features_and_hidden_units_of_very_different_ranges(gpu, dtype, d, H, C):
+    """Features that are not normalised (scales 10^-5 to 10^5, the weights making up for it), hidden units likewise, inputs that a
+    head ignores at values of 10^9: as accurate as normalised ones (float32 tolerance; a float32 product does not care)."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8760 + d, n=300, classes=(C, 7), models=(5, 3), feat_dim=d, hidden_dim=H, feat_dtype=dtype)
+    p, rng = w.profile, np.random.default_rng(8761)
+    up = (lambda v: v) if dtype == wl.F32 else wl.f32_to_bf16_bits
+    down = (lambda v: np.asarray(v, np.float32)) if dtype == wl.F32 else (lambda v: orc.widen(v).astype(np.float32))
+    if dtype == wl.F32:                                  # (bfloat16 features carry their own exponents)
+        s = (10.0 ** rng.uniform(-5.0, 5.0, d)).astype(np.float32)
+        w.requests.x = (w.requests.x * s).astype(np.float32)
+        w.requests.x[:, d // 2] = rng.uniform(1e9, 2e9, 300)
+        for a in range(2):
+            p.W1[a] = (p.W1[a] / s[:, None]).astype(np.float32)
+            p.W1[a][d // 2] = 0.0
+    if H:
+        for a in range(2):
+            t = (10.0 ** rng.uniform(-5.0, 5.0, H)).astype(np.float32)
+            p.W1[a], p.b1[a] = up(down(p.W1[a]) * t), (p.b1[a] * t).astype(np.float32)
+            p.W2[a] = up(down(p.W2[a]) / t[:, None])
+    ref_ea, ref_key = orc.score_requests(p, w.requests)
+    ctx = binding.Context(p, 300)
+    ea = torch.zeros((300, ctx.m_max), device="cuda:0")
+    ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
+    parity.assert_close("EA", ea.cpu().numpy(), ref_ea, TOL)
+    ctx.close()
