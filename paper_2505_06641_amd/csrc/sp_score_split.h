@@ -306,7 +306,7 @@ __device__ __forceinline__ float other_half(float v, int g) {
 // instruction per logit, which kernels that the matrix or vector units bound do not spend.
 template <bool FINE = false>
 __device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bias, f32x16& acc, float unscale, f32x4& ea_lo,
-                                             f32x4& ea_hi, float& ssum, float& ssum_hi, float& m2, int ct, int C, int g, int lane, bool valid,
+                                             f32x4& ea_hi, float& ssum, float& ssum_hi, float& m2, float& m2_rest, int ct, int C, int g, int lane, bool valid,
                                              int64_t dump_row, float* __restrict__ logits_out, float& best_z, int& best_c,
                                              const bool dump, const bool split) {
   // The other wavefront of this SIMD is, most of the time, streaming the MFMAs of its matrix phase and
@@ -348,9 +348,26 @@ __device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bi
   }
   mt = fmaxf(mt, other_half(mt, g));
   const float m2n = fmaxf(m2, mt * kLog2e);
-  const float scale = __builtin_amdgcn_exp2f(m2 - m2n);
+  float drop = m2 - m2n;
+  if (FINE) {
+    // The reference's own rounding, which for logits of millions is no longer small against the exponents: taken into account
+    // from a quarter on (it is zero up to 2^22), or the largest exponential would leave the halves' range.
+    float rest = mt * kLog2e >= m2 ? fmaf(mt, kLog2e, -m2n) : m2_rest;
+    rest = fabsf(rest) >= 0.25f ? rest : 0.f;
+    drop += m2_rest - rest;
+    m2_rest = rest;
+  }
+  const float scale = __builtin_amdgcn_exp2f(drop);
   m2 = m2n;
   const float shift = FINE ? -m2n : kExpShift - m2n;
+  if (FINE) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = fmaf(acc[v], kLog2e, shift);
+    if (__builtin_amdgcn_ballot_w64(m2_rest != 0.f) != 0ull) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[v] -= m2_rest;
+    }
+  }
   // Exponentials x accuracy-table tile on 16x16x32 MFMAs (16 variants x 16 requests x 32 classes each):
   // ea_lo of lane (row q = lane/16, j = lane%16) holds variants 4q..4q+3 of request j, ea_hi those of
   // request 16 + j.  A lane's own request is lane%32, so in the odd rows ea_lo belongs to the neighbouring
@@ -378,8 +395,8 @@ __device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bi
   for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
-      float p0 = __builtin_amdgcn_exp2f(fmaf(acc[8 * ks + e], kLog2e, shift));             // in (0, 2^14]
-      float p1 = __builtin_amdgcn_exp2f(fmaf(acc[8 * ks + e + 1], kLog2e, shift));
+      float p0 = __builtin_amdgcn_exp2f(FINE ? acc[8 * ks + e] : fmaf(acc[8 * ks + e], kLog2e, shift));             // in (0, 2^14]
+      float p1 = __builtin_amdgcn_exp2f(FINE ? acc[8 * ks + e + 1] : fmaf(acc[8 * ks + e + 1], kLog2e, shift));
       if (FINE) {
         p0 *= 16384.0f;
         p1 *= 16384.0f;
@@ -459,14 +476,14 @@ __device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, fl
                                               int64_t dump_row, float* __restrict__ logits_out, float& best_z,
                                               int& best_c) {
   using SB = SplitBlock<D>;
-  softmax_tile(blk + SB::kWUnits, blk + SB::kWUnits + SB::kTabUnits, acc, unscale, ea_lo, ea_hi, ssum, ssum, m2, ct, C, g, lane, valid,
+  softmax_tile(blk + SB::kWUnits, blk + SB::kWUnits + SB::kTabUnits, acc, unscale, ea_lo, ea_hi, ssum, ssum, m2, m2, ct, C, g, lane, valid,
                dump_row, logits_out, best_z, best_c, DUMP, SPLIT);
 }
 
 // After the last class tile: expected accuracies (eq. (9), with the prior's affine map), variance and key
 // (eq. (12)), the subgroup label, and the request's entries of the grouped arrays.
 __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w, const f32x4& ea_lo, const f32x4& ea_hi,
-                                               float lane_sum, float m2, float best_z, int best_c, int a, int M, int pos,
+                                               float lane_sum, float shift, float factor, float rest, float best_z, int best_c, int a, int M, int pos,
                                                int id, bool valid, int lane, const float2* __restrict__ dw_g,
                                                uint32_t* __restrict__ sortkey, const bool split) {
   const int r = lane & 31, g = lane >> 5;
@@ -522,13 +539,13 @@ __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w
     }
   }
   if (split) {
-    // the lane halves' candidates meet; the largest posterior is exp(z_max - reference) / sum
+    // the lane halves' candidates meet; the largest posterior is exp(z_max - reference) / sum, formed like the sum's terms
     const float oz = other_half(best_z, g);
     const int oc = __float_as_int(other_half(__int_as_float(best_c), g));
     const bool take = oz > best_z || (oz == best_z && oc < best_c);
     const float zmax = take ? oz : best_z;
     const int cmax = take ? oc : best_c;
-    const float pmax = __builtin_amdgcn_exp2f(fmaf(zmax, kLog2e, kExpShift - m2));
+    const float pmax = factor * (rest != 0.f ? 1.0f : __builtin_amdgcn_exp2f(fmaf(zmax, kLog2e, shift)));   // (z_max is the reference)
     if (g == 0) w.sub_g[pos] = (pmax * inv > 0.5f) ? 1 + cmax : 0;
   }
   if (g == 0) {
@@ -621,7 +638,7 @@ __device__ __forceinline__ void class_tiles_and_finish(
   }
 #undef SP_TILE
   if (DUMP) return;
-  score_epilogue(tb, w, ea_lo, ea_hi, ssum, m2, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, SPLIT);
+  score_epilogue(tb, w, ea_lo, ea_hi, ssum, kExpShift - m2, 1.0f, 0.f, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, SPLIT);
 }
 
 // Four consecutive features of a row of d >= 4 from feature k0 on (see row_slot_feature); rows of any width, so the piece

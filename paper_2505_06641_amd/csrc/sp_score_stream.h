@@ -226,7 +226,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
     }
   };
 
-  float m2 = kNegBig, best_z = kNegBig, ssum = 0.f, ssum_hi = 0.f;
+  float m2 = kNegBig, m2_rest = 0.f, best_z = kNegBig, ssum = 0.f, ssum_hi = 0.f;
   int best_c = 0x7fffffff;
   f32x4 ea_lo = {0.f, 0.f, 0.f, 0.f}, ea_hi = {0.f, 0.f, 0.f, 0.f};
   const int64_t dump_row = (int64_t)id * tb.Cmax;
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
       for (int hb = 0; hb < NB; ++hb) {
         if (hb < nbk)
           softmax_tile<true>(tab + hb * SplitBlock<32>::kTabUnits, tab + NB * SplitBlock<32>::kTabUnits + hb * SplitBlock<32>::kBiasUnits,
-                       acc[hb], un, ea_lo, ea_hi, ssum, ssum_hi, m2, grp * NB + hb, C, g, lane, valid, dump_row, logits_out, best_z, best_c,
+                       acc[hb], un, ea_lo, ea_hi, ssum, ssum_hi, m2, m2_rest, grp * NB + hb, C, g, lane, valid, dump_row, logits_out, best_z, best_c,
                        dump, split);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
         f32x16 z;
         logits_phase<D>(blk, xh, xl, z, lane);
         softmax_tile<true>(blk + SplitBlock<D>::kWUnits, blk + SplitBlock<D>::kWUnits + SplitBlock<D>::kTabUnits, z, unscale, ea_lo, ea_hi,
-                     ssum, ssum_hi, m2, ct, C, g, lane, valid, dump_row, logits_out, best_z, best_c, dump, split);
+                     ssum, ssum_hi, m2, m2_rest, ct, C, g, lane, valid, dump_row, logits_out, best_z, best_c, dump, split);
         if (ct + 1 < CT) {
           park(st + 1);
           __syncthreads();
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
   if (dump) return;
   // (the denominators lie like the numerators and span both lane halves; the epilogue adds the halves' sums)
   ssum = 0.5f * (r < 16 ? ssum : ssum_hi);
-  score_epilogue(tb, w, ea_lo, ea_hi, ssum, m2, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, split);
+  score_epilogue(tb, w, ea_lo, ea_hi, ssum, -m2, 16384.0f, m2_rest, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, split);
 }
 
 }  // namespace sp

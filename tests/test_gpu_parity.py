@@ -1281,3 +1281,52 @@ def test_features_and_hidden_units_of_very_different_ranges(gpu, dtype, d, H, C)
     ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
     parity.assert_close("EA", ea.cpu().numpy(), ref_ea, TOL)
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,d,H,C", [(wl.F32, 300, 0, 100), (wl.F32, 40, 0, 20), (wl.F32, 40, 24, 300), (wl.BF16, 64, 0, 100), (wl.BF16, 72, 40, 70)])
+@pytest.mark.parametrize("size", [3e5, 4e7, 6e9, 1e20])
+def test_logits_of_millions_and_more(gpu, dtype, d, H, C, size):
+    """Logits so large that the softmax is a choice: the largest logit's row of the table, in whatever tile of classes it lies
+    and whatever came before it."""
+    torch, binding = gpu
+    n = 200
+    w = wl.tiny(seed=8770 + d, n=n, classes=(C, 7), models=(5, 3), max_batch=4, feat_dim=d, hidden_dim=H, feat_dtype=dtype)
+    p, rng = w.profile, np.random.default_rng(8771)
+    last = p.W2 if H else p.W1
+    for a in range(2):
+        Ca = int(p.n_classes[a])
+        b = (size * rng.permutation(np.linspace(-1.0, 1.0, Ca))).astype(np.float32)     # what decides: every other class is far below
+        if H:
+            p.b2[a] = b
+        else:
+            p.b1[a] = b
+        last[a] = last[a] * 0 if dtype == wl.F32 else np.zeros_like(last[a])
+    ctx = binding.Context(p, n)
+    ea = torch.zeros((n, ctx.m_max), device="cuda:0")
+    ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
+    ctx.close()
+    for i in range(n):
+        a = int(w.requests.app[i])
+        top = int(np.argmax((p.b2 if H else p.b1)[a]))
+        want = p.acc[a][:, top].astype(np.float64)
+        parity.assert_close("EA", ea[i, :want.size].cpu().numpy(), want, TOL)
+
+
+@pytest.mark.parametrize("size", [3e5, 6e9])
+def test_subgroup_labels_of_large_logits(gpu, size):
+    """The subgroup label of logits of millions is the largest one's class: the service order is by label, then key."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8775, n=400, classes=(40,), models=(2,), max_batch=4, feat_dim=300)
+    w.profile.W1[0][:] = 0.0
+    w.profile.W1[0][0, 30] = w.profile.W1[0][1, 4] = np.float32(size)
+    w.requests.x[:] = 0.0
+    w.requests.x[np.arange(400), np.arange(400) % 2] = 1.0
+    ctx = binding.Context(w.profile, 400, policy=wl.Policy(split_groups=1))
+    key = torch.zeros(400, device="cuda:0")
+    order = torch.zeros(400, dtype=torch.int32, device="cuda:0")
+    ctx.sp_score(*binding.to_device(w.requests), key_out=key)
+    ctx.sp_debug_dump(binding.SP_DUMP_ORDER, order)
+    ctx.close()
+    ids = np.arange(400)
+    want = ids[np.lexsort((ids, -key.cpu().numpy().astype(np.float64), np.where(ids % 2 == 0, 31, 5)))]
+    assert np.array_equal(order.cpu().numpy(), want)
