@@ -237,6 +237,24 @@ sp_status upload_heads(sp_ctx* c, const sp_profile* p) {
   return SP_OK;
 }
 
+// Whether every weight that would be held as two halves is finite: an infinite one has no second half (infinity minus infinity),
+// where float32 arithmetic makes of it an excluded class or a unit that is off.
+template <typename T>
+bool finite_weights(const T* W, size_t n) {
+  for (size_t i = 0; i < n; ++i)
+    if (!std::isfinite(host_value(W[i]))) return false;
+  return true;
+}
+template <typename T>
+bool heads_splittable(const sp_profile* p) {
+  for (int a = 0; a < p->n_apps; ++a) {
+    const size_t C = p->n_classes[a], d = p->feat_dim, H = p->hidden_dim;
+    if (sizeof(T) == 4 && !finite_weights((const T*)p->W1[a], d * (H > 0 ? H : C))) return false;      // (bfloat16: taken as they are)
+    if (H > 0 && !finite_weights((const T*)p->W2[a], H * C)) return false;
+  }
+  return true;
+}
+
 sp_status pack_mfma_blocks(sp_ctx* c, const sp_profile* p);
 sp_status pack_mlp_blocks(sp_ctx* c, const sp_profile* p);
 sp_status pack_stream(sp_ctx* c, const sp_profile* p);
@@ -305,13 +323,13 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   } else if (c->H > 128 && c->H <= kMlpH && c->dtype == SP_BF16 && (c->d % 8) == 0) {
     c->mlp_bf16 = true;
     if ((s = pack_mlp_blocks(c, p)) != SP_OK) return s;
-  } else if (c->H <= kMlpH && c->d >= 8) {
+  } else if (c->H <= kMlpH && c->d >= 8 && (c->dtype == SP_F32 ? heads_splittable<float>(p) : heads_splittable<uint16_t>(p))) {
     // blocks of 32 first-layer rows (hidden units, or classes) a wavefront holds at a time
     const int rows = c->H > 0 ? c->H : c->Cmax;
     c->stream_nb = rows <= 32 ? 1 : (rows <= 64 ? 2 : (rows <= 128 ? 4 : 8));
     if ((s = pack_stream(c, p)) != SP_OK) return s;
   } else {
-    // what is left (hidden layers wider than 256, rows of a few features): plain matrices for the generic kernel
+    // what is left (hidden layers wider than 256, rows of a few features, infinite weights): plain matrices for the generic kernel
     s = (c->dtype == SP_BF16) ? upload_heads<uint16_t>(c, p) : upload_heads<float>(c, p);
     if (s != SP_OK) return s;
   }

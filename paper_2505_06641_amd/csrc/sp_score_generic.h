@@ -1,5 +1,5 @@
-// Scoring kernel for the head shapes that no matrix-core kernel takes (hidden layers wider than 256, rows of fewer than
-// eight features with a hidden layer or in bf16; any C; M <= 16; fp32 or bf16 inputs, fp32 arithmetic).  One wavefront owns RW requests of one application
+// Scoring kernel for the heads that no matrix-core kernel takes (hidden layers wider than 256, rows of fewer than
+// eight features with a hidden layer or in bf16, infinite weights; any C; M <= 16; fp32 or bf16 inputs, fp32 arithmetic).  One wavefront owns RW requests of one application
 // from the features to EA and the priority key; lanes span hidden units, then
 // classes.  The posterior is never written: each lane keeps an online-softmax
 // state (running max, running sum of exponentials, M running sums of

@@ -1330,3 +1330,28 @@ def test_subgroup_labels_of_large_logits(gpu, size):
     ids = np.arange(400)
     want = ids[np.lexsort((ids, -key.cpu().numpy().astype(np.float64), np.where(ids % 2 == 0, 31, 5)))]
     assert np.array_equal(order.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("dtype,d,H", [(wl.F32, 300, 0), (wl.F32, 40, 24), (wl.BF16, 64, 0), (wl.BF16, 71, 40)])
+def test_infinite_weights(gpu, dtype, d, H):
+    """A weight of -inf excludes a class (or turns a hidden unit off) for requests with a positive input there."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8780 + d, n=200, classes=(12, 7), models=(5, 3), feat_dim=d, hidden_dim=H, feat_dtype=dtype)
+    p = w.profile
+    ninf = np.float32(-np.inf) if dtype == wl.F32 else np.uint16(0xff80)
+    one = np.float32(1.0) if dtype == wl.F32 else np.uint16(0x3f80)
+    w.requests.x[:, 3] = one
+    ref = copy.deepcopy(w)                               # the same with a weight that is large enough
+    big = np.float32(-1e6) if dtype == wl.F32 else wl.f32_to_bf16_bits(np.float32([-1e6]))[0]
+    for q, v in ((w, ninf), (ref, big)):
+        for a in range(2):
+            q.profile.W1[a][3, 2] = v
+            if H:
+                q.profile.W1[a][:, 5], q.profile.b1[a][5] = 0, 1.0       # a unit that is always on
+                q.profile.W2[a][5, 4] = v
+    ref_ea, _ = orc.score_requests(ref.profile, ref.requests)
+    ctx = binding.Context(p, 200)
+    ea = torch.zeros((200, ctx.m_max), device="cuda:0")
+    ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
+    ctx.close()
+    parity.assert_close("EA", ea.cpu().numpy(), ref_ea, TOL if dtype == wl.F32 else 2e-3)
