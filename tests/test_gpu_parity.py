@@ -1355,3 +1355,20 @@ def test_infinite_weights(gpu, dtype, d, H):
     ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
     ctx.close()
     parity.assert_close("EA", ea.cpu().numpy(), ref_ea, TOL if dtype == wl.F32 else 2e-3)
+
+
+@pytest.mark.parametrize("B", [128, 211, 213, 256])
+def test_subgroup_rounds_of_the_largest_batches(gpu, B):
+    """Subgroups in one launch with the windows of the largest batches in LDS (more than 64 KB per workgroup from 212 on)."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8790 + B, n=3000, classes=(12, 3), models=(3, 2), max_batch=B, feat_dim=24, deadline=(20.0, 900.0),
+                beta=(0.05, 0.3), fractions=(0.8, 0.2))
+    w.profile.W1[0] = (w.profile.W1[0] * 6.0).astype(np.float32)
+    policy = wl.named_policy("sneakpeek")
+    policy.split_groups = 1
+    got, stats = full_parity(gpu, w, max_rounds=12, policy=policy)
+    assert stats["rounds"] > 3 and max(r["batch"] for r in got["log"]) > 64
+    ctx = binding.Context(w.profile, 3000, policy=policy)
+    ctx.sp_score(*binding.to_device(w.requests))
+    assert ctx.lib.sp_rounds_in_one_launch(ctx.h)
+    ctx.close()
