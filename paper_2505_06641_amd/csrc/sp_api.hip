@@ -74,7 +74,7 @@ struct sp_ctx {
   long long* h_ticks = nullptr;      // pinned mirror of ps.ticks
   Decision* h_log = nullptr;         // pinned: the last launch's decisions, written by the rounds kernel
   int32_t* h_lost = nullptr;         // pinned: a workgroup of the last launch has given up waiting
-  std::vector<Decision> log;         // the window's decisions as far as they have come to the host (rounds 0, 1, ...)
+  std::vector<Decision> log;         // the window's decisions as far as they have come to the host (rounds 0, 1, ...) and as it holds them
   double tick_ms = 0.0;              // milliseconds per timestamp tick
   std::vector<float> round_ms;       // per-round latencies of the last timed sp_schedule on that path
   int32_t rounds_in_call = 0;        // rounds the last sp_schedule call committed
@@ -650,6 +650,7 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
     ps.lost_host = (int32_t*)dp;
   }
   c->gen_base = 0;
+  c->log.reserve(kPersistRounds);
   c->persist = true;
   return SP_OK;
 }
@@ -1076,7 +1077,11 @@ sp_status sp_create(const sp_profile* profile, int device_id, sp_ctx** out) {
     delete c;
     return SP_EDEVICE;
   }
-  s = build_ctx(c, profile);
+  try {
+    s = build_ctx(c, profile);
+  } catch (const std::bad_alloc&) {                                // host copies of tables and packed weights
+    s = SP_ENOMEM;
+  }
   if (s == SP_OK) s = static_scratch_for(c, device_id, &c->static_scratch);
   if (s != SP_OK) {
     sp_destroy(c);
@@ -1163,7 +1168,8 @@ sp_status sp_greedy_round(sp_ctx* c, void* stream, sp_decision* out_host, int32_
   sp_status st = fetch_state(c, s, true);
   if (st != SP_OK) return st;
   if (c->rounds_done == before) return SP_DONE;
-  if ((int32_t)c->log.size() == before) c->log.push_back(c->h_state->last);
+  // (within what was reserved: a round allocates nothing; past it the log is copied from the device when it is asked for)
+  if ((int32_t)c->log.size() == before && c->log.size() < c->log.capacity()) c->log.push_back(c->h_state->last);
   if (out_host) std::memcpy(out_host, &c->h_state->last, sizeof(sp_decision));
   return SP_OK;
 }
@@ -1196,7 +1202,8 @@ sp_status sp_greedy_round_static(sp_ctx* c, void* stream, sp_decision* out_host,
   sp_status st = fetch_state(c, s, true);
   if (st != SP_OK) return st;
   if (c->rounds_done == before) return SP_DONE;
-  if ((int32_t)c->log.size() == before) c->log.push_back(c->h_state->last);
+  // (within what was reserved: a round allocates nothing; past it the log is copied from the device when it is asked for)
+  if ((int32_t)c->log.size() == before && c->log.size() < c->log.capacity()) c->log.push_back(c->h_state->last);
   if (out_host) std::memcpy(out_host, &c->h_state->last, sizeof(sp_decision));
   return SP_OK;
 }
@@ -1256,7 +1263,12 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
     st = fetch_state(c, s, true);    // tells how far the device got and whether the queue ran dry
     fetched = true;
     if (st != SP_OK) return st;
-    if (persist && (int32_t)c->log.size() == before) c->log.insert(c->log.end(), c->h_log, c->h_log + (c->rounds_done - before));
+    if (persist && (int32_t)c->log.size() == before) {
+      try {
+        c->log.insert(c->log.end(), c->h_log, c->h_log + (c->rounds_done - before));
+      } catch (const std::bad_alloc&) {                            // (then the log comes from the device, if it is asked for)
+      }
+    }
     if (persist && tm && c->timing_rounds)
       for (int i = 0; i < c->rounds_done - before; ++i)
         c->round_ms.push_back((float)((double)(c->h_ticks[i + 1] - c->h_ticks[i]) * c->tick_ms));

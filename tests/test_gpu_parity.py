@@ -1372,3 +1372,25 @@ def test_subgroup_rounds_of_the_largest_batches(gpu, B):
     ctx.sp_score(*binding.to_device(w.requests))
     assert ctx.lib.sp_rounds_in_one_launch(ctx.h)
     ctx.close()
+
+
+@pytest.mark.parametrize("single", [3, 64, 70])
+def test_log_of_single_rounds_and_scheduled_ones(gpu, single):
+    """The log of a window that single rounds began and sp_schedule ended, below and beyond the decisions that the host keeps
+    (64 without an allocation; otherwise the log is read back from the device)."""
+    torch, binding = gpu
+    w = wl.tiny(seed=8800, n=900, classes=(5, 3), models=(3, 2), max_batch=4, feat_dim=16, alpha=(0.1, 0.3), beta=(0.01, 0.05), deadline=(40.0, 300.0))
+    args = binding.to_device(w.requests)
+    ctx = binding.Context(w.profile, 900)
+    ctx.sp_score(*args)
+    _, want, log = ctx.sp_schedule(0, log_capacity=900)
+    assert len(log) > 100
+    ctx.sp_score(*args)
+    for k in range(single):
+        rc, dec = ctx.sp_greedy_round()
+        assert rc == binding.SP_OK and dec == log[k]
+    rc, got, again = ctx.sp_schedule(0, log_capacity=900)
+    assert got == want and again == log
+    rc, got, short = ctx.sp_schedule(0, log_capacity=single)            # after the end: the log once more
+    assert got == want and short == log[:single]
+    ctx.close()
