@@ -575,7 +575,8 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
                                                                int32_t* __restrict__ ids_out, float2* __restrict__ dw_out,
                                                                SegArgs sg, Window sw, State* st) {
   constexpr int kTile = kGroupThreads * ITEMS;
-  __shared__ uint32_t before[256], total[256];
+  __shared__ uint32_t before[256];
+  __shared__ __align__(16) uint32_t total[256];        // (read four words at a time: wave_digit_bases)
   __shared__ uint32_t red[kGroupWaves][2][64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (blockIdx.x == 0) {              // (the first: as the last it would wait for a place on a full chip)
