@@ -1200,38 +1200,44 @@ def test_infinite_feature_in_front_of_a_hidden_layer(gpu, dtype, d, at):
 
 
 def test_a_wait_that_runs_out_is_reported_by_its_own_call(gpu):
-    """Bounds on the waits from far too short to enough, one round per launch, an application that takes longer than the others
-    to find its window (which are the ones to give up): whichever workgroup loses patience, and whether or not the commit
+    """Bounds on the waits from far too short to enough, in steps of 2%, one round per launch, an application that takes about
+    a hundred times longer than the others to find its window: whichever workgroup loses patience, and whether or not the commit
     got its batch, a call that returns SP_OK has left nothing behind for the next one to fail on."""
     torch, binding = gpu
-    w = wl.tiny(seed=8740, n=24000, classes=(5,) * 6, models=(4, 4, 4, 4, 4, 4), max_batch=16, feat_dim=16, deadline=(4.0, 90.0),
-                fractions=(0.9, 0.02, 0.02, 0.02, 0.02, 0.02))
+    n = 400000
+    w = wl.tiny(seed=8740, n=n, classes=(5,) * 6, models=(4, 4, 4, 4, 4, 4), max_batch=16, feat_dim=8, deadline=(4.0, 90.0),
+                fractions=(0.99, 0.002, 0.002, 0.002, 0.002, 0.002))
     w.requests.deadline_rel_ms[w.requests.app == 0] = 1e-3           # dead from the start, all but the last in service order
     w.requests.weight[:] = 1.0
     first = np.nonzero(w.requests.app == 0)[0]
     w.requests.weight[first[-5:]] = 1e-6
     w.requests.deadline_rel_ms[first[-5:]] = 500.0
     args = binding.to_device(w.requests)
-    lost = 0
-    for polls in list(range(2, 40, 2)) + list(range(40, 200, 10)):
-        ctx = binding.Context(w.profile, 24000)
-        if not ctx.rounds_in_one_launch:
-            pytest.skip("this device does not hold the one-launch rounds kernel")
+    ctx, lost, polls = None, 0, 20.0
+    while polls < 600.0:
+        if ctx is None:
+            ctx = binding.Context(w.profile, n)
+            if not ctx.rounds_in_one_launch:
+                pytest.skip("this device does not hold the one-launch rounds kernel")
         ctx.sp_score(*args)
         torch.cuda.synchronize()
-        ctx.sp_debug_set_spin_limit(polls)
+        ctx.sp_debug_set_spin_limit(int(polls))
         try:
             rc, summ, _ = ctx.sp_schedule(1)
         except binding.SneakPeekError as e:
             assert e.status == binding.SP_EDEVICE
             lost += 1
+            ctx.close()                                  # (this one takes two kernels per round from here on)
+            ctx = None
         else:
             ctx.sp_debug_set_spin_limit(0)
             assert rc == binding.SP_OK and summ["n_rounds"] == 1
             rc, summ, _ = ctx.sp_schedule(1)
             assert rc == binding.SP_OK and summ["n_rounds"] == 2
-        ctx.close()
+        polls *= 1.02
     assert lost > 0
+    if ctx is not None:
+        ctx.close()
 
 
 @pytest.mark.parametrize("dtype,d,H,C", [(wl.F32, 300, 0, 100), (wl.F32, 40, 24, 30), (wl.F32, 40, 0, 150), (wl.BF16, 64, 0, 100), (wl.BF16, 72, 40, 20),
