@@ -1,10 +1,11 @@
-// Scoring kernel for logistic heads of more than 128 classes with float32 features on the matrix cores,
-// d <= 256 (padded to a multiple of 32), M <= 16: float32 products emulated by three half-precision MFMAs.
+// Scoring kernel for logistic heads of more than 128 classes, or on fewer than 8 features, with float32 features on the
+// matrix cores, d <= 256 (padded to a multiple of 32), M <= 16: float32 products emulated by three half-precision MFMAs.
 //
 // Every float32 operand v is scaled by a power of two (per request row for the
 // features, per application for the weights; exact) into (-2^15, 2^15) and
 // split as v = hi + lo with hi = fp16(v), lo = fp16(v - hi): 22 significant
-// bits.  x.w is then  hi.hi + lo.hi + hi.lo  on v_mfma_f32_32x32x16_f16 with
+// bits down to 2^-18 of the largest operand that shares the scale, 2^-40 of that
+// one below.  x.w is then  hi.hi + lo.hi + hi.lo  on v_mfma_f32_32x32x16_f16 with
 // float32 accumulation (fp16 x fp16 products are exact in float32; the dropped
 // lo.lo term is below 2^-22 of the product), at 16x the float32 MFMA rate per
 // instruction, i.e. 5.3x per float32 product.
@@ -302,8 +303,11 @@ __device__ __forceinline__ float other_half(float v, int g) {
 // softmax update, exponentials x table tile.  tab, bias: the tile's table and bias units (layout: SplitBlock).
 // dump, split: constants, or uniform switches.
 // FINE: the exponent is formed without the scale of 2^14 that the exponentials are split at, which is then multiplied on.
-// An exponent near 0 has a smaller rounding error than one near 14 (3e-7 of the largest exponential); it costs one
-// instruction per logit, which kernels that the matrix or vector units bound do not spend.
+// An exponent near 0 has a smaller rounding error than one near 14 (3e-7 of the largest exponential).  The exponentials are
+// split on a fixed grid, the denominator is summed by the matrix cores from the same halves as the numerators, and the
+// instructions' sums are added in float32 registers (the reason: top of sp_score_stream.h).  It costs about three more vector
+// instructions per logit and twice the table's matrix instructions (12 against 6 per class tile), which kernels that
+// the matrix or vector units bound do not spend.
 template <bool FINE = false>
 __device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bias, f32x16& acc, float unscale, f32x4& ea_lo,
                                              f32x4& ea_hi, float& ssum, float& ssum_hi, float& m2, float& m2_rest, int ct, int C, int g, int lane, bool valid,

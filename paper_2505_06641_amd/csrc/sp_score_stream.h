@@ -11,7 +11,8 @@
 // request's row.  A step costs memory more than matrix cores in all of these shapes, so features travel two steps ahead.
 //
 // bfloat16: products are exact, float32 accumulation.  float32: every operand is scaled by a power of two and split
-// into two half-precision numbers as in the logistic kernel (x.w = hi.hi + lo.hi + hi.lo).  A row's largest value is
+// into two half-precision numbers as in the logistic kernel (x.w = hi.hi + lo.hi + hi.lo), and so are the hidden activations
+// and the second layer of either type; inputs of very different ranges are brought together first (equalizing_exponents).  A row's largest value is
 // not known before the row has been read, so the scale follows a running maximum: when a step brings a larger value,
 // the request's accumulators are rescaled by the exact power of two.
 //
@@ -23,7 +24,6 @@
 // classes go in groups, each of which streams the rows again.  One-hidden-layer heads add bias, ReLU and split in
 // registers and walk the class tiles like the bfloat16 kernel; class blocks follow the slices through the same two
 // buffers.
-//
 //
 // Measured (rocprofv3, median us, before -> now): 32,768 rows of 768 floats, 100 classes 1543 -> 39.8 (2.5 TB/s of rows);
 // 65,536 rows of 512 bfloat16, 100 classes 1273 -> 26.5 (2.5 TB/s); 100,000 requests of 128-64-10/7/2 float32 heads 185 -> 26.4

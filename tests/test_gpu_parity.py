@@ -574,8 +574,7 @@ def test_largest_batch_variant_and_class_counts(gpu):
 
 
 def test_bf16_logistic_head_and_wide_fp32_head(gpu):
-    """Heads outside the matrix-core kernels' shapes run on the generic kernel: bf16 without a hidden layer,
-    fp32 wider than 256 features."""
+    """Heads of the streaming kernel: bf16 without a hidden layer, fp32 wider than 256 features."""
     w = wl.tiny(seed=104, n=500, classes=(6, 11), models=(3, 4), max_batch=7, feat_dim=40, hidden_dim=0,
                 feat_dtype=wl.BF16, deadline=(5.0, 90.0))
     full_parity(gpu, w, max_rounds=0, ea_tol=2e-3)
@@ -1400,3 +1399,23 @@ def test_log_of_single_rounds_and_scheduled_ones(gpu, single):
     rc, got, short = ctx.sp_schedule(0, log_capacity=single)            # after the end: the log once more
     assert got == want and short == log[:single]
     ctx.close()
+
+
+OTHER_HEADS = {  # the scoring kernels that the heads of the two tests of priors and of subgroups do not reach
+    "generic f32": dict(feat_dim=33, hidden_dim=260), "generic bf16": dict(feat_dim=24, hidden_dim=257, feat_dtype=wl.BF16),
+    "generic narrow": dict(feat_dim=5, hidden_dim=9), "wide bf16 mlp": dict(feat_dim=24, hidden_dim=200, feat_dtype=wl.BF16),
+    "classes walked": dict(feat_dim=40, hidden_dim=0)}
+
+
+@pytest.mark.parametrize("split", [False, True], ids=["priors", "priors and subgroups"])
+@pytest.mark.parametrize("head", OTHER_HEADS)
+def test_priors_and_subgroups_on_the_other_scoring_kernels(gpu, head, split):
+    kw = OTHER_HEADS[head]
+    bf16 = kw.get("feat_dtype") == wl.BF16
+    w = wl.tiny(seed=8820, n=1200, classes=(5, 12, 135, 2), models=(3, 1, 16, 7), max_batch=9, deadline=(6.0, 150.0),
+                fractions=(0.4, 0.1, 0.3, 0.2), **kw)
+    for a in range(4):                                   # sharper heads: a good share of confident requests
+        w.profile.W1[a] = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(w.profile.W1[a]) * 2.0) if bf16 else (w.profile.W1[a] * 3.0).astype(np.float32)
+    wl.attach_priors(w.profile, seed=8821)
+    full_parity(gpu, w, max_rounds=25, ea_tol=2e-3 if bf16 else None, want_cube=not bf16,
+                policy=wl.Policy(split_groups=1) if split else None)
