@@ -470,8 +470,8 @@ template <typename T, int NB, bool MLP>
 sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
   using SG = StreamStage<NB, MLP>;
   using I = StreamIn<T>;
-  using SB = SplitBlock<32 * NB>;
-  constexpr int kTab = SplitBlock<32>::kTabUnits, kBias = SplitBlock<32>::kBiasUnits;
+  using SB = SplitBlock<32 * NB, 3>;
+  constexpr int kTab = SplitBlock<32, 3>::kTabUnits, kBias = SplitBlock<32, 3>::kBiasUnits;
   const int A = p->n_apps, d = p->feat_dim, H = p->hidden_dim, nkc = (d + I::kChunk - 1) / I::kChunk;
   std::vector<int64_t> off(A);
   size_t total = 0;
@@ -526,17 +526,17 @@ sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
         for (int cl = 0; cl < C; ++cl) w2f[(size_t)j * C + cl] = std::ldexp(host_value(((const T*)p->W2[a])[(size_t)j * C + cl]), -eh[j]);
       }
       blocks.resize((size_t)CT * SB::kBytes);
-      un2[a] = pack_split_blocks<32 * NB, kMapTile>(w2f.data(), p->b2[a], p->acc[a], H, C, p->n_models[a], blocks.data());
+      un2[a] = pack_split_blocks<32 * NB, kMapTile, 3>(w2f.data(), p->b2[a], p->acc[a], H, C, p->n_models[a], blocks.data());
       for (int ct = 0; ct < CT; ++ct, at += (size_t)SG::kUnits * 16) std::memcpy(at, blocks.data() + (size_t)ct * SB::kBytes, SB::kBytes);
     } else {
       // tables and biases in the layout of the class blocks: packed as blocks of a head without inputs
-      blocks.resize((size_t)CT * SplitBlock<32>::kBytes);
-      pack_split_blocks<32, kMapRows>(nullptr, p->b1[a], p->acc[a], 0, C, p->n_models[a], blocks.data());
+      blocks.resize((size_t)CT * SplitBlock<32, 3>::kBytes);
+      pack_split_blocks<32, kMapRows, 3>(nullptr, p->b1[a], p->acc[a], 0, C, p->n_models[a], blocks.data());
       for (int g0 = 0; g0 < CT; g0 += NB) {
         for (int kc = 0; kc < nkc; ++kc, at += (size_t)SG::kUnits * 16)
           pack_stream_slice<T, NB>(W1, d, O, kc, 32 * g0, scale, reinterpret_cast<uint16_t*>(at));
         for (int hb = 0; hb < NB && g0 + hb < CT; ++hb) {
-          const unsigned char* from = blocks.data() + (size_t)(g0 + hb) * SplitBlock<32>::kBytes + (size_t)SplitBlock<32>::kWUnits * 16;
+          const unsigned char* from = blocks.data() + (size_t)(g0 + hb) * SplitBlock<32, 3>::kBytes + (size_t)SplitBlock<32, 3>::kWUnits * 16;
           std::memcpy(at + (size_t)hb * kTab * 16, from, (size_t)kTab * 16);
           std::memcpy(at + (size_t)(NB * kTab + hb * kBias) * 16, from + (size_t)kTab * 16, (size_t)kBias * 16);
         }

@@ -60,11 +60,12 @@ constexpr float kTableScale = 32768.0f;
 //                        class = 32 ct + 16 s + 8 (e/4) + 4 g + e%4 with g = lane/32, s = (lane/16)%2: the
 //                        A operand of a 16x16x32 MFMA whose K index 8 (lane/16) + e runs over the classes
 //                        in the order the exponentials sit in the lanes after the row swap (softmax_phase)
+//                        (TAB = 3: a third part, what the first two leave: the accuracy to its last bit)
 //   bias  [4][2]         unit (q*2 + g): floats j = 0..3 hold b[32 ct + 8 q + 4 g + j], -1e30 beyond C
-template <int D>
+template <int D, int TAB = 2>
 struct SplitBlock {
   static constexpr int kWUnits = (D / 16) * 2 * 64;
-  static constexpr int kTabUnits = 2 * 64;
+  static constexpr int kTabUnits = TAB * 64;
   static constexpr int kBiasUnits = 8;
   static constexpr int kChunks = (kWUnits + kTabUnits + kBiasUnits + 63) / 64;   // 1 KB pieces, one LDS-DMA each
   static constexpr int kUnits = kChunks * 64;
@@ -123,10 +124,10 @@ inline int row_slot_feature(int k, int d, int per) {
 }
 
 // Host-side packing of one application's head (called at context creation).  Returns 2^-ew.
-template <int D, int KMAP>
+template <int D, int KMAP, int TAB = 2>
 inline float pack_split_blocks(const float* W /*[d,C]*/, const float* b /*[C]*/, const float* acc /*[M,C]*/, int d,
                                int C, int M, unsigned char* out /*[CT * kBytes]*/) {
-  using SB = SplitBlock<D>;
+  using SB = SplitBlock<D, TAB>;
   float wmax = 0.f;
   for (size_t i = 0; i < (size_t)d * C; ++i) wmax = std::max(wmax, std::fabs(W[i]));
   const int ew = host_scale_exponent(wmax);
@@ -158,6 +159,7 @@ inline float pack_split_blocks(const float* W /*[d,C]*/, const float* b /*[C]*/,
         host_split(v, hi, lo);
         tab[((size_t)0 * 64 + lane) * 8 + e] = hi;
         tab[((size_t)1 * 64 + lane) * 8 + e] = lo;
+        if (TAB == 3) tab[((size_t)2 * 64 + lane) * 8 + e] = host_f32_to_f16_bits((v - host_f16_bits_to_f32(hi)) - host_f16_bits_to_f32(lo));
       }
     float* bias = reinterpret_cast<float*>(blk + (size_t)(SB::kWUnits + SB::kTabUnits) * 16);
     for (int q = 0; q < 4; ++q)
@@ -305,9 +307,9 @@ __device__ __forceinline__ float other_half(float v, int g) {
 // FINE: the exponent is formed without the scale of 2^14 that the exponentials are split at, which is then multiplied on.
 // An exponent near 0 has a smaller rounding error than one near 14 (3e-7 of the largest exponential).  The exponentials are
 // split on a fixed grid, the denominator is summed by the matrix cores from the same halves as the numerators, and the
-// instructions' sums are added in float32 registers (the reason: top of sp_score_stream.h).  It costs about three more vector
-// instructions per logit and twice the table's matrix instructions (12 against 6 per class tile), which kernels that
-// the matrix or vector units bound do not spend.
+// instructions' sums are added in float32 registers (the reason: top of sp_score_stream.h), accuracies come in three halves.
+// It costs about three more vector instructions per logit and more than twice the table's matrix instructions (14 against 6 per
+// class tile), which kernels that the matrix or vector units bound do not spend.
 template <bool FINE = false>
 __device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bias, f32x16& acc, float unscale, f32x4& ea_lo,
                                              f32x4& ea_hi, float& ssum, float& ssum_hi, float& m2, float& m2_rest, int ct, int C, int g, int lane, bool valid,
@@ -446,6 +448,7 @@ __device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bi
   const f16x8 th = as_f16x8(tab[lane]);
   const f16x8 tl = as_f16x8(tab[lane + 64]);
   if (FINE) {
+    const f16x8 tr = as_f16x8(tab[lane + 128]);
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f16x8 one;
 #pragma unroll
@@ -454,6 +457,7 @@ __device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bi
       f32x4 t = __builtin_amdgcn_mfma_f32_16x16x32_f16(tl, bl, zero, 0, 0, 0);
       f32x4 sl = __builtin_amdgcn_mfma_f32_16x16x32_f16(one, bl, zero, 0, 0, 0);
       const f32x4 sh = __builtin_amdgcn_mfma_f32_16x16x32_f16(one, bh, zero, 0, 0, 0);
+      t = __builtin_amdgcn_mfma_f32_16x16x32_f16(tr, bh, t, 0, 0, 0);
       t = __builtin_amdgcn_mfma_f32_16x16x32_f16(tl, bh, t, 0, 0, 0);
       const f32x4 u = __builtin_amdgcn_mfma_f32_16x16x32_f16(th, bh, zero, 0, 0, 0);
       t = __builtin_amdgcn_mfma_f32_16x16x32_f16(th, bl, t, 0, 0, 0);
@@ -486,6 +490,8 @@ __device__ __forceinline__ void softmax_phase(const float4* blk, f32x16& acc, fl
 
 // After the last class tile: expected accuracies (eq. (9), with the prior's affine map), variance and key
 // (eq. (12)), the subgroup label, and the request's entries of the grouped arrays.
+// FINE: the quotients rounded once.
+template <bool FINE = false>
 __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w, const f32x4& ea_lo, const f32x4& ea_hi,
                                                float lane_sum, float shift, float factor, float rest, float best_z, int best_c, int a, int M, int pos,
                                                int id, bool valid, int lane, const float2* __restrict__ dw_g,
@@ -506,7 +512,7 @@ __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w
   }
   // eacc[v] of lane (r, g) is table row 8*(v/4) + 4*g + v%4 for request r:
   // v 0..3 -> variants 4g..4g+3, v 4..7 -> variants 8+4g..8+4g+3; the sum of exponentials spans both lane halves
-  const float inv = 1.0f / (lane_sum + other_half(lane_sum, g)), inv_ea = inv * (1.0f / kTableScale);
+  const float den = lane_sum + other_half(lane_sum, g), inv = 1.0f / den, inv_ea = inv * (1.0f / kTableScale);
   // prior of Sec. 4.2 eq. (10)-(11) as an affine map of the expected accuracies (gain 1, bias 0 without one)
   const float gain = tb.ea_gain[a];
   const float* biasp = tb.ea_bias + a * tb.Mmax;
@@ -515,7 +521,9 @@ __device__ __forceinline__ void score_epilogue(const Tables& tb, const Window& w
 #pragma unroll
   for (int v = 0; v < 8; ++v) {
     const int m = 8 * (v >> 2) + 4 * g + (v & 3);
-    ea[v] = (m < M) ? fmaf(gain, eacc[v] * inv_ea, biasp[m]) : 0.f;
+    float q = eacc[v] * inv_ea;
+    if (FINE) q = fmaf(fmaf(-q, den * kTableScale, eacc[v]), inv_ea, q);
+    ea[v] = (m < M) ? fmaf(gain, q, biasp[m]) : 0.f;
     part += ea[v];
   }
   const float mean = (part + __shfl_xor(part, 32)) / (float)M;

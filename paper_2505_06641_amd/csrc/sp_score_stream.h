@@ -62,7 +62,7 @@ template <int NB, bool MLP>
 struct StreamStage {
   static constexpr int kThreads = stream_waves(NB) * kWave;
   static constexpr int kSlice = 256 * NB;
-  static constexpr int kBlock = MLP ? SplitBlock<32 * NB>::kUnits : NB * (SplitBlock<32>::kTabUnits + SplitBlock<32>::kBiasUnits);
+  static constexpr int kBlock = MLP ? SplitBlock<32 * NB, 3>::kUnits : NB * (SplitBlock<32, 3>::kTabUnits + SplitBlock<32, 3>::kBiasUnits);
   static constexpr int kMax = kSlice > kBlock ? kSlice : kBlock;
   static constexpr int kPer = (kMax + kThreads - 1) / kThreads;    // units per thread
   static constexpr int kUnits = kPer * kThreads;
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
 #pragma unroll
       for (int hb = 0; hb < NB; ++hb) {
         if (hb < nbk)
-          softmax_tile<true>(tab + hb * SplitBlock<32>::kTabUnits, tab + NB * SplitBlock<32>::kTabUnits + hb * SplitBlock<32>::kBiasUnits,
+          softmax_tile<true>(tab + hb * SplitBlock<32, 3>::kTabUnits, tab + NB * SplitBlock<32, 3>::kTabUnits + hb * SplitBlock<32, 3>::kBiasUnits,
                        acc[hb], un, ea_lo, ea_hi, ssum, ssum_hi, m2, m2_rest, grp * NB + hb, C, g, lane, valid, dump_row, logits_out, best_z, best_c,
                        dump, split);
         __builtin_amdgcn_sched_barrier(0);
@@ -447,7 +447,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
         __builtin_amdgcn_sched_barrier(0);
         f32x16 z;
         logits_phase<D>(blk, xh, xl, z, lane);
-        softmax_tile<true>(blk + SplitBlock<D>::kWUnits, blk + SplitBlock<D>::kWUnits + SplitBlock<D>::kTabUnits, z, unscale, ea_lo, ea_hi,
+        softmax_tile<true>(blk + SplitBlock<D, 3>::kWUnits, blk + SplitBlock<D, 3>::kWUnits + SplitBlock<D, 3>::kTabUnits, z, unscale, ea_lo, ea_hi,
                      ssum, ssum_hi, m2, m2_rest, ct, C, g, lane, valid, dump_row, logits_out, best_z, best_c, dump, split);
         if (ct + 1 < CT) {
           park(st + 1);
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
   if (dump) return;
   // (the denominators lie like the numerators and span both lane halves; the epilogue adds the halves' sums)
   ssum = 0.5f * (r < 16 ? ssum : ssum_hi);
-  score_epilogue(tb, w, ea_lo, ea_hi, ssum, -m2, 16384.0f, m2_rest, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, split);
+  score_epilogue<true>(tb, w, ea_lo, ea_hi, ssum, -m2, 16384.0f, m2_rest, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, split);
 }
 
 }  // namespace sp
