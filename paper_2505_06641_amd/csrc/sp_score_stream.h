@@ -117,9 +117,8 @@ inline void pack_stream_slice(const T* W /*[d, O]*/, int d, int O, int kc, int r
 // so inputs are multiplied by 2^e and their weights by 2^-e, e such that every input's largest weight has the same exponent.
 // In front of a hidden layer's outputs this is exact and free (the ReLU commutes with it: it goes into the first layer's
 // weights and biases); features are multiplied in the kernel (COLS), which only heads with a spread of more than kStreamSpread take:
-// below it what is lost is less than 2^-28 of the largest product.  It costs 2 us of 41 (32,768 rows of 768, 100 classes) and of
-// 29 (100,000 of a 128-64-10 head), but registers with wide hidden layers: 36 -> 47 us (128-128-20), 42 -> 124 (60,000 of 200-256-40,
-// which take 912 on the generic kernel).
+// below it what is lost is less than 2^-28 of the largest product.  It costs 0.5 to 1.5 us: 41.4 -> 42.7 (32,768 rows of 768, 100
+// classes), 29.4 -> 30.4 (100,000 of a 128-64-10 head), 42.8 -> 43.4 (60,000 of 200-256-40, which take 912 on the generic kernel).
 constexpr int kStreamSpread = 10, kStreamShiftMax = 60;
 // Exponents e (<= 0) of the rows of W [rows, cols], all zero where the rows' ranges are alike.  Rows of zeros get the smallest:
 // such an input must not set the scale for the others.
@@ -362,8 +361,9 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
     };
     for (int kc = k0;; kc += 2) {
       if constexpr (I::kF32) slice_f32(kc, x0); else slice_bf16(kc, x0);
-      if (kc + 1 >= nkc) break;
-      if constexpr (I::kF32) slice_f32(kc + 1, x1); else slice_bf16(kc + 1, x1);
+      if (kc + 1 < nkc) {                                // (one way out of the loop: with two, the accumulators are copied)
+        if constexpr (I::kF32) slice_f32(kc + 1, x1); else slice_bf16(kc + 1, x1);
+      }
       if (kc + 2 >= nkc) break;
     }
 
