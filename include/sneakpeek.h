@@ -72,12 +72,13 @@ typedef enum { SP_F32 = 0, SP_BF16 = 1 } sp_dtype;
  * Arithmetic.  bfloat16 products are exact, sums are float32.  Float32 features
  * and weights, hidden activations (of either type), exponentials and accuracies
  * are taken by the matrix cores as two half-precision numbers each under a
- * shared power-of-two scale (per request, per head, and, with hidden_dim > 0 or
- * more than 256 features or at most 128 classes, per input where the ranges of
+ * shared power-of-two scale (per request, per head, and, but for bfloat16 heads
+ * with hidden_dim > 128 and float32 logistic ones on up to 256 features with more
+ * than 128 classes, per input where the ranges of
  * a head's inputs differ by more than 2^10): 22 significant bits, and 2^-40 of the
  * largest value that shares the scale for values below 2^-18 of it, sums in float32.
  * Against 64 bits, expected accuracies are as close as with float32 products
- * (2-norm 5e-8 to 2.2e-7 over the heads measured).  Plain float32 arithmetic is
+ * (2-norm 4e-8 to 2.2e-7 over the heads measured).  Plain float32 arithmetic is
  * used where hidden_dim > 256, feat_dim < 8 (other than float32 logistic heads), or
  * a weight is infinite.
  */
