@@ -240,11 +240,7 @@ sp_status upload_heads(sp_ctx* c, const sp_profile* p) {
 // Whether every weight that would be held as two halves is finite: an infinite one has no second half (infinity minus infinity),
 // where float32 arithmetic makes of it an excluded class or a unit that is off.
 template <typename T>
-bool finite_weights(const T* W, size_t n) {
-  for (size_t i = 0; i < n; ++i)
-    if (!std::isfinite(host_value(W[i]))) return false;
-  return true;
-}
+bool finite_weights(const T* W, size_t n) { return std::isfinite(host_abs_max(W, n)); }
 template <typename T>
 bool heads_splittable(const sp_profile* p) {
   for (int a = 0; a < p->n_apps; ++a) {
@@ -482,7 +478,7 @@ sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
   }
   std::vector<unsigned char> host(total * SG::kUnits * 16, 0), blocks;
   std::vector<float> b1((size_t)(MLP ? A * 32 * NB : 1), 0.f), un1(A, 1.f), un2(A, 1.f), w2f;
-  std::vector<float> cols(I::kF32 ? (size_t)A * nkc * I::kChunk : 1, 1.f);
+  std::vector<float> cols;                               // (all ones where a head needs none; empty where no head does)
   std::vector<T> w1;
   for (int a = 0; a < A; ++a) {
     const int C = p->n_classes[a], O = MLP ? H : C, CT = (C + kClassTile - 1) / kClassTile;
@@ -501,6 +497,7 @@ sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
         if (W1 != w1.data()) w1.assign(W1, W1 + (size_t)d * O);
         for (size_t i = 0; i < w1.size(); ++i) w1[i] = host_times_2(w1[i], -ef[i / O]);
         W1 = w1.data();
+        cols.resize((size_t)A * nkc * I::kChunk, 1.f);
         for (int k = 0; k < nkc * I::kChunk; ++k) {
           const int f = stream_slot(k, d, 16 / (int)sizeof(T)).feature;
           if (f >= 0) cols[(size_t)a * nkc * I::kChunk + k] = std::ldexp(1.0f, ef[f]);
@@ -510,9 +507,7 @@ sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
     }
     float scale = 1.f;
     if (I::kF32) {
-      float wmax = 0.f;
-      for (size_t i = 0; i < (size_t)d * O; ++i) wmax = std::max(wmax, std::fabs(host_value(W1[i])));
-      const int ew = host_scale_exponent(wmax);
+      const int ew = host_scale_exponent(host_abs_max(W1, (size_t)d * O));
       scale = std::ldexp(1.0f, ew);
       un1[a] = std::ldexp(1.0f, -ew);
     }
@@ -523,7 +518,8 @@ sp_status pack_stream_nb(sp_ctx* c, const sp_profile* p) {
       w2f.resize((size_t)H * C);
       for (int j = 0; j < H; ++j) {
         b1[(size_t)a * 32 * NB + j] = std::ldexp(p->b1[a][j], eh[j]);
-        for (int cl = 0; cl < C; ++cl) w2f[(size_t)j * C + cl] = std::ldexp(host_value(((const T*)p->W2[a])[(size_t)j * C + cl]), -eh[j]);
+        const float up = std::ldexp(1.0f, -eh[j]);
+        for (int cl = 0; cl < C; ++cl) w2f[(size_t)j * C + cl] = host_value(((const T*)p->W2[a])[(size_t)j * C + cl]) * up;
       }
       blocks.resize((size_t)CT * SB::kBytes);
       un2[a] = pack_split_blocks<32 * NB, kMapTile, 3>(w2f.data(), p->b2[a], p->acc[a], H, C, p->n_models[a], blocks.data());

@@ -80,6 +80,17 @@ inline float host_times_2(float v, int e) { return std::ldexp(v, e); }
 inline uint16_t host_times_2(uint16_t v, int e) {       // (bfloat16 bits)
   return (uint16_t)(__builtin_bit_cast(uint32_t, std::ldexp(__builtin_bit_cast(float, (uint32_t)v << 16), e)) >> 16);
 }
+// Largest absolute value (an infinity or a NaN if there is one), on the bits: every weight passes here a few times.
+inline float host_abs_max(const float* v, size_t n) {
+  uint32_t m = 0;
+  for (size_t i = 0; i < n; ++i) m = std::max(m, __builtin_bit_cast(uint32_t, v[i]) & 0x7fffffffu);
+  return __builtin_bit_cast(float, m);
+}
+inline float host_abs_max(const uint16_t* v, size_t n) {
+  uint32_t m = 0;
+  for (size_t i = 0; i < n; ++i) m = std::max(m, (uint32_t)v[i] & 0x7fffu);
+  return __builtin_bit_cast(float, m << 16);
+}
 inline float host_value(float v) { return v; }
 inline float host_value(uint16_t v) { return __builtin_bit_cast(float, (uint32_t)v << 16); }
 struct StreamSlot { int feature; float part; };
@@ -127,8 +138,7 @@ inline std::vector<int> equalizing_exponents(const T* W, int rows, int cols) {
   std::vector<int> e(rows, 0);
   int top = INT_MIN, low = INT_MAX;
   for (int k = 0; k < rows; ++k) {
-    float m = 0.f;
-    for (int j = 0; j < cols; ++j) m = std::max(m, std::fabs(host_value(W[(size_t)k * cols + j])));
+    const float m = host_abs_max(W + (size_t)k * cols, (size_t)cols);
     if (!std::isfinite(m)) return std::vector<int>(rows, 0);
     if (m > 0.f) (void)std::frexp(m, &e[k]);
     else e[k] = INT_MIN;
