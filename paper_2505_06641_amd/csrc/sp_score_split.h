@@ -653,14 +653,11 @@ __device__ __forceinline__ void class_tiles_and_finish(
   score_epilogue(tb, w, ea_lo, ea_hi, ssum, kExpShift - m2, 1.0f, 0.f, best_z, best_c, a, M, pos, id, valid, lane, dw_g, sortkey, SPLIT);
 }
 
-// Four consecutive features of a row of d >= 4 from feature k0 on (see row_slot_feature); rows of any width, so the piece
+// Where four consecutive features of a row of d >= 4 lie, from feature k0 on (see row_slot_feature); rows of any width, so the piece
 // may lie at any multiple of four bytes.
 typedef f32x4 f32x4_dw __attribute__((aligned(4)));
-__device__ __forceinline__ f32x4 row_piece(const float* __restrict__ row, int k0, int d) {
-  const f32x4_dw* p = reinterpret_cast<const f32x4_dw*>(row + min(k0, d - 4));
-  // a streaming load, unless pieces straddle cache lines: the second half would have to be fetched again
-  if ((d & 3) == 0) return __builtin_nontemporal_load(p);
-  return *p;
+__device__ __forceinline__ const f32x4_dw* row_piece(const float* __restrict__ row, int k0, int d) {
+  return reinterpret_cast<const f32x4_dw*>(row + min(k0, d - 4));
 }
 
 // This lane's half of its request's features, k = g*D/2 + [0, D/2): the row scaled by a power of two into
@@ -686,13 +683,21 @@ __device__ __forceinline__ float load_split_features(const float* __restrict__ x
       const int at = piece < D / 8 ? piece : kHalf + piece - D / 8;
       float4 rows[2][kLoads];
       auto fetch_rows = [&](int ps, float4 (&dst)[kLoads]) {
+        auto load = [&](auto how) {
 #pragma unroll
-        for (int i = 0; i < kLoads; ++i) {
-          const int rid = __shfl(id, 8 * ps + kRows * i + sub);
-          // feature rows are read once: a streaming load, so that they do not push the packed blocks,
-          // which every workgroup of the die reads again, out of its L2
-          const f32x4 v = row_piece(x + (int64_t)rid * d, 4 * piece, d);
-          dst[i] = make_float4(v[0], v[1], v[2], v[3]);
+          for (int i = 0; i < kLoads; ++i) {
+            const f32x4 v = how(row_piece(x + (int64_t)__shfl(id, 8 * ps + kRows * i + sub) * d, 4 * piece, d));
+            dst[i] = make_float4(v[0], v[1], v[2], v[3]);
+          }
+        };
+        // feature rows are read once: streaming loads, so that they do not push the packed blocks, which every workgroup of
+        // the die reads again, out of its L2 (1,048,576 rows of 256: 1.160 GB fetched against 1.234 with plain loads, which also cost
+        // the kernels behind this one 4 us); not where pieces straddle cache lines: the second half would have to be fetched again
+        if (D == 256 && (d & 3) == 0) {
+          load([](const f32x4_dw* p) { return __builtin_nontemporal_load(p); });
+          asm volatile("");                              // (or the compiler makes one plain load of the two kinds)
+        } else {
+          load([](const f32x4_dw* p) { return *p; });
         }
       };
       fetch_rows(0, rows[0]);
