@@ -353,14 +353,19 @@ __device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bi
     best_z = up ? mt : best_z;
   }
   mt = fmaxf(mt, other_half(mt, g));
-  const float m2n = fmaxf(m2, mt * kLog2e);
+  float m2n = fmaxf(m2, mt * kLog2e);
   float drop = m2 - m2n;
-  if (FINE) {
-    // The reference's own rounding, which for logits of millions is no longer small against the exponents: taken into account
-    // from a quarter on (it is zero up to 2^22), or the largest exponential would leave the halves' range.
-    float rest = mt * kLog2e >= m2 ? fmaf(mt, kLog2e, -m2n) : m2_rest;
+  // The reference's own rounding, which for logits of millions is no longer small against the exponents: from a quarter on (it
+  // is less up to 2^22) it is taken into account, or the largest exponential would leave the halves' range.  Logits whose
+  // product with log2 e is beyond the largest float have the excess in it.
+  const bool large = FINE && __builtin_amdgcn_ballot_w64(!(fabsf(m2n) < 4194304.0f) || m2_rest != 0.f) != 0ull;
+  if (large) {
+    const float top = fminf(mt * kLog2e, 3.402823466e38f);
+    m2n = fmaxf(m2, top);
+    float rest = fmaf(mt, kLog2e, -top);
     rest = fabsf(rest) >= 0.25f ? rest : 0.f;
-    drop += m2_rest - rest;
+    rest = top > m2 ? rest : (top == m2 ? fmaxf(rest, m2_rest) : m2_rest);
+    drop = (m2 - m2n) + (m2_rest - rest);
     m2_rest = rest;
   }
   const float scale = __builtin_amdgcn_exp2f(drop);
@@ -369,7 +374,7 @@ __device__ __forceinline__ void softmax_tile(const float4* tab, const float4* bi
   if (FINE) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = fmaf(acc[v], kLog2e, shift);
-    if (__builtin_amdgcn_ballot_w64(m2_rest != 0.f) != 0ull) {
+    if (large) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[v] -= m2_rest;
     }

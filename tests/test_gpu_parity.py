@@ -1289,7 +1289,7 @@ def test_features_and_hidden_units_of_very_different_ranges(gpu, dtype, d, H, C)
 
 
 @pytest.mark.parametrize("dtype,d,H,C", [(wl.F32, 300, 0, 100), (wl.F32, 40, 0, 20), (wl.F32, 40, 24, 300), (wl.BF16, 64, 0, 100), (wl.BF16, 72, 40, 70)])
-@pytest.mark.parametrize("size", [3e5, 4e7, 6e9, 1e20])
+@pytest.mark.parametrize("size", [3e5, 4e7, 6e9, 1e20, 3.3e38])
 def test_logits_of_millions_and_more(gpu, dtype, d, H, C, size):
     """Logits so large that the softmax is a choice: the largest logit's row of the table, in whatever tile of classes it lies
     and whatever came before it."""
