@@ -99,8 +99,7 @@ inline int host_scale_exponent(float vmax) {
   int e = 0;
   (void)std::frexp(vmax, &e);            // vmax = f * 2^e, f in [0.5, 1)
   int ew = kSplitExp - e;
-  if (ew > 100) ew = 100;
-  if (ew < -100) ew = -100;
+  if (ew > 126) ew = 126;                // (the inverse stays a normal number; the largest floats ask for -113)
   return ew;
 }
 

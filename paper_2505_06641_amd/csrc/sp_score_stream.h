@@ -72,10 +72,6 @@ struct StreamStage {
 template <typename T>
 inline int stream_channel(int s, int g, int e) { return g * (StreamIn<T>::kChunk / 2) + 8 * s + e; }
 
-// Which feature slot k of the padded row holds (-1: zero), and the part of its weight that counts there.  A piece of 16 bytes
-// (`per` features) that would pass the row's end is read that much further left; the features that it repeats count by half
-// in either place (exact in both types).  With the whole weight in one place and zero in the other an infinite feature would
-// make NaNs, which a hidden layer's ReLU turns into zeros.  Pieces behind the row's end are zero.
 inline float host_times_2(float v, int e) { return std::ldexp(v, e); }
 inline uint16_t host_times_2(uint16_t v, int e) {       // (bfloat16 bits)
   return (uint16_t)(__builtin_bit_cast(uint32_t, std::ldexp(__builtin_bit_cast(float, (uint32_t)v << 16), e)) >> 16);
@@ -93,6 +89,10 @@ inline float host_abs_max(const uint16_t* v, size_t n) {
 }
 inline float host_value(float v) { return v; }
 inline float host_value(uint16_t v) { return __builtin_bit_cast(float, (uint32_t)v << 16); }
+// Which feature slot k of the padded row holds (-1: zero), and the part of its weight that counts there.  A piece of 16 bytes
+// (`per` features) that would pass the row's end is read that much further left; the features that it repeats count by half
+// in either place (exact in both types).  With the whole weight in one place and zero in the other an infinite feature would
+// make NaNs, which a hidden layer's ReLU turns into zeros.  Pieces behind the row's end are zero.
 struct StreamSlot { int feature; float part; };
 inline StreamSlot stream_slot(int k, int d, int per) {
   const int full = d / per * per;
@@ -300,9 +300,9 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
 #pragma unroll
         for (int j = 0; j < 4; ++j) amax = fmaxf(amax, fabsf(xv[q][j]));
       amax = fmaxf(amax, other_half(amax, g));
-      // amax = f 2^e with f in [0.5, 1): |x| 2^(15 - e) < 2^15; bounded so that scale and inverse stay normal numbers
+      // amax = f 2^e with f in [0.5, 1): |x| 2^(15 - e) < 2^15; bounded so that the scale stays a normal number
       const int e = (int)((__float_as_uint(amax) >> 23) & 0xffu) - 126;
-      const int want = min(max(kSplitExp - e, -113), 114);
+      const int want = min(max(kSplitExp - e, -113), 128);
       if (MLP) infinite |= e > 128;
       if (__builtin_amdgcn_ballot_w64(want < ex) != 0ull) {
         // two bits of headroom, so that the maximum of a few more values rarely asks for another rescaling
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
         }
       amax = fmaxf(amax, other_half(amax, g));
       int hx = 0;
-      if (amax >= 1e-30f && amax <= 3e38f) hx = kSplitExp - (int)(((__float_as_uint(amax) >> 23) & 0xffu) - 126u);
+      if (amax < __builtin_inff()) hx = min(kSplitExp - ((int)((__float_as_uint(amax) >> 23) & 0xffu) - 126), 126);
       const float hs = __uint_as_float((uint32_t)(127 + hx) << 23);
       const float unscale = __uint_as_float((uint32_t)(127 - hx) << 23) * hd.unscale2[a];
       f16x8 xh[D / 16], xl[D / 16];

@@ -1419,3 +1419,28 @@ def test_priors_and_subgroups_on_the_other_scoring_kernels(gpu, head, split):
     wl.attach_priors(w.profile, seed=8821)
     full_parity(gpu, w, max_rounds=25, ea_tol=2e-3 if bf16 else None, want_cube=not bf16,
                 policy=wl.Policy(split_groups=1) if split else None)
+
+
+@pytest.mark.parametrize("dtype,d,H", [(wl.F32, 300, 0), (wl.F32, 40, 0), (wl.F32, 40, 24), (wl.F32, 97, 200), (wl.BF16, 64, 0), (wl.BF16, 71, 40)])
+@pytest.mark.parametrize("f", [1e36, 1e-36])
+def test_weights_and_features_at_the_ends_of_the_range(gpu, dtype, d, H, f):
+    """Large weights on small inputs and the other way round, features and hidden units: products of ordinary size."""
+    torch, binding = gpu
+    up = (lambda v: np.asarray(v, np.float32)) if dtype == wl.F32 else wl.f32_to_bf16_bits
+    val = (lambda v: v) if dtype == wl.F32 else wl.bf16_bits_to_f32
+    for hidden in ([False, True] if H else [False]):
+        w = wl.tiny(seed=8830 + d, n=200, classes=(20, 6), models=(5, 3), feat_dim=d, hidden_dim=H, feat_dtype=dtype)
+        p = w.profile
+        if not hidden:
+            w.requests.x = up(val(w.requests.x) * np.float32(1.0 / f))
+        for a in range(2):
+            p.W1[a] = up(val(p.W1[a]) * np.float32(f))
+            if hidden:
+                p.b1[a] = (p.b1[a] * np.float32(f)).astype(np.float32)
+                p.W2[a] = up(val(p.W2[a]) * np.float32(1.0 / f))
+        ref_ea, _ = orc.score_requests(p, w.requests)
+        ctx = binding.Context(p, 200)
+        ea = torch.zeros((200, ctx.m_max), device="cuda:0")
+        ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
+        ctx.close()
+        parity.assert_close("EA", ea.cpu().numpy(), ref_ea, TOL if dtype == wl.F32 else 2e-3)
