@@ -33,6 +33,7 @@ struct sp_ctx {
   Tables tb{};
   Window w{};
   std::vector<void*> dev_allocs;
+  int32_t* by_cost = nullptr;        // [A] the applications in the order their scoring tiles are numbered in: costly ones first where that matters
   int A = 0, d = 0, H = 0, B = 0, Mmax = 0, Cmax = 0, dtype = 0;
   int64_t cap = 0;
   uint32_t* bufK[2] = {nullptr, nullptr};
@@ -258,6 +259,16 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p);
 sp_status ensure_split_buffers(sp_ctx* c);
 int score_tile(const sp_ctx* c);
 
+// What a scoring tile of an application of C classes costs, roughly, in units of a class tile: the kernel that walks the classes
+// spends about three on its prologue, heads with a hidden layer about ten on the layer and the prologue; the streaming kernel's
+// logistic heads are bound by reading the rows, once per group of classes.
+int tile_cost(const sp_ctx* c, int C) {
+  const int CT = (C + kClassTile - 1) / kClassTile;
+  if (c->mfma_D > 0) return 3 + CT;
+  if (c->stream_nb > 0 && c->H == 0) return (CT + c->stream_nb - 1) / c->stream_nb;
+  return 10 + CT;
+}
+
 sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   const int A = p->n_apps, B = p->max_batch;
   c->A = A; c->d = p->feat_dim; c->H = p->hidden_dim; c->B = B; c->dtype = p->feat_dtype;
@@ -292,16 +303,15 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
     }
     lmin[a] = lm;
   }
-  int32_t *d_ncls, *d_nmod, *d_pen, *d_acc_off;
+  int32_t *d_nmod, *d_pen, *d_acc_off;
   float *d_acc, *d_lat, *d_lmin;
-  if ((s = dev_upload(c, &d_ncls, ncls)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_nmod, nmod)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_pen, pen)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_acc_off, acc_off)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_acc, acc)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_lat, lat)) != SP_OK) return s;
   if ((s = dev_upload(c, &d_lmin, lmin)) != SP_OK) return s;
-  tb.n_classes = d_ncls; tb.n_models = d_nmod; tb.penalty = d_pen; tb.acc_off = d_acc_off;
+  tb.n_models = d_nmod; tb.penalty = d_pen; tb.acc_off = d_acc_off;
   tb.acc = d_acc; tb.lat = d_lat; tb.lmin = d_lmin;
   // no prior: gain 1, bias 0
   c->h_acc = acc; c->h_acc_off = acc_off; c->h_ncls = ncls; c->h_nmod = nmod;
@@ -328,6 +338,20 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
     // what is left (hidden layers wider than 256, rows of a few features, infinite weights): plain matrices for the generic kernel
     s = (c->dtype == SP_BF16) ? upload_heads<uint16_t>(c, p) : upload_heads<float>(c, p);
     if (s != SP_OK) return s;
+  }
+
+  {
+    // the numbers of classes, and behind them the order in which the applications' scoring tiles are numbered (see tile_of)
+    std::vector<int32_t> v(ncls);
+    for (int a = 0; a < A; ++a) v.push_back(a);
+    const auto cost = [&](int32_t a) { return tile_cost(c, ncls[a]); };
+    const auto [least, most] = std::minmax_element(v.begin() + A, v.end(), [&](int32_t a, int32_t b) { return cost(a) < cost(b); });
+    c->w.tiles_in_turn = 2 * cost(*most) > 3 * cost(*least) ? 1 : 0;
+    if (c->w.tiles_in_turn) std::stable_sort(v.begin() + A, v.end(), [&](int32_t a, int32_t b) { return cost(a) > cost(b); });
+    int32_t* at;
+    if ((s = dev_upload(c, &at, v)) != SP_OK) return s;
+    tb.n_classes = at;
+    c->by_cost = at + A;
   }
 
   // window buffers
@@ -890,7 +914,7 @@ int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev,
                         const float* weight_dev) {
   const int A = c->A;
   Window& w = c->w;
-  SegArgs seg_args{n, A, nullptr, score_tile(c), n <= kMergeMax ? kRun : kSortTile, w.seg, w.tile_start, w.unit_start, w.tile_desc, c->sort_desc};
+  SegArgs seg_args{n, A, nullptr, score_tile(c), n <= kMergeMax ? kRun : kSortTile, c->by_cost, w.seg, w.tile_start, w.unit_start, w.tile_desc, c->sort_desc};
   // a long window's ordering needs its digit totals cleared
   uint32_t* zero = n > kMergeMax ? c->dtot_key : nullptr;
   const int64_t zero_words = (int64_t)kMaxSortPasses * c->tiles_cap * 256;

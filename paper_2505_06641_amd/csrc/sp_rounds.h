@@ -204,11 +204,6 @@ __device__ __forceinline__ float4 window_entry(const Tables& tb, const Window& w
 __device__ __forceinline__ int n_groups(const Tables& tb, const Window& w) { return tb.pol_split ? *w.grp_n : tb.A; }
 __device__ __forceinline__ int group_app(const Tables& tb, const Window& w, int g) { return tb.pol_split ? w.grp_app[g] : g; }
 
-// Keeps a value's load where it stands: everything a kernel can ask for at its start then shares one trip to memory (about
-// 0.8 us), which the compiler would otherwise move behind the branches that come first.
-template <typename T>
-__device__ __forceinline__ void loaded_here(const T& v) { asm volatile("" : : "v"(v)); }
-
 __global__ __launch_bounds__(kRoundThreads) void k_round_score(Tables tb, Window w, float* __restrict__ cube_out) {
   __shared__ int32_t win[kMaxBatch];
   __shared__ float4 ent[kMaxBatch];

@@ -178,7 +178,7 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
   __shared__ f32x4 cols[COLS ? kStreamMaxD / 4 : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
-  const int tile = xcd_tile(blockIdx.x, __builtin_amdgcn_readfirstlane(w.tile_start[tb.A]));
+  const int tile = tile_of(w, blockIdx.x, __builtin_amdgcn_readfirstlane(w.tile_start[tb.A]));
   if (tile < 0) return;
   const int4 desc = w.tile_desc[tile];
   // (uniform, which the compiler cannot know of a load: tables and stages are then addressed from scalar registers)

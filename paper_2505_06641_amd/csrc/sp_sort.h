@@ -95,15 +95,14 @@ __device__ __forceinline__ uint4 wave_digit_bases(const uint32_t* __restrict__ t
   return b;
 }
 
-// Segment starts from the application-sorted keys (values in [0, A], A =
-// invalid): seg[a] = first position with key >= a; then the prefixes of
-// scoring tiles and sort units per application and the scoring tiles' descriptors.  One workgroup.
-// digit_tot, when given, holds the count of every application id (256 words; wavefront 0 turns them into the segment
-// starts without any search).
+// Where the applications' ranges start, the prefixes of scoring tiles and sort runs, and a descriptor for each of either, so that
+// a workgroup finds its place with a single load.  Scoring tiles are numbered application by application in the order of
+// by_cost (see tile_of), sort runs in ascending order.
 struct SegArgs {
   int32_t n, A;
   const uint32_t* sorted_app;   // application-sorted keys (not used where the counts of the ids are given)
   int32_t tile, unit;           // requests per scoring tile and per sort run
+  const int32_t* by_cost;       // [A]
   int32_t* seg;
   int32_t* tile_start;
   int32_t* unit_start;
@@ -111,28 +110,46 @@ struct SegArgs {
   int4* sort_desc;
 };
 
-// Body of k_segments for the first 256 threads of a workgroup (any others only keep the barriers company).
-__device__ __forceinline__ void segments_body(const SegArgs& g, const Window& w, const uint32_t* digit_tot) {
+// Until (and unless) the requests are split into subgroups, group g is application g.
+__device__ __forceinline__ void plain_group(const Window& w, int a, int beg, int end) {
+  w.head[a] = beg;
+  w.head[w.gcap + a] = beg;
+  w.grp_app[a] = a;
+  w.grp_end[a] = end;
+}
+
+// Last k < n with start[k] <= i (empty ranges share a start; start[0] = 0).
+__device__ __forceinline__ int range_of(const int* start, int n, int i) {
+  int lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (start[mid] <= i) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// The descriptors of all tiles and runs from the tables in LDS, by `threads` threads.
+__device__ __forceinline__ void write_descriptors(const SegArgs& g, const int* s_tile, const int* s_unit, const int* s_seg, const int* s_app,
+                                                  int tid, int threads) {
+  for (int t = tid; t < s_tile[g.A]; t += threads) {                // (application, first request, end of its range, 0)
+    const int k = range_of(s_tile, g.A, t), a = s_app[k];
+    g.tile_desc[t] = make_int4(a, s_seg[a] + (t - s_tile[k]) * g.tile, s_seg[a + 1], 0);
+  }
+  for (int u = tid; u < s_unit[g.A]; u += threads) {                // (start of the application, first element, end, 0)
+    const int a = range_of(s_unit, g.A, u);
+    g.sort_desc[u] = make_int4(s_seg[a], s_seg[a] + (u - s_unit[a]) * g.unit, s_seg[a + 1], 0);
+  }
+}
+
+// From the sorted ids (values in [0, A], A = invalid): seg[a] = first position with an id >= a.  One workgroup.
+__global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) {
   // A look-back that ran out has left holes in the sorted ids: the window will be refused, and until then it has no
   // requests, so that nothing reads what was never written.
-  const int n = digit_tot == nullptr && (w.st->err & kErrSortSync) ? 0 : g.n;
-  const int A = g.A, tile = g.tile, unit = g.unit;
+  const int n = (w.st->err & kErrSortSync) ? 0 : g.n;
+  const int A = g.A, tile = g.tile, unit = g.unit, tid = threadIdx.x;
   const uint32_t* __restrict__ sorted_app = g.sorted_app;
-  int32_t *seg = g.seg, *tile_start = g.tile_start, *unit_start = g.unit_start;
-  int4 *tile_desc = g.tile_desc, *sort_desc = g.sort_desc;
-  const bool on = threadIdx.x < 256;
-  if (digit_tot != nullptr) {
-    if (threadIdx.x < 64) {
-      const int lane = threadIdx.x;
-      const uint4 b = wave_digit_bases(digit_tot, 0u, lane);
-      const uint32_t bb[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (4 * lane + q <= A) seg[4 * lane + q] = (int)bb[q];
-      if (lane == 0) seg[A + 1] = n;
-    }
-  }
-  for (int a = threadIdx.x; on && a <= A + 1 && digit_tot == nullptr; a += 256) {
+  int32_t* seg = g.seg;
+  for (int a = tid; a <= A + 1; a += 256) {
     int lo = 0, hi = n;                     // lower_bound(sorted_app, a)
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
@@ -141,64 +158,54 @@ __device__ __forceinline__ void segments_body(const SegArgs& g, const Window& w,
     seg[a] = lo;                            // seg[A] = number of valid requests, seg[A+1] = n
   }
   __syncthreads();
-  // until (and unless) the requests are split into subgroups, group g is application g
-  for (int a = threadIdx.x; on && a < A; a += 256) {
-    w.head[a] = seg[a];
-    w.head[w.gcap + a] = seg[a];
-    w.grp_app[a] = a;
-    w.grp_end[a] = seg[a + 1];
-  }
-  if (threadIdx.x == 0) {
+  for (int a = tid; a < A; a += 256) plain_group(w, a, seg[a], seg[a + 1]);
+  if (tid == 0) {
     w.grp_n[0] = A;
     w.grp_n[1] = 1;
   }
   // prefixes of tiles and units over the applications: every thread takes a run of consecutive
-  // applications, the runs' totals are scanned across the workgroup (launched with 256 threads)
+  // applications, the runs' totals are scanned across the workgroup
   __shared__ int run_t[256], run_u[256];
-  __shared__ int s_tile[kSegTable + 1], s_seg[kSegTable + 1], s_unit[kSegTable + 1];   // used when A <= kSegTable
-  const int tid = on ? threadIdx.x : 0;          // threads beyond 255 shadow thread 0 and store nothing
+  __shared__ int s_tile[kSegTable + 1], s_seg[kSegTable + 1], s_unit[kSegTable + 1], s_app[kSegTable];   // used when A <= kSegTable
   const int per = (A + 255) / 256;
-  const int a_lo = on ? min(A, tid * per) : 0, a_hi = on ? min(A, a_lo + per) : 0;
+  const int a_lo = min(A, tid * per), a_hi = min(A, a_lo + per);
   int ts = 0, us = 0;
-  for (int a = a_lo; a < a_hi; ++a) {
-    const int na = seg[a + 1] - seg[a];
-    ts += (na + tile - 1) / tile;
-    us += (na + unit - 1) / unit;
+  for (int k = a_lo; k < a_hi; ++k) {
+    const int c = g.by_cost[k];
+    ts += (seg[c + 1] - seg[c] + tile - 1) / tile;
+    us += (seg[k + 1] - seg[k] + unit - 1) / unit;
   }
-  if (on) {
-    run_t[tid] = ts;
-    run_u[tid] = us;
-  }
+  run_t[tid] = ts;
+  run_u[tid] = us;
   __syncthreads();
   for (int o = 1; o < 256; o <<= 1) {
     const int t_up = tid >= o ? run_t[tid - o] : 0;
     const int u_up = tid >= o ? run_u[tid - o] : 0;
     __syncthreads();
-    if (on) {
-      run_t[tid] += t_up;
-      run_u[tid] += u_up;
-    }
+    run_t[tid] += t_up;
+    run_u[tid] += u_up;
     __syncthreads();
   }
   const int ts0 = run_t[tid] - ts, us0 = run_u[tid] - us;   // exclusive prefixes of this thread's run
   const bool table = A <= kSegTable;
   ts = ts0;
   us = us0;
-  for (int a = a_lo; a < a_hi; ++a) {
-    tile_start[a] = ts;
-    unit_start[a] = us;
-    const int sb = seg[a], na = seg[a + 1] - sb;
+  for (int k = a_lo; k < a_hi; ++k) {
+    const int c = g.by_cost[k];
+    g.tile_start[k] = ts;
+    g.unit_start[k] = us;
     if (table) {
-      s_tile[a] = ts;
-      s_unit[a] = us;
-      s_seg[a] = sb;
+      s_tile[k] = ts;
+      s_app[k] = c;
+      s_unit[k] = us;
+      s_seg[k] = seg[k];
     }
-    ts += (na + tile - 1) / tile;
-    us += (na + unit - 1) / unit;
+    ts += (seg[c + 1] - seg[c] + tile - 1) / tile;
+    us += (seg[k + 1] - seg[k] + unit - 1) / unit;
   }
-  if (on && tid == 255) {
-    tile_start[A] = run_t[255];
-    unit_start[A] = run_u[255];
+  if (tid == 255) {
+    g.tile_start[A] = run_t[255];
+    g.unit_start[A] = run_u[255];
     if (table) {
       s_tile[A] = run_t[255];
       s_unit[A] = run_u[255];
@@ -206,42 +213,21 @@ __device__ __forceinline__ void segments_body(const SegArgs& g, const Window& w,
     }
   }
   __syncthreads();
-  // one descriptor per scoring tile, so that a scoring workgroup finds its place with a single load
   if (table) {
-    // few applications: every thread places tiles by searching the prefixes in LDS
-    const int n_tiles = s_tile[A];
-    for (int t = tid; on && t < n_tiles; t += 256) {
-      int lo = 0, hi = A;                                // last a with s_tile[a] <= t (empty applications share a start)
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_tile[mid] <= t) lo = mid; else hi = mid;
-      }
-      tile_desc[t] = make_int4(lo, s_seg[lo] + (t - s_tile[lo]) * tile, s_seg[lo + 1], 0);
-    }
-    // and one per run: (start of the application, first element, end of the application, 0)
-    const int n_units = s_unit[A];
-    for (int u = tid; on && u < n_units; u += 256) {
-      int lo = 0, hi = A;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_unit[mid] <= u) lo = mid; else hi = mid;
-      }
-      sort_desc[u] = make_int4(s_seg[lo], s_seg[lo] + (u - s_unit[lo]) * unit, s_seg[lo + 1], 0);
-    }
+    write_descriptors(g, s_tile, s_unit, s_seg, s_app, tid, 256);
   } else {
     ts = ts0;
     us = us0;
-    for (int a = a_lo; a < a_hi; ++a) {
-      const int sb = seg[a], se = seg[a + 1], nt = (se - sb + tile - 1) / tile, nu = (se - sb + unit - 1) / unit;
-      for (int t = 0; t < nt; ++t) tile_desc[ts + t] = make_int4(a, sb + t * tile, se, 0);
-      for (int u = 0; u < nu; ++u) sort_desc[us + u] = make_int4(sb, sb + u * unit, se, 0);
+    for (int k = a_lo; k < a_hi; ++k) {
+      const int c = g.by_cost[k], cb = seg[c], ce = seg[c + 1], nt = (ce - cb + tile - 1) / tile;
+      const int sb = seg[k], se = seg[k + 1], nu = (se - sb + unit - 1) / unit;
+      for (int t = 0; t < nt; ++t) g.tile_desc[ts + t] = make_int4(c, cb + t * tile, ce, 0);
+      for (int u = 0; u < nu; ++u) g.sort_desc[us + u] = make_int4(sb, sb + u * unit, se, 0);
       ts += nt;
       us += nu;
     }
   }
 }
-
-__global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) { segments_body(g, w, nullptr); }
 
 __device__ __forceinline__ void clear_words(uint32_t* __restrict__ p, int64_t words) {
   if (p == nullptr) return;
@@ -564,6 +550,58 @@ __device__ __forceinline__ void group_sums(const uint32_t* __restrict__ counts, 
   __syncthreads();
 }
 
+// The segments from the number of requests of every application (and of invalid ids, total[A]), at most 255 of them: one thread
+// per application, tables in LDS, three barriers (a search over the sorted ids and tables in memory took 0.9 us more).
+__device__ __forceinline__ void segments_from_totals(const SegArgs& g, const Window& w, const uint32_t* total, int costly /*by_cost[tid]*/) {
+  __shared__ int s_seg[257], s_tile[257], s_unit[257], s_app[256];
+  __shared__ int wave_t[4], wave_u[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, A = g.A;
+  if (wave == 0) {
+    const uint4 b = wave_digit_bases(total, 0u, lane);
+    s_seg[4 * lane] = (int)b.x;
+    s_seg[4 * lane + 1] = (int)b.y;
+    s_seg[4 * lane + 2] = (int)b.z;
+    s_seg[4 * lane + 3] = (int)b.w;
+    if (lane == 0) s_seg[256] = g.n;
+  }
+  __syncthreads();
+  if (tid <= A + 1) g.seg[tid] = s_seg[tid];                        // seg[A] = number of valid requests, seg[A+1] = n
+  int ts = 0, us = 0, ti = 0, ui = 0;
+  if (tid < 256) {
+    if (tid < A) {
+      plain_group(w, tid, s_seg[tid], s_seg[tid + 1]);
+      s_app[tid] = costly;
+      ts = (s_seg[costly + 1] - s_seg[costly] + g.tile - 1) / g.tile;
+      us = (s_seg[tid + 1] - s_seg[tid] + g.unit - 1) / g.unit;
+    }
+    ti = (int)wave_scan_incl((uint32_t)ts);
+    ui = (int)wave_scan_incl((uint32_t)us);
+    if (lane == 63) {
+      wave_t[wave] = ti;
+      wave_u[wave] = ui;
+    }
+  }
+  if (tid == 0) {
+    w.grp_n[0] = A;
+    w.grp_n[1] = 1;
+  }
+  __syncthreads();
+  if (tid < 256) {
+    for (int v = 0; v < wave; ++v) {
+      ti += wave_t[v];
+      ui += wave_u[v];
+    }
+    if (tid <= A) {
+      s_tile[tid] = ti - ts;
+      s_unit[tid] = ui - us;
+      g.tile_start[tid] = ti - ts;
+      g.unit_start[tid] = ui - us;
+    }
+  }
+  __syncthreads();
+  write_descriptors(g, s_tile, s_unit, s_seg, s_app, tid, kGroupThreads);
+}
+
 // Every request to its grouped position (applications in ascending order, request ids ascending inside), with its deadline
 // and weight (the scoring kernel then reads them in order instead of gathering by request id, 4 useful bytes per 64-byte
 // line).  One extra workgroup turns the counts into segment starts and descriptors.  Bound by three or four dependent
@@ -580,9 +618,11 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
   __shared__ uint32_t red[kGroupWaves][2][64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (blockIdx.x == 0) {              // (the first: as the last it would wait for a place on a full chip)
+    const int costly = sg.by_cost[min(tid, A - 1)];
+    loaded_here(costly);
     group_sums(counts, n_tiles, 0, A, nbits, before, total, red);
     if (tid == 0 && total[A] != 0u) atomicOr(&st->err, kErrApp);
-    segments_body(sg, sw, total);
+    segments_from_totals(sg, sw, total, costly);
     return;
   }
   // neighbouring tiles write neighbouring runs of every application: on one die, so that the lines they meet in are whole

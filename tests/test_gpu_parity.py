@@ -1444,3 +1444,16 @@ def test_weights_and_features_at_the_ends_of_the_range(gpu, dtype, d, H, f):
         ctx.sp_score(*binding.to_device(w.requests), ea_out=ea)
         ctx.close()
         parity.assert_close("EA", ea.cpu().numpy(), ref_ea, TOL if dtype == wl.F32 else 2e-3)
+
+
+@pytest.mark.parametrize("n,classes,hidden", [
+    (5, (2, 300, 40), 0), (1021, (300, 2, 33, 161, 64, 1, 97), 0), (20011, (4, 700, 4, 130), 0),
+    (3000, tuple(2 + 37 * (a % 9) for a in range(300)), 0), (2500, (5, 400, 60), 24)],
+    ids=["fewer tiles than dies", "one or two tiles each", "many tiles", "more than 255 applications", "hidden layer"])
+def test_scoring_tiles_dealt_by_their_cost(gpu, n, classes, hidden):
+    """Applications of very different class counts: tiles are numbered from the costliest application to the cheapest."""
+    A = len(classes)
+    f = np.array([3.0 if a % 3 == 0 else 0.02 if a % 3 == 1 else 1.0 for a in range(A)])
+    w = wl.tiny(seed=900 + A, n=n, classes=classes, models=tuple(1 + a % 4 for a in range(A)), max_batch=8, feat_dim=40,
+                hidden_dim=hidden, deadline=(4.0, 80.0), fractions=tuple(f / f.sum()))
+    full_parity(gpu, w, max_rounds=4)
