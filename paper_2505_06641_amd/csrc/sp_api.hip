@@ -20,6 +20,7 @@
 #include "sp_score_mlp.h"
 #include "sp_score_stream.h"
 #include "sp_rounds_persist.h"
+#include "sp_round_single.h"
 #include "sp_sort.h"
 #include "sp_probe.h"
 
@@ -69,6 +70,7 @@ struct sp_ctx {
   bool persist = false;
   bool persist_split = false;        // ... and also with the per-wavefront windows that subgroups need in LDS
   Persist ps{};
+  bool single_ok = false;            // a round by itself may run in one workgroup
   uint32_t gen_base = 0;             // slot generations handed out so far
   int32_t spin_limit = kSpinLimit;   // polls before a wait between resident workgroups is given up
   int32_t sort_spin_limit = kSortSpinLimit;   // polls before a radix pass's look-back is given up (< 0: at once)
@@ -257,6 +259,7 @@ sp_status pack_mlp_blocks(sp_ctx* c, const sp_profile* p);
 sp_status pack_stream(sp_ctx* c, const sp_profile* p);
 sp_status setup_persist(sp_ctx* c, const sp_profile* p);
 sp_status ensure_split_buffers(sp_ctx* c);
+const void* single_kernel(int Mmax);
 int score_tile(const sp_ctx* c);
 
 // What a scoring tile of an application of C classes costs, roughly, in units of a class tile: the kernel that walks the classes
@@ -414,6 +417,12 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   }
   SP_HIP(c, hipMemset(w.st, 0, sizeof(State)));
   if ((s = setup_persist(c, p)) != SP_OK) return s;
+  c->single_ok = A <= kSingleApps && single_lds_bytes(A, Mmax, B) <= kSingleLds;
+  if (c->single_ok && single_lds_bytes(A, Mmax, B) > 48 * 1024 &&
+      hipFuncSetAttribute(single_kernel(Mmax), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSingleLds) != hipSuccess) {
+    (void)hipGetLastError();
+    c->single_ok = false;
+  }
   if (c->score_lds > 64 * 1024) {
     const int bytes = (int)c->score_lds;
 #define SP_SET_LDS(T, MT) \
@@ -701,6 +710,34 @@ bool rounds_in_one_launch_so_far(sp_ctx* c) {
   if (hipEventQuery(c->ev_groups) == hipSuccess) return c->h_grp_n[1] <= kMaxAppGroups;
   (void)hipGetLastError();                             // (not ready yet)
   return true;
+}
+
+// Whether a round that is a launch of its own runs in one workgroup (see kSingleEvals).  (A bound on the waits of resident
+// workgroups that a test has set asks for those.)
+bool round_single(const sp_ctx* c) {
+  const int64_t Bw = c->tb.Bcap;
+  if (c->tb.pol_split || !c->single_ok || Bw > kSingleBatch || c->spin_limit != kSpinLimit) return false;
+  int64_t evals = 0;
+  for (int a = 0; a < c->A; ++a) {
+    const int64_t mine = c->h_nmod[a] * (c->tb.pol_whole ? Bw : Bw * (Bw + 1) / 2);
+    evals = c->tb.pol_group_first ? std::max(evals, mine) : evals + mine;
+  }
+  return evals <= kSingleEvals;
+}
+
+const void* single_kernel(int Mmax) {
+  const int q = single_quads(Mmax);
+  return q == 1 ? (const void*)k_round_single<1> : q == 2 ? (const void*)k_round_single<2> : (const void*)k_round_single<4>;
+}
+
+void launch_round_single(sp_ctx* c, const Window& w, hipStream_t s, const Single& sg) {
+  const dim3 grid(1), blk(kSingleThreads);
+  const size_t lds = single_lds_bytes(c->A, c->Mmax, c->B);
+  switch (single_quads(c->Mmax)) {
+    case 1: hipLaunchKernelGGL(k_round_single<1>, grid, blk, lds, s, c->tb, w, sg); break;
+    case 2: hipLaunchKernelGGL(k_round_single<2>, grid, blk, lds, s, c->tb, w, sg); break;
+    default: hipLaunchKernelGGL(k_round_single<4>, grid, blk, lds, s, c->tb, w, sg); break;
+  }
 }
 
 void fill_u64(hipStream_t s, unsigned long long* p, size_t n) {
@@ -1046,6 +1083,10 @@ int group_count(sp_ctx* c) {
 }
 
 void launch_round(sp_ctx* c, const Window& w, hipStream_t s, int32_t* ids_out, float* cube) {
+  if (cube == nullptr && round_single(c)) {
+    launch_round_single(c, w, s, Single{Outputs{}, ids_out, nullptr, nullptr});
+    return;
+  }
   hipLaunchKernelGGL(k_round_score, dim3(group_count(c) * c->Mmax), dim3(kRoundThreads), 0, s, c->tb, w, cube);
   if (cube == nullptr)
     hipLaunchKernelGGL(k_round_commit, dim3(1), dim3(kRoundThreads), 0, s, c->tb, w, ids_out);
@@ -1255,10 +1296,13 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
     const bool want_outputs = c->n > 0 && (model_out_dev || round_out_dev || order_out_dev || util_out_dev);
     // the commit workgroup fills the caller's arrays itself where that is little next to the launch's rounds (not while the
     // stages are timed: the copy then has a time of its own)
-    const bool outputs_inside = persist && want_outputs && !tm && c->rounds_done == 0 && (int64_t)c->n <= (int64_t)kOutputsPerRound * chunk;
+    const bool single = persist && chunk == 1 && round_single(c);
+    const bool outputs_inside = persist && want_outputs && !tm && c->rounds_done == 0 &&
+                                (int64_t)c->n <= (single ? kSingleOutputs : (int64_t)kOutputsPerRound * chunk);
     if (persist) {
       c->ps.out = outputs_inside ? outs : Outputs{};
-      if ((st = launch_rounds_persistent(c, s, chunk)) != SP_OK) return st;
+      if (single) launch_round_single(c, c->w, s, Single{c->ps.out, nullptr, c->ps.log_host, c->ps.ticks});
+      else if ((st = launch_rounds_persistent(c, s, chunk)) != SP_OK) return st;
       if (tm && c->timing_rounds)
         SP_HIP(c, hipMemcpyAsync(c->h_ticks, c->ps.ticks, (kPersistRounds + 1) * sizeof(long long), hipMemcpyDeviceToHost, s));
     } else {

@@ -114,27 +114,26 @@ __device__ __forceinline__ unsigned long long triangle_best_kind(const float4* e
     // only_b > 0: that batch size alone is a candidate ("the group runs whole")
     const int n1 = (b1 <= nb && (only_b == 0 || b1 == only_b)) ? b1 : 0;
     const int n2 = (b2 <= nb && b2 != b1 && (only_b == 0 || b2 == only_b)) ? b2 : 0;
-    float s1 = 0.f, s2 = 0.f, s3 = 0.f;
+    float s1 = 0.f, s2 = 0.f;
     int j = sub;
     for (; j < n1 && j < n2; j += kPairLanes) {                 // both batch sizes use request j
       const float4 e = ent[j];
-      s1 += e.x * one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e1h, e1l);
-      s2 += e.x * one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e2h, e2l);
+      s1 = fmaf(e.x, one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e1h, e1l), s1);
+      s2 = fmaf(e.x, one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e2h, e2l), s2);
     }
     for (; j < n1; j += kPairLanes) {
       const float4 e = ent[j];
-      s1 += e.x * one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e1h, e1l);
+      s1 = fmaf(e.x, one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e1h, e1l), s1);
     }
     for (; j + kPairLanes < n2; j += 2 * kPairLanes) {          // only the larger one: two requests per trip
       const float4 e = ent[j], f = ent[j + kPairLanes];
-      s2 += e.x * one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e2h, e2l);
-      s3 += f.x * one_minus_penalty_f32<KIND>(f.y, f.w, f.z, e2h, e2l);
+      const float pe = one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e2h, e2l), pf = one_minus_penalty_f32<KIND>(f.y, f.w, f.z, e2h, e2l);
+      s2 = fmaf(f.x, pf, fmaf(e.x, pe, s2));
     }
     if (j < n2) {
       const float4 e = ent[j];
-      s2 += e.x * one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e2h, e2l);
+      s2 = fmaf(e.x, one_minus_penalty_f32<KIND>(e.y, e.w, e.z, e2h, e2l), s2);
     }
-    s2 += s3;
     s1 = kPairLanes == 8 ? sum8(s1) : sum16(s1);
     s2 = kPairLanes == 8 ? sum8(s2) : sum16(s2);
     if (sub == 0) {
@@ -314,6 +313,15 @@ struct Outputs {
   int32_t *model, *round_of, *order_of;
   float* util;
 };
+
+// One of the caller's arrays filled by `step` threads (this one is the first-th), 16 bytes per store (its start need not be
+// aligned to them).
+__device__ __forceinline__ void fill_output(int32_t* out, int n, int32_t v, int first, int step) {
+  if (out == nullptr) return;
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+  for (int i = 4 * first; i + 4 <= n; i += 4 * step) *reinterpret_cast<i32x4*>(out + i) = i32x4{v, v, v, v};
+  if (first < (n & 3)) out[(n & ~3) + first] = v;
+}
 
 // Members of one batch: outputs, pending flags and the three sums.  pos_of(j) gives the service position
 // of the j-th member.  All threads of the workgroup call it; the sums come back on thread 0.

@@ -112,24 +112,16 @@ __global__ void k_copy_outputs(int n, Window w, Outputs out) {
   if (i < n) copy_output(i, w, out);
 }
 
-// One of the caller's arrays filled by one workgroup, 16 bytes per store (its start need not be aligned to them).
-__device__ __forceinline__ void fill_output(int32_t* out, int n, int32_t v) {
-  if (out == nullptr) return;
-  typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
-  for (int i = 4 * threadIdx.x; i + 4 <= n; i += 4 * kRoundThreads) *reinterpret_cast<i32x4*>(out + i) = i32x4{v, v, v, v};
-  if ((int)threadIdx.x < (n & 3)) out[(n & ~3) + threadIdx.x] = v;
-}
-
 __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Persist& ps, double (*dsum)[kMaxBatch],
                                     unsigned long long* bcast) {
   State* st = w.st;
   const int tid = threadIdx.x;
   // the caller's arrays as a window without rounds leaves them, before this workgroup's own commits go into both (it has
   // nothing to do until the first decision, and is ahead of the rounds after it)
-  fill_output(ps.out.model, w.n, -1);
-  fill_output(ps.out.round_of, w.n, -1);
-  fill_output(ps.out.order_of, w.n, 0);
-  fill_output(reinterpret_cast<int32_t*>(ps.out.util), w.n, 0);
+  fill_output(ps.out.model, w.n, -1, tid, kRoundThreads);
+  fill_output(ps.out.round_of, w.n, -1, tid, kRoundThreads);
+  fill_output(ps.out.order_of, w.n, 0, tid, kRoundThreads);
+  fill_output(reinterpret_cast<int32_t*>(ps.out.util), w.n, 0, tid, kRoundThreads);
   if (st->done || st->err) {
     if (tid == 0) mirror_state(w);
     return;

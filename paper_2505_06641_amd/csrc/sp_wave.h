@@ -54,12 +54,39 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
   return ((unsigned long long)hi << 32) | (unsigned long long)lo;
 }
 
+// The same for packed candidates (a non-negative float's bits above 32 others) in two 32-bit maxima: of the upper words, then of
+// the lower ones where the upper word is the largest.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t wave_max_step32(uint32_t v) {
+  return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false));
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  v = wave_max_step32<0x111, 0xf>(v);
+  v = wave_max_step32<0x112, 0xf>(v);
+  v = wave_max_step32<0x114, 0xf>(v);
+  v = wave_max_step32<0x118, 0xf>(v);
+  v = wave_max_step32<0x142, 0xa>(v);
+  v = wave_max_step32<0x143, 0xc>(v);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ unsigned long long wave_max_packed(unsigned long long v) {
+  const uint32_t hi = wave_max_u32((uint32_t)(v >> 32));
+  const uint32_t lo = wave_max_u32((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0u);
+  return ((unsigned long long)hi << 32) | (unsigned long long)lo;
+}
+
+// Sum of a float over each aligned group of 4 lanes, on every lane of the group: lane ^ 1, then lane ^ 2.
+__device__ __forceinline__ float sum4(float v) {
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, false));    // quad_perm:[1,0,3,2]
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, false));    // quad_perm:[2,3,0,1]
+  return v;
+}
+
 // Sum of a float over each aligned group of 8 lanes, on every lane of the group: lane ^ 1 and lane ^ 2 inside
 // the quad, then the mirrored half (whose quad already holds one value).  Every lane adds the same two
 // numbers as in the butterfly over lane ^ 1, ^ 2, ^ 4, so the result has the same bits.
 __device__ __forceinline__ float sum8(float v) {
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, false));    // quad_perm:[1,0,3,2]
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, false));    // quad_perm:[2,3,0,1]
+  v = sum4(v);
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false));   // row_half_mirror
   return v;
 }

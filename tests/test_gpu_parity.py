@@ -1457,3 +1457,44 @@ def test_scoring_tiles_dealt_by_their_cost(gpu, n, classes, hidden):
     w = wl.tiny(seed=900 + A, n=n, classes=classes, models=tuple(1 + a % 4 for a in range(A)), max_batch=8, feat_dim=40,
                 hidden_dim=hidden, deadline=(4.0, 80.0), fractions=tuple(f / f.sum()))
     full_parity(gpu, w, max_rounds=4)
+
+
+@pytest.mark.parametrize("name", ["sneakpeek", "alg1", "maxacc_edf"])
+@pytest.mark.parametrize("A,M,B,n,due,fractions", [
+    (1, 1, 1, 40, (5.0, 60.0), None), (3, 4, 31, 3000, (5.0, 150.0), (0.9, 0.09, 0.01)), (2, 9, 64, 5000, (30.0, 400.0), None),
+    (15, 2, 33, 4000, (20.0, 300.0), None), (2, 3, 20, 30000, (4.0, 200.0), (0.97, 0.03)), (1, 16, 58, 63, (50.0, 500.0), None)],
+    ids=["one of each", "short windows", "batches of 64", "fifteen applications", "mostly dead", "fewer than a wavefront"])
+def test_single_rounds_in_one_workgroup(gpu, name, A, M, B, n, due, fractions):
+    """A round per call in one launch of one workgroup against two kernels per round: the same decisions and members to the last
+    bit, also with swap-in costs, from the first round until nothing is live."""
+    torch, binding = gpu
+    policy = wl.named_policy(name)
+    w = wl.tiny(seed=9100 + n, n=n, classes=(3,) * A, models=tuple(max(1, M - a % 3) for a in range(A)), max_batch=B, feat_dim=16, deadline=due,
+                alpha=(0.5, 20.0), beta=(0.05, 2.5), fractions=fractions)
+    w.profile.penalty[:] = [(wl.PEN_SIGMOID, wl.PEN_LINEAR, wl.PEN_STEP)[a % 3] for a in range(A)]
+    wl.attach_swap_costs(w.profile, 9100, skip_every=2)
+    args = binding.to_device(w.requests)
+    ctxs = [binding.Context(w.profile, n, policy=policy) for _ in range(2)]
+    ctxs[1].sp_debug_set_spin_limit(1 << 19)            # (any bound but the default keeps this kernel out)
+    ids = [torch.full((B,), -1, dtype=torch.int32, device="cuda:0") for _ in range(2)]
+    for c in ctxs:
+        c.sp_score(*args)
+    for k in range(60):
+        got = [c.sp_greedy_round(req_ids_out=i) for c, i in zip(ctxs, ids)]
+        assert got[0] == got[1], f"round {k}"
+        assert torch.equal(*ids), f"round {k}"
+        if got[0][0] == binding.SP_DONE:
+            break
+    assert k > 0
+    # what is left in one launch, from the state that either kernel has left
+    ends = [c.sp_schedule(0, log_capacity=n) for c in ctxs]
+    assert ends[0] == ends[1]
+    for c in ctxs:
+        c.close()
+
+
+@pytest.mark.parametrize("n", [1, 700, 16384, 16385])
+def test_one_scheduled_round_fills_the_outputs(gpu, n):
+    """sp_schedule of one round: the outputs of the requests it does not serve, below and beyond what its kernel fills itself."""
+    w = wl.tiny(seed=9200 + n, n=n, classes=(4, 2), models=(3, 2), max_batch=16, feat_dim=16, deadline=(20.0, 90.0))
+    full_parity(gpu, w, max_rounds=1)
