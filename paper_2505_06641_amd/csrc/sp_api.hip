@@ -69,6 +69,7 @@ struct sp_ctx {
   // all rounds of a chunk in one launch, when every (application, variant) pair fits on the device at once
   bool persist = false;
   bool persist_split = false;        // ... and also with the per-wavefront windows that subgroups need in LDS
+  int persist_wgs = 2, persist_split_wgs = 2;   // the instantiations that hold the grid (see k_rounds_persistent)
   Persist ps{};
   bool single_ok = false;            // a round by itself may run in one workgroup
   uint32_t gen_base = 0;             // slot generations handed out so far
@@ -643,11 +644,20 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
   if (n_pairs == 0 || n_pairs > (size_t)kMaxPairs || ring > ((size_t)32 << 20)) return SP_OK;
   int cus = 0, per_cu = 0, rate_khz = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) return SP_OK;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds_persistent<false>, kRoundThreads, 0) != hipSuccess) {
+  // the instantiation with more registers where two workgroups per compute unit hold the grid
+  c->persist_wgs = 2;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds_persistent<false, 2>, kRoundThreads, 0) != hipSuccess) {
     (void)hipGetLastError();
     return SP_OK;
   }
-  if ((size_t)per_cu * (size_t)cus < n_pairs + 2) return SP_OK;
+  if ((size_t)per_cu * (size_t)cus < n_pairs + 2) {
+    c->persist_wgs = 3;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds_persistent<false, 3>, kRoundThreads, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      return SP_OK;
+    }
+    if ((size_t)per_cu * (size_t)cus < n_pairs + 2) return SP_OK;
+  }
   if (hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, c->device) != hipSuccess || rate_khz <= 0)
     rate_khz = 100000;
   c->tick_ms = 1.0 / (double)rate_khz;
@@ -760,10 +770,12 @@ sp_status launch_rounds_persistent(sp_ctx* c, hipStream_t s, int n_rounds) {
   ps.gen_base = c->gen_base;
   c->gen_base += (uint32_t)n_rounds;
   *c->h_lost = 0;                                                // (the launch before has been waited for)
-  if (c->tb.pol_split)
-    hipLaunchKernelGGL(k_rounds_persistent<true>, dim3(ps.n_pairs + 2), dim3(kRoundThreads), persist_dynamic_lds(c), s, c->tb, c->w, ps);
-  else
-    hipLaunchKernelGGL(k_rounds_persistent<false>, dim3(ps.n_pairs + 2), dim3(kRoundThreads), 0, s, c->tb, c->w, ps);
+  const dim3 grid(ps.n_pairs + 2), blk(kRoundThreads);
+  const size_t dyn = persist_dynamic_lds(c);
+  if (c->tb.pol_split && c->persist_split_wgs == 2) hipLaunchKernelGGL((k_rounds_persistent<true, 2>), grid, blk, dyn, s, c->tb, c->w, ps);
+  else if (c->tb.pol_split) hipLaunchKernelGGL((k_rounds_persistent<true, 3>), grid, blk, dyn, s, c->tb, c->w, ps);
+  else if (c->persist_wgs == 2) hipLaunchKernelGGL((k_rounds_persistent<false, 2>), grid, blk, dyn, s, c->tb, c->w, ps);
+  else hipLaunchKernelGGL((k_rounds_persistent<false, 3>), grid, blk, dyn, s, c->tb, c->w, ps);
   return SP_OK;
 }
 
@@ -1544,11 +1556,15 @@ sp_status sp_set_policy(sp_ctx* c, const sp_policy* p) {
     if (c->persist) {
       int cus = 0, per_cu = 0;
       const size_t dyn = (size_t)(kRoundThreads / 64) * (size_t)c->B * (sizeof(float4) + sizeof(int32_t));
-      if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess &&
-          hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds_persistent<true>, kRoundThreads, dyn) == hipSuccess)
-        c->persist_split = (size_t)per_cu * (size_t)cus >= (size_t)c->ps.n_pairs + 2;
-      else
-        (void)hipGetLastError();
+      const size_t need = (size_t)c->ps.n_pairs + 2;
+      const auto fits = [&](auto kernel) {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kRoundThreads, dyn) == hipSuccess && (size_t)per_cu * (size_t)cus >= need;
+      };
+      if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess) {
+        c->persist_split_wgs = fits(k_rounds_persistent<true, 2>) ? 2 : 3;
+        c->persist_split = c->persist_split_wgs == 2 || fits(k_rounds_persistent<true, 3>);
+      }
+      (void)hipGetLastError();
     }
   }
   tb.pol_split = p->split_groups;

@@ -92,6 +92,14 @@ __device__ __forceinline__ unsigned long long slot_word0(float score, uint32_t g
          (valid ? 0x100ull : 0ull) | (unsigned long long)((b - 1) & 0xff);
 }
 
+// Candidate ids inside this kernel: fields (group, variant, batch size - 1) instead of a product, which orders them the same way
+// and needs no division to take apart on the way from one round to the next.
+__device__ __forceinline__ uint32_t pcid(int grp, int m) { return ((uint32_t)grp << 12) | ((uint32_t)m << 8); }
+__device__ __forceinline__ int pcid_group(uint32_t c) { return (int)(c >> 12); }
+__device__ __forceinline__ int pcid_model(uint32_t c) { return (int)(c >> 8) & 15; }
+__device__ __forceinline__ int pcid_batch(uint32_t c) { return (int)(c & 0xffu) + 1; }
+static_assert(kMaxModels <= 16 && kMaxBatch <= 256, "fields of a candidate id (groups: at most 65,536)");
+
 // A wait has run out.  The commit workgroup mirrors the state for the host when its own work ends, which may be before another
 // workgroup gives up: each of them tells the host itself.
 __device__ __forceinline__ void raise_lost(State* st, const Persist& ps) {
@@ -152,9 +160,7 @@ __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Per
     const uint32_t cid = 0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull);
     const float score = __uint_as_float((uint32_t)(best >> 32));
     const int B = tb.B;
-    const int b = (int)(cid % (uint32_t)B) + 1;
-    const int am = (int)(cid / (uint32_t)B);
-    const int m = am % tb.Mmax, grp = am / tb.Mmax;
+    const int b = pcid_batch(cid), m = pcid_model(cid), grp = pcid_group(cid);
     const int a = group_app(tb, w, grp);              // group = application unless the requests are split into subgroups
     const double E = start_time(tb, last, t, a, m) + (double)tb.lat[((int64_t)a * tb.Mmax + m) * B + (b - 1)];
     const unsigned long long* row = ps.ring + ((size_t)rl * tb.A + a) * B;
@@ -201,7 +207,7 @@ struct Best {
 // Over a wavefront (candidate ids are unique, so one lane holds the maximum).
 __device__ __forceinline__ Best wave_best(unsigned long long word, float lat, float swap) {
   Best b;
-  b.word = wave_max_u64(word);
+  b.word = wave_max_packed(word);
   const unsigned long long who = __ballot(word == b.word);
   const int lane = __builtin_amdgcn_readfirstlane(__ffsll((long long)who) - 1);
   b.lat = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lat), lane));
@@ -213,7 +219,6 @@ __device__ __forceinline__ Best wave_best(unsigned long long word, float lat, fl
 __device__ void persist_reduce_loop(const Tables& tb, const Window& w, const Persist& ps, unsigned long long* red,
                                     Best (*waves)[kRoundThreads / 64], int* timed_out) {
   const int tid = threadIdx.x;
-  const int B = tb.B;
   if (ps.all_to_all) return;                      // every pair takes the maximum itself
   const int my_slot = tid < ps.n_pairs ? tid : 0;
   const int my_m = ps.pair_model[my_slot];
@@ -243,9 +248,9 @@ __device__ void persist_reduce_loop(const Tables& tb, const Window& w, const Per
         v0 = ld_dev(slot);
         v1 = ld_dev(slot + 1);
         v2 = ld_dev(slot + 2);
-        v3 = ld_dev(slot + 3);
+        if (tb.pol_group_first) v3 = ld_dev(slot + 3);
         ok = ((uint32_t)(v0 >> 9) & kGenMask) == (gen & kGenMask) && (uint32_t)(v1 & 0xFFFFull) == (gen & 0xFFFFu) &&
-             (uint32_t)(v2 & 0xFFFFFFFFull) == gen && (uint32_t)(v3 & 0xFFFFFFFFull) == gen;
+             (uint32_t)(v2 & 0xFFFFFFFFull) == gen && (!tb.pol_group_first || (uint32_t)(v3 & 0xFFFFFFFFull) == gen);
         if (ok) break;
         __builtin_amdgcn_s_sleep(1);
       }
@@ -254,8 +259,7 @@ __device__ void persist_reduce_loop(const Tables& tb, const Window& w, const Per
       } else if (v0 & 0x100ull) {
         const int pm = q == 0 ? my_m : ps.pair_model[i];
         const int pg = (int)((uint32_t)(v1 >> 16) & 0xFFFFu);      // the candidate's group (the pair's application when unsplit)
-        const uint32_t cid = (uint32_t)((pg * tb.Mmax + pm) * B) + (uint32_t)(v0 & 0xffull);
-        const unsigned long long pk = pack_candidate(__uint_as_float((uint32_t)(v0 >> 32)), cid);
+        const unsigned long long pk = pack_candidate(__uint_as_float((uint32_t)(v0 >> 32)), pcid(pg, pm) | (uint32_t)(v0 & 0xffull));
         held[q] = pk;
         held_lat[q] = __uint_as_float((uint32_t)(v1 >> 32));
         held_swap[q] = __uint_as_float((uint32_t)(v2 >> 32));
@@ -273,7 +277,7 @@ __device__ void persist_reduce_loop(const Tables& tb, const Window& w, const Per
     for (int q = 0; q < kSlotsPerThread; ++q) {
       if (held[q] == 0ull) continue;
       const uint32_t cid = 0xFFFFFFFFu - (uint32_t)(held[q] & 0xFFFFFFFFull);
-      if (a_star >= 0 && (int)(cid / (uint32_t)B) / tb.Mmax != a_star) continue;
+      if (a_star >= 0 && pcid_group(cid) != a_star) continue;
       if (held[q] > mine) { mine = held[q]; mine_lat = held_lat[q]; mine_swap = held_swap[q]; }
     }
     // the wavefronts' maxima with what belongs to them, then one barrier; the array alternates between rounds
@@ -286,16 +290,15 @@ __device__ void persist_reduce_loop(const Tables& tb, const Window& w, const Per
       if (tid == 0) raise_lost(w.st, ps);
       break;
     }
-    Best top1 = waves[rl & 1][0];
-    for (int i = 1; i < kRoundThreads / 64; ++i)
-      if (waves[rl & 1][i].word > top1.word) top1 = waves[rl & 1][i];
+    const Best of = waves[rl & 1][tid & (kRoundThreads / 64 - 1)];
+    const Best top1 = wave_best(of.word, of.lat, of.swap);
     const unsigned long long all = top1.word;
-    if (tid == 0) {
-      unsigned long long* d = ps.decision + (size_t)(gen & 1u) * 4;
+    if (tid < 3) {                                             // three words side by side
       const uint32_t cidp1 = all != 0ull ? (0xFFFFFFFFu - (uint32_t)(all & 0xFFFFFFFFull)) + 1u : 0u;
-      st_dev(d, ((unsigned long long)__float_as_uint(all != 0ull ? top1.lat : 0.f) << 32) | (unsigned long long)gen);
-      st_dev(d + 1, ((unsigned long long)cidp1 << 32) | (unsigned long long)gen);
-      st_dev(d + 2, ((unsigned long long)__float_as_uint(all != 0ull ? top1.swap : 0.f) << 32) | (unsigned long long)gen);
+      const uint32_t word = tid == 1 ? cidp1 : all == 0ull ? 0u : __float_as_uint(tid == 0 ? top1.lat : top1.swap);
+      st_dev(ps.decision + (size_t)(gen & 1u) * 4 + tid, ((unsigned long long)word << 32) | (unsigned long long)gen);
+    }
+    if (tid == 0) {
       st_dev(ps.dec + rl, all | (1ull << 63));
       ps.ticks[rl + 1] = wall_clock64();
     }
@@ -343,11 +346,11 @@ __device__ __forceinline__ int wave_window(const Window& w, int kind, int head, 
 constexpr int kCachedRequests = 512;
 
 // SPLIT: the window's groups are subgroups of the applications (tb.pol_split); the plain instantiation holds
-// none of the secondary-group code, so that its 80 registers do (three workgroups per CU must fit: 512 pairs and two more on
-// 256 CUs).  Holding addresses and lane masks from one round to the next took it past them; formed where they are used, a
-// round takes 8.55 us instead of 8.8 (512 pairs) and 5.1 instead of 5.3 (64), with subgroups 9.0 instead of 9.4.
-template <bool SPLIT>
-__global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables tb, Window w, Persist ps) {
+// none of the secondary-group code.
+// WGS: workgroups that must fit on a compute unit.  Three leave 80 registers, which the plain instantiation with the looping triangles
+// just fits; grids of up to two per compute unit (510 pairs on 256) get 128 registers, and triangles with their entries held.
+template <bool SPLIT, int WGS>
+__global__ __launch_bounds__(kRoundThreads, 2 * WGS) void k_rounds_persistent(Tables tb, Window w, Persist ps) {
   __shared__ int32_t win[kWinCap];
   __shared__ float4 ent[kWinCap];
   __shared__ float om[kWinCap];              // ordering value of each entry (for the group priority)
@@ -356,8 +359,10 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
   __shared__ unsigned long long red[kRoundThreads / 64];
   __shared__ unsigned long long cand_max[2][kRoundThreads / 64];   // a round's candidates per wavefront (alternating)
   __shared__ Best waves[2][kRoundThreads / 64];
-  // block_sum_f64's scratch, or the commit workgroup's
-  __shared__ union { double one[kRoundThreads]; double three[3][kMaxBatch]; } dsum;
+  // this round's window without the entries that have died (every wavefront writes all of it), or the commit workgroup's sums
+  __shared__ union { struct { float4 ent[kMaxBatch]; float om[kMaxBatch]; } now; double dsum[3][kMaxBatch]; } own;
+  float4* const cent = own.now.ent;
+  float* const com = own.now.om;
   __shared__ struct { uint32_t cid; float lat, swap; } decided[2];   // a round's decision (alternating)
   __shared__ int timed_out;
   __shared__ int32_t slot_model[kAllToAllPairs];                // variants behind the slots
@@ -378,7 +383,7 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
     return;
   }
   if ((int)blockIdx.x == ps.n_pairs + 1) {
-    persist_commit_loop(tb, w, ps, dsum.three, red);
+    persist_commit_loop(tb, w, ps, own.dsum, red);
     return;
   }
   if (st->done || st->err) return;          // the state is rewritten only when the commit workgroup ends
@@ -491,8 +496,8 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
         wave_sync();
         if (lane == 0) evals += triangle_evals(nbs, tb.pol_whole);
         unsigned long long cand = triangle_best(scoring_penalty(tb, kind), went, lat_s, nbs, Bw, t + (double)swap_now,
-                                                (uint32_t)((g * tb.Mmax + m) * B), nullptr, tb.pol_whole ? nbs : 0, kWave, lane);
-        cand = wave_max_u64(cand);
+                                                pcid(g, m), nullptr, tb.pol_whole ? nbs : 0, kWave, lane);
+        cand = wave_max_packed(cand);
         if (tb.pol_group_first) {
           // eq. (14) over the window: the fixed-order sum a single wavefront forms in k_round_score
           double part = 0.0;
@@ -509,8 +514,8 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
       }
     }
 
-    // ---- primary group: drop what the last decision consumed and what has died since ----
-    {
+    // The primary group's list without what the last decision consumed and what has died.  The whole workgroup.
+    auto drop = [&] {
       const bool has = tid < nb;
       int pos = 0;
       float4 e = make_float4(0.f, 1.f, 0.f, 0.f);
@@ -533,7 +538,7 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
         __syncthreads();
       }
       shift = 0;
-    }
+    };
 
     // Walks on through the service order from scan_end and appends the live requests it meets, for at
     // most max_steps steps of 4 * nq positions per thread, until the window is full or the group's
@@ -590,62 +595,103 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
       __syncthreads();
     };
 
-    // ---- fewer than B entries left: the round has to wait for the walk ----
-    if (nb < Bw && scan_end < seg_e) walk(1 << 30, 1);
-    const int nbe = min(nb, Bw);
+    // ---- the round's window: the first Bw live entries of the list, from its first few chunks of 64 (those that hold Bw
+    // entries and sixteen more).  Every wavefront finds and writes all of them, the same values to the same places: it then
+    // reads what it has written itself, and no barrier is needed.  The list itself is put in order while candidates are exchanged. ----
+    bool in_order = false;
+    int nbe = 0;
+    {
+      const int look = min(nb, shift + (Bw + 16 + kWave - 1) / kWave * kWave);
+      for (int j0 = shift; j0 < look; j0 += kWave) {
+        const int j = j0 + lane;
+        const float4 e = ent[min(j, kWinCap - 1)];
+        const bool live = j < nb && !is_dead(kind, e.y, E0);
+        const unsigned long long bal = __ballot(live);
+        const int rank = nbe + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+        if (live && rank < Bw) {
+          cent[rank] = e;
+          if (tb.pol_group_first) com[rank] = om[j];
+        }
+        nbe += __popcll(bal);
+      }
+      if (nbe < Bw && (look < nb || scan_end < seg_e)) {           // (uniform) not enough there: the round has to wait for the rest
+        in_order = true;
+        drop();
+        if (nb < Bw && scan_end < seg_e) walk(1 << 30, 1);
+        nbe = nb;
+        for (int j = lane; j < min(nb, Bw); j += kWave) {
+          cent[j] = ent[j];
+          if (tb.pol_group_first) com[j] = om[j];
+        }
+      }
+      nbe = min(nbe, Bw);
+      wave_sync();
+    }
 
-    // ---- the window's positions for the commit workgroup (with subgroups: after the decision) ----
-    if (!SPLIT && m == 0 && tid < nbe)
-      st_dev(ps.ring + ((size_t)rl * tb.A + a) * B + tid, ((unsigned long long)gen << 32) | (unsigned long long)(uint32_t)win[tid]);
-
-    // ---- triangle: the same code as k_round_score ----
+    // ---- triangle: the sums of k_round_score ----
     unsigned long long best = 0ull;
     if (tid == 0) evals += triangle_evals(nbe, tb.pol_whole);
-    if (nbe > 0)
-      best = triangle_best(scoring_penalty(tb, kind), ent, lat_s, nbe, Bw, t + (double)swap_now,
-                           (uint32_t)((gprim * tb.Mmax + m) * B), nullptr, tb.pol_whole ? nbe : 0);
+    if (nbe > 0) {
+      if (WGS == 2 && pair_lanes(Bw) == 16)
+        best = triangle_held(scoring_penalty(tb, kind), cent, lat_s, nbe, Bw, t + (double)swap_now, pcid(gprim, m), tb.pol_whole ? nbe : 0, tid);
+      else
+        best = triangle_best(scoring_penalty(tb, kind), cent, lat_s, nbe, Bw, t + (double)swap_now, pcid(gprim, m), nullptr, tb.pol_whole ? nbe : 0);
+    }
     float prio = 0.f;
-    if (tb.pol_group_first) {          // eq. (14) over the window, the same fixed-order sum as in k_round_score
-      const double psum = block_sum_f64(tid < nbe ? (double)om[tid] : 0.0, dsum.one);
-      prio = nbe > 0 ? (float)(psum / (double)nbe) : 0.f;
+    if (tb.pol_group_first && wave == 0) {   // eq. (14) over the window, in the order of block_sum_f64
+      double v[kMaxBatch / kWave];
+#pragma unroll
+      for (int q = 0; q < kMaxBatch / kWave; ++q) v[q] = q * kWave + lane < nbe ? (double)com[q * kWave + lane] : 0.0;
+      double sum = (v[0] + v[2]) + (v[1] + v[3]);
+#pragma unroll
+      for (int o = kWave / 2; o > 0; o >>= 1) sum += __shfl_down(sum, o);
+      prio = nbe > 0 ? (float)(__shfl(sum, 0) / (double)nbe) : 0.f;
     }
     if (SPLIT && ng > 1 && lane == 0) {
       sec_best[wave] = wbest;
       sec_top[wave] = wtop;
       sec_prio[wave] = wprio;
     }
-    best = wave_max_u64(best);
+    best = wave_max_packed(best);
     if (lane == 0) cand_max[rl & 1][wave] = best;
     __syncthreads();                     // (also makes the wavefronts' secondary results visible)
 
-    // ---- publish this pair's best candidate over its groups ----
-    if (tid == 0) {
-      for (int i = 1; i < kRoundThreads / 64; ++i) best = cand_max[rl & 1][i] > best ? cand_max[rl & 1][i] : best;
+    // ---- publish this pair's best candidate over its groups: four lanes, a word each ----
+    if (wave == 0) {
+      constexpr int kW = kRoundThreads / 64;
+      best = wave_max_packed(lane < kW ? cand_max[rl & 1][lane] : 0ull);
       if (SPLIT && ng > 1) {
+        const unsigned long long sec = lane < kW ? sec_best[lane] : 0ull;
         if (tb.pol_group_first) {
           // first the group with the highest priority among those that have a candidate, then its candidate
-          unsigned long long ftop = best != 0ull ? (((unsigned long long)ordered_bits(prio) << 32) |
-                                                    (unsigned long long)(0xFFFFFFFFu - (uint32_t)gprim)) : 0ull;
-          for (int i = 0; i < kRoundThreads / 64; ++i)
-            if (sec_best[i] != 0ull && sec_top[i] > ftop) { ftop = sec_top[i]; best = sec_best[i]; prio = sec_prio[i]; }
+          unsigned long long top = sec != 0ull ? sec_top[lane] : 0ull;
+          if (lane == kW && best != 0ull) top = ((unsigned long long)ordered_bits(prio) << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)gprim);
+          const unsigned long long cand = lane == kW ? best : sec;
+          const float pr = lane < kW ? sec_prio[lane] : prio;
+          const unsigned long long ftop = wave_max_u64(top);
+          const int who = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(top == ftop)) - 1);
+          best = ftop != 0ull ? (unsigned long long)__shfl((long long)cand, who) : 0ull;
+          prio = ftop != 0ull ? __shfl(pr, who) : prio;
         } else {
-          for (int i = 0; i < kRoundThreads / 64; ++i) best = sec_best[i] > best ? sec_best[i] : best;
+          best = wave_max_packed(sec > best ? sec : best);
         }
       }
-      unsigned long long* slot = ps.slots + ((size_t)(gen & 1u) * ps.n_pairs + pair) * 4;
       const bool valid = best != 0ull;
-      const uint32_t bcid = 0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull);
-      const int b = valid ? (int)(bcid % (uint32_t)B) + 1 : 1;
-      const uint32_t bg = valid ? (bcid / (uint32_t)B) / (uint32_t)tb.Mmax : (uint32_t)a;
-      st_dev(slot + 3, ((unsigned long long)__float_as_uint(prio) << 32) | (unsigned long long)gen);
-      st_dev(slot + 2, ((unsigned long long)__float_as_uint(swap_now) << 32) | (unsigned long long)gen);
-      st_dev(slot + 1, ((unsigned long long)__float_as_uint(lat_s[b - 1]) << 32) | ((unsigned long long)(bg & 0xFFFFu) << 16) |
-                           (unsigned long long)(gen & 0xFFFFu));
-      st_dev(slot, slot_word0(__uint_as_float((uint32_t)(best >> 32)), gen, valid, b));
+      const uint32_t bcid = 0xFFFFFFFFu - (uint32_t)best;
+      const int b = valid ? pcid_batch(bcid) : 1;
+      const uint32_t bg = valid ? (uint32_t)pcid_group(bcid) : (uint32_t)a;
+      const unsigned long long w0 = slot_word0(__uint_as_float((uint32_t)(best >> 32)), gen, valid, b);
+      const unsigned long long w1 = ((unsigned long long)__float_as_uint(lat_s[b - 1]) << 32) | ((unsigned long long)(bg & 0xFFFFu) << 16) |
+                                    (unsigned long long)(gen & 0xFFFFu);
+      const unsigned long long w23 = ((unsigned long long)__float_as_uint(lane == 2 ? swap_now : prio) << 32) | (unsigned long long)gen;
+      if (lane < 4) st_dev(ps.slots + ((size_t)(gen & 1u) * ps.n_pairs + pair) * 4 + lane, lane == 0 ? w0 : lane == 1 ? w1 : w23);
     }
 
-    // ---- look-ahead: one step of the walk while the candidates are exchanged ----
-    // (three dependent trips to memory, about twice the exchange: only once less than two windows are left)
+    // ---- while the candidates are exchanged: the list in order, the window's positions for the commit workgroup (with
+    // subgroups after the decision), and one step of the walk once less than two windows are left ----
+    if (!in_order) drop();
+    if (!SPLIT && m == 0 && tid < nbe)
+      st_dev(ps.ring + ((size_t)rl * tb.A + a) * B + tid, ((unsigned long long)gen << 32) | (unsigned long long)(uint32_t)win[tid]);
     if (nb < min(2 * Bw, cap) && scan_end < seg_e) walk(1, 4);
 
     // ---- few pairs: the first wavefront takes the maximum over all pairs' slots (the reducer's rule on the same words), two
@@ -668,9 +714,9 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
             v0 = ld_dev(slot);
             v1 = ld_dev(slot + 1);
             v2 = ld_dev(slot + 2);
-            v3 = ld_dev(slot + 3);
+            if (tb.pol_group_first) v3 = ld_dev(slot + 3);
             ok = ((uint32_t)(v0 >> 9) & kGenMask) == (gen & kGenMask) && (uint32_t)(v1 & 0xFFFFull) == (gen & 0xFFFFu) &&
-                 (uint32_t)(v2 & 0xFFFFFFFFull) == gen && (uint32_t)(v3 & 0xFFFFFFFFull) == gen;
+                 (uint32_t)(v2 & 0xFFFFFFFFull) == gen && (!tb.pol_group_first || (uint32_t)(v3 & 0xFFFFFFFFull) == gen);
             if (ok) break;
             __builtin_amdgcn_s_sleep(1);
           }
@@ -678,8 +724,7 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
             timed_out = 1;
           } else if (v0 & 0x100ull) {
             const int pg = (int)((uint32_t)(v1 >> 16) & 0xFFFFu);
-            const uint32_t c2 = (uint32_t)((pg * tb.Mmax + slot_model[i]) * B) + (uint32_t)(v0 & 0xffull);
-            held[q] = pack_candidate(__uint_as_float((uint32_t)(v0 >> 32)), c2);
+            held[q] = pack_candidate(__uint_as_float((uint32_t)(v0 >> 32)), pcid(pg, slot_model[i]) | (uint32_t)(v0 & 0xffull));
             held_lat[q] = __uint_as_float((uint32_t)(v1 >> 32));
             held_swap[q] = __uint_as_float((uint32_t)(v2 >> 32));
             const unsigned long long pt = ((unsigned long long)ordered_bits(__uint_as_float((uint32_t)(v3 >> 32))) << 32) |
@@ -695,7 +740,7 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           const uint32_t c2 = 0xFFFFFFFFu - (uint32_t)(held[q] & 0xFFFFFFFFull);
-          if (held[q] == 0ull || (g_star >= 0 && (int)(c2 / (uint32_t)B) / tb.Mmax != g_star)) continue;
+          if (held[q] == 0ull || (g_star >= 0 && pcid_group(c2) != g_star)) continue;
           if (held[q] > mine) { mine = held[q]; mine_lat = held_lat[q]; mine_swap = held_swap[q]; }
         }
         const Best all = wave_best(mine, mine_lat, mine_swap);
@@ -736,8 +781,7 @@ __global__ __launch_bounds__(kRoundThreads, 6) void k_rounds_persistent(Tables t
     const float lat_sel = decided[rl & 1].lat, swap_sel = decided[rl & 1].swap;
     if (cidp1 == 0u) break;                                  // nothing live anywhere
     const uint32_t cid = cidp1 - 1u;
-    const int bsel = (int)(cid % (uint32_t)B) + 1;
-    const int gsel = (int)(cid / (uint32_t)B) / tb.Mmax, msel = (int)(cid / (uint32_t)B) % tb.Mmax;
+    const int bsel = pcid_batch(cid), gsel = pcid_group(cid), msel = pcid_model(cid);
     const bool mine = gsel >= glo && gsel < glo + ng;        // a group of this application
     if (mine && gsel == gprim) {
       shift = bsel;
