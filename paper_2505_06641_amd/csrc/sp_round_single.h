@@ -152,26 +152,10 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
       if (__popcll(__ballot(live)) >= kWave / 2 || scan + kWave >= end) {
         scan = min(scan + kWave, end);
       } else {
-        typedef uint32_t u32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
-        typedef float f32x4_t __attribute__((ext_vector_type(4)));
         int n = 0;
         do {
           const int base = scan & ~3, p0 = base + kSingleScan * lane;
-          uint32_t mask = 0;
-          if (p0 < end) {                              // (both arrays are padded by 16)
-            f32x4_t sd[kSingleScan / 4];
-#pragma unroll
-            for (int q = 0; q < kSingleScan / 4; ++q) sd[q] = *reinterpret_cast<const f32x4_t*>(w.D_s + p0 + 4 * q);
-            const u32x4_dw al = *reinterpret_cast<const u32x4_dw*>(w.alive_s + p0);
-#pragma unroll
-            for (int q = 0; q < kSingleScan / 4; ++q)
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                const int at = p0 + 4 * q + j;
-                const bool ok = ((al[q] >> (8 * j)) & 0xffu) != 0 && !is_dead(kind, sd[q][j], E0) && at >= scan && at < end;
-                mask |= ok ? (1u << (4 * q + j)) : 0u;
-              }
-          }
+          uint32_t mask = live_mask<kSingleScan / 4>(w, kind, E0, p0, scan, end);
           const int cnt = __popc(mask), incl = (int)wave_scan_incl((uint32_t)cnt);
           const int total = n + __builtin_amdgcn_readlane(incl, kWave - 1);
           int rank = n + incl - cnt;

@@ -247,6 +247,39 @@ __device__ __forceinline__ float4 window_entry(const Tables& tb, const Window& w
 __device__ __forceinline__ int n_groups(const Tables& tb, const Window& w) { return tb.pol_split ? *w.grp_n : tb.A; }
 __device__ __forceinline__ int group_app(const Tables& tb, const Window& w, int g) { return tb.pol_split ? w.grp_app[g] : g; }
 
+// Which of the 4 QUADS service positions from p0 on (a multiple of four) are live and inside [head, seg_e): one bit each.  All loads
+// go out before the first is used: one trip to memory (a loop over the quads took four).
+template <int QUADS>
+__device__ __forceinline__ uint32_t live_mask(const Window& w, int kind, double E0, int p0, int head, int seg_e) {
+  uint32_t mask = 0;
+  if (p0 < seg_e) {                                    // (both arrays are padded by 16)
+    typedef uint32_t words __attribute__((ext_vector_type(4), aligned(4)));
+    float4 dv[QUADS];
+    uint32_t alw[4];
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) dv[q] = *reinterpret_cast<const float4*>(w.D_s + p0 + 4 * q);
+    if (QUADS == 4) {
+      const words v = *reinterpret_cast<const words*>(w.alive_s + p0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) alw[q] = v[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < QUADS; ++q) alw[q] = *reinterpret_cast<const uint32_t*>(w.alive_s + p0 + 4 * q);
+    }
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+      const float dd[4] = {dv[q].x, dv[q].y, dv[q].z, dv[q].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int pos = p0 + 4 * q + j;
+        const bool live = ((alw[q] >> (8 * j)) & 0xffu) != 0 && !is_dead(kind, dd[j], E0) && pos >= head && pos < seg_e;
+        mask |= live ? (1u << (4 * q + j)) : 0u;
+      }
+    }
+  }
+  return mask;
+}
+
 __global__ __launch_bounds__(kRoundThreads) void k_round_score(Tables tb, Window w, float* __restrict__ cube_out) {
   __shared__ int32_t win[kMaxBatch];
   __shared__ float4 ent[kMaxBatch];
@@ -287,20 +320,7 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_score(Tables tb, Window
   for (int step = 0; base < seg_e && found < Bw; ++step) {
     const int nq = step == 0 ? 1 : 4;                  // groups of 4 positions per thread
     const int p0 = base + 4 * nq * tid;
-    uint32_t mask = 0;
-    if (p0 < seg_e) {
-      for (int q = 0; q < nq; ++q) {
-        const uint32_t alw = *reinterpret_cast<const uint32_t*>(w.alive_s + p0 + 4 * q);
-        const float4 dv = *reinterpret_cast<const float4*>(w.D_s + p0 + 4 * q);
-        const float dd[4] = {dv.x, dv.y, dv.z, dv.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int pos = p0 + 4 * q + j;
-          const bool live = ((alw >> (8 * j)) & 0xffu) != 0 && !is_dead(kind, dd[j], E0) && pos >= head && pos < seg_e;
-          mask |= live ? (1u << (4 * q + j)) : 0u;
-        }
-      }
-    }
+    const uint32_t mask = nq == 1 ? live_mask<1>(w, kind, E0, p0, head, seg_e) : live_mask<4>(w, kind, E0, p0, head, seg_e);
     // exclusive prefix of the per-thread counts over the workgroup
     const int cnt = __popc(mask);
     const int incl = (int)wave_scan_incl((uint32_t)cnt);

@@ -137,7 +137,7 @@ __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Per
   __syncthreads();
   int r = st->round, next_order = st->next_order, n_sched = st->n_sched;
   double t = st->t, twu = st->total_wu, tu = st->total_u, tv = st->total_viol;
-  bool done = false, failed = false, any = false;
+  bool done = false, failed = false;
   Decision last = st->last;                 // app -1 before the window's first batch
   for (int rl = 0; rl < ps.n_rounds; ++rl) {
     const uint32_t gen = ps.gen_base + (uint32_t)rl + 1u;
@@ -181,7 +181,6 @@ __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Per
     if (__syncthreads_or(lost ? 1 : 0)) { failed = true; break; }
     last.app = a; last.model = m; last.batch = b; last.round = r;
     last.t_start = t; last.t_end = E; last.score = score; last.batch_utility = (float)wu;
-    any = true;
     if (tid == 0) {
       if (r < w.log_cap) w.log[r] = last;
       ps.log_host[rl] = last;
@@ -190,12 +189,16 @@ __device__ void persist_commit_loop(const Tables& tb, const Window& w, const Per
     twu += wu; tu += su; tv += viol;
   }
   if (tid == 0) {
-    st->t = t; st->round = r; st->next_order = next_order; st->n_sched = n_sched;
-    st->total_wu = twu; st->total_u = tu; st->total_viol = tv;
-    if (any) st->last = last;
-    if (done) st->done = 1;
+    // the host reads the pinned copy: nothing is copied behind the kernel.  It is written alongside, not read back from the other
+    // one (a trip to memory at the end of every launch).
+    for (State* s : {st, w.st_host}) {
+      s->t = t; s->round = r; s->next_order = next_order; s->n_sched = n_sched;
+      s->total_wu = twu; s->total_u = tu; s->total_viol = tv;
+      s->last = last;
+      s->done = done ? 1 : 0;
+    }
+    w.st_host->err = 0u;                    // (or this launch would have left at once)
     if (failed) raise_lost(st, ps);
-    mirror_state(w);                        // the host reads this copy: nothing is copied behind the kernel
   }
 }
 
@@ -314,18 +317,7 @@ __device__ __forceinline__ int wave_window(const Window& w, int kind, int head, 
   int found = 0;
   for (int base = head & ~3; base < seg_e && found < Bw; base += 4 * kWave) {
     const int p0 = base + 4 * lane;
-    uint32_t mask = 0;
-    if (p0 < seg_e) {
-      const uint32_t alw = *reinterpret_cast<const uint32_t*>(w.alive_s + p0);
-      const float4 dv = *reinterpret_cast<const float4*>(w.D_s + p0);
-      const float dd[4] = {dv.x, dv.y, dv.z, dv.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int pos = p0 + j;
-        const bool live = ((alw >> (8 * j)) & 0xffu) != 0 && !is_dead(kind, dd[j], E0) && pos >= head && pos < seg_e;
-        mask |= live ? (1u << j) : 0u;
-      }
-    }
+    const uint32_t mask = live_mask<1>(w, kind, E0, p0, head, seg_e);
     const int cnt = __popc(mask);
     const int incl = (int)wave_scan_incl((uint32_t)cnt);
     int rank = found + incl - cnt;
@@ -541,28 +533,15 @@ __global__ __launch_bounds__(kRoundThreads, 2 * WGS) void k_rounds_persistent(Ta
     };
 
     // Walks on through the service order from scan_end and appends the live requests it meets, for at
-    // most max_steps steps of 4 * nq positions per thread, until the window is full or the group's
+    // most max_steps steps of 4 * nq positions per thread, until the list holds `enough` or the group's
     // range ends.  Uniform over the workgroup.
-    auto walk = [&](int max_steps, int first_nq) {
+    auto walk = [&](int max_steps, int first_nq, int enough) {
       const int nb_old = nb;
-      for (int step = 0; step < max_steps && nb < cap && scan_end < seg_e; ++step) {
+      for (int step = 0; step < max_steps && nb < enough && scan_end < seg_e; ++step) {
         const int nq = step == 0 ? first_nq : 4;           // groups of 4 positions per thread
         const int base = scan_end & ~3;
         const int p0 = base + 4 * nq * tid;
-        uint32_t mask = 0;
-        if (p0 < seg_e) {
-          for (int q = 0; q < nq; ++q) {
-            const uint32_t alw = *reinterpret_cast<const uint32_t*>(w.alive_s + p0 + 4 * q);
-            const float4 dv = *reinterpret_cast<const float4*>(w.D_s + p0 + 4 * q);
-            const float dd[4] = {dv.x, dv.y, dv.z, dv.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int pos = p0 + 4 * q + j;
-              const bool live = ((alw >> (8 * j)) & 0xffu) != 0 && !is_dead(kind, dd[j], E0) && pos >= scan_end && pos < seg_e;
-              mask |= live ? (1u << (4 * q + j)) : 0u;
-            }
-          }
-        }
+        const uint32_t mask = nq == 1 ? live_mask<1>(w, kind, E0, p0, scan_end, seg_e) : live_mask<4>(w, kind, E0, p0, scan_end, seg_e);
         const int cnt = __popc(mask);
         const int incl = (int)wave_scan_incl((uint32_t)cnt);
         if (lane == 63) wave_cnt[wave] = incl;
@@ -617,7 +596,7 @@ __global__ __launch_bounds__(kRoundThreads, 2 * WGS) void k_rounds_persistent(Ta
       if (nbe < Bw && (look < nb || scan_end < seg_e)) {           // (uniform) not enough there: the round has to wait for the rest
         in_order = true;
         drop();
-        if (nb < Bw && scan_end < seg_e) walk(1 << 30, 1);
+        if (nb < Bw && scan_end < seg_e) walk(1 << 30, rl == 0 ? 1 : 4, Bw);       // (most requests are live at a window's start)
         nbe = nb;
         for (int j = lane; j < min(nb, Bw); j += kWave) {
           cent[j] = ent[j];
@@ -692,7 +671,7 @@ __global__ __launch_bounds__(kRoundThreads, 2 * WGS) void k_rounds_persistent(Ta
     if (!in_order) drop();
     if (!SPLIT && m == 0 && tid < nbe)
       st_dev(ps.ring + ((size_t)rl * tb.A + a) * B + tid, ((unsigned long long)gen << 32) | (unsigned long long)(uint32_t)win[tid]);
-    if (nb < min(2 * Bw, cap) && scan_end < seg_e) walk(1, 4);
+    if (nb < min(2 * Bw, cap) && scan_end < seg_e) walk(1, 4, cap);
 
     // ---- few pairs: the first wavefront takes the maximum over all pairs' slots (the reducer's rule on the same words), two
     // slots per lane, and passes it on behind one barrier; else its first lane waits for the reducer's decision ----
