@@ -34,6 +34,7 @@ struct sp_ctx {
   Tables tb{};
   Window w{};
   std::vector<void*> dev_allocs;
+  int32_t tiles_in_turn = 0;         // 1: scoring tiles are dealt to the dies in turn (see tile_of)
   int32_t* by_cost = nullptr;        // [A] the applications in the order their scoring tiles are numbered in: costly ones first where that matters
   int A = 0, d = 0, H = 0, B = 0, Mmax = 0, Cmax = 0, dtype = 0;
   int64_t cap = 0;
@@ -262,6 +263,7 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p);
 sp_status ensure_split_buffers(sp_ctx* c);
 const void* single_kernel(int Mmax);
 int score_tile(const sp_ctx* c);
+int64_t score_grid(const sp_ctx* c, int64_t n);
 
 // What a scoring tile of an application of C classes costs, roughly, in units of a class tile: the kernel that walks the classes
 // spends about three on its prologue, heads with a hidden layer about ten on the layer and the prologue; the streaming kernel's
@@ -350,8 +352,8 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
     for (int a = 0; a < A; ++a) v.push_back(a);
     const auto cost = [&](int32_t a) { return tile_cost(c, ncls[a]); };
     const auto [least, most] = std::minmax_element(v.begin() + A, v.end(), [&](int32_t a, int32_t b) { return cost(a) < cost(b); });
-    c->w.tiles_in_turn = 2 * cost(*most) > 3 * cost(*least) ? 1 : 0;
-    if (c->w.tiles_in_turn) std::stable_sort(v.begin() + A, v.end(), [&](int32_t a, int32_t b) { return cost(a) > cost(b); });
+    c->tiles_in_turn = 2 * cost(*most) > 3 * cost(*least) ? 1 : 0;
+    if (c->tiles_in_turn) std::stable_sort(v.begin() + A, v.end(), [&](int32_t a, int32_t b) { return cost(a) > cost(b); });
     int32_t* at;
     if ((s = dev_upload(c, &at, v)) != SP_OK) return s;
     tb.n_classes = at;
@@ -362,9 +364,8 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   const size_t N = (size_t)c->cap;
   Window& w = c->w;
   if ((s = dev_alloc(c, &w.seg, A + 2)) != SP_OK) return s;
-  if ((s = dev_alloc(c, &w.tile_start, A + 1)) != SP_OK) return s;
   if ((s = dev_alloc(c, &w.unit_start, A + 1)) != SP_OK) return s;
-  if ((s = dev_alloc(c, &w.tile_desc, (size_t)c->cap / score_tile(c) + A + 1)) != SP_OK) return s;
+  if ((s = dev_alloc(c, &w.tile_desc, (size_t)score_grid(c, c->cap))) != SP_OK) return s;
   if ((s = dev_alloc(c, &w.ea, N * Mmax)) != SP_OK) return s;
   if ((s = dev_alloc(c, &w.key, N)) != SP_OK) return s;
   if ((s = dev_alloc(c, &w.D_s, N + 16)) != SP_OK) return s;      // +16: the window scan reads whole 16-groups
@@ -607,7 +608,7 @@ template <typename T, bool MLP, bool COLS = false>
 void launch_score_stream(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, const float2* dw, uint32_t* sortkey,
                          float* logits) {
   const int tile = stream_tile(c->stream_nb);
-  const dim3 grid((unsigned)((c->n + tile - 1) / tile + c->A + kXcds)), blk(tile / 32 * kWave);   // see xcd_tile
+  const dim3 grid((unsigned)score_grid(c, c->n)), blk(tile / 32 * kWave);
 #define SP_LAUNCH_ST(NB) \
   hipLaunchKernelGGL((k_score_stream<T, NB, MLP, COLS>), grid, blk, 0, s, c->tb, c->w, (const T*)x, ids, dw, sortkey, c->stream, logits)
   switch (c->stream_nb) {
@@ -859,6 +860,9 @@ int score_tile(const sp_ctx* c) {
   return (c->mfma_D > 0 || c->mlp_bf16) ? kMfTile : (c->stream_nb > 0 ? stream_tile(c->stream_nb) : kScoreTile);
 }
 
+// Workgroups of a scoring launch: at least 8 * ceil(tiles / 8), see xcd_tile.
+int64_t score_grid(const sp_ctx* c, int64_t n) { return (n + score_tile(c) - 1) / score_tile(c) + c->A + kXcds; }
+
 // Address of the static scratch array on `device` (which must be current), looked up once per device.
 sp_status static_scratch_for(sp_ctx* c, int device, unsigned char** out) {
   if (device < 0 || device >= kStaticMaxDevices) return SP_ECAPACITY;
@@ -878,7 +882,7 @@ constexpr size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 void launch_score(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, const float2* dw, uint32_t* sortkey,
                   float* logits) {
   if (c->mlp_bf16) {
-    const int grid = (c->n + kMfTile - 1) / kMfTile + c->A + kXcds;   // at least 8 * ceil(tiles / 8): see xcd_tile
+    const int grid = (int)score_grid(c, c->n);
 #define SP_LAUNCH_MLP(DUMP, SPLIT)                                                                                \
     hipLaunchKernelGGL((k_score_mlp_bf16<DUMP, SPLIT>), dim3(grid), dim3(kMfThreads), 0, s, c->tb, c->w,          \
                        (const uint16_t*)x, ids, dw, sortkey, (const unsigned char*)c->w1p,                       \
@@ -891,7 +895,7 @@ void launch_score(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, c
     return;
   }
   if (c->mfma_D > 0) {
-    const int grid = (c->n + kMfTile - 1) / kMfTile + c->A + kXcds;   // at least 8 * ceil(tiles / 8): see xcd_tile
+    const int grid = (int)score_grid(c, c->n);
     const dim3 blk(kMfThreads);
 #define SP_LAUNCH_MF(DD)                                                                                          \
     do {                                                                                                          \
@@ -932,7 +936,7 @@ void launch_score(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, c
     }
     return;
   }
-  const int grid = (c->n + kScoreTile - 1) / kScoreTile + c->A;
+  const int grid = (int)score_grid(c, c->n);
   if (c->dtype == SP_BF16)
     launch_score_generic<uint16_t>(c, s, grid, x, ids, dw, sortkey, logits);
   else
@@ -963,7 +967,8 @@ int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev,
                         const float* weight_dev) {
   const int A = c->A;
   Window& w = c->w;
-  SegArgs seg_args{n, A, nullptr, score_tile(c), n <= kMergeMax ? kRun : kSortTile, c->by_cost, w.seg, w.tile_start, w.unit_start, w.tile_desc, c->sort_desc};
+  SegArgs seg_args{n, A, nullptr, score_tile(c), n <= kMergeMax ? kRun : kSortTile, c->by_cost, c->tiles_in_turn, (int32_t)score_grid(c, n), w.seg,
+                   w.unit_start, w.tile_desc, c->sort_desc};
   // a long window's ordering needs its digit totals cleared
   uint32_t* zero = n > kMergeMax ? c->dtot_key : nullptr;
   const int64_t zero_words = (int64_t)kMaxSortPasses * c->tiles_cap * 256;

@@ -76,9 +76,8 @@ struct State {
 struct Window {
   int32_t n;
   int32_t* seg;               // [A+2] start of each app's range in service order; seg[A] = #valid, seg[A+1] = n
-  int32_t* tile_start;        // [A+1] prefix of scoring tiles over the applications in the order their tiles are numbered in
-  int32_t tiles_in_turn;      // 1: the tiles are dealt to the dies in turn (see tile_of)
-  int4* tile_desc;            // per scoring tile: (application, first position, end of the application's range, 0)
+  int4* tile_desc;            // per workgroup of the scoring launch: its tile's (application, first position, end of the application's
+                              // range, 0); application -1 without a tile
   int32_t* unit_start;        // [A+1] prefix of sort units
   float* ea;                  // [n, Mmax]
   float* key;                 // [n]
@@ -124,14 +123,20 @@ __device__ __forceinline__ int xcd_tile(int wg, int n_tiles) {
   return (j < per && tile < n_tiles) ? tile : -1;
 }
 
-// The scoring tile a workgroup takes.  Where the applications' tiles cost about the same, every die gets a contiguous eighth of
+// The scoring tile a workgroup takes (the scoring kernels find its descriptor under their own number: a trip to memory less than
+// looking up the number of tiles first).  Where the applications' tiles cost about the same, every die gets a contiguous eighth of
 // them.  Where they differ (tile_cost), an eighth of the tiles is no eighth of the work (the dies' shares were 3,168 to
 // 99 class tiles for 200,003 requests of twelve applications of 2 to 1,000 classes, most of the chip idle at the end): the tiles
 // are then numbered from the most class tiles to the fewest and dealt to the dies in turn, so that every die gets an eighth of
 // every application and the small tiles fill the end.  Weights are then pulled into every die's L2.
-__device__ __forceinline__ int tile_of(const Window& w, int wg, int n_tiles) {
-  if (w.tiles_in_turn) return wg < n_tiles ? wg : -1;
+__device__ __forceinline__ int tile_of(bool in_turn, int wg, int n_tiles) {
+  if (in_turn) return wg < n_tiles ? wg : -1;
   return xcd_tile(wg, n_tiles);
+}
+// The workgroup that takes a tile.
+__device__ __forceinline__ int workgroup_of(bool in_turn, int tile, int n_tiles) {
+  const int per = (n_tiles + kXcds - 1) / kXcds;
+  return in_turn ? tile : tile % per * kXcds + tile / per;
 }
 
 // Keeps a value's load where it stands: everything a kernel can ask for at its start then shares one trip to memory (about

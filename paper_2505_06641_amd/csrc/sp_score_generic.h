@@ -78,9 +78,8 @@ __global__ __launch_bounds__(kScoreWaves* kWave) void k_score_generic(
   constexpr int RW = kScoreRW;
   extern __shared__ float lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tile = blockIdx.x;
-  if (tile >= w.tile_start[tb.A]) return;
-  const int4 desc = w.tile_desc[tile];
+  const int4 desc = w.tile_desc[blockIdx.x];
+  if (desc.x < 0) return;
   const int a = desc.x, seg_e = desc.z;
   const int p0 = desc.y + wave * RW;                                           // first service position of this wave
   const int nr = min(RW, seg_e - p0);                                          // may be <= 0

@@ -173,14 +173,14 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
   using I = StreamIn<T>;
   using SG = StreamStage<NB, MLP>;
   constexpr int S = I::kSteps, CH = I::kChunk, D = 32 * NB;
+  constexpr int kTurns = I::kF32 ? 3 : 2;                // matrix instructions per block and half of a slice
   static_assert(!COLS || I::kF32, "bfloat16 features are not scaled");
   __shared__ f32x4 buf[2][SG::kUnits];
   __shared__ f32x4 cols[COLS ? kStreamMaxD / 4 : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
-  const int tile = tile_of(w, blockIdx.x, __builtin_amdgcn_readfirstlane(w.tile_start[tb.A]));
-  if (tile < 0) return;
-  const int4 desc = w.tile_desc[tile];
+  const int4 desc = w.tile_desc[blockIdx.x];
+  if (desc.x < 0) return;
   // (uniform, which the compiler cannot know of a load: tables and stages are then addressed from scalar registers)
   const int a = __builtin_amdgcn_readfirstlane(desc.x), seg_e = __builtin_amdgcn_readfirstlane(desc.z);
   const int pos = desc.y + wave * 32 + r;
@@ -264,26 +264,63 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[hb][v] = 0.f;
 
-    // the running slice's weight fragments, kFrags per block of 32 rows, read one block ahead of the MFMAs that take
-    // them (not with eight blocks: the registers are needed for the accumulators)
+    // The running slice's weight fragments, kFrags per block of 32 rows.  Two blocks run side by side: a matrix instruction that
+    // takes the result of the one before can issue every 52 cycles only, an independent one every 32 (and the sums of one block
+    // would wait for its last instruction with nothing to fill the time).  The fragments of half of a pair's steps are read ahead of the
+    // instructions that take those of the other half.  With eight blocks the registers are needed for the accumulators: block by
+    // block there.
     constexpr int kFrags = S * I::kParts;
     static_assert(kFrags == 4, "one block of a slice is four fragments for either type");
-    constexpr bool kAhead = NB < 8;
-    auto blocks = [&](auto mfmas) {
+    auto blocks = [&](auto mfma /* (half of the steps, two fragments, sums) */) {
       const f32x4* cur = buf[st & 1] + lane;
-      f32x4 wf[2][kFrags];
-      auto read = [&](int hb) {
+      if constexpr (NB == 1 || NB == 8) {
+        f32x4 wf[kFrags];
 #pragma unroll
-        for (int i = 0; i < kFrags; ++i) wf[kAhead ? hb & 1 : 0][i] = cur[(hb * kFrags + i) * 64];
-      };
-      if (kAhead) read(0);
+        for (int hb = 0; hb < NB; ++hb) {
 #pragma unroll
-      for (int hb = 0; hb < NB; ++hb) {
-        if (!kAhead) read(hb);
-        else if (hb + 1 < NB) read(hb + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (hb < nbk) mfmas(hb, wf[kAhead ? hb & 1 : 0]);
-        __builtin_amdgcn_sched_barrier(0);
+          for (int i = 0; i < kFrags; ++i) wf[i] = cur[(hb * kFrags + i) * 64];
+          __builtin_amdgcn_sched_barrier(0);
+          if (hb < nbk) {
+            f32x16 part;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) part[v] = 0.f;
+#pragma unroll
+            for (int i = 0; i < kFrags / 2 * kTurns; ++i) mfma(i / kTurns, i % kTurns, wf[2 * (i / kTurns)], wf[2 * (i / kTurns) + 1], part);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[hb][v] += part[v];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+        f32x4 wf[2][kFrags];                                       // fragments of either block: 2 * block + i
+        auto read = [&](int u) {                                   // half u of the slice: pair u / 2, its steps' half u % 2
+#pragma unroll
+          for (int i = 0; i < kFrags; ++i) wf[u & 1][i] = cur[((2 * (u >> 1) + (i >> 1)) * kFrags + 2 * (u & 1) + (i & 1)) * 64];
+        };
+        read(0);
+#pragma unroll
+        for (int p = 0; p < NB / 2; ++p) {
+          if (2 * p >= nbk) continue;                              // (a last block that holds nothing keeps its neighbour company)
+          f32x16 part[2];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) part[0][v] = part[1][v] = 0.f;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int u = 2 * p + h;
+            if (u + 1 < NB) read(u + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < kTurns; ++i) {
+              mfma(h, i, wf[u & 1][0], wf[u & 1][1], part[0]);
+              mfma(h, i, wf[u & 1][2], wf[u & 1][3], part[1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[2 * p][v] += part[0][v];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[2 * p + 1][v] += part[1][v];
+        }
       }
     };
     // one step: stage st + 1 and the features of step kc + 2 start, the MFMAs of step kc run, stage st + 1 is stored.
@@ -329,19 +366,9 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
       __builtin_amdgcn_sched_barrier(0);
       load_x(xs, kc + 2);
       __builtin_amdgcn_sched_barrier(0);
-      blocks([&](int hb, const f32x4 (&wf)[kFrags]) {
-        f32x16 part;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) part[v] = 0.f;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-          const f16x8 wh = __builtin_bit_cast(f16x8, wf[(2 * s) % kFrags]), wl = __builtin_bit_cast(f16x8, wf[(2 * s + 1) % kFrags]);
-          part = __builtin_amdgcn_mfma_f32_32x32x16_f16(wl, xh[s], part, 0, 0, 0);
-          part = __builtin_amdgcn_mfma_f32_32x32x16_f16(wh, xl[s], part, 0, 0, 0);
-          part = __builtin_amdgcn_mfma_f32_32x32x16_f16(wh, xh[s], part, 0, 0, 0);
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[hb][v] += part[v];
+      blocks([&](int half, int turn, const f32x4& whf, const f32x4& wlf, f32x16& part) {
+        const f16x8 wh = __builtin_bit_cast(f16x8, whf), wl = __builtin_bit_cast(f16x8, wlf);
+        part = __builtin_amdgcn_mfma_f32_32x32x16_f16(turn == 0 ? wl : wh, turn == 1 ? xl[half] : xh[half], part, 0, 0, 0);
       });
       park(st + 1);
       __syncthreads();
@@ -355,15 +382,8 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
       for (int q = 0; q < 4; ++q) xc[q] = as_bf16x8(xs[q]);
       load_x(xs, kc + 2);
       __builtin_amdgcn_sched_barrier(0);
-      blocks([&](int hb, const f32x4 (&wf)[kFrags]) {
-        f32x16 part;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) part[v] = 0.f;
-#pragma unroll
-        for (int s = 0; s < kFrags; ++s)
-          part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(wf[s]), xc[s], part, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[hb][v] += part[v];
+      blocks([&](int half, int turn, const f32x4& w0, const f32x4& w1, f32x16& part) {
+        part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(turn == 0 ? w0 : w1), xc[2 * half + turn], part, 0, 0, 0);
       });
       park(st + 1);
       __syncthreads();

@@ -103,8 +103,8 @@ struct SegArgs {
   const uint32_t* sorted_app;   // application-sorted keys (not used where the counts of the ids are given)
   int32_t tile, unit;           // requests per scoring tile and per sort run
   const int32_t* by_cost;       // [A]
+  int32_t in_turn, grid;        // how the tiles are dealt, and to how many workgroups (see tile_of)
   int32_t* seg;
-  int32_t* tile_start;
   int32_t* unit_start;
   int4* tile_desc;
   int4* sort_desc;
@@ -131,9 +131,15 @@ __device__ __forceinline__ int range_of(const int* start, int n, int i) {
 // The descriptors of all tiles and runs from the tables in LDS, by `threads` threads.
 __device__ __forceinline__ void write_descriptors(const SegArgs& g, const int* s_tile, const int* s_unit, const int* s_seg, const int* s_app,
                                                   int tid, int threads) {
-  for (int t = tid; t < s_tile[g.A]; t += threads) {                // (application, first request, end of its range, 0)
-    const int k = range_of(s_tile, g.A, t), a = s_app[k];
-    g.tile_desc[t] = make_int4(a, s_seg[a] + (t - s_tile[k]) * g.tile, s_seg[a + 1], 0);
+  const int n_tiles = s_tile[g.A];
+  for (int wg = tid; wg < g.grid; wg += threads) {                  // (application, first request, end of its range, 0)
+    const int t = tile_of(g.in_turn, wg, n_tiles);
+    int4 d = make_int4(-1, 0, 0, 0);
+    if (t >= 0) {
+      const int k = range_of(s_tile, g.A, t), a = s_app[k];
+      d = make_int4(a, s_seg[a] + (t - s_tile[k]) * g.tile, s_seg[a + 1], 0);
+    }
+    g.tile_desc[wg] = d;
   }
   for (int u = tid; u < s_unit[g.A]; u += threads) {                // (start of the application, first element, end, 0)
     const int a = range_of(s_unit, g.A, u);
@@ -192,7 +198,6 @@ __global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) {
   us = us0;
   for (int k = a_lo; k < a_hi; ++k) {
     const int c = g.by_cost[k];
-    g.tile_start[k] = ts;
     g.unit_start[k] = us;
     if (table) {
       s_tile[k] = ts;
@@ -204,7 +209,6 @@ __global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) {
     us += (seg[k + 1] - seg[k] + unit - 1) / unit;
   }
   if (tid == 255) {
-    g.tile_start[A] = run_t[255];
     g.unit_start[A] = run_u[255];
     if (table) {
       s_tile[A] = run_t[255];
@@ -221,11 +225,13 @@ __global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) {
     for (int k = a_lo; k < a_hi; ++k) {
       const int c = g.by_cost[k], cb = seg[c], ce = seg[c + 1], nt = (ce - cb + tile - 1) / tile;
       const int sb = seg[k], se = seg[k + 1], nu = (se - sb + unit - 1) / unit;
-      for (int t = 0; t < nt; ++t) g.tile_desc[ts + t] = make_int4(c, cb + t * tile, ce, 0);
+      for (int t = 0; t < nt; ++t) g.tile_desc[workgroup_of(g.in_turn, ts + t, run_t[255])] = make_int4(c, cb + t * tile, ce, 0);
       for (int u = 0; u < nu; ++u) g.sort_desc[us + u] = make_int4(sb, sb + u * unit, se, 0);
       ts += nt;
       us += nu;
     }
+    for (int wg = tid; wg < g.grid; wg += 256)
+      if (tile_of(g.in_turn, wg, run_t[255]) < 0) g.tile_desc[wg] = make_int4(-1, 0, 0, 0);
   }
 }
 
@@ -594,7 +600,6 @@ __device__ __forceinline__ void segments_from_totals(const SegArgs& g, const Win
     if (tid <= A) {
       s_tile[tid] = ti - ts;
       s_unit[tid] = ui - us;
-      g.tile_start[tid] = ti - ts;
       g.unit_start[tid] = ui - us;
     }
   }
