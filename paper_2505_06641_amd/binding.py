@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from typing import Optional
 
 import numpy as np
@@ -48,7 +49,19 @@ class sp_decision(C.Structure):
                 ("score", C.c_float), ("batch_utility", C.c_float)]
 
     def as_dict(self):
-        return {k: getattr(self, k) for k, _ in self._fields_}
+        return dict(zip(_DECISION_KEYS, _DECISION.unpack_from(self)))
+
+    @staticmethod
+    def dicts(array, n):
+        """The first n of an array of decisions (all fields of one at once: 0.4 us each instead of 2)."""
+        if n == 0:
+            return []
+        return [dict(zip(_DECISION_KEYS, v)) for v in _DECISION.iter_unpack(memoryview(array).cast("B")[:n * _DECISION.size])]
+
+
+_DECISION = struct.Struct("=4i2d2f")                      # sp_decision: no padding between its fields
+_DECISION_KEYS = [k for k, _ in sp_decision._fields_]
+assert _DECISION.size == C.sizeof(sp_decision)
 
 
 class sp_summary(C.Structure):
@@ -57,7 +70,12 @@ class sp_summary(C.Structure):
                 ("n_dropped", C.c_int32), ("done", C.c_int32)]
 
     def as_dict(self):
-        return {k: getattr(self, k) for k, _ in self._fields_}
+        return dict(zip(_SUMMARY_KEYS, _SUMMARY.unpack_from(self)))
+
+
+_SUMMARY = struct.Struct("=3d4i")
+_SUMMARY_KEYS = [k for k, _ in sp_summary._fields_]
+assert _SUMMARY.size == C.sizeof(sp_summary)
 
 
 class sp_timing(C.Structure):
@@ -189,14 +207,31 @@ def marshal_profile(profile, max_requests: int):
 
 
 def _dptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream_ptr(stream):
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    """The stream's handle; by default that of the current device's current stream."""
+    return _current_stream() if stream is None else stream.cuda_stream
+
+
+def _find_current_stream():
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+
+    def current():                            # (a handle without a stream object around it: 0.2 us instead of 2)
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return raw(device())
+    return current
+
+
+def _current_stream():
+    global _current_stream
+    _current_stream = _find_current_stream()
+    return _current_stream()
 
 
 class Context:
@@ -276,7 +311,7 @@ class Context:
                                   _dptr(order_out), _dptr(util_out), log, int(log_capacity), C.byref(sm))
         self._check(rc, "sp_schedule", ok=(SP_OK, SP_DONE))
         n_log = min(sm.n_rounds, log_capacity)
-        return rc, sm.as_dict(), [log[i].as_dict() for i in range(n_log)]
+        return rc, sm.as_dict(), sp_decision.dicts(log, n_log)
 
     def sp_set_prior(self, app, alpha, evidence_k):
         """alpha: host array of C_a floats, or None to remove the application's prior."""
