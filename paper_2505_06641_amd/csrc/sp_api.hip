@@ -1066,8 +1066,7 @@ const uint32_t* order_requests(sp_ctx* c, hipStream_t s, int n, uint32_t* sortke
   merge_plan(n, levels, ways);
   SortedRun from{sortkey, c->bufV[2], c->bufL[1]}, to{spare_key, c->bufV[1], c->bufL[0]};
 #define SP_RUNS(SPLIT, LAST)                                                                                     \
-  hipLaunchKernelGGL((k_sort_runs<SPLIT, LAST>), dim3(grid), dim3(kRunThreads), 0, s, plan, from, to,            \
-                     (const int32_t*)w.sub_g, c->sub_passes, n, w, edf)
+  hipLaunchKernelGGL((k_sort_runs<SPLIT, LAST>), dim3(grid), dim3(kRun), 0, s, plan, from, to, (const int32_t*)w.sub_g, n, w, edf)
 #define SP_MERGE(SPLIT, LAST)                                                                                    \
   hipLaunchKernelGGL((k_merge_runs<SPLIT, LAST>), dim3(grid * kRunItems), dim3(kRunThreads), 0, s, plan, from, to, len, ways, n, w, edf)
   bool last = levels == 0;

@@ -704,11 +704,10 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
 
 // ---- ordering inside the applications ----
 
-// Requests per run.  Short runs spread even a small window over the chip: with 4,096 a run took 19 us to sort and the first
-// merge of two runs 10; with 1,024 sorting takes 6 and a merge of up to sixteen runs 6 to 8.
+// Requests per run.  Short runs spread even a small window over the chip: with 4,096 a run took 19 us to sort (by radix passes) and
+// the first merge of two runs 10; with 1,024 sorting takes 7 and a merge of up to sixteen runs 6 to 8.
 constexpr int kRun = 1024;
-constexpr int kRunThreads = 256;
-constexpr int kRunWaves = kRunThreads / kWave;
+constexpr int kRunThreads = 256;                       // (of a merge: four workgroups for a run's length)
 constexpr int kRunItems = kRun / kRunThreads;
 constexpr int kMergeWays = 16;                         // most runs merged at a time
 constexpr int kMergeMax = 262144;                      // longest window that is ordered this way (see the top of this file)
@@ -764,131 +763,84 @@ __device__ __forceinline__ void finish_position(const Window& w, int at, uint32_
 }
 
 // The last launch also resets the per-request outputs (by request id) and what lies behind the valid requests.
-template <int ITEMS>
+template <int THREADS>
 __device__ __forceinline__ void finish_rest(const Window& w, int n, int n_valid_at, const int32_t* __restrict__ seg) {
-  const int nv = seg[n_valid_at];
-#pragma unroll
-  for (int c = 0; c < ITEMS; ++c) {
-    const int i = (blockIdx.x * ITEMS + c) * kRunThreads + threadIdx.x;
-    if (i >= n) break;
-    if (i >= nv) w.alive_s[i] = 0;
-    w.model[i] = -1;
-    w.round_of[i] = -1;
-    w.order_of[i] = 0;
-    w.util[i] = 0.f;
-  }
+  const int nv = seg[n_valid_at], i = blockIdx.x * THREADS + threadIdx.x;
+  if (i >= n) return;
+  if (i >= nv) w.alive_s[i] = 0;
+  w.model[i] = -1;
+  w.round_of[i] = -1;
+  w.order_of[i] = 0;
+  w.util[i] = 0.f;
 }
 
-// Mask of lanes whose 8-bit digit equals mine: per bit one vote and, on either half of the mask, one three-input operation.
-__device__ __forceinline__ void match_byte(uint32_t digit, bool valid, uint32_t& lo, uint32_t& hi) {
-  const unsigned long long m = __ballot(valid);
-  lo = (uint32_t)m;
-  hi = (uint32_t)(m >> 32);
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const uint32_t mine = (uint32_t)((int32_t)(digit << (31 - b)) >> 31);      // all ones where my bit is set
-    const unsigned long long vote = __ballot(mine != 0u);
-    lo &= ~((uint32_t)vote ^ mine);
-    hi &= ~((uint32_t)(vote >> 32) ^ mine);
-  }
+// The value of lane ^ J, without LDS: quad permutes, a mirrored half row and a reversed quad, a row turned by eight, swapped rows
+// and halves.
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v, int lane) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  if (J == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false);
+  if (J == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false);
+  if (J == 4) return (uint32_t)__builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false), 0x1B, 0xf, 0xf, false);
+  if (J == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false);
+  const u32x2 sw = J == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return (lane & J) ? sw[0] : sw[1];
+}
+// The steps of a bitonic stage inside a wavefront, from distance J down: ascending where `up`.
+template <int J>
+__device__ __forceinline__ void bitonic_steps(unsigned long long& v, bool up, int lane) {
+  const unsigned long long p = ((unsigned long long)lane_xor<J>((uint32_t)(v >> 32), lane) << 32) | (unsigned long long)lane_xor<J>((uint32_t)v, lane);
+  v = (p < v) == (((lane & J) == 0) == up) ? p : v;
+  if constexpr (J > 1) bitonic_steps<J / 2>(v, up, lane);
 }
 
-// Sorts one run in LDS: stable radix passes of 8 bits, elements in registers between the passes (a wavefront holds four
-// chunks of 64 consecutive elements), counts per wavefront scanned over wavefronts and digits by one thread per digit.
-// Bound by the latency of its four barriers and LDS round trips per pass.
+// Sorts one run by one element per thread: a bitonic network over (label, key, place in the run) packed into 58 bits, so that
+// no two are equal and the order is stable.  The 45 steps between lanes of a wavefront (of 55 for a full run) take no LDS and no barrier, the
+// others one of each; runs of fewer elements take the stages they need.  Bound by about eight vector instructions a step with four
+// wavefronts per SIMD: 6.8 us for full runs, 4.0 for 256 elements, 7.2 with subgroups; 8.0, 8.2 and 10.2 with stable passes of 8 bits
+// through LDS (four barriers each); 8.4, 6.3 and 8.9 with four elements per thread in four wavefronts, one to a SIMD.
 template <bool SPLIT, bool FINISH>
-__global__ __launch_bounds__(kRunThreads) void k_sort_runs(SortPlan sp, SortedRun in, SortedRun out, const int32_t* __restrict__ sub_g,
-                                                           int sub_passes, int n, Window w, int edf) {
-  static_assert(kRunThreads == 256 && kRunWaves == 4 && kRunItems == 4, "one thread per digit, four wavefronts of four chunks");
-  __shared__ unsigned long long buf[kRun];                     // key << 32 | element, in sorted order
-  __shared__ uint32_t lab[SPLIT ? kRun : 1];
-  __shared__ __align__(16) uint32_t cnt[kRunWaves][256];
-  __shared__ uint32_t wave_tot[kRunWaves];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (FINISH) finish_rest<kRunItems>(w, n, sp.nseg, sp.seg);
+__global__ __launch_bounds__(kRun) void k_sort_runs(SortPlan sp, SortedRun in, SortedRun out, const int32_t* __restrict__ sub_g, int n,
+                                                    Window w, int edf) {
+  static_assert(kRun == 1024, "ten bits of place, one element per thread");
+  __shared__ unsigned long long exchange[2][kRun];
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (FINISH) finish_rest<kRun>(w, n, sp.nseg, sp.seg);
   int s0, beg, end, se;
   if (!my_run<1>(sp, s0, beg, end, se)) return;
   const int len = end - beg;
-  uint32_t key[kRunItems], lb[kRunItems];
-  int32_t val[kRunItems];
-#pragma unroll
-  for (int c = 0; c < kRunItems; ++c) {
-    const int e = (wave * kRunItems + c) * 64 + lane;
-    key[c] = e < len ? in.key[beg + e] : 0u;
-    lb[c] = SPLIT && e < len ? (uint32_t)sub_g[beg + e] : 0u;
-    val[c] = beg + e;
+  unsigned long long v = ~0ull;                                // behind everything (labels have 16 bits: 65,536 slots)
+  if (tid < len) {
+    v = ((unsigned long long)in.key[beg + tid] << 10) | (unsigned long long)tid;
+    if (SPLIT) v |= (unsigned long long)(uint32_t)sub_g[beg + tid] << 42;
   }
-  const int n_pass = 4 + (SPLIT ? sub_passes : 0);
-  for (int p = 0; p < n_pass; ++p) {
-    const int shift = 8 * (p & 3);
-    // (a wavefront's own row of counts, which its own LDS operations reach in order)
-    *reinterpret_cast<uint4*>(&cnt[wave][4 * lane]) = make_uint4(0u, 0u, 0u, 0u);
-    wave_sync();
-    uint32_t dg[kRunItems], lo[kRunItems], hi[kRunItems], ahead[kRunItems];
-#pragma unroll
-    for (int c = 0; c < kRunItems; ++c) {
-      const bool valid = (wave * kRunItems + c) * 64 + lane < len;
-      dg[c] = ((SPLIT && p >= 4 ? lb[c] : key[c]) >> shift) & 255u;
-      match_byte(dg[c], valid, lo[c], hi[c]);
-      const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi[c], __builtin_amdgcn_mbcnt_lo(lo[c], 0u));
-      ahead[c] = before;
-      if (valid && before == 0u) ahead[c] = atomicAdd(&cnt[wave][dg[c]], (uint32_t)(__popc(lo[c]) + __popc(hi[c])));
+  bitonic_steps<1>(v, (tid & 2) == 0, lane);
+  bitonic_steps<2>(v, (tid & 4) == 0, lane);
+  bitonic_steps<4>(v, (tid & 8) == 0, lane);
+  bitonic_steps<8>(v, (tid & 16) == 0, lane);
+  bitonic_steps<16>(v, (tid & 32) == 0, lane);
+  bitonic_steps<32>(v, (tid & 64) == 0, lane);
+  int turn = 0;
+  for (int k = 128; k / 2 < len; k *= 2) {                     // (uniform)
+    const bool up = (tid & k) == 0;
+    for (int j = k / 2; j >= 64; j /= 2) {
+      exchange[turn][tid] = v;
+      __syncthreads();
+      const unsigned long long p = exchange[turn][tid ^ j];
+      v = (p < v) == (((tid & j) == 0) == up) ? p : v;
+      turn ^= 1;                                               // (read until the next step's barrier)
     }
-#pragma unroll
-    for (int c = 0; c < kRunItems; ++c) {
-      // the first lane of each digit holds the wavefront's earlier elements of it
-      const int leader = lo[c] ? __ffs((int)lo[c]) - 1 : (hi[c] ? 31 + __ffs((int)hi[c]) : lane);
-      const uint32_t base = __shfl(ahead[c], leader);
-      ahead[c] = leader == lane ? base : base + ahead[c];
-    }
-    __syncthreads();
-    uint32_t c4[kRunWaves], all = 0;
-#pragma unroll
-    for (int v = 0; v < kRunWaves; ++v) {
-      c4[v] = all;
-      all += cnt[v][tid];
-    }
-    const uint32_t incl = wave_scan_incl(all);
-    if (lane == 63) wave_tot[wave] = incl;
-    __syncthreads();
-    uint32_t start = incl - all;
-#pragma unroll
-    for (int v = 0; v < kRunWaves; ++v) start += v < wave ? wave_tot[v] : 0u;
-#pragma unroll
-    for (int v = 0; v < kRunWaves; ++v) cnt[v][tid] = start + c4[v];
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < kRunItems; ++c) {
-      if ((wave * kRunItems + c) * 64 + lane < len) {
-        const uint32_t at = cnt[wave][dg[c]] + ahead[c];
-        buf[at] = ((unsigned long long)key[c] << 32) | (unsigned long long)(uint32_t)val[c];
-        if (SPLIT) lab[at] = lb[c];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < kRunItems; ++c) {
-      const int e = (wave * kRunItems + c) * 64 + lane;
-      if (e < len) {
-        const unsigned long long kv = buf[e];
-        key[c] = (uint32_t)(kv >> 32);
-        val[c] = (int32_t)(uint32_t)kv;
-        if (SPLIT) lb[c] = lab[e];
-      }
-    }
+    bitonic_steps<32>(v, up, lane);
   }
-#pragma unroll
-  for (int c = 0; c < kRunItems; ++c) {
-    const int e = (wave * kRunItems + c) * 64 + lane;
-    if (e < len) {
-      if (SPLIT) out.label[beg + e] = lb[c];
-      if (FINISH) {
-        finish_position(w, beg + e, key[c], val[c], edf);
-      } else {
-        out.key[beg + e] = key[c];
-        out.pos[beg + e] = val[c];
-      }
-    }
+  if (tid >= len) return;
+  const uint32_t key = (uint32_t)(v >> 10);
+  const int32_t pos = beg + (int)(v & 1023u);
+  if (SPLIT) out.label[beg + tid] = (uint32_t)(v >> 42);
+  if (FINISH) {
+    finish_position(w, beg + tid, key, pos, edf);
+  } else {
+    out.key[beg + tid] = key;
+    out.pos[beg + tid] = pos;
   }
 }
 
@@ -910,7 +862,7 @@ __global__ __launch_bounds__(kRunThreads) void k_merge_runs(SortPlan sp, SortedR
   __shared__ int n_active;
   __shared__ uint32_t whole;                                   // elements of chunks that lie wholly before
   const int tid = threadIdx.x;
-  if (FINISH) finish_rest<1>(w, n, sp.nseg, sp.seg);
+  if (FINISH) finish_rest<kRunThreads>(w, n, sp.nseg, sp.seg);
   int s0, beg, end, se;
   if (!my_run<kRunItems>(sp, s0, beg, end, se)) return;
   const int na = se - s0, len = end - beg, o = beg - s0;
@@ -1023,7 +975,7 @@ __global__ void k_gather_sub_keys(int n_valid_at, const int32_t* __restrict__ se
 // After the last pass: positions of the application-grouped array travelled as values.
 __global__ void k_finish_order(int n, int n_valid_at, const int32_t* __restrict__ seg, const int32_t* __restrict__ grouped_pos,
                                const uint32_t* __restrict__ sorted_keys, Window w, int edf) {
-  finish_rest<1>(w, n, n_valid_at, seg);
+  finish_rest<kRunThreads>(w, n, n_valid_at, seg);
   if (w.st->err & kErrSortSync) return;                // (the passes have left positions unwritten)
   const int pos = blockIdx.x * kRunThreads + threadIdx.x;
   if (pos < seg[n_valid_at]) finish_position(w, pos, sorted_keys[pos], grouped_pos[pos], edf);
