@@ -487,8 +487,10 @@ __global__ __launch_bounds__(kRoundThreads, 2 * WGS) void k_rounds_persistent(Ta
         }
         wave_sync();
         if (lane == 0) evals += triangle_evals(nbs, tb.pol_whole);
-        unsigned long long cand = triangle_best(scoring_penalty(tb, kind), went, lat_s, nbs, Bw, t + (double)swap_now,
-                                                pcid(g, m), nullptr, tb.pol_whole ? nbs : 0, kWave, lane);
+        const int only_b = tb.pol_whole ? nbs : 0;
+        unsigned long long cand = nbs <= 16 && pair_lanes(Bw) == 16
+            ? triangle_few(scoring_penalty(tb, kind), went, lat_s, nbs, t + (double)swap_now, pcid(g, m), only_b, lane)
+            : triangle_best(scoring_penalty(tb, kind), went, lat_s, nbs, Bw, t + (double)swap_now, pcid(g, m), nullptr, only_b, kWave, lane);
         cand = wave_max_packed(cand);
         if (tb.pol_group_first) {
           // eq. (14) over the window: the fixed-order sum a single wavefront forms in k_round_score

@@ -1498,3 +1498,48 @@ def test_one_scheduled_round_fills_the_outputs(gpu, n):
     """sp_schedule of one round: the outputs of the requests it does not serve, below and beyond what its kernel fills itself."""
     w = wl.tiny(seed=9200 + n, n=n, classes=(4, 2), models=(3, 2), max_batch=16, feat_dim=16, deadline=(20.0, 90.0))
     full_parity(gpu, w, max_rounds=1)
+
+
+@pytest.mark.parametrize("B,sizes", [(40, (300, 16, 17, 15, 1, 40, 2)), (64, (16, 17, 64, 9, 200)), (65, (16, 17, 8, 100))],
+                         ids=["B40", "B64", "B65"])
+def test_subgroups_of_a_few_requests(gpu, B, sizes):
+    """Secondary subgroups around the sixteen requests up to which batch sizes are evaluated four at a time."""
+    C, n = len(sizes), sum(sizes)
+    w = wl.tiny(seed=9300 + B, n=n, classes=(C,), models=(3,), max_batch=B, feat_dim=16, deadline=(20.0, 500.0), fractions=(1.0,))
+    lab = np.random.default_rng(9301).permutation(np.repeat(np.arange(C), sizes))
+    w.requests.x[:] = 0.0
+    w.requests.x[np.arange(n), lab] = 1.0
+    w.profile.W1[0] = np.zeros((16, C), dtype=np.float32)
+    w.profile.W1[0][np.arange(C), np.arange(C)] = 8.0
+    policy = wl.named_policy("sneakpeek")
+    policy.split_groups = 1
+    full_parity(gpu, w, max_rounds=0, policy=policy)
+
+
+@pytest.mark.parametrize("split", [0, 1], ids=["plain", "subgroups"])
+@pytest.mark.parametrize("B", [12, 70])
+@pytest.mark.parametrize("A,M", [(32, 16), (30, 16)], ids=["512 pairs", "480 pairs"])
+def test_rounds_of_many_pairs(gpu, A, M, B, split):
+    """Three resident workgroups per compute unit (more than 510 pairs) and two, batches below and beyond 64."""
+    torch, binding = gpu
+    w = wl.tiny(seed=9400 + A, n=6000, classes=(4,) * A, models=(M,) * A, max_batch=B, feat_dim=16, deadline=(15.0, 200.0))
+    policy = wl.named_policy("sneakpeek")
+    policy.split_groups = split
+    ctx = binding.Context(w.profile, 6000, policy=policy)
+    assert ctx.rounds_in_one_launch
+    ctx.close()
+    full_parity(gpu, w, max_rounds=12, policy=policy)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 129, 255, 257, 511, 513, 1023, 1024, 1025, 2047])
+@pytest.mark.parametrize("split", [0, 1], ids=["plain", "subgroups"])
+def test_runs_of_every_stage_of_the_network(gpu, n, split):
+    """Ordering of one application around the powers of two where the sorting network takes another stage, with many equal keys."""
+    w = wl.tiny(seed=9500 + n, n=n, classes=(3,), models=(2,), max_batch=8, feat_dim=16, deadline=(20.0, 90.0), fractions=(1.0,))
+    same = np.random.default_rng(9501).random(n) < 0.5
+    w.requests.x[same] = w.requests.x[0]
+    w.requests.weight[same] = w.requests.weight[0]
+    w.requests.deadline_rel_ms[same] = w.requests.deadline_rel_ms[0]
+    policy = wl.named_policy("sneakpeek")
+    policy.split_groups = split
+    full_parity(gpu, w, max_rounds=2, policy=policy)
