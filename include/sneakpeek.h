@@ -330,8 +330,10 @@ int32_t sp_max_classes(const sp_ctx* ctx);
 /* How sp_schedule runs the greedy rounds (Alg. 1, Sec. 5.2) on this context: 1 = all rounds of a chunk in
  * one launch (every (application, variant) pair fits on the device at once and, with group splitting, no
  * application of the scored window has more than 64 groups: after sp_score the call waits for that count),
- * 0 = two kernels per round.  The decisions are the same either way.  sp_greedy_round always takes the
- * second way. */
+ * 0 = two kernels per round.  The decisions are the same either way.  A round that is a call of its own
+ * (sp_greedy_round, sp_greedy_round_static, sp_schedule with max_rounds 1) is one launch of one workgroup
+ * where the profile is small (up to 15 applications, batches of up to 64, some 30,000 evaluations, no group
+ * splitting); else sp_greedy_round takes two kernels. */
 int32_t sp_rounds_in_one_launch(const sp_ctx* ctx);
 
 /*

@@ -97,7 +97,7 @@ __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v
 // Groups of kPairLanes = pair_lanes(B) lanes own the batch sizes (p+1, B-p), so all groups do the same amount of work;
 // both batch sizes of a pair run in the same loop (two independent chains per lane), and the completion
 // time of each batch size is carried as a float pair so that the loop stays in float32.
-// Every kernel that scores rounds calls this function: their scores agree bit for bit.
+// Every kernel that scores rounds forms the same sums, here or in one of the variants below: their scores agree bit for bit.
 template <int KIND, int kPairLanes>
 __device__ __forceinline__ unsigned long long triangle_best_kind(const float4* ent, const float* lat, int nb, int B,
                                                                 double t, uint32_t cid0, float* cube_out, int only_b,
@@ -171,7 +171,7 @@ __device__ __forceinline__ unsigned long long triangle_best(int kind, const floa
 
 // The same for largest batches of up to 64 by the 512 threads of a workgroup, one pair of batch sizes per 16 lanes: a lane's (up
 // to four) entries are read once, side by side, and the evaluations of both sizes do not wait for each other.  The same sums in
-// the same order.  0.5 us for batches of 32 and 64 where the loops above take 1.1.
+// the same order.  0.7 us for batches of 32 and 64 where the loops above take 1.1.
 template <int KIND>
 __device__ __forceinline__ unsigned long long triangle_held_kind(const float4* ent, const float* lat, int nb, int B, double t, uint32_t cid0,
                                                                 int only_b, int tid) {

@@ -11,6 +11,10 @@
 //     refills the look-ahead runs one step per round while the candidates are being exchanged; a round
 //     waits for it only when fewer than B entries remain while the application still has unvisited
 //     requests.  Every position of the service order is visited once per launch, not once per round;
+//   * between a decision and the candidates of the next round lies no barrier: every wavefront finds the live entries of the
+//     window by itself, the list is put in order while the candidates are exchanged.  A round of 12 pairs takes 2.9 to
+//     3.3 us (4.2 with the list put in order first and looping triangles), of 64 pairs 4.5 in the mean (5.1), of 512 pairs 7.1
+//     to 8.2 (8.6 to 8.9); one that has to wait for the walk 3 to 4 more, which the means hold;
 //   * the arg max over all pairs goes through one slot per pair and a reducing workgroup: every pair
 //     publishes its best candidate, the reducer polls the slots (one per thread), takes the maximum and
 //     publishes the decision, which one thread of every pair polls.  With few pairs (kAllToAllPairs) there
@@ -339,8 +343,8 @@ constexpr int kCachedRequests = 512;
 
 // SPLIT: the window's groups are subgroups of the applications (tb.pol_split); the plain instantiation holds
 // none of the secondary-group code.
-// WGS: workgroups that must fit on a compute unit.  Three leave 80 registers, which the plain instantiation with the looping triangles
-// just fits; grids of up to two per compute unit (510 pairs on 256) get 128 registers, and triangles with their entries held.
+// WGS: workgroups that must fit on a compute unit.  Three leave 80 registers (3 spilled with the looping triangles, 27 with
+// subgroups); grids of up to two per compute unit (510 pairs on 256) get 128 (none, 3), and triangles with their entries held.
 template <bool SPLIT, int WGS>
 __global__ __launch_bounds__(kRoundThreads, 2 * WGS) void k_rounds_persistent(Tables tb, Window w, Persist ps) {
   __shared__ int32_t win[kWinCap];

@@ -25,7 +25,7 @@
 // registers and walk the class tiles like the bfloat16 kernel; class blocks follow the slices through the same two
 // buffers.
 //
-// Measured (rocprofv3, median us, before -> now): 32,768 rows of 768 floats, 100 classes 1543 -> 40.6 (2.5 TB/s of rows);
+// Measured (rocprofv3, median us, before -> now): 32,768 rows of 768 floats, 100 classes 1543 -> 38.7 (2.6 TB/s of rows);
 // 65,536 rows of 512 bfloat16, 100 classes 1273 -> 26.2 (2.6 TB/s); 100,000 requests of 128-64-10/7/2 float32 heads 185 -> 27.0
 // (1.9 TB/s), all three from the generic kernel; 30,011 of 384-128-100/37/10 bfloat16 heads 29 -> 20.6 (1.1 TB/s), from the
 // kernel that pads the hidden layer to 256.  A large copy reaches 5.2 TB/s on this card (read and written).
