@@ -977,13 +977,26 @@ int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev,
     int nbits = 1;
     while ((1 << nbits) <= A) ++nbits;
     const int tile = group_tile(n), tiles = (n + tile - 1) / tile;
+    static_assert(group_tile(kGroupSelf) == 2 * kGroupThreads, "tiles of the short windows");
+    const dim3 place_grid((tiles + kXcds - 1) / kXcds * kXcds + 1);
+    if (n <= kGroupSelf && A <= kGroupSelfApps) {
+#define SP_GROUP(QUADS)                                                                                                 \
+      hipLaunchKernelGGL((k_group_place<2, QUADS>), place_grid, dim3(kGroupThreads), 0, s, n, A, nbits, app_dev, deadline_ms_dev, \
+                         weight_dev, (const uint32_t*)nullptr, tiles, c->bufV[0], c->dw_g[0], seg_args, w, w.st)
+      if (n <= 2048) SP_GROUP(1);
+      else if (n <= 8192) SP_GROUP(4);
+      else if (n <= 16384) SP_GROUP(8);
+      else SP_GROUP(16);
+#undef SP_GROUP
+      return c->bufV[0];
+    }
 #define SP_GROUP(ITEMS)                                                                                                 \
     do {                                                                                                                \
       hipLaunchKernelGGL(k_group_count<ITEMS>, dim3(tiles), dim3(kGroupThreads), 0, s, n, A, nbits, app_dev,            \
                          c->group_counts, w.st, zero, zero_words);                                                      \
       if (tiles > kGroupDirect)                                                                                         \
         hipLaunchKernelGGL(k_group_scan, dim3(A + 1), dim3(1024), 0, s, c->group_counts, tiles);                        \
-      hipLaunchKernelGGL(k_group_place<ITEMS>, dim3((tiles + kXcds - 1) / kXcds * kXcds + 1), dim3(kGroupThreads), 0, s, n, A, nbits, app_dev, \
+      hipLaunchKernelGGL(k_group_place<ITEMS>, place_grid, dim3(kGroupThreads), 0, s, n, A, nbits, app_dev,             \
                          deadline_ms_dev, weight_dev, (const uint32_t*)c->group_counts, tiles, c->bufV[0], c->dw_g[0],  \
                          seg_args, w, w.st);                                                                            \
     } while (0)

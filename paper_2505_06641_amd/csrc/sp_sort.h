@@ -1,7 +1,8 @@
 // Grouping and ordering of a window's requests (Alg. 1 "HashMap<app : request list>" and "requests in g sorted by
 // priority"; eq. (12); Sec. 5.3.2 with subgroups).
 //
-// Grouping by application.  Up to 255 applications: one kernel counts the applications of every tile of the queue
+// Grouping by application.  Short windows of up to seven applications: one kernel, in which every workgroup counts the whole
+// window.  Else up to 255 applications: one kernel counts the applications of every tile of the queue
 // (k_group_count), a second one places the requests (k_group_place): a tile reads the counts of all tiles, which are few
 // (tiles times applications words), so no tile waits for another.  More applications: two or three stable radix passes
 // over the ids (k_digit_totals, k_radix_pass), whose tiles learn the digit counts of the tiles before them by looking back
@@ -556,6 +557,77 @@ __device__ __forceinline__ void group_sums(const uint32_t* __restrict__ counts, 
   __syncthreads();
 }
 
+// Short windows of few applications: a workgroup counts the whole window itself, in one trip to memory, which spares the launch
+// before it: 3.6 us for 256 requests where two launches take 1.7 + 4.2, 5.1 for 4,096 (2.4 + 5.0), 5.8 for 16,384 (2.8 + 5.1), 7.2 for
+// 32,768 (3.9 + 5.5), and the gap between them.  Per call 34.5 -> 31.7 us, 157.0 -> 154.6, 90.4 -> 87.1, 68.6 -> 67.9: the ids that every
+// workgroup reads, 128 KB at the end of this range, take up what is saved soon after.  Eight bits per application and thread, up to
+// kGroupSelfApps applications and the invalid ids.
+constexpr int kGroupSelf = 32768, kGroupSelfApps = 7;
+
+// What group_sums gives, from the ids themselves; n <= 2,048 QUADS.
+template <int QUADS>
+__device__ __forceinline__ void group_sums_self(const int32_t* __restrict__ app, int n, int tile, int tile_size, int A, uint32_t* before,
+                                                uint32_t* total, uint32_t (*red)[2][64]) {
+  static_assert(4 * QUADS <= 255, "a thread's counts take eight bits each");
+  static_assert(kGroupSelfApps < 8, "and a quad's four");
+  static_assert(kGroupSelf <= 0xffff, "the workgroup's sixteen");
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  u32x4 id[QUADS];
+  if (n >= 4) {                                        // (uniform)
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) id[q] = *(const u32x4*)(app + min(4 * (q * kGroupThreads + tid), n - 4));
+  } else {
+    for (int q = 0; q < QUADS; ++q)
+      for (int e = 0; e < 4; ++e) id[q][e] = (uint32_t)app[min(e, n - 1)];
+  }
+  uint32_t all[2] = {0u, 0u}, ahead[2] = {0u, 0u};     // a byte per application: even ones, odd ones
+#pragma unroll
+  for (int q = 0; q < QUADS; ++q) {
+    const int i = 4 * (q * kGroupThreads + tid);
+    uint32_t mine = 0u;                                // four bits each
+    if (i + 3 < n) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mine += 1u << (4u * min(id[q][e], (uint32_t)A));
+    } else if (i < n) {                                // the last quad of the window, which was loaded from n - 4 on
+      const int at = n >= 4 ? n - 4 : 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mine += (uint32_t)(at + e >= i && at + e < n) << (4u * min(id[q][e], (uint32_t)A));
+    }
+    const bool before_tile = i < tile * tile_size;     // (tiles are whole quads)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t m = (mine >> (4 * h)) & 0x0f0f0f0fu;
+      all[h] += m;
+      ahead[h] += before_tile ? m : 0u;
+    }
+  }
+  // sums over the wavefront in sixteen bits
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t sum = wave_scan_incl(((v ? all : ahead)[j >> 1] >> (8 * (j & 1))) & 0x00ff00ffu);
+      if (lane == 63) red[wave][v][j] = sum;
+    }
+  }
+  __syncthreads();
+  if (tid < 256) {
+    uint32_t sb = 0, stt = 0;
+    if (tid <= A) {
+      const int j = (tid & 1) * 2 + ((tid >> 1) & 1), shift = 16 * (tid >> 2);
+#pragma unroll
+      for (int v = 0; v < kGroupWaves; ++v) {
+        sb += (red[v][0][j] >> shift) & 0xffffu;
+        stt += (red[v][1][j] >> shift) & 0xffffu;
+      }
+    }
+    before[tid] = sb;
+    total[tid] = stt;
+  }
+  __syncthreads();
+}
+
 // The segments from the number of requests of every application (and of invalid ids, total[A]), at most 255 of them: one thread
 // per application, tables in LDS, three barriers (k_group_place takes 4.0 us for 256 requests where tables in memory took 4.8).
 __device__ __forceinline__ void segments_from_totals(const SegArgs& g, const Window& w, const uint32_t* total, int costly /*by_cost[tid]*/) {
@@ -611,7 +683,8 @@ __device__ __forceinline__ void segments_from_totals(const SegArgs& g, const Win
 // and weight (the scoring kernel then reads them in order instead of gathering by request id, 4 useful bytes per 64-byte
 // line).  One extra workgroup turns the counts into segment starts and descriptors.  Bound by three or four dependent
 // trips to memory (2 us each), not by its 28 bytes per request.
-template <int ITEMS>
+// SELF > 0: the first kernel of a short window; it counts 2,048 SELF ids itself and resets the window's state.
+template <int ITEMS, int SELF = 0>
 __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int nbits, const int32_t* __restrict__ app,
                                                                const float* __restrict__ D, const float* __restrict__ weight,
                                                                const uint32_t* __restrict__ counts, int n_tiles,
@@ -625,7 +698,12 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
   if (blockIdx.x == 0) {              // (the first: as the last it would wait for a place on a full chip)
     const int costly = sg.by_cost[min(tid, A - 1)];
     loaded_here(costly);
-    group_sums(counts, n_tiles, 0, A, nbits, before, total, red);
+    if constexpr (SELF > 0) {
+      if (tid == 0) reset_state(st);
+      group_sums_self<SELF>(app, n, 0, kTile, A, before, total, red);
+    } else {
+      group_sums(counts, n_tiles, 0, A, nbits, before, total, red);
+    }
     if (tid == 0 && total[A] != 0u) atomicOr(&st->err, kErrApp);
     segments_from_totals(sg, sw, total, costly);
     return;
@@ -651,7 +729,9 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
     key[c] = i < n ? sort_key_at((const uint32_t*)app, i, A, bad) : 0u;
     pay[c] = i < n ? make_float2(D[i], weight[i]) : make_float2(0.f, 0.f);
   }
-  group_sums(counts, n_tiles, tile, A, nbits, before, total, red);       // (its barriers cover the cleared counts)
+  // (the barriers in here cover the cleared counts)
+  if constexpr (SELF > 0) group_sums_self<SELF>(app, n, tile, kTile, A, before, total, red);
+  else group_sums(counts, n_tiles, tile, A, nbits, before, total, red);
   // rank inside the wavefront: lanes with my application ahead of me in this chunk, plus the wavefront's earlier chunks
   const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   uint32_t rank[ITEMS];

@@ -1049,6 +1049,41 @@ def _service_order(w, key, edf=False):
     return np.concatenate(out)
 
 
+@pytest.mark.parametrize("A", [1, 2, 7, 8])
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 1023, 1025, 2048, 2049, 2051, 8190, 8192, 8193, 16384, 16387, 32767, 32768, 32769])
+def test_short_windows_counted_and_placed_in_one_launch(gpu, n, A):
+    """Window lengths around the ids per thread of the kernel that counts for itself, up to one application more than it takes; ids
+    that start at any four bytes, so that the last quad of a window ends at the end of the array.  Whole numbers, no tolerance."""
+    torch, binding = gpu
+    rng = np.random.default_rng(100 * n + A)
+    frac = rng.pareto(1.0, A) + 0.01
+    w = wl.tiny(seed=8700 + A, n=n, classes=(2,) * A, models=(1,) * A, max_batch=2, feat_dim=8, fractions=tuple(frac / frac.sum()))
+    ctx = binding.Context(w.profile, n)
+    key = torch.zeros(n, device="cuda:0")
+    order = torch.zeros(n, dtype=torch.int32, device="cuda:0")
+    seg = torch.zeros(A + 1, dtype=torch.int32, device="cuda:0")
+    x, app, D, wt = binding.to_device(w.requests)
+    for lead in (0, 1, 3):
+        shifted = torch.full((n + lead,), A - 1, dtype=torch.int32, device="cuda:0")
+        shifted[lead:] = app
+        ctx.sp_score(x, shifted[lead:], D, wt, key_out=key)
+        ctx.sp_debug_dump(binding.SP_DUMP_ORDER, order)
+        assert np.array_equal(order.cpu().numpy(), _service_order(w, key.cpu().numpy()))
+        ctx.sp_debug_dump(binding.SP_DUMP_SEGMENTS, seg)
+        assert np.array_equal(seg.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(w.requests.app, minlength=A))]))
+    # ids outside [0, A) are counted apart and refused
+    bad = app.clone()
+    bad[n // 2] = -1
+    bad[n - 1] = 1 << 30
+    ctx.sp_score(x, bad, D, wt, key_out=key)
+    with pytest.raises(binding.SneakPeekError):
+        ctx.sp_schedule()
+    ctx.sp_score(x, app, D, wt, key_out=key)              # and leave nothing behind
+    ctx.sp_debug_dump(binding.SP_DUMP_ORDER, order)
+    assert np.array_equal(order.cpu().numpy(), _service_order(w, key.cpu().numpy()))
+    ctx.close()
+
+
 @pytest.mark.parametrize("policy", ["sneakpeek", "lo_edf"])
 @pytest.mark.parametrize("n,A,ties", [
     (1, 1, 0), (255, 2, 0), (1023, 1, 0), (1024, 1, 0), (1025, 1, 0), (3000, 1, 3), (4097, 3, 0), (16384, 1, 0), (16385, 1, 2),
