@@ -87,8 +87,8 @@ __device__ __forceinline__ unsigned long long single_pair(const float4* e4, cons
   }
   const float r1 = sum4((s1[0] + s1[1]) + (s1[2] + s1[3]));
   const float r2 = sum4((s2[0] + s2[1]) + (s2[2] + s2[3]));
-  // (the larger score; the smaller size where they are equal)
-  const bool second = n2 > 0 && (n1 == 0 || r2 > r1);
+  // (the order of packed candidates: by the scores' bits, where a NaN is above every number, then the smaller size)
+  const bool second = n2 > 0 && (n1 == 0 || __float_as_uint(r2) > __float_as_uint(r1));
   return (n1 | n2) > 0 ? pack_candidate(second ? r2 : r1, cid0 + (uint32_t)((second ? b2 : b1) - 1)) : 0ull;
 }
 

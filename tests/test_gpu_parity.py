@@ -1578,3 +1578,53 @@ def test_runs_of_every_stage_of_the_network(gpu, n, split):
     policy = wl.named_policy("sneakpeek")
     policy.split_groups = split
     full_parity(gpu, w, max_rounds=2, policy=policy)
+
+
+@pytest.mark.parametrize("A,M,B,edf", [(1, 3, 16, 0), (3, 4, 32, 0), (2, 4, 64, 1), (1, 4, 15, 1)])
+def test_scores_that_are_no_numbers_win_on_every_route(gpu, A, M, B, edf):
+    """An infinite weight whose request is lost inside the larger batches (infinity times zero), or, earliest deadline first with unit
+    weights, a request with NaN features behind the first half of the window: some sizes' scores are NaN.  A NaN is above every
+    number in a round's maximum, whichever kernel takes it; ties go to the smallest size."""
+    torch, binding = gpu
+    n = 400
+    w = wl.tiny(seed=9600 + B, n=n, classes=(3,) * A, models=(M,) * A, max_batch=B, feat_dim=16, deadline=(30.0, 300.0), alpha=(1.0, 1.1),
+                beta=(0.5, 0.55))
+    policy = wl.Policy(order=wl.ORDER_EDF, weight=wl.WEIGHT_UNIT) if edf else wl.Policy()
+    rng = np.random.default_rng(9601)
+    for a in range(A):
+        mine = np.nonzero(w.requests.app == a)[0]
+        if edf:                                       # in the last quarter of the first window in service order
+            at = np.argsort(w.requests.deadline_rel_ms[mine], kind="stable")[3 * B // 4]
+            w.requests.x[mine[at]] = np.nan
+        else:                                         # first in service order, lost in the last quarter of the batch sizes
+            i = mine[rng.integers(mine.size)]
+            w.requests.weight[i] = np.inf
+            w.requests.deadline_rel_ms[i] = float(w.profile.lat_ms[a][:, 3 * B // 4].max())
+            w.profile.penalty[a] = wl.PEN_STEP
+    args = binding.to_device(w.requests)
+    ctxs = [binding.Context(w.profile, n, policy=policy) for _ in range(3)]
+    ctxs[1].sp_debug_set_spin_limit(1 << 19)          # (two kernels per round)
+    ids = [torch.full((B,), -1, dtype=torch.int32, device="cuda:0") for _ in range(2)]
+    for c in ctxs:
+        c.sp_score(*args)
+    cube = torch.zeros((A, ctxs[0].m_max, B), device="cuda:0")
+    ctxs[1].sp_debug_dump(binding.SP_DUMP_SCORE_CUBE, cube)
+    first = cube.cpu().numpy()
+    assert np.isnan(first).any() and not np.isnan(first[..., : (B + 1) // 2]).any()
+    log = []
+    decided = lambda d: None if d is None else (d["app"], d["model"], d["batch"], d["t_start_ms"], d["t_end_ms"])
+    for k in range(12):
+        got = [c.sp_greedy_round(req_ids_out=i) for c, i in zip(ctxs[:2], ids)]
+        if k == 0:                                    # from the scores themselves
+            a, m, b = np.unravel_index(int(np.nonzero(np.isnan(first).ravel())[0][0]), first.shape)
+            assert decided(got[1][1])[:3] == (a, m, b + 1)
+        assert got[0][0] == got[1][0] and decided(got[0][1]) == decided(got[1][1]), f"round {k}"
+        if got[0][0] == binding.SP_DONE:
+            break
+        assert torch.equal(*ids), f"round {k}"
+        log.append(decided(got[1][1]))
+    assert ctxs[2].rounds_in_one_launch
+    _, _, one_launch = ctxs[2].sp_schedule(len(log), log_capacity=len(log))
+    assert [decided(d) for d in one_launch] == log
+    for c in ctxs:
+        c.close()
