@@ -19,7 +19,8 @@ constexpr int kSingleWaves = kSingleThreads / kWave;
 constexpr int kSingleApps = kSingleWaves - 1;        // one wavefront brings each window, the others clear outputs
 constexpr int kSingleBatch = kWave;                  // largest batch: one lane per member
 constexpr int kSingleCap = 2 * kWave;                // entries per application: a window that lacks one, and 64 more
-constexpr int kSingleScan = 16;                      // service positions per lane and step of a walk over dead requests
+constexpr int kSingleScan = 16;                      // service positions per lane of a walk over dead requests, in each ...
+constexpr int kSingleBlocks = 4;                     // ... of the blocks of a step
 // Utility evaluations of a round up to which this kernel is used (with the group-first rule one application's: the others are not
 // evaluated).  us per call of sp_greedy_round, two kernels against this one: 27.0 / 21.7 (408 evaluations), 28.6 / 23.2 (8,448),
 // 28.6 / 25.0 (16,896), 28.9 / 26.1 (33,280, batches of 64), 29.0 / 29.8 (33,792, batches of 32), 28.7 / 31.7 (66,560); group
@@ -92,6 +93,63 @@ __device__ __forceinline__ unsigned long long single_pair(const float4* e4, cons
   return (n1 | n2) > 0 ? pack_candidate(second ? r2 : r1, cid0 + (uint32_t)((second ? b2 : b1) - 1)) : 0ull;
 }
 
+// The smallest deadline that is_dead leaves alive at E0 >= 0: a comparison in 32 bits then says the same as its own in 64, for every
+// deadline (E0 > D, or E0 >= 2 D; halving is exact).
+__device__ __forceinline__ float least_live(int kind, double E0) {
+  const double bound = kind == 0 ? E0 : 0.5 * E0;
+  const float f = (float)bound;
+  const bool above = kind == 0 ? (double)f >= bound : (double)f > bound;
+  return above ? f : __uint_as_float(__float_as_uint(f) + 1u);         // (f >= 0: the next float)
+}
+
+// One step of a wavefront's walk over service positions that are mostly dead: the live ones among the next BLOCKS * 1,024 go to
+// `found` behind the n that are there, up to kWave in all.  All loads go out before the first is used, from addresses that stay
+// inside the application's range, so that no branch parts them.  About 1.3 us for 4,096 positions; with 1,024 a step and comparisons
+// in 64 bits 1.5 us for each.  us per call of sp_greedy_round, two kernels / steps of 1,024 / these (one application; most die at once,
+// or in the course of the window): 65,536 requests 35 / 36 / 25 and 28 / 21 / 20, 262,144 48 / 84 / 35 and 29 / 26 / 21, 1,048,576 102 /
+// 272 / 73 and 35 / 42 / 24.
+template <int BLOCKS>
+__device__ __forceinline__ void walk_dead(const Window& w, float least, int& scan, int end, int32_t* found, int& n, int lane) {
+  typedef uint32_t words __attribute__((ext_vector_type(4), aligned(4)));
+  constexpr int kBlock = kSingleScan * kWave;
+  const int base = scan & ~3, p0 = base + kSingleScan * lane, last = (end - 1) & ~3;     // (both arrays are padded by 16)
+  float4 d[BLOCKS][kSingleScan / 4];
+  words alive[BLOCKS];
+#pragma unroll
+  for (int u = 0; u < BLOCKS; ++u) {
+    const int at = min(p0 + u * kBlock, last);
+#pragma unroll
+    for (int q = 0; q < kSingleScan / 4; ++q) d[u][q] = *reinterpret_cast<const float4*>(w.D_s + at + 4 * q);
+    alive[u] = *reinterpret_cast<const words*>(w.alive_s + at);
+  }
+#pragma unroll
+  for (int u = 0; u < BLOCKS; ++u) {
+    if (n >= kWave) break;                             // (uniform)
+    const int pu = p0 + u * kBlock;
+    uint32_t mask = 0;
+#pragma unroll
+    for (int q = 0; q < kSingleScan / 4; ++q) {
+      const uint32_t due = (d[u][q].x >= least ? 1u : 0u) | (d[u][q].y >= least ? 2u : 0u) | (d[u][q].z >= least ? 4u : 0u) |
+                           (d[u][q].w >= least ? 8u : 0u);
+      const uint32_t pending = (alive[u][q] * 0x01020408u) >> 24;      // (four bytes of 0 or 1 to four bits, others above them)
+      mask |= (due & pending) << (4 * q);
+    }
+    // inside [scan, end)
+    mask &= ~0u << min(max(scan - pu, 0), kSingleScan);
+    mask &= (1u << min(max(end - pu, 0), kSingleScan)) - 1u;
+    const int cnt = __popc(mask), incl = (int)wave_scan_incl((uint32_t)cnt);
+    int rank = n + incl - cnt;
+    n = min(n + __builtin_amdgcn_readlane(incl, kWave - 1), kWave);
+    while (mask != 0 && rank < kWave) {
+      const int j = __ffs((int)mask) - 1;
+      mask &= mask - 1;
+      found[rank++] = pu + j;
+    }
+  }
+  wave_sync();
+  scan = n == kWave ? __builtin_amdgcn_readfirstlane(found[kWave - 1]) + 1 : min(base + BLOCKS * kBlock, end);
+}
+
 // QUADS: groups of four variants.
 template <int QUADS>
 __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Window w, Single sg) {
@@ -142,8 +200,8 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
     int scan = __builtin_amdgcn_readfirstlane((r & 1) ? head_odd : head_even);
     const double E0 = t + (double)a_lmin;
     int held = 0;
-    // 64 at a time: two dependent trips to memory where half of the next 64 positions are live, else one for every 1,024
-    // positions and two more
+    // 64 at a time: two dependent trips to memory where half of the next 64 positions are live, else one for 1,024 positions, one
+    // for every 4,096 after them, and two more
     while (held < Bw && scan < end) {
       int pos = min(scan + lane, end - 1);
       int id = w.id_s[pos];
@@ -153,21 +211,9 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
         scan = min(scan + kWave, end);
       } else {
         int n = 0;
-        do {
-          const int base = scan & ~3, p0 = base + kSingleScan * lane;
-          uint32_t mask = live_mask<kSingleScan / 4>(w, kind, E0, p0, scan, end);
-          const int cnt = __popc(mask), incl = (int)wave_scan_incl((uint32_t)cnt);
-          const int total = n + __builtin_amdgcn_readlane(incl, kWave - 1);
-          int rank = n + incl - cnt;
-          while (mask != 0 && rank < kWave) {
-            const int j = __ffs((int)mask) - 1;
-            mask &= mask - 1;
-            found_s[wave][rank++] = p0 + j;
-          }
-          wave_sync();
-          n = min(total, kWave);
-          scan = total >= kWave ? __builtin_amdgcn_readfirstlane(found_s[wave][kWave - 1]) + 1 : min(base + kSingleScan * kWave, end);
-        } while (n < Bw && scan < end);
+        const float least = least_live(kind, E0);
+        walk_dead<1>(w, least, scan, end, found_s[wave], n, lane);
+        while (n < Bw && scan < end) walk_dead<kSingleBlocks>(w, least, scan, end, found_s[wave], n, lane);
         live = lane < n;
         pos = n > 0 ? found_s[wave][min(lane, n - 1)] : end - 1;
         id = w.id_s[pos];

@@ -1628,3 +1628,42 @@ def test_scores_that_are_no_numbers_win_on_every_route(gpu, A, M, B, edf):
     assert [decided(d) for d in one_launch] == log
     for c in ctxs:
         c.close()
+
+
+@pytest.mark.parametrize("density", [0.0004, 0.01, 0.2])
+@pytest.mark.parametrize("n,A,B", [(1030, 1, 16), (5125, 1, 64), (20000, 2, 33), (70001, 1, 20)])
+def test_single_rounds_past_long_stretches_of_the_dead(gpu, n, A, B, density):
+    """Queues of which few are live, anywhere in service order: the walk of the one-workgroup round, 1,024 positions and then 4,096 a
+    step, against two kernels per round, to the last bit, and sp_schedule of one round against both.  The dead ones miss the first
+    round by one float, half of the live ones just make it."""
+    torch, binding = gpu
+    w = wl.tiny(seed=9700 + n, n=n, classes=(3,) * A, models=(3,) * A, max_batch=B, feat_dim=16, deadline=(40.0, 900.0))
+    rng = np.random.default_rng(int(9701 + n + 1e5 * density))
+    dead = rng.random(n) >= density
+    dead[-1] = False
+    w.profile.penalty[:] = [(wl.PEN_SIGMOID, wl.PEN_STEP)[(a + n) % 2] for a in range(A)]
+    due = w.requests.deadline_rel_ms
+    for a in range(A):
+        step = w.profile.penalty[a] == wl.PEN_STEP
+        e0 = np.float32(w.profile.lat_ms[a][:, 0].min())                 # dead: e0 > D, or e0 >= 2 D
+        lost = np.nextafter(e0, np.float32(0)) if step else e0 / np.float32(2)
+        mine = w.requests.app == a
+        due[mine & dead] = lost
+        due[mine & ~dead & (rng.random(n) < 0.5)] = np.nextafter(lost, np.float32(np.inf))
+    args = binding.to_device(w.requests)
+    ctxs = [binding.Context(w.profile, n) for _ in range(3)]
+    ctxs[1].sp_debug_set_spin_limit(1 << 19)            # (two kernels per round)
+    ids = [torch.full((B,), -1, dtype=torch.int32, device="cuda:0") for _ in range(2)]
+    for c in ctxs:
+        c.sp_score(*args)
+    for k in range(40):
+        got = [c.sp_greedy_round(req_ids_out=i) for c, i in zip(ctxs, ids)]
+        assert got[0] == got[1] and torch.equal(*ids), f"round {k}"
+        rc, _, log = ctxs[2].sp_schedule(1, log_capacity=k + 1)
+        assert rc == got[0][0]
+        if rc == binding.SP_DONE:
+            break
+        assert log[k] == got[0][1], f"round {k}"
+    assert k > 0
+    for c in ctxs:
+        c.close()
