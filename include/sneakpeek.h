@@ -218,7 +218,9 @@ sp_status sp_greedy_round_static(sp_ctx* ctx, void* stream, sp_decision* out_hos
  * exhausted (both fill the outputs).
  * When every (application, variant) pair fits on the device at once (see
  * sp_rounds_in_one_launch), up to 64 rounds run inside one kernel whose
- * workgroups wait for each other with bounded waits.  If the device is shared
+ * workgroups wait for each other with bounded waits; contexts of a process
+ * whose launches of that kind do not fit the device side by side take turns
+ * (the call waits on the host).  If the device is shared
  * with other long-running work and such a wait runs out, the call returns
  * SP_EDEVICE, the context switches to two kernels per round for good, and the
  * window has to be scored again (SP_ESTATE until then).                        */

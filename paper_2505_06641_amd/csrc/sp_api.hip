@@ -7,6 +7,8 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <chrono>
+#include <condition_variable>
 #include <mutex>
 #include <new>
 #include <string>
@@ -71,6 +73,7 @@ struct sp_ctx {
   bool persist = false;
   bool persist_split = false;        // ... and also with the per-wavefront windows that subgroups need in LDS
   int persist_wgs = 2, persist_split_wgs = 2;   // the instantiations that hold the grid (see k_rounds_persistent)
+  int cus = 0, persist_per_cu = 0, persist_split_per_cu = 0;   // compute units, and workgroups of those instantiations on one
   Persist ps{};
   bool single_ok = false;            // a round by itself may run in one workgroup
   uint32_t gen_base = 0;             // slot generations handed out so far
@@ -124,7 +127,62 @@ constexpr int kStaticMaxDevices = 64;
 static unsigned char* g_scratch_ptr[kStaticMaxDevices];   // device address of `scratch` on each GPU seen so far
 static std::mutex g_scratch_mu;
 
+// Grids of resident workgroups (k_rounds_persistent) that contexts of this process have on each GPU at the moment, by the workgroups
+// of the kind that a compute unit holds.
+struct Residents {
+  int64_t workgroups = 0;
+  int grids[9] = {};
+};
+static Residents g_residents[kStaticMaxDevices];
+static std::mutex g_residents_mu;
+static std::condition_variable g_residents_left;
+
 namespace {
+
+// Room for one more such grid while this object lives.  Whether a grid fits has been asked of an empty GPU; its workgroups wait for
+// each other, so it must also fit beside the others: a compute unit holds, of any mix, as many workgroups as of the kind of which it
+// holds the fewest (and every die gets its eighth of each grid).  Two grids that do not fit side by side, each left with a part of
+// the GPU, would both wait until their polls run out.  A grid's rounds end by themselves, within a millisecond as a rule: the call
+// waits for them.
+class ResidentRoom {
+ public:
+  bool take(int device, int cus, int64_t workgroups, int per_cu) {
+    const int kind = std::min(per_cu, 8);
+    workgroups = (workgroups + kXcds - 1) / kXcds * kXcds;
+    Residents& r = g_residents[device];
+    const auto fits = [&] {
+      int least = kind;
+      for (int k = 1; k < least; ++k)
+        if (r.grids[k] > 0) least = k;
+      return r.workgroups == 0 || r.workgroups + workgroups <= (int64_t)least * cus;
+    };
+    std::unique_lock<std::mutex> lock(g_residents_mu);
+    if (!g_residents_left.wait_for(lock, std::chrono::seconds(2), fits)) return false;
+    r.workgroups += workgroups;
+    ++r.grids[kind];
+    held_ = &r;
+    workgroups_ = workgroups;
+    kind_ = kind;
+    return true;
+  }
+  ResidentRoom() = default;
+  ResidentRoom(const ResidentRoom&) = delete;
+  ResidentRoom& operator=(const ResidentRoom&) = delete;
+  ~ResidentRoom() {
+    if (held_ == nullptr) return;
+    {
+      std::lock_guard<std::mutex> lock(g_residents_mu);
+      held_->workgroups -= workgroups_;
+      --held_->grids[kind_];
+    }
+    g_residents_left.notify_all();
+  }
+
+ private:
+  Residents* held_ = nullptr;
+  int64_t workgroups_ = 0;
+  int kind_ = 0;
+};
 
 struct DeviceGuard {
   int prev = -1;
@@ -620,6 +678,13 @@ void launch_score_stream(sp_ctx* c, hipStream_t s, const void* x, const int32_t*
 #undef SP_LAUNCH_ST
 }
 
+// Whether a resident grid leaves a third of the device to other streams' kernels, whose workgroups come and go while it gathers
+// (the largest grid, 514 workgroups, takes two thirds of it at three per compute unit; 498 of 512 places took all of it, and waits
+// ran out beside a stream of small kernels).  us per round with two / three workgroups per compute unit, 330 pairs: 4.48 / 4.64
+// (batches of 12), 5.4 / 5.5 (64), 6.66 / 6.64 (128), with subgroups 7.9 / 9.9, 12.8 / 15.1, 16.4 / 18.5; 496 pairs: 4.43 / 4.64, 5.7 /
+// 5.8, 6.9 / 6.9, 8.3 / 10.5, 12.8 / 15.2, 15.5 / 17.9.
+bool room_to_share(int cus, int per_cu, size_t workgroups) { return 3 * workgroups <= 2 * (size_t)per_cu * (size_t)cus; }
+
 // The one-launch rounds path needs every (application, variant) pair plus the commit workgroup resident at
 // once; contexts too large for that keep the two-kernels-per-round path.
 sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
@@ -645,13 +710,13 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
   if (n_pairs == 0 || n_pairs > (size_t)kMaxPairs || ring > ((size_t)32 << 20)) return SP_OK;
   int cus = 0, per_cu = 0, rate_khz = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) return SP_OK;
-  // the instantiation with more registers where two workgroups per compute unit hold the grid
+  // the instantiation with more registers where the grid takes up to two thirds of the device with it
   c->persist_wgs = 2;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds_persistent<false, 2>, kRoundThreads, 0) != hipSuccess) {
     (void)hipGetLastError();
     return SP_OK;
   }
-  if ((size_t)per_cu * (size_t)cus < n_pairs + 2) {
+  if (!room_to_share(cus, per_cu, n_pairs + 2)) {
     c->persist_wgs = 3;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds_persistent<false, 3>, kRoundThreads, 0) != hipSuccess) {
       (void)hipGetLastError();
@@ -659,6 +724,8 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
     }
     if ((size_t)per_cu * (size_t)cus < n_pairs + 2) return SP_OK;
   }
+  c->cus = cus;
+  c->persist_per_cu = per_cu;
   if (hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, c->device) != hipSuccess || rate_khz <= 0)
     rate_khz = 100000;
   c->tick_ms = 1.0 / (double)rate_khz;
@@ -1316,16 +1383,20 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
   if (tm) SP_HIP(c, hipEventRecord(c->ev[4], s));
   c->round_ms.clear();
   while (!c->done) {
-    const bool persist = rounds_in_one_launch_so_far(c);
-    int chunk = persist ? kPersistRounds : 64;
+    bool persist = rounds_in_one_launch_so_far(c);
+    static_assert(kPersistRounds == 64, "rounds of a chunk, in one launch or not");
+    int chunk = kPersistRounds;
     if (max_rounds > 0) chunk = std::min(chunk, start + max_rounds - c->rounds_done);
     if (chunk <= 0) break;
+    const bool single = persist && chunk == 1 && round_single(c);
+    ResidentRoom room;                                           // (until the launch has been waited for)
+    if (persist && !single)
+      persist = room.take(c->device, c->cus, (int64_t)c->ps.n_pairs + 2, c->tb.pol_split ? c->persist_split_per_cu : c->persist_per_cu);
     const int32_t before = c->rounds_done;
     const Outputs outs{model_out_dev, round_out_dev, order_out_dev, util_out_dev};
     const bool want_outputs = c->n > 0 && (model_out_dev || round_out_dev || order_out_dev || util_out_dev);
     // the commit workgroup fills the caller's arrays itself where that is little next to the launch's rounds (not while the
     // stages are timed: the copy then has a time of its own)
-    const bool single = persist && chunk == 1 && round_single(c);
     const bool outputs_inside = persist && want_outputs && !tm && c->rounds_done == 0 &&
                                 (int64_t)c->n <= (single ? kSingleOutputs : (int64_t)kOutputsPerRound * chunk);
     if (persist) {
@@ -1577,9 +1648,11 @@ sp_status sp_set_policy(sp_ctx* c, const sp_policy* p) {
       const auto fits = [&](auto kernel) {
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kRoundThreads, dyn) == hipSuccess && (size_t)per_cu * (size_t)cus >= need;
       };
+      const auto fits_beside_others = [&](auto kernel) { return fits(kernel) && room_to_share(cus, per_cu, need); };
       if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess) {
-        c->persist_split_wgs = fits(k_rounds_persistent<true, 2>) ? 2 : 3;
+        c->persist_split_wgs = fits_beside_others(k_rounds_persistent<true, 2>) ? 2 : 3;
         c->persist_split = c->persist_split_wgs == 2 || fits(k_rounds_persistent<true, 3>);
+        c->persist_split_per_cu = per_cu;
       }
       (void)hipGetLastError();
     }

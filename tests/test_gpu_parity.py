@@ -1553,9 +1553,9 @@ def test_subgroups_of_a_few_requests(gpu, B, sizes):
 
 @pytest.mark.parametrize("split", [0, 1], ids=["plain", "subgroups"])
 @pytest.mark.parametrize("B", [12, 70])
-@pytest.mark.parametrize("A,M", [(32, 16), (30, 16)], ids=["512 pairs", "480 pairs"])
+@pytest.mark.parametrize("A,M", [(32, 16), (30, 16), (21, 16)], ids=["512 pairs", "480 pairs", "336 pairs"])
 def test_rounds_of_many_pairs(gpu, A, M, B, split):
-    """Three resident workgroups per compute unit (more than 510 pairs) and two, batches below and beyond 64."""
+    """Three resident workgroups per compute unit (more than 339 pairs on 256) and two, batches below and beyond 64."""
     torch, binding = gpu
     w = wl.tiny(seed=9400 + A, n=6000, classes=(4,) * A, models=(M,) * A, max_batch=B, feat_dim=16, deadline=(15.0, 200.0))
     policy = wl.named_policy("sneakpeek")
@@ -1667,3 +1667,49 @@ def test_single_rounds_past_long_stretches_of_the_dead(gpu, n, A, B, density):
     assert k > 0
     for c in ctxs:
         c.close()
+
+
+def test_windows_of_several_contexts_side_by_side(gpu):
+    """Contexts of 300 and 500 pairs on streams and threads of their own, whose resident grids do not fit the device together: a call
+    waits for room.  Decisions and outputs as of each context alone; no wait on the device runs out."""
+    import threading
+    torch, binding = gpu
+    n, reps = 8000, 12
+    kinds = [(30, 10, 0), (31, 16, 0), (30, 10, 1)]
+    work, errors = [], []
+    for i, (A, M, split) in enumerate(kinds):
+        w = wl.tiny(seed=9800 + i, n=n, classes=(4,) * A, models=(M,) * A, max_batch=12, feat_dim=16, deadline=(15.0, 400.0))
+        policy = wl.named_policy("sneakpeek")
+        policy.split_groups = split
+        ctx = binding.Context(w.profile, n, policy=policy)
+        assert ctx.rounds_in_one_launch
+        args = binding.to_device(w.requests)
+        ctx.sp_score(*args)
+        model = torch.zeros(n, dtype=torch.int32, device="cuda:0")
+        ref = ctx.sp_schedule(0, model_out=model, log_capacity=n)
+        work.append((ctx, args, ref, model.clone(), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    start = threading.Barrier(len(work))
+
+    def serve(ctx, args, ref, ref_model, stream):
+        try:
+            with torch.cuda.stream(stream):
+                model = torch.full((n,), 99, dtype=torch.int32, device="cuda:0")
+                start.wait()
+                for _ in range(reps):
+                    ctx.sp_score(*args, stream=stream)
+                    got = ctx.sp_schedule(0, model_out=model, log_capacity=n, stream=stream)
+                    assert got == ref
+                    assert torch.equal(model, ref_model)
+        except BaseException as e:
+            errors.append(e)
+
+    threads = [threading.Thread(target=serve, args=w) for w in work]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for w in work:
+        assert w[0].lib.sp_rounds_in_one_launch(w[0].h)
+        w[0].close()
