@@ -6,7 +6,7 @@
 // are dealt to sixteen wavefronts, four lanes per pair of batch sizes; every wavefront takes the maximum over the wavefronts'
 // candidates; one of them writes the batch out.  Bound by its dependent trips to memory (state; records; accuracies; about 0.8 us
 // each) and by about 1.5 us of triangles: 5.6 us for one application of three variants and batches of 16 (13.8 in a launch of
-// resident workgroups), 8.7 for three of four and batches of 32 (9.0 + 6.0 as two kernels, and the gap between them).
+// resident workgroups), 7.9 for three of four and batches of 32 (9.0 + 6.0 as two kernels, and the gap between them).
 #pragma once
 #include "sp_rounds.h"
 
@@ -20,7 +20,7 @@ constexpr int kSingleApps = kSingleWaves - 1;        // one wavefront brings eac
 constexpr int kSingleBatch = kWave;                  // largest batch: one lane per member
 constexpr int kSingleCap = 2 * kWave;                // entries per application: a window that lacks one, and 64 more
 constexpr int kSingleScan = 16;                      // service positions per lane of a walk over dead requests, in each ...
-constexpr int kSingleBlocks = 4;                     // ... of the blocks of a step
+constexpr int kSingleBlocks = 2;                     // ... of the blocks of a step
 // Utility evaluations of a round up to which this kernel is used (with the group-first rule one application's: the others are not
 // evaluated).  us per call of sp_greedy_round, two kernels against this one: 27.0 / 21.7 (408 evaluations), 28.6 / 23.2 (8,448),
 // 28.6 / 25.0 (16,896), 28.9 / 26.1 (33,280, batches of 64), 29.0 / 29.8 (33,792, batches of 32), 28.7 / 31.7 (66,560); group
@@ -102,28 +102,27 @@ __device__ __forceinline__ float least_live(int kind, double E0) {
   return above ? f : __uint_as_float(__float_as_uint(f) + 1u);         // (f >= 0: the next float)
 }
 
-// One step of a wavefront's walk over service positions that are mostly dead: the live ones among the next BLOCKS * 1,024 go to
+// One step of a wavefront's walk over service positions that are mostly dead: the live ones among the next kSingleBlocks * 1,024 go to
 // `found` behind the n that are there, up to kWave in all.  All loads go out before the first is used, from addresses that stay
-// inside the application's range, so that no branch parts them.  About 1.3 us for 4,096 positions; with 1,024 a step and comparisons
-// in 64 bits 1.5 us for each.  us per call of sp_greedy_round, two kernels / steps of 1,024 / these (one application; most die at once,
-// or in the course of the window): 65,536 requests 35 / 36 / 25 and 28 / 21 / 20, 262,144 48 / 84 / 35 and 29 / 26 / 21, 1,048,576 102 /
-// 272 / 73 and 35 / 42 / 24.
-template <int BLOCKS>
+// inside the application's range, so that no branch parts them.  About 0.9 us for 2,048 positions; 1,024 a step with comparisons in
+// 64 bits took 1.5 us.  us per call of sp_greedy_round, two kernels / those steps / these (one application; most die at once, or in the
+// course of the window): 16,384 requests 33 / 27 / 23 and 28 / 20.5 / 19, 65,536 35 / 35 / 25 and 28 / 21 / 19, 262,144 48 / 84 / 37 and 29
+// / 26 / 20, 1,048,576 102 / 272 / 91 and 35 / 42 / 25.  Four blocks take more than 64 registers: 5.5 -> 6.0 us for the smallest windows.
 __device__ __forceinline__ void walk_dead(const Window& w, float least, int& scan, int end, int32_t* found, int& n, int lane) {
   typedef uint32_t words __attribute__((ext_vector_type(4), aligned(4)));
   constexpr int kBlock = kSingleScan * kWave;
   const int base = scan & ~3, p0 = base + kSingleScan * lane, last = (end - 1) & ~3;     // (both arrays are padded by 16)
-  float4 d[BLOCKS][kSingleScan / 4];
-  words alive[BLOCKS];
+  float4 d[kSingleBlocks][kSingleScan / 4];
+  words alive[kSingleBlocks];
 #pragma unroll
-  for (int u = 0; u < BLOCKS; ++u) {
+  for (int u = 0; u < kSingleBlocks; ++u) {
     const int at = min(p0 + u * kBlock, last);
 #pragma unroll
     for (int q = 0; q < kSingleScan / 4; ++q) d[u][q] = *reinterpret_cast<const float4*>(w.D_s + at + 4 * q);
     alive[u] = *reinterpret_cast<const words*>(w.alive_s + at);
   }
 #pragma unroll
-  for (int u = 0; u < BLOCKS; ++u) {
+  for (int u = 0; u < kSingleBlocks; ++u) {
     if (n >= kWave) break;                             // (uniform)
     const int pu = p0 + u * kBlock;
     uint32_t mask = 0;
@@ -131,7 +130,8 @@ __device__ __forceinline__ void walk_dead(const Window& w, float least, int& sca
     for (int q = 0; q < kSingleScan / 4; ++q) {
       const uint32_t due = (d[u][q].x >= least ? 1u : 0u) | (d[u][q].y >= least ? 2u : 0u) | (d[u][q].z >= least ? 4u : 0u) |
                            (d[u][q].w >= least ? 8u : 0u);
-      const uint32_t pending = (alive[u][q] * 0x01020408u) >> 24;      // (four bytes of 0 or 1 to four bits, others above them)
+      // (four bytes of 0 or 1 to four bits, others above them; what lies behind the window's end may be anything)
+      const uint32_t pending = ((alive[u][q] & 0x01010101u) * 0x01020408u) >> 24;
       mask |= (due & pending) << (4 * q);
     }
     // inside [scan, end)
@@ -147,7 +147,7 @@ __device__ __forceinline__ void walk_dead(const Window& w, float least, int& sca
     }
   }
   wave_sync();
-  scan = n == kWave ? __builtin_amdgcn_readfirstlane(found[kWave - 1]) + 1 : min(base + BLOCKS * kBlock, end);
+  scan = n == kWave ? __builtin_amdgcn_readfirstlane(found[kWave - 1]) + 1 : min(base + kSingleBlocks * kBlock, end);
 }
 
 // QUADS: groups of four variants.
@@ -200,8 +200,8 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
     int scan = __builtin_amdgcn_readfirstlane((r & 1) ? head_odd : head_even);
     const double E0 = t + (double)a_lmin;
     int held = 0;
-    // 64 at a time: two dependent trips to memory where half of the next 64 positions are live, else one for 1,024 positions, one
-    // for every 4,096 after them, and two more
+    // 64 at a time: two dependent trips to memory where half of the next 64 positions are live, else one for every 2,048
+    // positions and two more
     while (held < Bw && scan < end) {
       int pos = min(scan + lane, end - 1);
       int id = w.id_s[pos];
@@ -212,8 +212,7 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
       } else {
         int n = 0;
         const float least = least_live(kind, E0);
-        walk_dead<1>(w, least, scan, end, found_s[wave], n, lane);
-        while (n < Bw && scan < end) walk_dead<kSingleBlocks>(w, least, scan, end, found_s[wave], n, lane);
+        do walk_dead(w, least, scan, end, found_s[wave], n, lane); while (n < Bw && scan < end);
         live = lane < n;
         pos = n > 0 ? found_s[wave][min(lane, n - 1)] : end - 1;
         id = w.id_s[pos];
