@@ -36,8 +36,8 @@ struct sp_ctx {
   Tables tb{};
   Window w{};
   std::vector<void*> dev_allocs;
-  int32_t tiles_in_turn = 0;         // 1: scoring tiles are dealt to the dies in turn (see tile_of)
-  int32_t* by_cost = nullptr;        // [A] the applications in the order their scoring tiles are numbered in: costly ones first where that matters
+  int32_t* by_cost = nullptr;        // [A] the applications, costly scoring tiles first (see tile_of)
+  int32_t* tile_costs = nullptr;     // [A] what a tile of each costs; null where that is about the same
   int A = 0, d = 0, H = 0, B = 0, Mmax = 0, Cmax = 0, dtype = 0;
   int64_t cap = 0;
   uint32_t* bufK[2] = {nullptr, nullptr};
@@ -405,17 +405,19 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   }
 
   {
-    // the numbers of classes, and behind them the order in which the applications' scoring tiles are numbered (see tile_of)
+    // the numbers of classes, behind them the order in which the applications' scoring tiles are numbered where they are dealt in
+    // turn, and what a tile of each costs (see tile_of)
     std::vector<int32_t> v(ncls);
     for (int a = 0; a < A; ++a) v.push_back(a);
     const auto cost = [&](int32_t a) { return tile_cost(c, ncls[a]); };
-    const auto [least, most] = std::minmax_element(v.begin() + A, v.end(), [&](int32_t a, int32_t b) { return cost(a) < cost(b); });
-    c->tiles_in_turn = 2 * cost(*most) > 3 * cost(*least) ? 1 : 0;
-    if (c->tiles_in_turn) std::stable_sort(v.begin() + A, v.end(), [&](int32_t a, int32_t b) { return cost(a) > cost(b); });
+    std::stable_sort(v.begin() + A, v.end(), [&](int32_t a, int32_t b) { return cost(a) > cost(b); });
+    const bool differ = 2 * cost(v[A]) > 3 * cost(v[2 * A - 1]);
+    for (int a = 0; a < A; ++a) v.push_back(cost(a));
     int32_t* at;
     if ((s = dev_upload(c, &at, v)) != SP_OK) return s;
     tb.n_classes = at;
     c->by_cost = at + A;
+    c->tile_costs = differ ? at + 2 * A : nullptr;
   }
 
   // window buffers
@@ -1034,7 +1036,7 @@ int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev,
                         const float* weight_dev) {
   const int A = c->A;
   Window& w = c->w;
-  SegArgs seg_args{n, A, nullptr, score_tile(c), n <= kMergeMax ? kRun : kSortTile, c->by_cost, c->tiles_in_turn, (int32_t)score_grid(c, n), w.seg,
+  SegArgs seg_args{n, A, nullptr, score_tile(c), n <= kMergeMax ? kRun : kSortTile, c->by_cost, c->tile_costs, (int32_t)score_grid(c, n), w.seg,
                    w.unit_start, w.tile_desc, c->sort_desc};
   // a long window's ordering needs its digit totals cleared
   uint32_t* zero = n > kMergeMax ? c->dtot_key : nullptr;

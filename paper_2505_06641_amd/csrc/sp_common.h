@@ -124,8 +124,8 @@ __device__ __forceinline__ int xcd_tile(int wg, int n_tiles) {
 }
 
 // The scoring tile a workgroup takes (the scoring kernels find its descriptor under their own number: a trip to memory less than
-// looking up the number of tiles first).  Where the applications' tiles cost about the same, every die gets a contiguous eighth of
-// them.  Where they differ (tile_cost), an eighth of the tiles is no eighth of the work (the dies' shares were 3,168 to
+// looking up the number of tiles first).  Where the dies' contiguous eighths of the tiles cost about the same, every die gets one.
+// Where they do not (tile_cost, dies_uneven), an eighth of the tiles is no eighth of the work (the dies' shares were 3,168 to
 // 99 class tiles for 200,003 requests of twelve applications of 2 to 1,000 classes, most of the chip idle at the end): the tiles
 // are then numbered from the most class tiles to the fewest and dealt to the dies in turn, so that every die gets an eighth of
 // every application and the small tiles fill the end: that scoring kernel takes 104 us instead of 263.  Weights are then pulled into

@@ -97,14 +97,15 @@ __device__ __forceinline__ uint4 wave_digit_bases(const uint32_t* __restrict__ t
 }
 
 // Where the applications' ranges start, the prefixes of scoring tiles and sort runs, and a descriptor for each of either, so that
-// a workgroup finds its place with a single load.  Scoring tiles are numbered application by application in the order of
-// by_cost (see tile_of), sort runs in ascending order.
+// a workgroup finds its place with a single load.  Scoring tiles are numbered application by application, in the order of
+// by_cost where they are dealt in turn (see tile_of), sort runs in ascending order.
 struct SegArgs {
   int32_t n, A;
   const uint32_t* sorted_app;   // application-sorted keys (not used where the counts of the ids are given)
   int32_t tile, unit;           // requests per scoring tile and per sort run
-  const int32_t* by_cost;       // [A]
-  int32_t in_turn, grid;        // how the tiles are dealt, and to how many workgroups (see tile_of)
+  const int32_t* by_cost;       // [A] applications, costly tiles first
+  const int32_t* cost;          // [A] what a scoring tile of each costs; null where that is about the same (tiles in contiguous eighths)
+  int32_t grid;                 // workgroups that the tiles are dealt to
   int32_t* seg;
   int32_t* unit_start;
   int4* tile_desc;
@@ -129,12 +130,31 @@ __device__ __forceinline__ int range_of(const int* start, int n, int i) {
   return lo;
 }
 
+// What the dies' contiguous eighths of a window's tiles cost: an application's tiles [first, first + count) added to them.
+__device__ __forceinline__ void add_to_dies(unsigned long long* dies, int first, int count, int cost, int n_tiles) {
+  const int per = (n_tiles + kXcds - 1) / kXcds, end = first + count;
+  if (count <= 0) return;                              // (else there are tiles)
+  for (int d = first / per; d * per < end; ++d) atomicAdd(&dies[d], (unsigned long long)(min(end, (d + 1) * per) - max(first, d * per)) * (unsigned)cost);
+}
+// Tiles are dealt in turn where the costliest eighth holds over 1/32 more than its share: as much as contiguous eighths gain
+// where they are even (weights in one L2).  us of the scoring kernel, contiguous / in turn, a million requests of 256 floats: 31 applications of
+// 1,000 classes and one of 10 1,531 / 1,546 (100,000 requests 189 / 193), 1,000 and 600 classes by turns (64 floats) 630 / 645; 16 of 1,000
+// and then 16 of 500 1,484 / 1,248, 32 from 1,000 down to 318 1,366 / 1,143; half a million, half of them of the one with 10: 801 / 516.
+__device__ __forceinline__ bool dies_uneven(const unsigned long long* dies) {
+  unsigned long long most = 0ull, sum = 0ull;
+  for (int d = 0; d < kXcds; ++d) {
+    most = dies[d] > most ? dies[d] : most;
+    sum += dies[d];
+  }
+  return 32ull * kXcds * most > 33ull * sum;
+}
+
 // The descriptors of all tiles and runs from the tables in LDS, by `threads` threads.
-__device__ __forceinline__ void write_descriptors(const SegArgs& g, const int* s_tile, const int* s_unit, const int* s_seg, const int* s_app,
+__device__ __forceinline__ void write_descriptors(const SegArgs& g, bool in_turn, const int* s_tile, const int* s_unit, const int* s_seg, const int* s_app,
                                                   int tid, int threads) {
   const int n_tiles = s_tile[g.A];
   for (int wg = tid; wg < g.grid; wg += threads) {                  // (application, first request, end of its range, 0)
-    const int t = tile_of(g.in_turn, wg, n_tiles);
+    const int t = tile_of(in_turn, wg, n_tiles);
     int4 d = make_int4(-1, 0, 0, 0);
     if (t >= 0) {
       const int k = range_of(s_tile, g.A, t), a = s_app[k];
@@ -173,32 +193,54 @@ __global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) {
   // prefixes of tiles and units over the applications: every thread takes a run of consecutive
   // applications, the runs' totals are scanned across the workgroup
   __shared__ int run_t[256], run_u[256];
+  __shared__ unsigned long long dies[kXcds];
   __shared__ int s_tile[kSegTable + 1], s_seg[kSegTable + 1], s_unit[kSegTable + 1], s_app[kSegTable];   // used when A <= kSegTable
   const int per = (A + 255) / 256;
   const int a_lo = min(A, tid * per), a_hi = min(A, a_lo + per);
+  const auto tiles_of = [&](int c) { return (seg[c + 1] - seg[c] + tile - 1) / tile; };
+  const auto scan_runs = [&] {
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {
+      const int t_up = tid >= o ? run_t[tid - o] : 0;
+      const int u_up = tid >= o ? run_u[tid - o] : 0;
+      __syncthreads();
+      run_t[tid] += t_up;
+      run_u[tid] += u_up;
+      __syncthreads();
+    }
+  };
   int ts = 0, us = 0;
+  bool in_turn = false;
+  if (g.cost != nullptr) {                             // (uniform)
+    if (tid < kXcds) dies[tid] = 0ull;
+    for (int k = a_lo; k < a_hi; ++k) ts += tiles_of(k);
+    run_t[tid] = ts;
+    run_u[tid] = 0;
+    scan_runs();
+    int first = run_t[tid] - ts;
+    for (int k = a_lo; k < a_hi; ++k) {
+      const int nt = tiles_of(k);
+      add_to_dies(dies, first, nt, g.cost[k], run_t[255]);
+      first += nt;
+    }
+    __syncthreads();
+    in_turn = dies_uneven(dies);
+    ts = 0;
+  }
+  const auto app_at = [&](int k) { return in_turn ? g.by_cost[k] : k; };
   for (int k = a_lo; k < a_hi; ++k) {
-    const int c = g.by_cost[k];
-    ts += (seg[c + 1] - seg[c] + tile - 1) / tile;
+    ts += tiles_of(app_at(k));
     us += (seg[k + 1] - seg[k] + unit - 1) / unit;
   }
-  run_t[tid] = ts;
+  run_t[tid] = ts;                                     // (read by others before the last barrier only)
   run_u[tid] = us;
-  __syncthreads();
-  for (int o = 1; o < 256; o <<= 1) {
-    const int t_up = tid >= o ? run_t[tid - o] : 0;
-    const int u_up = tid >= o ? run_u[tid - o] : 0;
-    __syncthreads();
-    run_t[tid] += t_up;
-    run_u[tid] += u_up;
-    __syncthreads();
-  }
+  scan_runs();
   const int ts0 = run_t[tid] - ts, us0 = run_u[tid] - us;   // exclusive prefixes of this thread's run
   const bool table = A <= kSegTable;
   ts = ts0;
   us = us0;
   for (int k = a_lo; k < a_hi; ++k) {
-    const int c = g.by_cost[k];
+    const int c = app_at(k);
     g.unit_start[k] = us;
     if (table) {
       s_tile[k] = ts;
@@ -206,7 +248,7 @@ __global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) {
       s_unit[k] = us;
       s_seg[k] = seg[k];
     }
-    ts += (seg[c + 1] - seg[c] + tile - 1) / tile;
+    ts += tiles_of(c);
     us += (seg[k + 1] - seg[k] + unit - 1) / unit;
   }
   if (tid == 255) {
@@ -219,20 +261,20 @@ __global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) {
   }
   __syncthreads();
   if (table) {
-    write_descriptors(g, s_tile, s_unit, s_seg, s_app, tid, 256);
+    write_descriptors(g, in_turn, s_tile, s_unit, s_seg, s_app, tid, 256);
   } else {
     ts = ts0;
     us = us0;
     for (int k = a_lo; k < a_hi; ++k) {
-      const int c = g.by_cost[k], cb = seg[c], ce = seg[c + 1], nt = (ce - cb + tile - 1) / tile;
+      const int c = app_at(k), cb = seg[c], ce = seg[c + 1], nt = tiles_of(c);
       const int sb = seg[k], se = seg[k + 1], nu = (se - sb + unit - 1) / unit;
-      for (int t = 0; t < nt; ++t) g.tile_desc[workgroup_of(g.in_turn, ts + t, run_t[255])] = make_int4(c, cb + t * tile, ce, 0);
+      for (int t = 0; t < nt; ++t) g.tile_desc[workgroup_of(in_turn, ts + t, run_t[255])] = make_int4(c, cb + t * tile, ce, 0);
       for (int u = 0; u < nu; ++u) g.sort_desc[us + u] = make_int4(sb, sb + u * unit, se, 0);
       ts += nt;
       us += nu;
     }
     for (int wg = tid; wg < g.grid; wg += 256)
-      if (tile_of(g.in_turn, wg, run_t[255]) < 0) g.tile_desc[wg] = make_int4(-1, 0, 0, 0);
+      if (tile_of(in_turn, wg, run_t[255]) < 0) g.tile_desc[wg] = make_int4(-1, 0, 0, 0);
   }
 }
 
@@ -629,10 +671,13 @@ __device__ __forceinline__ void group_sums_self(const int32_t* __restrict__ app,
 }
 
 // The segments from the number of requests of every application (and of invalid ids, total[A]), at most 255 of them: one thread
-// per application, tables in LDS, three barriers (k_group_place takes 4.0 us for 256 requests where tables in memory took 4.8).
-__device__ __forceinline__ void segments_from_totals(const SegArgs& g, const Window& w, const uint32_t* total, int costly /*by_cost[tid]*/) {
+// per application, tables in LDS, three barriers (k_group_place takes 4.0 us for 256 requests where tables in memory took 4.8), two
+// more where tiles differ in cost.
+__device__ __forceinline__ void segments_from_totals(const SegArgs& g, const Window& w, const uint32_t* total, int costly /*by_cost[tid]*/,
+                                                     int cost /*cost[tid], or 0*/) {
   __shared__ int s_seg[257], s_tile[257], s_unit[257], s_app[256];
-  __shared__ int wave_t[4], wave_u[4];
+  __shared__ int wave_t[4], wave_u[4], wave_i[4];
+  __shared__ unsigned long long dies[kXcds];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, A = g.A;
   if (wave == 0) {
     const uint4 b = wave_digit_bases(total, 0u, lane);
@@ -641,15 +686,28 @@ __device__ __forceinline__ void segments_from_totals(const SegArgs& g, const Win
     s_seg[4 * lane + 2] = (int)b.z;
     s_seg[4 * lane + 3] = (int)b.w;
     if (lane == 0) s_seg[256] = g.n;
+    if (lane < kXcds) dies[lane] = 0ull;
   }
   __syncthreads();
   if (tid <= A + 1) g.seg[tid] = s_seg[tid];                        // seg[A] = number of valid requests, seg[A+1] = n
+  bool in_turn = false;
+  if (g.cost != nullptr) {                                          // (uniform)
+    const int nt = tid < A ? (s_seg[tid + 1] - s_seg[tid] + g.tile - 1) / g.tile : 0;
+    int first = (int)wave_scan_incl((uint32_t)nt) - nt;
+    if (lane == 63 && wave < 4) wave_i[wave] = first + nt;
+    __syncthreads();
+    for (int v = 0; v < min(wave, 4); ++v) first += wave_i[v];
+    if (tid < A) add_to_dies(dies, first, nt, cost, wave_i[0] + wave_i[1] + wave_i[2] + wave_i[3]);
+    __syncthreads();
+    in_turn = dies_uneven(dies);
+  }
   int ts = 0, us = 0, ti = 0, ui = 0;
   if (tid < 256) {
     if (tid < A) {
+      const int c = in_turn ? costly : tid;
       plain_group(w, tid, s_seg[tid], s_seg[tid + 1]);
-      s_app[tid] = costly;
-      ts = (s_seg[costly + 1] - s_seg[costly] + g.tile - 1) / g.tile;
+      s_app[tid] = c;
+      ts = (s_seg[c + 1] - s_seg[c] + g.tile - 1) / g.tile;
       us = (s_seg[tid + 1] - s_seg[tid] + g.unit - 1) / g.unit;
     }
     ti = (int)wave_scan_incl((uint32_t)ts);
@@ -676,7 +734,7 @@ __device__ __forceinline__ void segments_from_totals(const SegArgs& g, const Win
     }
   }
   __syncthreads();
-  write_descriptors(g, s_tile, s_unit, s_seg, s_app, tid, kGroupThreads);
+  write_descriptors(g, in_turn, s_tile, s_unit, s_seg, s_app, tid, kGroupThreads);
 }
 
 // Every request to its grouped position (applications in ascending order, request ids ascending inside), with its deadline
@@ -696,8 +754,8 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
   __shared__ uint32_t red[kGroupWaves][2][64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (blockIdx.x == 0) {              // (the first: as the last it would wait for a place on a full chip)
-    const int costly = sg.by_cost[min(tid, A - 1)];
-    loaded_here(costly);
+    const int costly = sg.by_cost[min(tid, A - 1)], cost = sg.cost != nullptr ? sg.cost[min(tid, A - 1)] : 0;
+    loaded_here(costly); loaded_here(cost);
     if constexpr (SELF > 0) {
       if (tid == 0) reset_state(st);
       group_sums_self<SELF>(app, n, 0, kTile, A, before, total, red);
@@ -705,7 +763,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
       group_sums(counts, n_tiles, 0, A, nbits, before, total, red);
     }
     if (tid == 0 && total[A] != 0u) atomicOr(&st->err, kErrApp);
-    segments_from_totals(sg, sw, total, costly);
+    segments_from_totals(sg, sw, total, costly, cost);
     return;
   }
   // neighbouring tiles write neighbouring runs of every application: on one die, so that the lines they meet in are whole

@@ -1494,6 +1494,13 @@ def test_scoring_tiles_dealt_by_their_cost(gpu, n, classes, hidden):
     full_parity(gpu, w, max_rounds=4)
 
 
+@pytest.mark.parametrize("n,A", [(3, 16), (2048, 16), (16391, 16), (5000, 304)])
+def test_scoring_tiles_in_even_eighths(gpu, n, A):
+    """Large and small heads by turns: the dies' contiguous eighths cost the same although the tiles do not."""
+    w = wl.tiny(seed=950 + A, n=n, classes=(300, 20) * (A // 2), models=(2,) * A, max_batch=8, feat_dim=40, deadline=(4.0, 80.0))
+    full_parity(gpu, w, max_rounds=4)
+
+
 @pytest.mark.parametrize("name", ["sneakpeek", "alg1", "maxacc_edf"])
 @pytest.mark.parametrize("A,M,B,n,due,fractions", [
     (1, 1, 1, 40, (5.0, 60.0), None), (3, 4, 31, 3000, (5.0, 150.0), (0.9, 0.09, 0.01)), (2, 9, 64, 5000, (30.0, 400.0), None),
@@ -1633,8 +1640,8 @@ def test_scores_that_are_no_numbers_win_on_every_route(gpu, A, M, B, edf):
 @pytest.mark.parametrize("density", [0.0004, 0.01, 0.2])
 @pytest.mark.parametrize("n,A,B", [(1030, 1, 16), (5125, 1, 64), (20000, 2, 33), (70001, 1, 20)])
 def test_single_rounds_past_long_stretches_of_the_dead(gpu, n, A, B, density):
-    """Queues of which few are live, anywhere in service order: the walk of the one-workgroup round, 1,024 positions and then 4,096 a
-    step, against two kernels per round, to the last bit, and sp_schedule of one round against both.  The dead ones miss the first
+    """Queues of which few are live, anywhere in service order: the walk of the one-workgroup round, 2,048 positions a step,
+    against two kernels per round, to the last bit, and sp_schedule of one round against both.  The dead ones miss the first
     round by one float, half of the live ones just make it."""
     torch, binding = gpu
     w = wl.tiny(seed=9700 + n, n=n, classes=(3,) * A, models=(3,) * A, max_batch=B, feat_dim=16, deadline=(40.0, 900.0))
