@@ -332,11 +332,13 @@ int32_t sp_max_classes(const sp_ctx* ctx);
 /* How sp_schedule runs the greedy rounds (Alg. 1, Sec. 5.2) on this context: 1 = all rounds of a chunk in
  * one launch (every (application, variant) pair fits on the device at once and, with group splitting, no
  * application of the scored window has more than 64 groups: after sp_score the call waits for that count),
- * 0 = two kernels per round.  The decisions are the same either way.  A round that is a call of its own
- * (sp_greedy_round, sp_greedy_round_static, sp_schedule with max_rounds 1) is one launch of one workgroup
- * where the profile is small (up to 15 applications, batches of up to 64, some 30,000 evaluations, no group
- * splitting); else sp_greedy_round takes two kernels. */
+ * 0 = two kernels per round.  The decisions are the same either way. */
 int32_t sp_rounds_in_one_launch(const sp_ctx* ctx);
+/* How a round that is a call of its own runs (sp_greedy_round, sp_greedy_round_static; sp_schedule with max_rounds 1 on contexts whose
+ * rounds run in one launch) under the current policy: 1 = one launch of one workgroup, where the profile is small (up to 15
+ * applications, batches of up to 64, some 30,000 evaluations, no group splitting), 0 = two kernels (sp_schedule: the launch of
+ * resident workgroups).  The decisions are the same either way. */
+int32_t sp_rounds_in_one_workgroup(const sp_ctx* ctx);
 
 /*
  * Test hook, not on the hot path (implements nothing of the paper).  The one-launch rounds kernel tags the words
@@ -354,7 +356,9 @@ sp_status sp_debug_set_generation(sp_ctx* ctx, uint32_t generation);
  * bounded polling; a wait that runs out (the device is shared with other long-running work and the grid is
  * not resident as a whole) makes every workgroup leave, sp_schedule return SP_EDEVICE, and the context use
  * two kernels per round from then on (the window has to be scored again).  polls > 0 shortens the bound so
- * that a test can take that path with every kernel still ending normally; 0 restores the default (2^20).
+ * that a test can take that path with every kernel still ending normally; 0 restores the default (2^20).  While a
+ * bound is set, no round runs in one workgroup (see sp_rounds_in_one_workgroup): rounds that are calls of their own take two
+ * kernels, sp_schedule with max_rounds 1 the resident workgroups that the bound is for.
  * SP_EINVAL: ctx NULL or polls < 0.
  */
 sp_status sp_debug_set_spin_limit(sp_ctx* ctx, int32_t polls);

@@ -22,7 +22,7 @@ SP_DUMP_ORDER, SP_DUMP_SEGMENTS, SP_DUMP_SCORE_CUBE, SP_DUMP_LOGITS = 0, 1, 2, 3
 
 EXPORTS = ["sp_create", "sp_destroy", "sp_score", "sp_greedy_round", "sp_greedy_round_static", "sp_schedule", "sp_debug_dump",
            "sp_strerror", "sp_last_hip_error", "sp_max_models", "sp_max_classes",
-           "sp_rounds_in_one_launch", "sp_debug_mfma_rate", "sp_debug_copy_rate", "sp_debug_set_generation", "sp_debug_set_spin_limit", "sp_debug_set_sort_spin_limit", "sp_set_prior", "sp_set_swap_cost", "sp_set_policy",
+           "sp_rounds_in_one_launch", "sp_rounds_in_one_workgroup", "sp_debug_mfma_rate", "sp_debug_copy_rate", "sp_debug_set_generation", "sp_debug_set_spin_limit", "sp_debug_set_sort_spin_limit", "sp_set_prior", "sp_set_swap_cost", "sp_set_policy",
            "sp_set_timing", "sp_get_timing", "sp_get_round_times"]
 
 
@@ -132,6 +132,8 @@ def load_library(path: Optional[str] = None):
     lib.sp_set_swap_cost.restype = C.c_int
     lib.sp_rounds_in_one_launch.argtypes = [vp]
     lib.sp_rounds_in_one_launch.restype = C.c_int32
+    lib.sp_rounds_in_one_workgroup.argtypes = [vp]
+    lib.sp_rounds_in_one_workgroup.restype = C.c_int32
     lib.sp_debug_set_generation.argtypes = [vp, C.c_uint32]
     lib.sp_debug_set_generation.restype = C.c_int
     lib.sp_debug_set_spin_limit.argtypes = [vp, C.c_int32]

@@ -1687,6 +1687,8 @@ int32_t sp_rounds_in_one_launch(const sp_ctx* c) {
   return (g.ok && rounds_in_one_launch(const_cast<sp_ctx*>(c))) ? 1 : 0;
 }
 
+int32_t sp_rounds_in_one_workgroup(const sp_ctx* c) { return c && round_single(c) ? 1 : 0; }
+
 sp_status sp_debug_set_spin_limit(sp_ctx* c, int32_t polls) {
   if (!c || polls < 0) return SP_EINVAL;
   c->spin_limit = polls == 0 ? kSpinLimit : polls;

@@ -1501,16 +1501,16 @@ def test_scoring_tiles_in_even_eighths(gpu, n, A):
     full_parity(gpu, w, max_rounds=4)
 
 
-@pytest.mark.parametrize("name", ["sneakpeek", "alg1", "maxacc_edf"])
+@pytest.mark.parametrize("name", ["sneakpeek", "alg1", "maxacc_edf", "group first"])
 @pytest.mark.parametrize("A,M,B,n,due,fractions", [
-    (1, 1, 1, 40, (5.0, 60.0), None), (3, 4, 31, 3000, (5.0, 150.0), (0.9, 0.09, 0.01)), (2, 9, 64, 5000, (30.0, 400.0), None),
+    (1, 1, 1, 40, (5.0, 60.0), None), (3, 4, 31, 3000, (5.0, 150.0), (0.9, 0.09, 0.01)), (2, 6, 64, 5000, (30.0, 400.0), None),
     (15, 2, 33, 4000, (20.0, 300.0), None), (2, 3, 20, 30000, (4.0, 200.0), (0.97, 0.03)), (1, 16, 58, 63, (50.0, 500.0), None)],
     ids=["one of each", "short windows", "batches of 64", "fifteen applications", "mostly dead", "fewer than a wavefront"])
 def test_single_rounds_in_one_workgroup(gpu, name, A, M, B, n, due, fractions):
     """A round per call in one launch of one workgroup against two kernels per round: the same decisions and members to the last
     bit, also with swap-in costs, from the first round until nothing is live."""
     torch, binding = gpu
-    policy = wl.named_policy(name)
+    policy = wl.Policy(select=wl.SELECT_GROUP_FIRST) if name == "group first" else wl.named_policy(name)
     w = wl.tiny(seed=9100 + n, n=n, classes=(3,) * A, models=tuple(max(1, M - a % 3) for a in range(A)), max_batch=B, feat_dim=16, deadline=due,
                 alpha=(0.5, 20.0), beta=(0.05, 2.5), fractions=fractions)
     w.profile.penalty[:] = [(wl.PEN_SIGMOID, wl.PEN_LINEAR, wl.PEN_STEP)[a % 3] for a in range(A)]
@@ -1518,6 +1518,7 @@ def test_single_rounds_in_one_workgroup(gpu, name, A, M, B, n, due, fractions):
     args = binding.to_device(w.requests)
     ctxs = [binding.Context(w.profile, n, policy=policy) for _ in range(2)]
     ctxs[1].sp_debug_set_spin_limit(1 << 19)            # (any bound but the default keeps this kernel out)
+    assert [c.lib.sp_rounds_in_one_workgroup(c.h) for c in ctxs] == [1, 0]
     ids = [torch.full((B,), -1, dtype=torch.int32, device="cuda:0") for _ in range(2)]
     for c in ctxs:
         c.sp_score(*args)
@@ -1611,6 +1612,7 @@ def test_scores_that_are_no_numbers_win_on_every_route(gpu, A, M, B, edf):
     args = binding.to_device(w.requests)
     ctxs = [binding.Context(w.profile, n, policy=policy) for _ in range(3)]
     ctxs[1].sp_debug_set_spin_limit(1 << 19)          # (two kernels per round)
+    assert [c.lib.sp_rounds_in_one_workgroup(c.h) for c in ctxs] == [1, 0, 1]
     ids = [torch.full((B,), -1, dtype=torch.int32, device="cuda:0") for _ in range(2)]
     for c in ctxs:
         c.sp_score(*args)
@@ -1660,6 +1662,7 @@ def test_single_rounds_past_long_stretches_of_the_dead(gpu, n, A, B, density):
     args = binding.to_device(w.requests)
     ctxs = [binding.Context(w.profile, n) for _ in range(3)]
     ctxs[1].sp_debug_set_spin_limit(1 << 19)            # (two kernels per round)
+    assert [c.lib.sp_rounds_in_one_workgroup(c.h) for c in ctxs] == [1, 0, 1]
     ids = [torch.full((B,), -1, dtype=torch.int32, device="cuda:0") for _ in range(2)]
     for c in ctxs:
         c.sp_score(*args)
