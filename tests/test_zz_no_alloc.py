@@ -2,9 +2,11 @@
 candidates through the library's static device array) against sp_greedy_round, through the C ABI.
 
 Two windows in a row on the same GPU, the second smaller in every dimension (fewer applications,
-variants, batch sizes and requests), so that the static array still holds the first window's words
-when the second one runs.  Both entry points start from identically scored contexts; every round's
-decision record, status and member ids must be bit-identical, and so must the schedule that follows.
+variants, batch sizes and requests) and still too large for a round in one workgroup, which exchanges
+nothing through memory: the static array still holds the first window's words when the second one
+runs.  Then one whose rounds run in one workgroup, through either entry point.  Both entry points start
+from identically scored contexts; every round's decision record, status and member ids must be
+bit-identical, and so must the schedule that follows.
 """
 import numpy as np
 import pytest
@@ -24,7 +26,7 @@ def gpu():
     return torch, binding
 
 
-def rounds_both_ways(gpu, w, n_rounds):
+def rounds_both_ways(gpu, w, n_rounds, one_workgroup):
     """n_rounds single-round calls on two contexts of the same window: one through each entry point."""
     torch, binding = gpu
     p, rq = w.profile, w.requests
@@ -33,6 +35,7 @@ def rounds_both_ways(gpu, w, n_rounds):
     got = {}
     for name in ("sp_greedy_round", "sp_greedy_round_static"):
         ctx = binding.Context(p, rq.n)
+        assert ctx.lib.sp_rounds_in_one_workgroup(ctx.h) == one_workgroup
         ctx.sp_score(x, app, D, wt)
         ids = torch.full((B,), -1, dtype=torch.int32, device="cuda:0")
         recs = []
@@ -68,12 +71,14 @@ def assert_same(ref, new):
 
 def test_static_round_matches_twice_in_a_row_second_window_smaller(gpu):
     big = wl.make("cfg4", n_requests=8192)       # 8 applications, 8 variants, batch sizes up to 64
-    small = wl.make("cfg2", n_requests=700)      # 3 applications, 4 variants, batch sizes up to 32
-    ref, new = rounds_both_ways(gpu, big, 12)
+    small = wl.tiny(seed=7, n=700, classes=(9,) * 7, models=(7,) * 7, max_batch=48, feat_dim=16, deadline=(20.0, 200.0))
+    tiny = wl.make("cfg2", n_requests=700)       # 3 applications, 4 variants, batch sizes up to 32: one workgroup
+    ref, new = rounds_both_ways(gpu, big, 12, 0)
     assert any(r[1] is not None and r[1]["batch"] > 1 for r in ref[0])
     assert_same(ref, new)
-    ref, new = rounds_both_ways(gpu, small, 12)
-    assert_same(ref, new)
+    for w, one_workgroup in ((small, 0), (tiny, 1)):
+        ref, new = rounds_both_ways(gpu, w, 12, one_workgroup)
+        assert_same(ref, new)
 
 
 def test_static_round_status_codes(gpu):
