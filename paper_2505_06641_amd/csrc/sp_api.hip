@@ -37,7 +37,7 @@ struct sp_ctx {
   Window w{};
   std::vector<void*> dev_allocs;
   int32_t* by_cost = nullptr;        // [A] the applications, costly scoring tiles first (see tile_of)
-  int32_t* tile_costs = nullptr;     // [A] what a tile of each costs; null where that is about the same
+  int32_t* tile_costs = nullptr;     // [A] what a tile of each costs; null where that is the same
   int A = 0, d = 0, H = 0, B = 0, Mmax = 0, Cmax = 0, dtype = 0;
   int64_t cap = 0;
   uint32_t* bufK[2] = {nullptr, nullptr};
@@ -324,11 +324,12 @@ int score_tile(const sp_ctx* c);
 int64_t score_grid(const sp_ctx* c, int64_t n);
 
 // What a scoring tile of an application of C classes costs, roughly, in units of a class tile: the kernel that walks the classes
-// spends about three on its prologue, heads with a hidden layer about ten on the layer and the prologue; the streaming kernel's
-// logistic heads are bound by reading the rows, once per group of classes.
+// spends about five on its prologue (5.2 to 6.0 for 64 to 256 features, from kernel times over 32 to 1,024 classes), heads with a
+// hidden layer about ten on the layer and the prologue (7.7 to 11.2 for the heads measured, 17 for 256 features and 24 units); the
+// streaming kernel's logistic heads are bound by reading the rows, once per group of classes.
 int tile_cost(const sp_ctx* c, int C) {
   const int CT = (C + kClassTile - 1) / kClassTile;
-  if (c->mfma_D > 0) return 3 + CT;
+  if (c->mfma_D > 0) return 5 + CT;
   if (c->stream_nb > 0 && c->H == 0) return (CT + c->stream_nb - 1) / c->stream_nb;
   return 10 + CT;
 }
@@ -411,7 +412,7 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
     for (int a = 0; a < A; ++a) v.push_back(a);
     const auto cost = [&](int32_t a) { return tile_cost(c, ncls[a]); };
     std::stable_sort(v.begin() + A, v.end(), [&](int32_t a, int32_t b) { return cost(a) > cost(b); });
-    const bool differ = 2 * cost(v[A]) > 3 * cost(v[2 * A - 1]);
+    const bool differ = 32 * cost(v[A]) > 33 * cost(v[2 * A - 1]);       // (else no window's eighths can: see dies_uneven)
     for (int a = 0; a < A; ++a) v.push_back(cost(a));
     int32_t* at;
     if ((s = dev_upload(c, &at, v)) != SP_OK) return s;

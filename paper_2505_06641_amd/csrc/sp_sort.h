@@ -104,7 +104,7 @@ struct SegArgs {
   const uint32_t* sorted_app;   // application-sorted keys (not used where the counts of the ids are given)
   int32_t tile, unit;           // requests per scoring tile and per sort run
   const int32_t* by_cost;       // [A] applications, costly tiles first
-  const int32_t* cost;          // [A] what a scoring tile of each costs; null where that is about the same (tiles in contiguous eighths)
+  const int32_t* cost;          // [A] what a scoring tile of each costs; null where that is the same (tiles in contiguous eighths)
   int32_t grid;                 // workgroups that the tiles are dealt to
   int32_t* seg;
   int32_t* unit_start;
@@ -139,7 +139,8 @@ __device__ __forceinline__ void add_to_dies(unsigned long long* dies, int first,
 // Tiles are dealt in turn where the costliest eighth holds over 1/32 more than its share: as much as contiguous eighths gain
 // where they are even (weights in one L2).  us of the scoring kernel, contiguous / in turn, a million requests of 256 floats: 31 applications of
 // 1,000 classes and one of 10 1,531 / 1,546 (100,000 requests 189 / 193), 1,000 and 600 classes by turns (64 floats) 630 / 645; 16 of 1,000
-// and then 16 of 500 1,484 / 1,248, 32 from 1,000 down to 318 1,366 / 1,143; half a million, half of them of the one with 10: 801 / 516.
+// and then 16 of 850 1,540 / 1,460, of 680 1,535 / 1,350 (100,000 requests 188 / 171), of 500 1,484 / 1,248, 32 from 1,000 down to 318
+// 1,366 / 1,143; half a million, half of them of the one with 10: 801 / 516.
 __device__ __forceinline__ bool dies_uneven(const unsigned long long* dies) {
   unsigned long long most = 0ull, sum = 0ull;
   for (int d = 0; d < kXcds; ++d) {
@@ -601,9 +602,10 @@ __device__ __forceinline__ void group_sums(const uint32_t* __restrict__ counts, 
 
 // Short windows of few applications: a workgroup counts the whole window itself, in one trip to memory, which spares the launch
 // before it: 3.6 us for 256 requests where two launches take 1.7 + 4.2, 5.1 for 4,096 (2.4 + 5.0), 5.8 for 16,384 (2.8 + 5.1), 7.2 for
-// 32,768 (3.9 + 5.5), and the gap between them.  Per call 34.5 -> 31.7 us, 157.0 -> 154.6, 90.4 -> 87.1, 68.6 -> 67.9: the ids that every
-// workgroup reads, 128 KB at the end of this range, take up what is saved soon after.  Eight bits per application and thread, up to
-// kGroupSelfApps applications and the invalid ids.
+// 32,768 (3.9 + 5.5), and the gap between them.  The ids that every workgroup reads are 128 KB at the end of this range; at twice the ids
+// per thread it is the slower way: us per scoring call of three applications, one launch / two, 44.2 / 45.6 (32,768 requests), 46.3 / 45.7
+// (32,769), 47.1 / 46.2 (40,000), 49.9 / 48.7 (65,535); with one application and with seven the same.  Eight bits per application and
+// thread, up to kGroupSelfApps applications and the invalid ids.
 constexpr int kGroupSelf = 32768, kGroupSelfApps = 7;
 
 // What group_sums gives, from the ids themselves; n <= 2,048 QUADS.
