@@ -1482,11 +1482,14 @@ def test_weights_and_features_at_the_ends_of_the_range(gpu, dtype, d, H, f):
 
 
 @pytest.mark.parametrize("n,classes,hidden", [
-    (5, (2, 300, 40), 0), (1021, (300, 2, 33, 161, 64, 1, 97), 0), (20011, (4, 700, 4, 130), 0),
-    (3000, tuple(2 + 37 * (a % 9) for a in range(300)), 0), (2500, (5, 400, 60), 24)],
-    ids=["fewer tiles than dies", "one or two tiles each", "many tiles", "more than 255 applications", "hidden layer"])
+    (5, (2, 300, 40), 0), (1021, (300, 2, 33, 161, 64, 1, 97), 0), (20011, (4, 700, 4, 130), 0), (68011, (4, 300, 4, 130), 0),
+    (3000, tuple(2 + 37 * (a % 9) for a in range(300)), 0), (3000, tuple(2 + 37 * (a % 9) for a in range(253)), 0), (2500, (5, 400, 60), 24),
+    (40003, (5, 140, 60), 24)],
+    ids=["fewer tiles than dies", "one or two tiles each", "fewer tiles than compute units", "many tiles", "more than 255 applications",
+         "253 applications", "hidden layer", "hidden layer, many tiles"])
 def test_scoring_tiles_dealt_by_their_cost(gpu, n, classes, hidden):
-    """Applications of very different class counts: tiles are numbered from the costliest application to the cheapest."""
+    """Applications of very different class counts: beyond a tile per compute unit (256) tiles are numbered from the costliest
+    application to the cheapest."""
     A = len(classes)
     f = np.array([3.0 if a % 3 == 0 else 0.02 if a % 3 == 1 else 1.0 for a in range(A)])
     w = wl.tiny(seed=900 + A, n=n, classes=classes, models=tuple(1 + a % 4 for a in range(A)), max_batch=8, feat_dim=40,
@@ -1494,7 +1497,7 @@ def test_scoring_tiles_dealt_by_their_cost(gpu, n, classes, hidden):
     full_parity(gpu, w, max_rounds=4)
 
 
-@pytest.mark.parametrize("n,A", [(3, 16), (2048, 16), (16391, 16), (5000, 304)])
+@pytest.mark.parametrize("n,A", [(3, 16), (2048, 16), (68007, 16), (5000, 304)])
 def test_scoring_tiles_in_even_eighths(gpu, n, A):
     """Large and small heads by turns: the dies' contiguous eighths cost the same although the tiles do not."""
     w = wl.tiny(seed=950 + A, n=n, classes=(300, 20) * (A // 2), models=(2,) * A, max_batch=8, feat_dim=40, deadline=(4.0, 80.0))
