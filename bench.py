@@ -301,7 +301,7 @@ def main():
                      "ms_per_step_with_all_stage_events": ms_per_step_all_events},
         "roofline": roof,
     }
-    # utility evaluations the rounds really performed (per round and (group, variant): nb (nb + 1) / 2 terms
+    # utility evaluations behind the rounds' candidates (per round and (group, variant): nb (nb + 1) / 2 terms
     # for a candidate window of nb requests), counted by the kernels themselves
     r_ms = float(np.mean(rounds_ms))
     out["utility_evaluations"] = {"per_step": int(n_evals), "per_round_mean": float(n_evals) / max(1, n_rounds),

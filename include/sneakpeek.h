@@ -144,7 +144,10 @@ typedef struct {
                               rounds kernel instead)                                          */
   int64_t utility_evaluations;  /* terms key * EA * (1 - penalty) summed by the rounds of the
                               window so far: per round and (group, variant), nb (nb + 1) / 2
-                              for a candidate window of nb requests (nb under SP_BATCH_WHOLE) */
+                              for a candidate window of nb requests (nb under SP_BATCH_WHOLE).
+                              A round's candidates count whether or not its kernel has to
+                              evaluate them: with SP_SELECT_GROUP_FIRST a round in one
+                              workgroup evaluates the chosen application's alone            */
 } sp_timing;
 
 /* Application registration (Sec. 3.2 "System Architecture": owners upload

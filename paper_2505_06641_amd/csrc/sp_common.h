@@ -68,7 +68,7 @@ struct State {
   int32_t done;               // 1 once a round found nothing live
   uint32_t err;               // kErr* bits
   int32_t pad;
-  unsigned long long n_evals; // utility evaluations (terms of the candidates' sums) by the rounds so far
+  unsigned long long n_evals; // terms of the candidates' sums of the rounds so far (a kernel may evaluate fewer, see sp_timing)
   Decision last;              // the most recent committed batch
 };
 

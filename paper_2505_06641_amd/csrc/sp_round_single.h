@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
     // first position that may still be live, for the next round
     const int skip = wave == a ? b : 0, held = held_s[wave];
     w.head[((r + (a >= 0 ? 1 : 0)) & 1) * w.gcap + wave] = skip < held ? meta[wave * kSingleCap + skip].x : scan_s[wave];
-    atomicAdd(&st->n_evals, triangle_evals(min(held, Bw), tb.pol_whole) * (unsigned long long)tb.n_models[wave]);
+    atomicAdd(&st->n_evals, triangle_evals(min(held, Bw), tb.pol_whole) * (unsigned long long)tb.n_models[wave]);   // (as every route counts)
   }
   if (wave != kSingleWaves - 1) return;
   // ---- the batch: outputs, pending flags, the three sums (one member per lane, in the order of commit_members), the state ----
