@@ -146,7 +146,8 @@ namespace {
 // waits for them.
 class ResidentRoom {
  public:
-  bool take(int device, int cus, int64_t workgroups, int per_cu) {
+  // Waits up to `patience`.
+  bool take(int device, int cus, int64_t workgroups, int per_cu, std::chrono::milliseconds patience) {
     const int kind = std::min(per_cu, 8);
     workgroups = (workgroups + kXcds - 1) / kXcds * kXcds;
     Residents& r = g_residents[device];
@@ -157,7 +158,7 @@ class ResidentRoom {
       return r.workgroups == 0 || r.workgroups + workgroups <= (int64_t)least * cus;
     };
     std::unique_lock<std::mutex> lock(g_residents_mu);
-    if (!g_residents_left.wait_for(lock, std::chrono::seconds(2), fits)) return false;
+    if (!g_residents_left.wait_for(lock, patience, fits)) return false;
     r.workgroups += workgroups;
     ++r.grids[kind];
     held_ = &r;
@@ -685,12 +686,13 @@ void launch_score_stream(sp_ctx* c, hipStream_t s, const void* x, const int32_t*
 #undef SP_LAUNCH_ST
 }
 
-// Whether a resident grid leaves a third of the device to other streams' kernels, whose workgroups come and go while it gathers
-// (the largest grid, 514 workgroups, takes two thirds of it at three per compute unit; 498 of 512 places took all of it, and waits
-// ran out beside a stream of small kernels).  us per round with two / three workgroups per compute unit, 330 pairs: 4.48 / 4.64
-// (batches of 12), 5.4 / 5.5 (64), 6.66 / 6.64 (128), with subgroups 7.9 / 9.9, 12.8 / 15.1, 16.4 / 18.5; 496 pairs: 4.43 / 4.64, 5.7 /
-// 5.8, 6.9 / 6.9, 8.3 / 10.5, 12.8 / 15.2, 15.5 / 17.9.
-bool room_to_share(int cus, int per_cu, size_t workgroups) { return 3 * workgroups <= 2 * (size_t)per_cu * (size_t)cus; }
+// Whether a grid of two workgroups per compute unit leaves room for other streams' kernels: at most one of its own on each.  Beside
+// one there is room for a workgroup of three to a unit, but not for a second of two as long as smaller ones take every register that
+// is given back, and the launch waits in vain for the rest of its grid (beside two streams of matrix products and one of elementwise
+// kernels 336, 384 and 496 pairs lost waits with two to a unit, none up to 255; with three to a unit none up to 496).  us per round with two /
+// three workgroups per compute unit, 240 pairs: 4.1 / 4.2 (batches of 12), 4.9 / 5.0 (64), 6.1 / 6.0 (128), with subgroups 7.5 / 9.1, 11.8
+// / 13.4, 15.0 / 16.5; 330 pairs: 4.5 / 4.6, 5.4 / 5.5, 6.7 / 6.6, 7.9 / 9.9, 12.8 / 15.1, 16.4 / 18.5.
+bool room_to_share(int cus, size_t workgroups) { return workgroups <= (size_t)cus; }
 
 // The one-launch rounds path needs every (application, variant) pair plus the commit workgroup resident at
 // once; contexts too large for that keep the two-kernels-per-round path.
@@ -717,13 +719,13 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
   if (n_pairs == 0 || n_pairs > (size_t)kMaxPairs || ring > ((size_t)32 << 20)) return SP_OK;
   int cus = 0, per_cu = 0, rate_khz = 0;
   if ((cus = c->cus) <= 0) return SP_OK;
-  // the instantiation with more registers where the grid takes up to two thirds of the device with it
+  // the instantiation with more registers where the grid takes up to one place per compute unit
   c->persist_wgs = 2;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds_persistent<false, 2>, kRoundThreads, 0) != hipSuccess) {
     (void)hipGetLastError();
     return SP_OK;
   }
-  if (!room_to_share(cus, per_cu, n_pairs + 2)) {
+  if ((size_t)per_cu * (size_t)cus < n_pairs + 2 || !room_to_share(cus, n_pairs + 2)) {
     c->persist_wgs = 3;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds_persistent<false, 3>, kRoundThreads, 0) != hipSuccess) {
       (void)hipGetLastError();
@@ -1399,8 +1401,17 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
     if (chunk <= 0) break;
     const bool single = persist && chunk == 1 && round_single(c);
     ResidentRoom room;                                           // (until the launch has been waited for)
-    if (persist && !single)
-      persist = room.take(c->device, c->cus, (int64_t)c->ps.n_pairs + 2, c->tb.pol_split ? c->persist_split_per_cu : c->persist_per_cu);
+    if (persist && !single) {
+      const auto take = [&](int ms) {
+        return room.take(c->device, c->cus, (int64_t)c->ps.n_pairs + 2, c->tb.pol_split ? c->persist_split_per_cu : c->persist_per_cu,
+                         std::chrono::milliseconds(ms));
+      };
+      // (a call that has to wait lets its stream reach the launch first, so that it does not hold the room while other work runs)
+      if (!take(0)) {
+        SP_HIP(c, hipStreamSynchronize(s));
+        persist = take(2000);
+      }
+    }
     const int32_t before = c->rounds_done;
     const Outputs outs{model_out_dev, round_out_dev, order_out_dev, util_out_dev};
     const bool want_outputs = c->n > 0 && (model_out_dev || round_out_dev || order_out_dev || util_out_dev);
@@ -1658,7 +1669,7 @@ sp_status sp_set_policy(sp_ctx* c, const sp_policy* p) {
       const auto fits = [&](auto kernel) {
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kRoundThreads, dyn) == hipSuccess && (size_t)per_cu * (size_t)cus >= need;
       };
-      const auto fits_beside_others = [&](auto kernel) { return fits(kernel) && room_to_share(cus, per_cu, need); };
+      const auto fits_beside_others = [&](auto kernel) { return fits(kernel) && room_to_share(cus, need); };
       c->persist_split_wgs = fits_beside_others(k_rounds_persistent<true, 2>) ? 2 : 3;
       c->persist_split = c->persist_split_wgs == 2 || fits(k_rounds_persistent<true, 3>);
       c->persist_split_per_cu = per_cu;

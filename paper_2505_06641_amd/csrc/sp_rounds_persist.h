@@ -344,8 +344,8 @@ constexpr int kCachedRequests = 512;
 // SPLIT: the window's groups are subgroups of the applications (tb.pol_split); the plain instantiation holds
 // none of the secondary-group code.
 // WGS: workgroups that must fit on a compute unit.  Three leave 80 registers (3 spilled with the looping triangles, 27 with
-// subgroups); grids that take up to two thirds of the device at two per compute unit (339 pairs on 256) get 128 (none, 3), and
-// triangles with their entries held.
+// subgroups); grids of up to one workgroup per compute unit (254 pairs on 256) get 128 (none, 3), and triangles with their entries
+// held.
 template <bool SPLIT, int WGS>
 __global__ __launch_bounds__(kRoundThreads, 2 * WGS) void k_rounds_persistent(Tables tb, Window w, Persist ps) {
   __shared__ int32_t win[kWinCap];

@@ -1564,9 +1564,10 @@ def test_subgroups_of_a_few_requests(gpu, B, sizes):
 
 @pytest.mark.parametrize("split", [0, 1], ids=["plain", "subgroups"])
 @pytest.mark.parametrize("B", [12, 70])
-@pytest.mark.parametrize("A,M", [(32, 16), (30, 16), (21, 16)], ids=["512 pairs", "480 pairs", "336 pairs"])
+@pytest.mark.parametrize("A,M", [(32, 16), (30, 16), (15, 16)], ids=["512 pairs", "480 pairs", "240 pairs"])
 def test_rounds_of_many_pairs(gpu, A, M, B, split):
-    """Three resident workgroups per compute unit (more than 339 pairs on 256) and two, batches below and beyond 64."""
+    """The kernel with room for three workgroups per compute unit (more than 254 pairs on 256) and for two, batches below and beyond
+    64."""
     torch, binding = gpu
     w = wl.tiny(seed=9400 + A, n=6000, classes=(4,) * A, models=(M,) * A, max_batch=B, feat_dim=16, deadline=(15.0, 200.0))
     policy = wl.named_policy("sneakpeek")
@@ -1726,3 +1727,42 @@ def test_windows_of_several_contexts_side_by_side(gpu):
     for w in work:
         assert w[0].lib.sp_rounds_in_one_launch(w[0].h)
         w[0].close()
+
+
+@pytest.mark.parametrize("A,M,split", [(15, 16, 0), (31, 16, 0), (31, 16, 1)], ids=["240 pairs", "496 pairs", "496 pairs, subgroups"])
+def test_rounds_beside_another_stream_of_kernels(gpu, A, M, split):
+    """Matrix products without end on two other streams: the resident grid finds its places, no wait runs out."""
+    import threading
+    torch, binding = gpu
+    n = 8000
+    w = wl.tiny(seed=9850 + A, n=n, classes=(4,) * A, models=(M,) * A, max_batch=12, feat_dim=16, deadline=(15.0, 400.0))
+    policy = wl.named_policy("sneakpeek")
+    policy.split_groups = split
+    ctx = binding.Context(w.profile, n, policy=policy)
+    args = binding.to_device(w.requests)
+    ctx.sp_score(*args)
+    ref = ctx.sp_schedule(0, log_capacity=n)
+    torch.cuda.synchronize()
+    stop = threading.Event()
+
+    def busy():
+        with torch.cuda.stream(torch.cuda.Stream()):
+            a, b = (torch.randn(2048, 2048, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
+            while not stop.is_set():
+                for _ in range(20):
+                    a @ b
+                torch.cuda.current_stream().synchronize()
+
+    threads = [threading.Thread(target=busy) for _ in range(2)]
+    for t in threads:
+        t.start()
+    try:
+        stream = torch.cuda.Stream()
+        for _ in range(20):
+            ctx.sp_score(*args, stream=stream)
+            assert ctx.sp_schedule(0, log_capacity=n, stream=stream) == ref
+    finally:
+        stop.set()
+        for t in threads:
+            t.join()
+    ctx.close()
