@@ -203,9 +203,9 @@ __device__ __forceinline__ unsigned long long triangle_held_kind(const float4* e
   }
   s1 = sum16(s1);
   s2 = sum16(s2);
-  // (the order of packed candidates: by the scores' bits, where a NaN is above every number, then the smaller size)
-  const bool second = n2 > 0 && (n1 == 0 || __float_as_uint(s2) > __float_as_uint(s1));
-  return (n1 | n2) > 0 ? pack_candidate(second ? s2 : s1, cid0 + (uint32_t)((second ? b2 : b1) - 1)) : 0ull;
+  const unsigned long long c1 = n1 > 0 ? pack_candidate(s1, cid0 + (uint32_t)(b1 - 1)) : 0ull;
+  const unsigned long long c2 = n2 > 0 ? pack_candidate(s2, cid0 + (uint32_t)(b2 - 1)) : 0ull;
+  return c2 > c1 ? c2 : c1;
 }
 __device__ __forceinline__ unsigned long long triangle_held(int kind, const float4* ent, const float* lat, int nb, int B, double t, uint32_t cid0,
                                                            int only_b, int tid) {
