@@ -485,8 +485,8 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   }
   SP_HIP(c, hipMemset(w.st, 0, sizeof(State)));
   if ((s = setup_persist(c, p)) != SP_OK) return s;
-  c->single_ok = A <= kSingleApps && single_lds_bytes(A, Mmax, B) <= kSingleLds;
-  if (c->single_ok && single_lds_bytes(A, Mmax, B) > 48 * 1024 &&
+  c->single_ok = A <= kSingleApps;
+  if (c->single_ok && single_lds_bytes(A, Mmax, B, std::min(B, kSingleBatch)) > 48 * 1024 &&
       hipFuncSetAttribute(single_kernel(Mmax), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSingleLds) != hipSuccess) {
     (void)hipGetLastError();
     c->single_ok = false;
@@ -803,6 +803,7 @@ bool rounds_in_one_launch_so_far(sp_ctx* c) {
 bool round_single(const sp_ctx* c) {
   const int64_t Bw = c->tb.Bcap;
   if (c->tb.pol_split || !c->single_ok || Bw > kSingleBatch || c->spin_limit != kSpinLimit) return false;
+  if (single_lds_bytes(c->A, c->Mmax, c->B, (int)Bw) > kSingleLds) return false;
   int64_t evals = 0;
   for (int a = 0; a < c->A; ++a) {
     const int64_t mine = c->h_nmod[a] * (c->tb.pol_whole ? Bw : Bw * (Bw + 1) / 2);
@@ -818,7 +819,7 @@ const void* single_kernel(int Mmax) {
 
 void launch_round_single(sp_ctx* c, const Window& w, hipStream_t s, const Single& sg) {
   const dim3 grid(1), blk(kSingleThreads);
-  const size_t lds = single_lds_bytes(c->A, c->Mmax, c->B);
+  const size_t lds = single_lds_bytes(c->A, c->Mmax, c->B, c->tb.Bcap);
   switch (single_quads(c->Mmax)) {
     case 1: hipLaunchKernelGGL(k_round_single<1>, grid, blk, lds, s, c->tb, w, sg); break;
     case 2: hipLaunchKernelGGL(k_round_single<2>, grid, blk, lds, s, c->tb, w, sg); break;

@@ -18,7 +18,8 @@ constexpr int kSingleThreads = 1024;
 constexpr int kSingleWaves = kSingleThreads / kWave;
 constexpr int kSingleApps = kSingleWaves - 1;        // one wavefront brings each window, the others clear outputs
 constexpr int kSingleBatch = kWave;                  // largest batch: one lane per member
-constexpr int kSingleCap = 2 * kWave;                // entries per application: a window that lacks one, and 64 more
+// Entries per application: a window that lacks one, and 64 more (whole groups of sixteen are read).
+__host__ __device__ inline int single_cap(int Bcap) { return (Bcap - 1 + kWave + 15) / 16 * 16; }
 constexpr int kSingleScan = 16;                      // service positions per lane of a walk over dead requests, in each ...
 constexpr int kSingleBlocks = 2;                     // ... of the blocks of a step
 // Utility evaluations of a round up to which this kernel is used (with the group-first rule one application's: the others are not
@@ -26,7 +27,9 @@ constexpr int kSingleBlocks = 2;                     // ... of the blocks of a s
 // 28.6 / 25.0 (16,896), 28.9 / 26.1 (33,280, batches of 64), 29.0 / 29.8 (33,792, batches of 32), 28.7 / 31.7 (66,560); group
 // first 31.4 / 24.7 (66,560 in all, 8,320 of one application), 31.9 / 31.5 (199,680, 16,640).
 constexpr int64_t kSingleEvals = 30000;
-constexpr size_t kSingleLds = 144 * 1024;            // dynamic LDS
+// Dynamic LDS.  A workgroup that asks for more waits for a compute unit that is next to empty: beside two streams of matrix products and
+// one of elementwise kernels one call in ten took 0.4 to 0.7 ms with 122 to 146 KB, 0.07 as with two kernels up to 120.
+constexpr size_t kSingleLds = 110 * 1024;
 // Requests up to which it fills the caller's outputs (while it reads the windows).
 constexpr int kSingleOutputs = 16384;
 
@@ -40,8 +43,8 @@ struct Single {
 // Groups of four variants whose accuracies an entry holds.
 constexpr int single_quads(int Mmax) { return Mmax <= 4 ? 1 : Mmax <= 8 ? 2 : 4; }
 // Dynamic LDS: entries, latencies.
-inline size_t single_lds_bytes(int A, int Mmax, int B) {
-  return (size_t)A * kSingleCap * (2 + single_quads(Mmax)) * 16 + (size_t)A * Mmax * B * 4;
+inline size_t single_lds_bytes(int A, int Mmax, int B, int Bcap) {
+  return (size_t)A * single_cap(Bcap) * (2 + single_quads(Mmax)) * 16 + (size_t)A * Mmax * B * 4;
 }
 
 // Candidate ids inside this kernel: fields instead of a product, the same order.
@@ -162,11 +165,11 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
   __shared__ unsigned long long best_s[kSingleWaves];
   State* st = w.st;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int A = tb.A, B = tb.B, Bw = tb.Bcap, Mmax = tb.Mmax;
+  const int A = tb.A, B = tb.B, Bw = tb.Bcap, Mmax = tb.Mmax, cap = single_cap(Bw);
   float4* const dd = reinterpret_cast<float4*>(single_lds);                              // [A][cap] weight in a batch's sum, D, 1/D, 2D
-  int4* const meta = reinterpret_cast<int4*>(dd + A * kSingleCap);                       // [A][cap] service position, request id, weight, ordering value
-  ea_quad* const eas = reinterpret_cast<ea_quad*>(meta + A * kSingleCap);                // [A][QUADS][cap] expected accuracies
-  float* const lat_s = reinterpret_cast<float*>(eas + A * QUADS * kSingleCap);           // [A][Mmax][B]
+  int4* const meta = reinterpret_cast<int4*>(dd + A * cap);                       // [A][cap] service position, request id, weight, ordering value
+  ea_quad* const eas = reinterpret_cast<ea_quad*>(meta + A * cap);                // [A][QUADS][cap] expected accuracies
+  float* const lat_s = reinterpret_cast<float*>(eas + A * QUADS * cap);           // [A][Mmax][B]
   const bool owner = wave < A;
 
   // ---- what the launch starts from: one trip to memory ----
@@ -230,10 +233,10 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
       const unsigned long long bal = __ballot(live);
       if (live) {
         const int at = held + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-        dd[wave * kSingleCap + at] = make_float4(tb.pol_unit_weight ? 1.0f : key, D, 1.0f / D, 2.0f * D);
-        meta[wave * kSingleCap + at] = make_int4(pos, id, __float_as_int(wt), __float_as_int(tb.pol_edf ? -D : key));
+        dd[wave * cap + at] = make_float4(tb.pol_unit_weight ? 1.0f : key, D, 1.0f / D, 2.0f * D);
+        meta[wave * cap + at] = make_int4(pos, id, __float_as_int(wt), __float_as_int(tb.pol_edf ? -D : key));
 #pragma unroll
-        for (int q = 0; q < QUADS; ++q) eas[(wave * QUADS + q) * kSingleCap + at] = ea[q];
+        for (int q = 0; q < QUADS; ++q) eas[(wave * QUADS + q) * cap + at] = ea[q];
       }
       held += __popcll(bal);
     }
@@ -242,7 +245,7 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
       // eq. (14) over the window, in the order of block_sum_f64
       wave_sync();
       const int nw = min(held, Bw);
-      double s = lane < nw ? (double)__int_as_float(meta[wave * kSingleCap + lane].w) : 0.0;
+      double s = lane < nw ? (double)__int_as_float(meta[wave * cap + lane].w) : 0.0;
 #pragma unroll
       for (int o = kWave / 2; o > 0; o >>= 1) s += __shfl_down(s, o);
       if (lane == 0) prio_s[wave] = nw > 0 ? (float)(s / (double)nw) : 0.f;
@@ -280,8 +283,8 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
     const bool on = slot < n_slots && p < nw && (only_a < 0 || a == only_a);     // (past nw neither size is a candidate)
     const int kind = scoring_penalty(tb, kind_s[a]);
     const double t0 = (last_a == a && last_m == m) ? t : t + (double)swap_s[a][m];
-    const float4* e4 = dd + a * kSingleCap;
-    const float* ea_m = reinterpret_cast<const float*>(eas + (a * QUADS + (m >> 2)) * kSingleCap) + (m & 3);
+    const float4* e4 = dd + a * cap;
+    const float* ea_m = reinterpret_cast<const float*>(eas + (a * QUADS + (m >> 2)) * cap) + (m & 3);
     const float* lat = lat_s + (a * Mmax + m) * B;
     const int only_b = tb.pol_whole ? nw : 0;
     unsigned long long c = 0ull;
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
   if (owner && lane == 0) {
     // first position that may still be live, for the next round
     const int skip = wave == a ? b : 0, held = held_s[wave];
-    w.head[((r + (a >= 0 ? 1 : 0)) & 1) * w.gcap + wave] = skip < held ? meta[wave * kSingleCap + skip].x : scan_s[wave];
+    w.head[((r + (a >= 0 ? 1 : 0)) & 1) * w.gcap + wave] = skip < held ? meta[wave * cap + skip].x : scan_s[wave];
     atomicAdd(&st->n_evals, triangle_evals(min(held, Bw), tb.pol_whole) * (unsigned long long)tb.n_models[wave]);   // (as every route counts)
   }
   if (wave != kSingleWaves - 1) return;
@@ -315,10 +318,10 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
   const double E = ((last_a == a && last_m == m) ? t : t + (double)swap_s[a][m]) + (double)lat_s[(a * Mmax + m) * B + b - 1];
   double wu = 0.0, su = 0.0, viol = 0.0;
   if (lane < b) {
-    const int at = a * kSingleCap + lane;
+    const int at = a * cap + lane;
     const int4 mt = meta[at];
     const float4 e = dd[at];
-    const float acc = reinterpret_cast<const float*>(eas + (a * QUADS + (m >> 2)) * kSingleCap + lane)[m & 3];
+    const float acc = reinterpret_cast<const float*>(eas + (a * QUADS + (m >> 2)) * cap + lane)[m & 3];
     const int pos = mt.x, id = mt.y;
     const float u = acc * one_minus_penalty(kind_s[a], e.y, e.z, E);
     w.model[id] = m;

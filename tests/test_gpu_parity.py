@@ -1766,3 +1766,14 @@ def test_rounds_beside_another_stream_of_kernels(gpu, A, M, split):
         for t in threads:
             t.join()
     ctx.close()
+
+
+@pytest.mark.parametrize("A,M,B,one", [(13, 16, 4, 1), (15, 16, 4, 0), (16, 1, 2, 0), (1, 1, 65, 0)], ids=["small batches", "too much LDS", "16 applications", "65"])
+def test_which_rounds_run_in_one_workgroup(gpu, A, M, B, one):
+    """Either side of the lines by LDS, applications and batches; the decisions are the oracle's."""
+    torch, binding = gpu
+    w = wl.tiny(seed=9900 + A + B, n=700, classes=(3,) * A, models=(M,) * A, max_batch=B, feat_dim=16, deadline=(20.0, 300.0))
+    ctx = binding.Context(w.profile, 700)
+    assert ctx.lib.sp_rounds_in_one_workgroup(ctx.h) == one
+    ctx.close()
+    full_parity(gpu, w, max_rounds=1)
