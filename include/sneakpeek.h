@@ -339,7 +339,7 @@ int32_t sp_max_classes(const sp_ctx* ctx);
 int32_t sp_rounds_in_one_launch(const sp_ctx* ctx);
 /* How a round that is a call of its own runs (sp_greedy_round, sp_greedy_round_static; sp_schedule with max_rounds 1 on contexts whose
  * rounds run in one launch) under the current policy: 1 = one launch of one workgroup, where the profile is small (up to 15
- * applications, batches of up to 64, some 30,000 evaluations, no group splitting), 0 = two kernels (sp_schedule: the launch of
+ * applications, batches of up to 64, some 30,000 evaluations of a round, no group splitting), 0 = two kernels (sp_schedule: the launch of
  * resident workgroups).  The decisions are the same either way. */
 int32_t sp_rounds_in_one_workgroup(const sp_ctx* ctx);
 

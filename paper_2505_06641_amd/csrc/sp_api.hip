@@ -798,18 +798,19 @@ bool rounds_in_one_launch_so_far(sp_ctx* c) {
   return true;
 }
 
-// Whether a round that is a launch of its own runs in one workgroup (see kSingleEvals).  (A bound on the waits of resident
+// Whether a round that is a launch of its own runs in one workgroup (see kSingleCost).  (A bound on the waits of resident
 // workgroups that a test has set asks for those.)
 bool round_single(const sp_ctx* c) {
   const int64_t Bw = c->tb.Bcap;
   if (c->tb.pol_split || !c->single_ok || Bw > kSingleBatch || c->spin_limit != kSpinLimit) return false;
   if (single_lds_bytes(c->A, c->Mmax, c->B, (int)Bw) > kSingleLds) return false;
-  int64_t evals = 0;
+  int64_t evals = 0, slots = 0;
   for (int a = 0; a < c->A; ++a) {
     const int64_t mine = c->h_nmod[a] * (c->tb.pol_whole ? Bw : Bw * (Bw + 1) / 2);
     evals = c->tb.pol_group_first ? std::max(evals, mine) : evals + mine;
+    slots += c->h_nmod[a] * ((Bw + 1) / 2);
   }
-  return evals <= kSingleEvals;
+  return evals + kSingleSlot * slots <= (c->tb.pol_group_first ? kSingleCostGroupFirst : kSingleCost);
 }
 
 const void* single_kernel(int Mmax) {

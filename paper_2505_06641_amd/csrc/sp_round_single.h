@@ -22,11 +22,15 @@ constexpr int kSingleBatch = kWave;                  // largest batch: one lane 
 __host__ __device__ inline int single_cap(int Bcap) { return (Bcap - 1 + kWave + 15) / 16 * 16; }
 constexpr int kSingleScan = 16;                      // service positions per lane of a walk over dead requests, in each ...
 constexpr int kSingleBlocks = 2;                     // ... of the blocks of a step
-// Utility evaluations of a round up to which this kernel is used (with the group-first rule one application's: the others are not
-// evaluated).  us per call of sp_greedy_round, two kernels against this one: 27.0 / 21.7 (408 evaluations), 28.6 / 23.2 (8,448),
-// 28.6 / 25.0 (16,896), 28.9 / 26.1 (33,280, batches of 64), 29.0 / 29.8 (33,792, batches of 32), 28.7 / 31.7 (66,560); group
-// first 31.4 / 24.7 (66,560 in all, 8,320 of one application), 31.9 / 31.5 (199,680, 16,640).
-constexpr int64_t kSingleEvals = 30000;
+// Up to what this kernel is used: a round's utility evaluations (with the group-first rule one application's: the others are not
+// evaluated), and kSingleSlot for each pair of batch sizes of each (application, variant), which four lanes take together.  us per call
+// of sp_greedy_round, two kernels against this one, and evaluations + 14 pairs of sizes: 23.5 / 17.2 (1,472: one application of 16
+// variants, batches of 8), 24.1 / 18.9 (11,136: six of 8, 15), 24.0 / 21.4 (24,064: two of 16, 32), 24.3 / 22.8 (29,952: eight of 8, 24),
+// 24.8 / 24.5 (33,600: six of 16, 20), 24.0 / 22.5 (40,448: one of 16, 64), 24.4 / 25.5 (41,184: eleven of 8, 24), 24.7 / 26.9 (42,000:
+// fifteen of 8, 20), 25.0 / 27.9 (40,832: eleven of 16, 15), 24.2 / 25.3 (45,360: fifteen of 2, 48).  Group first: 27.3 / 20.5 (18,560:
+// eight of 8, 32), 27.3 / 22.3 (30,912: eight of 8, 48), 27.8 / 24.5 (37,120: eight of 16, 32), 27.2 / 26.2 (54,784: three of 16, 64),
+// 27.6 / 27.7 (56,064: eleven of 8, 64), 27.3 / 27.6 (61,952: four of 16, 64).
+constexpr int64_t kSingleSlot = 14, kSingleCost = 40500, kSingleCostGroupFirst = 55000;
 // Dynamic LDS.  A workgroup that asks for more waits for a compute unit that is next to empty: beside two streams of matrix products and
 // one of elementwise kernels one call in ten took 0.4 to 0.7 ms with 122 to 146 KB, 0.07 as with two kernels up to 120.
 constexpr size_t kSingleLds = 110 * 1024;

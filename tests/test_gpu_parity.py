@@ -1768,12 +1768,18 @@ def test_rounds_beside_another_stream_of_kernels(gpu, A, M, split):
     ctx.close()
 
 
-@pytest.mark.parametrize("A,M,B,one", [(13, 16, 4, 1), (15, 16, 4, 0), (16, 1, 2, 0), (1, 1, 65, 0)], ids=["small batches", "too much LDS", "16 applications", "65"])
-def test_which_rounds_run_in_one_workgroup(gpu, A, M, B, one):
-    """Either side of the lines by LDS, applications and batches; the decisions are the oracle's."""
+@pytest.mark.parametrize("classes,models,B,select,one", [
+    (2, (16, 16), 32, wl.SELECT_JOINT, 1), (1, (16,), 64, wl.SELECT_JOINT, 1), (11, (16,) * 11, 15, wl.SELECT_JOINT, 0),
+    (15, (8,) * 15, 20, wl.SELECT_JOINT, 0), (15, (8,) * 15, 20, wl.SELECT_GROUP_FIRST, 1), (4, (16,) * 4, 64, wl.SELECT_GROUP_FIRST, 0),
+    (13, (16,) * 13, 4, wl.SELECT_JOINT, 1), (15, (16,) * 15, 4, wl.SELECT_JOINT, 0), (16, (1,) * 16, 2, wl.SELECT_JOINT, 0), (1, (1,), 65, wl.SELECT_JOINT, 0)],
+    ids=["two of 16", "one of 16, 64", "many pairs", "many pairs, 20", "group first", "group first, 64", "small batches", "too much LDS", "16 applications", "65"])
+def test_which_rounds_run_in_one_workgroup(gpu, classes, models, B, select, one):
+    """Either side of the lines by evaluations and pairs of batch sizes, LDS, applications and batches; the decisions are the oracle's."""
     torch, binding = gpu
-    w = wl.tiny(seed=9900 + A + B, n=700, classes=(3,) * A, models=(M,) * A, max_batch=B, feat_dim=16, deadline=(20.0, 300.0))
-    ctx = binding.Context(w.profile, 700)
+    A, n = classes, 700
+    w = wl.tiny(seed=9900 + A + B, n=n, classes=(3,) * A, models=models, max_batch=B, feat_dim=16, deadline=(20.0, 300.0))
+    policy = wl.Policy(select=select)
+    ctx = binding.Context(w.profile, n, policy=policy)
     assert ctx.lib.sp_rounds_in_one_workgroup(ctx.h) == one
     ctx.close()
-    full_parity(gpu, w, max_rounds=1)
+    full_parity(gpu, w, max_rounds=1, policy=policy)
