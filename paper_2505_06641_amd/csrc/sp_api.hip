@@ -75,6 +75,10 @@ struct sp_ctx {
   int persist_wgs = 2, persist_split_wgs = 2;   // the instantiations that hold the grid (see k_rounds_persistent)
   int cus = 0, persist_per_cu = 0, persist_split_per_cu = 0;   // compute units, and workgroups of those instantiations on one
   Persist ps{};
+  unsigned long long* h_ended = nullptr;       // pinned, behind h_state: the last launch that has told the host of its end (see tell_host_ended)
+  unsigned long long* h_ended_dev = nullptr;   // its device-visible address
+  unsigned long long launches = 0;   // launches that were to tell it so far
+  hipEvent_t ev_ended = nullptr;     // recorded behind such a launch of sp_schedule (see fetch_state)
   bool single_ok = false;            // a round by itself may run in one workgroup
   uint32_t gen_base = 0;             // slot generations handed out so far
   int32_t spin_limit = kSpinLimit;   // polls before a wait between resident workgroups is given up
@@ -476,13 +480,18 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   if ((s = dev_alloc(c, &c->seg1, 2)) != SP_OK) return s;
   for (int i = 0; i < (app_passes(A) > 1 ? 2 : 1); ++i)
     if ((s = dev_alloc(c, &c->dw_g[i], N)) != SP_OK) return s;
-  SP_HIP(c, hipHostMalloc((void**)&c->h_state, sizeof(State), hipHostMallocDefault));
-  std::memset(c->h_state, 0, sizeof(State));
   {
+    // the state's copy, and on a line of its own the word by which launches tell their end (read while they may still be ending: coherent)
+    const size_t ended_at = (sizeof(State) + 127) / 128 * 128;
+    SP_HIP(c, hipHostMalloc((void**)&c->h_state, ended_at + sizeof(*c->h_ended), hipHostMallocCoherent));
+    std::memset((void*)c->h_state, 0, ended_at + sizeof(*c->h_ended));
+    c->h_ended = (unsigned long long*)((unsigned char*)c->h_state + ended_at);
     void* dp = nullptr;
     SP_HIP(c, hipHostGetDevicePointer(&dp, c->h_state, 0));
     c->w.st_host = (State*)dp;
+    c->h_ended_dev = (unsigned long long*)((unsigned char*)dp + ended_at);
   }
+  SP_HIP(c, hipEventCreateWithFlags(&c->ev_ended, hipEventDisableTiming));
   SP_HIP(c, hipMemset(w.st, 0, sizeof(State)));
   if ((s = setup_persist(c, p)) != SP_OK) return s;
   c->single_ok = A <= kSingleApps;
@@ -747,6 +756,8 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
   if ((s = dev_alloc(c, &ps.ring, ring)) != SP_OK) return s;
   if ((s = dev_alloc(c, &ps.dec, kPersistRounds)) != SP_OK) return s;
   if ((s = dev_alloc(c, &ps.decision, 8)) != SP_OK) return s;
+  if ((s = dev_alloc(c, &ps.left, 1)) != SP_OK) return s;
+  SP_HIP(c, hipMemset(ps.left, 0, sizeof(uint32_t)));
   SP_HIP(c, hipMemset(ps.decision, 0, 8 * 8));
   if ((s = dev_alloc(c, &ps.ticks, kPersistRounds + 1)) != SP_OK) return s;
   SP_HIP(c, hipMemset(ps.slots, 0, 8 * n_pairs * 8));
@@ -754,12 +765,12 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
   SP_HIP(c, hipMemset(ps.dec, 0, kPersistRounds * 8));
   SP_HIP(c, hipMemset(ps.ticks, 0, (kPersistRounds + 1) * 8));
   SP_HIP(c, hipHostMalloc((void**)&c->h_ticks, (kPersistRounds + 1) * sizeof(long long), hipHostMallocDefault));
-  SP_HIP(c, hipHostMalloc((void**)&c->h_log, kPersistRounds * sizeof(Decision), hipHostMallocDefault));
+  SP_HIP(c, hipHostMalloc((void**)&c->h_log, kPersistRounds * sizeof(Decision), hipHostMallocCoherent));
   {
     void* dp = nullptr;
     SP_HIP(c, hipHostGetDevicePointer(&dp, c->h_log, 0));
     ps.log_host = (Decision*)dp;
-    SP_HIP(c, hipHostMalloc((void**)&c->h_lost, sizeof(int32_t), hipHostMallocDefault));
+    SP_HIP(c, hipHostMalloc((void**)&c->h_lost, sizeof(int32_t), hipHostMallocCoherent));
     *c->h_lost = 0;
     SP_HIP(c, hipHostGetDevicePointer(&dp, c->h_lost, 0));
     ps.lost_host = (int32_t*)dp;
@@ -834,7 +845,7 @@ void fill_u64(hipStream_t s, unsigned long long* p, size_t n) {
 
 // Up to kPersistRounds rounds in one launch.  An ordinary launch: setup_persist has checked that the whole
 // grid fits on the device at once, and the kernel's waits are bounded.
-sp_status launch_rounds_persistent(sp_ctx* c, hipStream_t s, int n_rounds) {
+sp_status launch_rounds_persistent(sp_ctx* c, const Window& w, hipStream_t s, int n_rounds) {
   Persist& ps = c->ps;
   if (c->gen_base + (uint32_t)n_rounds + 2u >= kGenMask) {       // generation numbers about to wrap: start over
     fill_u64(s, ps.slots, 8 * (size_t)ps.n_pairs);
@@ -850,10 +861,10 @@ sp_status launch_rounds_persistent(sp_ctx* c, hipStream_t s, int n_rounds) {
   *c->h_lost = 0;                                                // (the launch before has been waited for)
   const dim3 grid(ps.n_pairs + 2), blk(kRoundThreads);
   const size_t dyn = persist_dynamic_lds(c);
-  if (c->tb.pol_split && c->persist_split_wgs == 2) hipLaunchKernelGGL((k_rounds_persistent<true, 2>), grid, blk, dyn, s, c->tb, c->w, ps);
-  else if (c->tb.pol_split) hipLaunchKernelGGL((k_rounds_persistent<true, 3>), grid, blk, dyn, s, c->tb, c->w, ps);
-  else if (c->persist_wgs == 2) hipLaunchKernelGGL((k_rounds_persistent<false, 2>), grid, blk, dyn, s, c->tb, c->w, ps);
-  else hipLaunchKernelGGL((k_rounds_persistent<false, 3>), grid, blk, dyn, s, c->tb, c->w, ps);
+  if (c->tb.pol_split && c->persist_split_wgs == 2) hipLaunchKernelGGL((k_rounds_persistent<true, 2>), grid, blk, dyn, s, c->tb, w, ps);
+  else if (c->tb.pol_split) hipLaunchKernelGGL((k_rounds_persistent<true, 3>), grid, blk, dyn, s, c->tb, w, ps);
+  else if (c->persist_wgs == 2) hipLaunchKernelGGL((k_rounds_persistent<false, 2>), grid, blk, dyn, s, c->tb, w, ps);
+  else hipLaunchKernelGGL((k_rounds_persistent<false, 3>), grid, blk, dyn, s, c->tb, w, ps);
   return SP_OK;
 }
 
@@ -1201,11 +1212,46 @@ void launch_round(sp_ctx* c, const Window& w, hipStream_t s, int32_t* ids_out, f
     hipLaunchKernelGGL(k_round_commit, dim3(1), dim3(kRoundThreads), 0, s, c->tb, w, ids_out);
 }
 
-// Brings the window state to the host.  mirrored: a round kernel is on the stream, whose commits write the state into the
-// pinned copy themselves; otherwise it is copied here.
-sp_status fetch_state(sp_ctx* c, hipStream_t s, bool mirrored = false) {
-  if (!mirrored) SP_HIP(c, hipMemcpyAsync(c->h_state, c->w.st, sizeof(State), hipMemcpyDeviceToHost, s));
+// `w` for a launch whose end the host waits for by its word, the last one of a call on its stream.
+Window telling(sp_ctx* c, Window w) {
+  w.ended_host = c->h_ended_dev;
+  w.ended = ++c->launches;
+  return w;
+}
+
+// Waits for that launch, and by it for the stream.  The host polls for a while (as it does in hipStreamSynchronize at first); behind
+// longer work, and where the launch does not run at all (a stream that is being captured, a failed one), the runtime waits, and says so.
+sp_status wait_ended(sp_ctx* c, hipStream_t s) {
+  const auto patience = std::chrono::milliseconds(5);
+  const auto since = std::chrono::steady_clock::now();
+  do {
+    for (int i = 0; i < 64; ++i) {
+      if (__atomic_load_n(c->h_ended, __ATOMIC_ACQUIRE) == c->launches) return SP_OK;
+      __builtin_ia32_pause();
+    }
+  } while (std::chrono::steady_clock::now() - since < patience);
   SP_HIP(c, hipStreamSynchronize(s));
+  return SP_OK;
+}
+
+// Where the window's state comes from: copied behind what is on the stream, or written into the pinned copy by a round kernel's commits;
+// then the last launch on the stream may be one that tells the host.  kToldMarked: an event goes behind it while it runs.  The runtime
+// would do that itself when the program waits for the stream next, and the program for it (12 us instead of 4; 3 after
+// hipStreamSynchronize); it costs a microsecond and a half of the next window where the program does not wait.  us per window of 256
+// requests, without and with a wait behind it: hipStreamSynchronize 31.3 and 34.3, told 28.2 and 38.1, told and marked 30.5 and 30.9;
+// sp_score and eight calls of sp_greedy_round: 193.5 and 195.6, 162.0 and 192.9, 168.2 and 194.7.
+enum class Fetch { kCopied, kMirrored, kTold, kToldMarked };
+
+sp_status fetch_state(sp_ctx* c, hipStream_t s, Fetch how) {
+  if (how == Fetch::kTold || how == Fetch::kToldMarked) {
+    SP_HIP(c, hipGetLastError());
+    if (how == Fetch::kToldMarked) SP_HIP(c, hipEventRecord(c->ev_ended, s));
+    const sp_status st = wait_ended(c, s);
+    if (st != SP_OK) return st;
+  } else {
+    if (how == Fetch::kCopied) SP_HIP(c, hipMemcpyAsync(c->h_state, c->w.st, sizeof(State), hipMemcpyDeviceToHost, s));
+    SP_HIP(c, hipStreamSynchronize(s));
+  }
   SP_HIP(c, hipGetLastError());
   c->rounds_done = c->h_state->round;
   c->done = c->h_state->done != 0;
@@ -1272,6 +1318,7 @@ void sp_destroy(sp_ctx* c) {
   if (c->h_lost) (void)hipHostFree(c->h_lost);
   if (c->h_grp_n) (void)hipHostFree(c->h_grp_n);
   if (c->ev_groups) (void)hipEventDestroy(c->ev_groups);
+  if (c->ev_ended) (void)hipEventDestroy(c->ev_ended);
   for (hipEvent_t e : c->ev)
     if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->round_ev) (void)hipEventDestroy(e);
@@ -1334,8 +1381,8 @@ sp_status sp_greedy_round(sp_ctx* c, void* stream, sp_decision* out_host, int32_
   if (!g.ok) return SP_EDEVICE;
   hipStream_t s = (hipStream_t)stream;
   const int32_t before = c->rounds_done;
-  launch_round(c, c->w, s, req_ids_out_dev, nullptr);
-  sp_status st = fetch_state(c, s, true);
+  launch_round(c, telling(c, c->w), s, req_ids_out_dev, nullptr);
+  sp_status st = fetch_state(c, s, Fetch::kTold);
   if (st != SP_OK) return st;
   if (c->rounds_done == before) return SP_DONE;
   // (within what was reserved: a round allocates nothing; past it the log is copied from the device when it is asked for)
@@ -1368,8 +1415,8 @@ sp_status sp_greedy_round_static(sp_ctx* c, void* stream, sp_decision* out_host,
   w.win_pos = reinterpret_cast<int32_t*>(base + o_pos);
   w.win_n = reinterpret_cast<int32_t*>(base + o_n);
   const int32_t before = c->rounds_done;
-  launch_round(c, w, s, req_ids_out_dev, nullptr);
-  sp_status st = fetch_state(c, s, true);
+  launch_round(c, telling(c, w), s, req_ids_out_dev, nullptr);
+  sp_status st = fetch_state(c, s, Fetch::kTold);
   if (st != SP_OK) return st;
   if (c->rounds_done == before) return SP_DONE;
   // (within what was reserved: a round allocates nothing; past it the log is copied from the device when it is asked for)
@@ -1421,15 +1468,17 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
     // stages are timed: the copy then has a time of its own)
     const bool outputs_inside = persist && want_outputs && !tm && c->rounds_done == 0 &&
                                 (int64_t)c->n <= (single ? kSingleOutputs : (int64_t)kOutputsPerRound * chunk);
+    const bool told = !tm && (!want_outputs || outputs_inside);   // (the rounds are the last launch on the stream)
+    const Window w = told ? telling(c, c->w) : c->w;
     if (persist) {
       c->ps.out = outputs_inside ? outs : Outputs{};
-      if (single) launch_round_single(c, c->w, s, Single{c->ps.out, nullptr, c->ps.log_host, c->ps.ticks});
-      else if ((st = launch_rounds_persistent(c, s, chunk)) != SP_OK) return st;
+      if (single) launch_round_single(c, w, s, Single{c->ps.out, nullptr, c->ps.log_host, c->ps.ticks});
+      else if ((st = launch_rounds_persistent(c, w, s, chunk)) != SP_OK) return st;
       if (tm && c->timing_rounds)
         SP_HIP(c, hipMemcpyAsync(c->h_ticks, c->ps.ticks, (kPersistRounds + 1) * sizeof(long long), hipMemcpyDeviceToHost, s));
     } else {
       for (int i = 0; i < chunk; ++i) {
-        launch_round(c, c->w, s, nullptr, nullptr);
+        launch_round(c, i + 1 == chunk ? w : c->w, s, nullptr, nullptr);
         if (tm && c->timing_rounds && c->n_round_ev < kMaxRoundEvents) SP_HIP(c, hipEventRecord(c->round_ev[c->n_round_ev++], s));
       }
     }
@@ -1446,7 +1495,7 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
       }
     }
     outputs_copied = want_outputs;
-    st = fetch_state(c, s, true);    // tells how far the device got and whether the queue ran dry
+    st = fetch_state(c, s, told ? Fetch::kToldMarked : Fetch::kMirrored);    // tells how far the device got and whether the queue ran dry
     fetched = true;
     if (st != SP_OK) return st;
     if (persist && (int32_t)c->log.size() == before) {
@@ -1459,7 +1508,7 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
       for (int i = 0; i < c->rounds_done - before; ++i)
         c->round_ms.push_back((float)((double)(c->h_ticks[i + 1] - c->h_ticks[i]) * c->tick_ms));
   }
-  if (!fetched && (st = fetch_state(c, s)) != SP_OK) return st;
+  if (!fetched && (st = fetch_state(c, s, Fetch::kCopied)) != SP_OK) return st;
   c->timed_rounds = tm && fetched;
   c->rounds_in_call = c->rounds_done - start;
   bool pending = false;

@@ -110,7 +110,22 @@ struct Window {
   int32_t* last_ids;          // [B] members of the last committed batch
   State* st;
   State* st_host;             // pinned host copy of *st that the round kernels keep current (device-visible address)
+  unsigned long long* ended_host;   // pinned: where the launch that the host waits for says that it has ended, or null
+  unsigned long long ended;   // ... and what it writes there
 };
+
+// How a launch tells the waiting host that it has ended.  A host that polls a word in pinned memory goes on 4 to 5 us sooner than one in
+// hipStreamSynchronize, which has a barrier packet of its own processed first (a call of sp_greedy_round 25 -> 20 us).  What the call
+// promises stays: everything the launch wrote is in memory, for every stream and for the host, before the word is.
+// Every wavefront's stores have arrived in its die's L2.
+__device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// By one thread, behind a barrier that all wavefronts of its workgroup have passed after stores_arrived(): the die's L2 is written back,
+// then the word.
+__device__ __forceinline__ void tell_host_ended(const Window& w) {
+  if (w.ended_host == nullptr) return;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+  __hip_atomic_store(w.ended_host, w.ended, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Which tile a workgroup takes.  Consecutive workgroup ids go to the chip's eight accelerator dies (XCDs) in turn, each with
 // an L2 of its own; tiles are ordered by application, so giving every die one contiguous eighth of the tiles lets what the

@@ -188,7 +188,10 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
   loaded_here(a_kind); loaded_here(a_end); loaded_here(head_even); loaded_here(head_odd); loaded_here(a_lmin); loaded_here(a_swap);
   loaded_here(lat0); loaded_here(models); loaded_here(twu); loaded_here(tu); loaded_here(tv); loaded_here(next_order); loaded_here(last_m);
   if (stopped) {
-    if (tid == 0) mirror_state(w);
+    if (tid == 0) {
+      mirror_state(w);
+      tell_host_ended(w);
+    }
     return;
   }
   const int r = __builtin_amdgcn_readfirstlane(round0);
@@ -310,13 +313,20 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
     w.head[((r + (a >= 0 ? 1 : 0)) & 1) * w.gcap + wave] = skip < held ? meta[wave * cap + skip].x : scan_s[wave];
     atomicAdd(&st->n_evals, triangle_evals(min(held, Bw), tb.pol_whole) * (unsigned long long)tb.n_models[wave]);   // (as every route counts)
   }
-  if (wave != kSingleWaves - 1) return;
+  if (wave != kSingleWaves - 1) {
+    stores_arrived();
+    __syncthreads();                                   // (the last wavefront tells the host)
+    return;
+  }
   // ---- the batch: outputs, pending flags, the three sums (one member per lane, in the order of commit_members), the state ----
   if (best == 0ull) {                                  // nothing live anywhere
     if (lane == 0) {
       st->done = 1;
       mirror_state(w);
     }
+    stores_arrived();
+    __syncthreads();
+    if (lane == 0) tell_host_ended(w);
     return;
   }
   const double E = ((last_a == a && last_m == m) ? t : t + (double)swap_s[a][m]) + (double)lat_s[(a * Mmax + m) * B + b - 1];
@@ -349,24 +359,28 @@ __global__ __launch_bounds__(kSingleThreads) void k_round_single(Tables tb, Wind
     su += __shfl_down(su, o);
     viol += __shfl_down(viol, o);
   }
-  if (lane != 0) return;
   const Decision dc{a, m, b, r, t, E, __uint_as_float((uint32_t)(best >> 32)), (float)wu};
-  if (r < w.log_cap) w.log[r] = dc;
-  if (sg.log_host) sg.log_host[0] = dc;
-  if (sg.ticks) sg.ticks[1] = wall_clock64();
-  // (the host's copy is written alongside, not read back from this one)
-  for (State* s : {st, w.st_host}) {
-    s->last = dc;
-    s->t = E;
-    s->total_wu = twu + wu;
-    s->total_u = tu + su;
-    s->total_viol = tv + viol;
-    s->round = r + 1;
-    s->next_order = next_order + b;
-    s->n_sched = next_order + b - 1;                   // (orders count from one)
-    s->done = 0;                                       // (or this launch would have left at once)
-    s->err = 0u;
+  if (lane == 0) {
+    if (r < w.log_cap) w.log[r] = dc;
+    if (sg.log_host) sg.log_host[0] = dc;
+    if (sg.ticks) sg.ticks[1] = wall_clock64();
+    // (the host's copy is written alongside, not read back from this one)
+    for (State* s : {st, w.st_host}) {
+      s->last = dc;
+      s->t = E;
+      s->total_wu = twu + wu;
+      s->total_u = tu + su;
+      s->total_viol = tv + viol;
+      s->round = r + 1;
+      s->next_order = next_order + b;
+      s->n_sched = next_order + b - 1;                   // (orders count from one)
+      s->done = 0;                                       // (or this launch would have left at once)
+      s->err = 0u;
+    }
   }
+  stores_arrived();
+  __syncthreads();
+  if (lane == 0) tell_host_ended(w);
 }
 
 }  // namespace sp

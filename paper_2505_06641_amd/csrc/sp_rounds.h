@@ -467,7 +467,10 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Windo
   loaded_here(mine); loaded_here(my_prio); loaded_here(now.t); loaded_here(now.total_wu); loaded_here(now.total_u);
   loaded_here(now.total_viol); loaded_here(now.round); loaded_here(now.next_order); loaded_here(now.n_sched); loaded_here(now.n_evals);
   if (now.done || now.err) {
-    if (tid == 0) mirror_state(w);
+    if (tid == 0) {
+      mirror_state(w);
+      tell_host_ended(w);
+    }
     return;
   }
   unsigned long long best = mine;
@@ -480,6 +483,7 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Windo
     if (tid == 0) {
       st->done = 1;
       mirror_state(w);
+      tell_host_ended(w);
     }
     return;
   }
@@ -531,6 +535,10 @@ __global__ __launch_bounds__(kRoundThreads) void k_round_commit(Tables tb, Windo
     *st = now;                        // (nobody else writes the state while this kernel runs)
     if (w.st_host != nullptr) *w.st_host = now;
   }
+  if (w.ended_host == nullptr) return;
+  stores_arrived();
+  __syncthreads();
+  if (tid == 0) tell_host_ended(w);
 }
 
 // Window state at the start of a window.

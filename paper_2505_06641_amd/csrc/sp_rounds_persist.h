@@ -77,6 +77,7 @@ struct Persist {
   Decision* log_host;           // [kPersistRounds] pinned: the launch's decisions for the host
   int32_t* lost_host;           // pinned: set by any workgroup whose wait has run out
   long long* ticks;             // [kPersistRounds + 1]: constant-rate timestamps, launch start then each decision
+  uint32_t* left;               // workgroups that have ended their work; zero between launches
 };
 
 __device__ __forceinline__ unsigned long long ld_dev(const unsigned long long* p) {
@@ -337,6 +338,19 @@ __device__ __forceinline__ int wave_window(const Window& w, int kind, int head, 
   return min(found, Bw);
 }
 
+// A workgroup's work has ended: the last one of the grid tells the host.  The commit workgroup alone writes through its L2, which it
+// writes back first.
+__device__ __forceinline__ void persist_leave(const Window& w, const Persist& ps, bool committed = false) {
+  if (w.ended_host == nullptr) return;
+  stores_arrived();
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  if (committed) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+  if (atomicAdd(ps.left, 1u) + 1u != gridDim.x) return;
+  __hip_atomic_store(ps.left, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  tell_host_ended(w);
+}
+
 // Requests of small secondary groups that a resident pair keeps in LDS (512: ten KB beside the windows, so that three
 // workgroups still share a CU at batch sizes up to 128).
 constexpr int kCachedRequests = 512;
@@ -377,15 +391,21 @@ __global__ __launch_bounds__(kRoundThreads, 2 * WGS) void k_rounds_persistent(Ta
   // no round done and takes two kernels per round
   if (SPLIT && w.grp_n[1] > kMaxAppGroups) {
     if ((int)blockIdx.x == ps.n_pairs + 1 && threadIdx.x == 0) mirror_state(w);
+    persist_leave(w, ps, true);
     return;
   }
   if ((int)blockIdx.x == ps.n_pairs + 1) {
     persist_commit_loop(tb, w, ps, own.dsum, red);
+    persist_leave(w, ps, true);
     return;
   }
-  if (st->done || st->err) return;          // the state is rewritten only when the commit workgroup ends
+  if (st->done || st->err) {                // the state is rewritten only when the commit workgroup ends
+    persist_leave(w, ps);
+    return;
+  }
   if ((int)blockIdx.x == ps.n_pairs) {
     persist_reduce_loop(tb, w, ps, red, waves, &timed_out);
+    persist_leave(w, ps);
     return;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -811,8 +831,10 @@ __global__ __launch_bounds__(kRoundThreads, 2 * WGS) void k_rounds_persistent(Ta
   // first position of every group of this application that may still be live, for whoever continues the window
   __syncthreads();
   if (m == 0)
-    for (int i = tid; i < ng; i += kRoundThreads)
-      w.head[(r & 1) * w.gcap + glo + i] = i == prim ? (shift < nb ? win[shift] : scan_end) : head_s[i];
+    for (int i = tid; i < ng; i += kRoundThreads)            // (past this die's L2: another workgroup tells the host that all have ended)
+      __hip_atomic_store(w.head + (r & 1) * w.gcap + glo + i, i == prim ? (shift < nb ? win[shift] : scan_end) : head_s[i], __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+  persist_leave(w, ps);
 }
 
 __global__ void k_fill_u64(unsigned long long* p, int64_t n, unsigned long long v) {

@@ -1783,3 +1783,51 @@ def test_which_rounds_run_in_one_workgroup(gpu, classes, models, B, select, one)
     assert ctx.lib.sp_rounds_in_one_workgroup(ctx.h) == one
     ctx.close()
     full_parity(gpu, w, max_rounds=1, policy=policy)
+
+
+@pytest.mark.parametrize("route", ["one workgroup", "resident workgroups", "two kernels"])
+def test_outputs_are_there_for_other_streams_when_a_call_returns(gpu, route):
+    """A call has waited for its stream when it returns: what it wrote is read at once on another stream, whether the work in front
+    of it is short or longer than the host polls, and the next call may come on that stream."""
+    torch, binding = gpu
+    w = wl.make("cfg2", n_requests=2048)
+    p, rq = w.profile, w.requests
+    ctx = binding.Context(p, rq.n)
+    if route == "two kernels":
+        ctx.sp_debug_set_spin_limit(1 << 19)           # (no rounds in one workgroup)
+    args = binding.to_device(rq)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    big = torch.randn((4096, 4096), device="cuda:0")
+    torch.cuda.synchronize()
+    want = None
+    for i in range(40):
+        a, b = streams[i % 2], streams[(i + 1) % 2]
+        ids = torch.full((4, p.max_batch), -1, dtype=torch.int32, device="cuda:0")
+        outs = [torch.full((rq.n,), 99, dtype=torch.int32, device="cuda:0") for _ in range(3)] + [torch.full((rq.n,), -7.0, device="cuda:0")]
+        torch.cuda.synchronize()
+        if i % 10 == 9:
+            with torch.cuda.stream(a):
+                for _ in range(60):                    # (about 10 ms)
+                    torch.mm(big, big)
+        ctx.sp_score(*args, stream=a)
+        got = []
+        if route == "resident workgroups":
+            got.append(ctx.sp_schedule(3, *outs, log_capacity=8, stream=a)[2])
+            with torch.cuda.stream(b):
+                got.append(torch.stack([o.view(torch.int32) for o in outs]).cpu().numpy())
+            got.append(ctx.sp_schedule(2, *outs, log_capacity=8, stream=b)[2])
+        else:
+            for k in range(4):
+                s, other = (a, b) if k % 2 else (b, a)
+                if k == 0:
+                    s, other = a, b
+                got.append(ctx.sp_greedy_round(req_ids_out=ids[k], stream=s)[1])
+                with torch.cuda.stream(other):
+                    got.append(ids[k].cpu().numpy())
+        torch.cuda.synchronize()
+        if want is None:
+            want = got
+            assert route == "resident workgroups" or (got[1] >= 0).any()
+        for g, h in zip(got, want):
+            assert np.array_equal(g, h) if isinstance(g, np.ndarray) else g == h
+    ctx.close()
