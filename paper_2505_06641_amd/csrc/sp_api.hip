@@ -24,6 +24,7 @@
 #include "sp_rounds_persist.h"
 #include "sp_round_single.h"
 #include "sp_sort.h"
+#include "sp_order.h"
 #include "sp_probe.h"
 
 using namespace sp;
@@ -476,7 +477,7 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   if (N > (size_t)kMergeMax && (s = dev_alloc(c, &c->dtot_key, (size_t)kMaxSortPasses * c->tiles_cap * 256)) != SP_OK) return s;
   if ((s = dev_alloc(c, &c->sort_state, (size_t)c->tiles_cap * 256)) != SP_OK) return s;
   SP_HIP(c, hipMemset(c->sort_state, 0, (size_t)c->tiles_cap * 256 * sizeof(unsigned long long)));
-  if ((s = dev_alloc(c, &c->sort_desc, N / kRun + A + kXcds)) != SP_OK) return s;
+  if ((s = dev_alloc(c, &c->sort_desc, std::max(std::min(N, (size_t)kRankMax) / kRanks, N / kRun) + A + kXcds)) != SP_OK) return s;
   if ((s = dev_alloc(c, &c->seg1, 2)) != SP_OK) return s;
   for (int i = 0; i < (app_passes(A) > 1 ? 2 : 1); ++i)
     if ((s = dev_alloc(c, &c->dw_g[i], N)) != SP_OK) return s;
@@ -1049,6 +1050,18 @@ void radix_pass(sp_ctx* c, hipStream_t s, const SortPlan& plan, int tiles, const
                        c->sort_state, gen, c->sort_spin_limit, keys_out, vals_out, c->w.st, SortCarry{});
 }
 
+// Whether a window is ordered in one launch (k_order).  Its workgroups each read all keys of their application, so its time grows with
+// the largest one; runs and merges take one to four launches.  us per scoring call (16 features, 10 classes), runs and merges / one launch: one
+// application of 256 requests 13.6 / 14.5, 768 16.5 / 15.6, 4,096 22.4 / 19.0, 16,384 28.3 / 23.7, 65,536 39.5 / 38.1, 100,000 50.0 / 52.7; three
+// (0.5, 0.3, 0.2) of 16,384 25.0 / 22.9, 65,536 37.0 / 33.0, 100,000 45.8 / 41.9; eight of 16,384 25.8 / 20.6, 65,536 33.9 / 26.6, 100,000
+// 45.4 / 35.0, 131,072 (more workgroups than compute units) 49.2 / 48.8.  Deadlines as keys are often few different ones, and then it is the
+// slower way: of three deadlines one application of 16,384 27.6 / 37.2, 65,536 42.8 / 58.0, eight of 65,536 33.8 / 37.3.
+bool one_launch_order(const sp_ctx* c, int n) {
+  return n > kRankMin && n <= (c->A <= 2 ? kRankMaxFew : kRankMax) && !c->tb.pol_edf && !(c->tb.pol_split && c->Cmax >= kRankLabels);
+}
+// Requests of a sort run, for the descriptors.
+int sort_unit(const sp_ctx* c, int n) { return one_launch_order(c, n) ? kRanks : n <= kMergeMax ? kRun : kSortTile; }
+
 // Requests grouped by application: ids, deadlines and weights at their grouped positions, segment starts, descriptors.
 // Returns the array that holds the ids.
 int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev, const float* deadline_ms_dev,
@@ -1058,7 +1071,7 @@ int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev,
   // (up to a tile per compute unit there is nothing to even out: 33.5 us per scoring call instead of 34.4 for 16,384 requests of twelve
   // bfloat16 hidden heads)
   const int32_t* costs = ((int64_t)n + score_tile(c) - 1) / score_tile(c) + A > c->cus ? c->tile_costs : nullptr;
-  SegArgs seg_args{n, A, nullptr, score_tile(c), n <= kMergeMax ? kRun : kSortTile, c->by_cost, costs, (int32_t)score_grid(c, n), w.seg,
+  SegArgs seg_args{n, A, nullptr, score_tile(c), sort_unit(c, n), c->by_cost, costs, (int32_t)score_grid(c, n), w.seg,
                    w.unit_start, w.tile_desc, c->sort_desc};
   // a long window's ordering needs its digit totals cleared
   uint32_t* zero = n > kMergeMax ? c->dtot_key : nullptr;
@@ -1164,6 +1177,16 @@ const uint32_t* order_requests(sp_ctx* c, hipStream_t s, int n, uint32_t* sortke
     hipLaunchKernelGGL(k_finish_order, dim3((n + kRunThreads - 1) / kRunThreads), dim3(kRunThreads), 0, s, n, A, (const int32_t*)w.seg, v_in,
                        (const uint32_t*)k_in, w, edf);
     return k_in;
+  }
+  if (one_launch_order(c, n)) {
+    const dim3 grid((n / kRanks + A + kXcds - 1) / kXcds * kXcds);
+    stage_event();
+    if (split)
+      hipLaunchKernelGGL(k_order<true>, grid, dim3(kRankThreads), 0, s, plan, (const uint32_t*)sortkey, (const int32_t*)w.sub_g, c->bufL[0], n, w, edf);
+    else
+      hipLaunchKernelGGL(k_order<false>, grid, dim3(kRankThreads), 0, s, plan, (const uint32_t*)sortkey, (const int32_t*)nullptr, (uint32_t*)nullptr,
+                         n, w, edf);
+    return c->bufL[0];
   }
   const int grid = (n / kRun + A + kXcds - 1) / kXcds * kXcds;
   int levels, ways;

@@ -9,7 +9,7 @@
 // through published words.
 //
 // Ordering inside each application by the inverted bits of the priority key (or the deadline bits, or (subgroup, key)).
-// Up to kMergeMax requests: runs of kRun consecutive requests are sorted by one workgroup each in LDS (k_sort_runs); runs are
+// Windows of some length by priority keys: one launch (sp_order.h).  Else up to kMergeMax requests: runs of kRun consecutive requests are sorted by one workgroup each in LDS (k_sort_runs); runs are
 // then merged several at a time (k_merge_runs): a workgroup takes consecutive elements of one run and finds the place of each
 // by counting, with binary searches in LDS, what precedes it in the sibling runs.  No workgroup waits for another, the number
 // of launches follows from the window's size alone (one for up to 1,024 requests, two for up to 16,384, three beyond), and

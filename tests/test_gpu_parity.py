@@ -1831,3 +1831,87 @@ def test_outputs_are_there_for_other_streams_when_a_call_returns(gpu, route):
         for g, h in zip(got, want):
             assert np.array_equal(g, h) if isinstance(g, np.ndarray) else g == h
     ctx.close()
+
+
+def _sampled_positions(n):
+    return ((n - 16) * np.repeat(np.arange(512), 16)) // 511 + np.tile(np.arange(16), 512)
+
+
+def _weights(shape, n, rng):
+    """Weights that make priority keys of one variant and one deadline: as they are, but for rounding that keeps their order."""
+    u = rng.random(n)
+    if shape == "equal":
+        return np.ones(n)
+    if shape == "three":
+        return rng.integers(1, 4, n) * 0.25
+    if shape == "zeros":
+        return np.where(u < 0.5, 0.0, u)
+    if shape == "two scales":
+        return np.where(rng.random(n) < 0.5, u, 1e-30 * (1.0 + u))
+    if shape == "rising":
+        return np.arange(1, n + 1) / n
+    if shape == "almost equal":
+        return 1.0 + rng.integers(0, 5, n) * 2.0 ** -23
+    if shape == "sample apart" and n > 8192:            # the requests that are sampled say nothing about the others
+        w = 0.25 + 0.5 * u
+        w[_sampled_positions(n)] = 1.0
+        return w
+    return u
+
+
+@pytest.mark.parametrize("shape", ["spread", "equal", "three", "zeros", "two scales", "rising", "almost equal", "sample apart"])
+@pytest.mark.parametrize("n,A", [(512, 1), (513, 1), (1025, 1), (4096, 1), (4097, 1), (8192, 1), (8193, 1), (20011, 1), (65536, 1), (65537, 1), (65536, 2),
+                                 (65536, 8), (106496, 3), (106497, 3)])
+def test_ordering_in_one_launch(gpu, n, A, shape):
+    """Window lengths around the steps of the one-launch ordering, keys that are evenly spread, equal, clustered, sorted or unlike
+    what its sample tells.  Whole numbers, no tolerance."""
+    torch, binding = gpu
+    rng = np.random.default_rng(n + A)
+    w = wl.tiny(seed=8800 + A, n=n, classes=(2,) * A, models=(1,) * A, max_batch=2, feat_dim=8)
+    w.requests.deadline_rel_ms[:] = 10.0
+    w.requests.weight[:] = _weights(shape, n, rng).astype(np.float32)
+    ctx = binding.Context(w.profile, n)
+    key = torch.zeros(n, device="cuda:0")
+    order = torch.zeros(n, dtype=torch.int32, device="cuda:0")
+    x, app, D, wt = binding.to_device(w.requests)
+    for _ in range(2):
+        ctx.sp_score(x, app, D, wt, key_out=key)
+        ctx.sp_debug_dump(binding.SP_DUMP_ORDER, order)
+        assert np.array_equal(order.cpu().numpy(), _service_order(w, key.cpu().numpy()))
+    ctx.close()
+
+
+@pytest.mark.parametrize("shape", ["spread", "three", "equal"])
+@pytest.mark.parametrize("n,C", [(9000, 300), (9000, 5000), (40000, 40), (3000, 5000)])
+def test_ordering_by_subgroup_in_one_launch(gpu, n, C, shape):
+    """The same by (subgroup, key, id): few and many subgroups (more than there are bins), keys evenly spread and equal."""
+    torch, binding = gpu
+    rng = np.random.default_rng(n + C)
+    w = wl.tiny(seed=8900, n=n, classes=(C, 3), models=(1, 1), max_batch=2, feat_dim=8, fractions=(0.9, 0.1))
+    for a in range(2):
+        w.profile.W1[a] = (w.profile.W1[a] * 40.0).astype(np.float32)          # confident heads: most requests in a subgroup
+    w.requests.deadline_rel_ms[:] = 10.0
+    w.requests.weight[:] = _weights(shape, n, rng).astype(np.float32)
+    ctx = binding.Context(w.profile, n, policy=wl.Policy(split_groups=1))
+    key = torch.zeros(n, device="cuda:0")
+    order = torch.zeros(n, dtype=torch.int32, device="cuda:0")
+    x, app, D, wt = binding.to_device(w.requests)
+    ctx.sp_score(x, app, D, wt, key_out=key)
+    ctx.sp_debug_dump(binding.SP_DUMP_ORDER, order)
+    z = torch.zeros((n, ctx.c_max), device="cuda:0")
+    ctx.sp_debug_dump(binding.SP_DUMP_LOGITS, z, x=x, app=app)
+    z, key, order = z.cpu().numpy().astype(np.float64), key.cpu().numpy(), order.cpu().numpy()
+    ctx.close()
+    at = 0
+    for a in range(2):
+        ids = np.nonzero(w.requests.app == a)[0]
+        th = orc.posterior(z[ids, :int(w.profile.n_classes[a])])
+        top = th.max(axis=1)
+        label = np.where(top > 0.5, 1 + th.argmax(axis=1), 0)
+        clear = np.abs(top - 0.5) > 1e-4                # (at the threshold either label is right)
+        got = order[at:at + ids.shape[0]]
+        at += ids.shape[0]
+        assert np.array_equal(np.sort(got), ids)
+        keep = np.isin(got, ids[clear])
+        want = ids[clear][np.lexsort((ids[clear], -key[ids[clear]].astype(np.float64), label[clear]))]
+        assert np.array_equal(got[keep], want)
