@@ -1264,6 +1264,10 @@ sp_status wait_ended(sp_ctx* c, hipStream_t s) {
 // requests, without and with a wait behind it: hipStreamSynchronize 31.3 and 34.3, told 28.2 and 38.1, told and marked 30.5 and 30.9;
 // sp_score and eight calls of sp_greedy_round: 193.5 and 195.6, 162.0 and 192.9, 168.2 and 194.7.
 enum class Fetch { kCopied, kMirrored, kTold, kToldMarked };
+// Requests up to which sp_schedule waits in that way.  In hipStreamSynchronize the runtime also puts away what it has kept of a
+// context's first launches, 20 to 30 us beside a window that runs longer than that, which a program that synchronises then waits for:
+// 65,536 requests, first pass with a wait behind it 226 (told: 243), repeated ones 195 (189); 16,384 requests 101 to 106 (104 to 107) and 87 (83).
+constexpr int kToldRequests = 16384;
 
 sp_status fetch_state(sp_ctx* c, hipStream_t s, Fetch how) {
   if (how == Fetch::kTold || how == Fetch::kToldMarked) {
@@ -1491,7 +1495,7 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
     // stages are timed: the copy then has a time of its own)
     const bool outputs_inside = persist && want_outputs && !tm && c->rounds_done == 0 &&
                                 (int64_t)c->n <= (single ? kSingleOutputs : (int64_t)kOutputsPerRound * chunk);
-    const bool told = !tm && (!want_outputs || outputs_inside);   // (the rounds are the last launch on the stream)
+    const bool told = !tm && c->n <= kToldRequests && (!want_outputs || outputs_inside);   // (the rounds are the last launch on the stream)
     const Window w = told ? telling(c, c->w) : c->w;
     if (persist) {
       c->ps.out = outputs_inside ? outs : Outputs{};
