@@ -680,11 +680,30 @@ sp_status pack_stream(sp_ctx* c, const sp_profile* p) {
   return c->H > 0 ? pack_stream_t<uint16_t, true>(c, p) : pack_stream_t<uint16_t, false>(c, p);
 }
 
+// Whether two teams of wavefronts share a tile's rows (kTeamSlices); of logistic heads.
+bool stream_teams(const sp_ctx* c) {
+  const int tile = stream_tile(c->stream_nb), chunk = kStBytes / (c->dtype == SP_F32 ? 4 : 2);
+  return c->stream_nb <= 4 && c->Cmax <= 32 * c->stream_nb && c->d > (kTeamSlices - 1) * chunk && ((int64_t)c->n + tile - 1) / tile <= c->cus;
+}
+
 template <typename T, bool MLP, bool COLS = false>
 void launch_score_stream(sp_ctx* c, hipStream_t s, const void* x, const int32_t* ids, const float2* dw, uint32_t* sortkey,
                          float* logits) {
   const int tile = stream_tile(c->stream_nb);
   const dim3 grid((unsigned)score_grid(c, c->n)), blk(tile / 32 * kWave);
+  if constexpr (!MLP) {
+    if (stream_teams(c)) {
+#define SP_LAUNCH_ST(NB) \
+      hipLaunchKernelGGL((k_score_stream<T, NB, false, COLS, 2>), grid, dim3(2 * tile / 32 * kWave), 0, s, c->tb, c->w, (const T*)x, ids, dw, sortkey, c->stream, logits)
+      switch (c->stream_nb) {
+        case 1: SP_LAUNCH_ST(1); break;
+        case 2: SP_LAUNCH_ST(2); break;
+        default: SP_LAUNCH_ST(4); break;
+      }
+#undef SP_LAUNCH_ST
+      return;
+    }
+  }
 #define SP_LAUNCH_ST(NB) \
   hipLaunchKernelGGL((k_score_stream<T, NB, MLP, COLS>), grid, blk, 0, s, c->tb, c->w, (const T*)x, ids, dw, sortkey, c->stream, logits)
   switch (c->stream_nb) {

@@ -6,9 +6,9 @@
 // A wavefront owns 32 requests and keeps the whole transposed output tile of the first layer (32 NB rows: hidden
 // units, or classes) in NB float32 accumulators while it streams its requests' features from memory, kStBytes per
 // row and step; the matching weight slices, packed at context creation in the order the lanes read them, go through
-// two LDS buffers shared by the workgroup's four wavefronts.  Features never pass through LDS: the order of a slice's
-// channels is free as long as the weights are packed in the same one, so a lane takes 64 consecutive bytes of its
-// request's row.  A step costs memory more than matrix cores in all of these shapes, so features travel two steps ahead.
+// two LDS buffers shared by the workgroup's four wavefronts.  The order of a slice's channels is free as long as the weights
+// are packed in the same one, so a lane takes 64 consecutive bytes of its request's row: straight from memory, or (stream_turns)
+// out of LDS.  A step costs memory more than matrix cores in all of these shapes, so features travel two steps ahead.
 //
 // bfloat16: products are exact, float32 accumulation.  float32: every operand is scaled by a power of two and split
 // into two half-precision numbers as in the logistic kernel (x.w = hi.hi + lo.hi + hi.lo), and so are the hidden activations
@@ -46,6 +46,22 @@ constexpr int stream_tile(int nb) { return stream_waves(nb) * 32; }    // reques
 // 93).  From 129 classes on it would hold eight blocks of rows and lose (130 classes: 110 us against 103, 52 against 50).
 constexpr int kStreamClasses = 128;
 constexpr int kStBytes = 128;                    // bytes of a feature row per step (one cache line)
+
+// Slices of a row from which two teams of wavefronts share a tile's rows (KS == 2), each with every other slice: a workgroup is alone on
+// its compute unit while a window has no more tiles than there are units, and then waits at every step for the weights' and the rows'
+// way from memory, with one wavefront per SIMD.  The teams' sums meet in LDS, each team takes half of the classes from there on.  Logistic
+// heads; weights travel two steps ahead.  us per call, one team / two, no row turned: 100 classes, 32,768 rows of 768 floats 50.0 / 47.0, of 1024
+// 57.8 / 53.3, 1,000 rows 39.6 / 36.0; 10 classes 47.8 / 40.9; 512 bfloat16 (8 slices) 35.0 / 34.0; 8 slices of floats 31.0 / 29.4, 4 slices
+// 25.8 / 26.1; with more tiles than units (33,000 to 50,000 rows) no difference, and one team shares the unit with other workgroups.
+constexpr int kTeamSlices = 6;
+// Whether rows are read in whole lines and turned in LDS.  Without that an instruction of a wavefront touches 64 lines for 16 bytes each, 256
+// cycles of address processing per step and wavefront (measured: 10 classes, 1,024 floats, one step in 1.0 us whatever else it did, now 0.55);
+// with it 8 lines, and the turn takes four LDS writes and four reads.  us per call, as it lies in memory / turned: 10 classes, rows of 700 floats,
+// 100,000 115.5 / 97.6, 30,000 39.9 / 37.8; 60 classes 108.7 / 99.7, 40.8 / 38.9; bfloat16 hidden layers of 64 and 128, 384 features, 30,000
+// 32.6 / 30.7, 34.6 / 33.4.  Not where registers run out: 100 classes of floats 54.9 / 58.0 (60,000 rows of 512); nor for hidden layers on floats,
+// which take fewer wavefronts per SIMD then: 100,000 of 100-32-10 46.0 / 48.9, of 128-64-10 49.7 / 50.2.
+template <typename T, int NB, bool MLP, int KS>
+constexpr bool stream_turns() { return sizeof(T) == 4 ? !MLP && NB <= 2 : NB <= 2 || (NB == 4 && (MLP || KS == 2)); }
 
 template <typename T>
 struct StreamIn {
@@ -166,8 +182,8 @@ static __device__ f32x4 stream_zeros;            // what lies behind a row's end
 // 16 bytes of a feature row: rows start at any multiple of the element size
 typedef f32x4 f32x4_any __attribute__((aligned(2)));
 
-template <typename T, int NB, bool MLP, bool COLS = false>
-__global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
+template <typename T, int NB, bool MLP, bool COLS = false, int KS = 1>
+__global__ __launch_bounds__(KS * stream_waves(NB) * kWave, 2) void k_score_stream(
     Tables tb, Window w, const T* __restrict__ x, const int32_t* __restrict__ ids, const float2* __restrict__ dw_g,
     uint32_t* __restrict__ sortkey, StreamHeads hd, float* __restrict__ logits_out) {
   using I = StreamIn<T>;
@@ -175,9 +191,13 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
   constexpr int S = I::kSteps, CH = I::kChunk, D = 32 * NB;
   constexpr int kTurns = I::kF32 ? 3 : 2;                // matrix instructions per block and half of a slice
   static_assert(!COLS || I::kF32, "bfloat16 features are not scaled");
-  __shared__ f32x4 buf[2][SG::kUnits];
+  static_assert(KS == 1 || (KS == 2 && !MLP && NB <= 4), "logistic heads with all classes in one group");
+  __shared__ f32x4 bufs[KS][2][SG::kUnits];
   __shared__ f32x4 cols[COLS ? kStreamMaxD / 4 : 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // (KS == 2: which of the two teams of wavefronts, and the place in it)
+  const int team = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / SG::kThreads);
+  const int tid = KS == 1 ? (int)threadIdx.x : (int)threadIdx.x & (SG::kThreads - 1), lane = tid & 63, wave = tid >> 6;
+  f32x4 (&buf)[2][SG::kUnits] = bufs[team];
   const int r = lane & 31, g = lane >> 5;
   const int4 desc = w.tile_desc[blockIdx.x];
   if (desc.x < 0) return;
@@ -191,47 +211,76 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
   const int nkc = (d + CH - 1) / CH;
   const int n_groups = MLP ? 1 : (CT + NB - 1) / NB;
   const int n_stages = MLP ? nkc + CT : n_groups * (nkc + 1);
+  const int steps = (nkc + KS - 1) / KS;                 // a team's share of the slices: every KS-th
+  const auto slice_of = [&](int i) { return KS * i + team; };
   const bool dump = logits_out != nullptr, split = tb.pol_split != 0;
 
-  // ---- stages: loaded into registers one ahead, stored into the idle buffer when the running one is done ----
+  // ---- stages: loaded into registers one or (kAhead) two ahead, stored into the idle buffer when the running one is done ----
+  constexpr bool kAhead = KS == 2;
   const f32x4* src;
   {
     const int64_t o = hd.off[a];
     const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)o), hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)o >> 32));
     src = reinterpret_cast<const f32x4*>(hd.stages + (int64_t)(((uint64_t)hi << 32) | lo));
   }
-  f32x4 wst[SG::kPer];
-  auto fetch = [&](int st) {
-    const f32x4* p = src + (size_t)min(st, n_stages - 1) * SG::kUnits;
+  typedef f32x4 Staged[SG::kPer];
+  Staged w0, w1;
+  auto fetch = [&](int st, Staged& wst) {
+    // (a team whose last slice does not exist multiplies zeros by another one's weights)
+    const int at = KS == 1 ? min(st, n_stages - 1) : st >= steps ? nkc : min(slice_of(st), nkc - 1);
+    const f32x4* p = src + (size_t)at * SG::kUnits;
 #pragma unroll
     for (int i = 0; i < SG::kPer; ++i) wst[i] = p[(uint32_t)(tid + i * SG::kThreads)];
   };
-  auto park = [&](int st) {
+  auto park = [&](int st, const Staged& wst) {
     f32x4* b = buf[st & 1] + tid;
 #pragma unroll
     for (int i = 0; i < SG::kPer; ++i) b[i * SG::kThreads] = wst[i];
   };
 
-  // ---- features: this lane's 64 bytes of a step ----
-  const unsigned char* row = reinterpret_cast<const unsigned char*>(x + (int64_t)id * d);
+  // ---- features: this lane's 64 bytes of a step, 16 at a time.  kTurn: read in whole lines, eight lanes a row, and turned in LDS (a
+  // wavefront its own rows), where piece p of row r lies in place p ^ (r % 8) of the row: no bank conflicts on either side ----
+  constexpr bool kTurn = stream_turns<T, NB, MLP, KS>();
+  __shared__ f32x4 turn[KS * stream_waves(NB)][kTurn || KS == 2 ? 32 * 8 : 1];
+  constexpr int kRows = kTurn ? 4 : 1;
+  const unsigned char* rows[kRows];
+#pragma unroll
+  for (int q = 0; q < kRows; ++q)
+    rows[q] = reinterpret_cast<const unsigned char*>(x + (int64_t)(kTurn ? __shfl(id, 8 * q + (lane >> 3)) : id) * d);
   const int row_bytes = d * (int)sizeof(T);              // >= 16
   auto load_x = [&](f32x4 (&xs)[4], int kc) {
-    const int at = kStBytes * kc + 64 * g;
+    const int first = kStBytes * kc + (kTurn ? 16 * ((lane & 7) ^ (lane >> 3)) : 64 * g);
+    const auto at = [&](int q) { return kTurn ? first : first + 16 * q; };
     if (kStBytes * (kc + 1) <= row_bytes) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        if constexpr (I::kF32) xs[q] = *reinterpret_cast<const f32x4_dw*>(row + at + 16 * q);
-        else xs[q] = *reinterpret_cast<const f32x4_any*>(row + at + 16 * q);
+        const unsigned char* p = rows[kTurn ? q : 0] + at(q);
+        if constexpr (I::kF32) xs[q] = *reinterpret_cast<const f32x4_dw*>(p);
+        else xs[q] = *reinterpret_cast<const f32x4_any*>(p);
       }
     } else if (kc < nkc) {                               // the last, partial step (see stream_slot)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const unsigned char* p = row + min(at + 16 * q, row_bytes - 16);
-        xs[q] = *reinterpret_cast<const f32x4_any*>(at + 16 * q < row_bytes ? p : reinterpret_cast<const unsigned char*>(&stream_zeros));
+        const unsigned char* p = rows[kTurn ? q : 0] + min(at(q), row_bytes - 16);
+        xs[q] = *reinterpret_cast<const f32x4_any*>(at(q) < row_bytes ? p : reinterpret_cast<const unsigned char*>(&stream_zeros));
       }
     } else {                                             // past it
 #pragma unroll
       for (int q = 0; q < 4; ++q) xs[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  auto turned = [&](const f32x4 (&xs)[4], f32x4 (&xv)[4]) {
+    if constexpr (kTurn) {
+      f32x4* const own = turn[threadIdx.x >> 6];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) own[64 * q + lane] = xs[q];
+      wave_sync();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xv[q] = own[8 * r + ((4 * g + q) ^ (r & 7))];
+      wave_sync();
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xv[q] = xs[q];
     }
   };
 
@@ -244,10 +293,11 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
   bool infinite = false;                                 // float32, hidden layer: the row holds an infinity
   const float un1 = I::kF32 ? hd.unscale1[a] : 1.f;
 
-  fetch(0);
-  park(0);
+  fetch(0, w0);
+  park(0, w0);
+  if (kAhead) fetch(1, w1);
   if (COLS)
-    for (int i = tid; i < nkc * (CH / 4); i += SG::kThreads) cols[i] = reinterpret_cast<const f32x4*>(hd.cols)[(size_t)a * nkc * (CH / 4) + i];
+    for (int i = threadIdx.x; i < nkc * (CH / 4); i += KS * SG::kThreads) cols[i] = reinterpret_cast<const f32x4*>(hd.cols)[(size_t)a * nkc * (CH / 4) + i];
   __syncthreads();
 
   int st = 0;                                            // running stage
@@ -256,8 +306,8 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
     f32x4 x0[4], x1[4];
     int k0 = 0;
     asm volatile("" : "+s"(k0));                         // (a zero that the compiler cannot see: it would keep every address of the
-    load_x(x0, k0);                                      // first steps in registers from one group to the next)
-    load_x(x1, k0 + 1);
+    load_x(x0, slice_of(k0));                            // first steps in registers from one group to the next)
+    load_x(x1, slice_of(k0 + 1));
     ex = 1000;
 #pragma unroll
     for (int hb = 0; hb < NB; ++hb)
@@ -323,14 +373,22 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
         }
       }
     };
-    // one step: stage st + 1 and the features of step kc + 2 start, the MFMAs of step kc run, stage st + 1 is stored.
-    // The features of step kc are converted, or copied, first: that frees their registers for step kc + 2.
-    auto slice_f32 = [&](int kc, f32x4 (&xs)[4]) {
-      fetch(st + 1);
+    // one step: stage st + 1 and the features of step i + 2 start, the MFMAs of step i run, stage st + 1 is stored.
+    // The features of step i are converted, or copied, first: that frees their registers for step i + 2.  (kAhead: stage st + 2 starts, and
+    // stage st + 1 has been on its way since the step before.)
+    auto slice_f32 = [&](int i, f32x4 (&xs)[4], Staged& w_new, Staged& w_next) {
+      if (kAhead) fetch(st + 2, w_new); else fetch(st + 1, w0);
       __builtin_amdgcn_sched_barrier(0);
       f32x4 xv[4];
+      turned(xs, xv);
+      if (kTurn) {                                                 // (the registers are free already)
+        load_x(xs, slice_of(i + 2));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (COLS) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) xv[q] = COLS ? xs[q] * cols[kc * (CH / 4) + 4 * g + q] : xs[q];
+        for (int q = 0; q < 4; ++q) xv[q] *= cols[(KS == 1 ? i : min(slice_of(i), nkc - 1)) * (CH / 4) + 4 * g + q];
+      }
       float amax = 0.f;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
@@ -364,44 +422,135 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
           xl[k >> 3][k & 7] = lo[0]; xl[k >> 3][(k & 7) + 1] = lo[1];
         }
       __builtin_amdgcn_sched_barrier(0);
-      load_x(xs, kc + 2);
-      __builtin_amdgcn_sched_barrier(0);
+      if (!kTurn) {
+        load_x(xs, slice_of(i + 2));
+        __builtin_amdgcn_sched_barrier(0);
+      }
       blocks([&](int half, int turn, const f32x4& whf, const f32x4& wlf, f32x16& part) {
         const f16x8 wh = __builtin_bit_cast(f16x8, whf), wl = __builtin_bit_cast(f16x8, wlf);
         part = __builtin_amdgcn_mfma_f32_32x32x16_f16(turn == 0 ? wl : wh, turn == 1 ? xl[half] : xh[half], part, 0, 0, 0);
       });
-      park(st + 1);
+      park(st + 1, kAhead ? w_next : w0);
       __syncthreads();
       ++st;
     };
-    auto slice_bf16 = [&](int kc, f32x4 (&xs)[4]) {
-      fetch(st + 1);
+    auto slice_bf16 = [&](int i, f32x4 (&xs)[4], Staged& w_new, Staged& w_next) {
+      if (kAhead) fetch(st + 2, w_new); else fetch(st + 1, w0);
       __builtin_amdgcn_sched_barrier(0);
+      f32x4 xv[4];
+      turned(xs, xv);
       bf16x8 xc[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) xc[q] = as_bf16x8(xs[q]);
-      load_x(xs, kc + 2);
+      for (int q = 0; q < 4; ++q) xc[q] = as_bf16x8(xv[q]);
+      load_x(xs, slice_of(i + 2));
       __builtin_amdgcn_sched_barrier(0);
       blocks([&](int half, int turn, const f32x4& w0, const f32x4& w1, f32x16& part) {
         part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(turn == 0 ? w0 : w1), xc[2 * half + turn], part, 0, 0, 0);
       });
-      park(st + 1);
+      park(st + 1, kAhead ? w_next : w0);
       __syncthreads();
       ++st;
     };
-    for (int kc = k0;; kc += 2) {
-      if constexpr (I::kF32) slice_f32(kc, x0); else slice_bf16(kc, x0);
-      if (kc + 1 < nkc) {                                // (one way out of the loop: with two, the accumulators are copied)
-        if constexpr (I::kF32) slice_f32(kc + 1, x1); else slice_bf16(kc + 1, x1);
+    for (int i = k0;; i += 2) {
+      if constexpr (I::kF32) slice_f32(i, x0, w0, w1); else slice_bf16(i, x0, w0, w1);
+      if (i + 1 < steps) {                               // (one way out of the loop: with two, the accumulators are copied)
+        if constexpr (I::kF32) slice_f32(i + 1, x1, w1, w0); else slice_bf16(i + 1, x1, w1, w0);
       }
-      if (kc + 2 >= nkc) break;
+      if (i + 2 >= steps) break;
     }
 
+    if constexpr (KS == 2) {
+      // The teams' sums meet: each finishes half of the blocks (of one block the first team all) with what the other has summed for
+      // them, both brought to the smaller of the two scales.
+      constexpr int kOwn = NB == 1 ? 1 : NB / 2;
+      // (a team's idle buffer and the places where its rows were turned; nobody reads either any more)
+      static_assert(kOwn == 1 || SG::kUnits >= 4 * SG::kThreads, "room for a block in a buffer");
+      const auto meet = [&](int of, int j) { return j + 1 == kOwn ? turn[of * stream_waves(NB)] : bufs[of][(st & 1) ^ 1]; };
+      __shared__ int32_t meet_ex[2][SG::kThreads];
+      const bool second = team != 0;
+      f32x16 fin[kOwn];
+#pragma unroll
+      for (int j = 0; j < kOwn; ++j) {
+        const int hi = NB == 1 ? 0 : kOwn + j;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          f32x4 give;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            fin[j][4 * q + v] = second ? acc[hi][4 * q + v] : acc[j][4 * q + v];
+            give[v] = second ? acc[j][4 * q + v] : acc[hi][4 * q + v];
+          }
+          meet(team, j)[q * SG::kThreads + tid] = give;
+        }
+      }
+      meet_ex[team][tid] = ex;
+      __syncthreads();
+      const int ex_other = meet_ex[team ^ 1][tid], ex_min = min(ex, ex_other);
+      const float f_mine = I::kF32 ? __builtin_amdgcn_ldexpf(1.0f, max(ex_min - ex, -1000)) : 1.0f;
+      const float f_other = I::kF32 ? __builtin_amdgcn_ldexpf(1.0f, max(ex_min - ex_other, -1000)) : 1.0f;
+      const float un = I::kF32 ? __builtin_amdgcn_ldexpf(un1, -ex_min) : 1.f;
+      const float4* tab = reinterpret_cast<const float4*>(buf[st & 1]);
+      const int first = NB == 1 ? 2 * team : kOwn * team;          // (of one block the second team has none)
+#pragma unroll
+      for (int j = 0; j < kOwn; ++j) {
+        const int hb = first + j;
+        if (hb >= nbk) continue;                                   // (uniform)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 take = meet(team ^ 1, j)[q * SG::kThreads + tid];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) fin[j][4 * q + v] = I::kF32 ? fmaf(fin[j][4 * q + v], f_mine, take[v] * f_other) : fin[j][4 * q + v] + take[v];
+        }
+        softmax_tile<true>(tab + hb * SplitBlock<32, 3>::kTabUnits, tab + NB * SplitBlock<32, 3>::kTabUnits + hb * SplitBlock<32, 3>::kBiasUnits,
+                     fin[j], un, ea_lo, ea_hi, ssum, ssum_hi, m2, m2_rest, hb, C, g, lane, valid, dump_row, logits_out, best_z, best_c, dump, split);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (dump) return;
+      // ... and so do their expected accuracies and denominators, in the first team's registers.
+      __syncthreads();
+      float* const part = reinterpret_cast<float*>(turn) + tid;
+      constexpr int kParts = 14;
+      static_assert(sizeof(turn) >= kParts * SG::kThreads * sizeof(float), "room for a team's results");
+      const auto cell = [&](int k) -> float& { return part[k * SG::kThreads]; };
+      if (second) {
+        cell(0) = m2; cell(1) = m2_rest; cell(2) = ssum; cell(3) = ssum_hi; cell(4) = best_z; cell(5) = __int_as_float(best_c);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { cell(6 + v) = ea_lo[v]; cell(10 + v) = ea_hi[v]; }
+      }
+      __syncthreads();
+      if (second) return;
+      const float om2 = cell(0), orest = cell(1), top = fmaxf(m2, om2);
+      const float rest = m2 > om2 ? m2_rest : m2 == om2 ? fmaxf(m2_rest, orest) : orest;
+      // factors of this lane's request and, for the sums of the requests that the neighbouring row holds, of that one (see softmax_tile)
+      const auto factors = [&](float scale, float& lo, float& hi) {
+        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(scale), __float_as_uint(scale), false, false);
+        const bool odd = (lane & 16) != 0;
+        const float nb = __uint_as_float(odd ? sw[0] : sw[1]);
+        lo = odd ? nb : scale;
+        hi = odd ? scale : nb;
+      };
+      float mine_lo, mine_hi, other_lo, other_hi;
+      factors(__builtin_amdgcn_exp2f((m2 - top) + (m2_rest - rest)), mine_lo, mine_hi);
+      factors(__builtin_amdgcn_exp2f((om2 - top) + (orest - rest)), other_lo, other_hi);
+      ssum = fmaf(ssum, mine_lo, cell(2) * other_lo);
+      ssum_hi = fmaf(ssum_hi, mine_hi, cell(3) * other_hi);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        ea_lo[v] = fmaf(ea_lo[v], mine_lo, cell(6 + v) * other_lo);
+        ea_hi[v] = fmaf(ea_hi[v], mine_hi, cell(10 + v) * other_hi);
+      }
+      const float oz = cell(4);
+      if (oz > best_z) { best_z = oz; best_c = __float_as_int(cell(5)); }     // (its classes come later)
+      m2 = top;
+      m2_rest = rest;
+      break;
+    }
     const float un = I::kF32 ? __builtin_amdgcn_ldexpf(un1, -ex) : 1.f;
     if constexpr (!MLP) {
       // the group's table and bias are the running stage; the next group's first slice follows
       const float4* tab = reinterpret_cast<const float4*>(buf[st & 1]);
-      fetch(st + 1);
+      fetch(st + 1, w0);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int hb = 0; hb < NB; ++hb) {
@@ -412,9 +561,10 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
         __builtin_amdgcn_sched_barrier(0);
       }
       if (grp + 1 < n_groups) {
-        park(st + 1);
+        park(st + 1, w0);
         __syncthreads();
         ++st;
+        if (kAhead) fetch(st + 1, w1);
       }
     } else {
       // Rows with an infinity (their halves are NaN): every hidden unit by the features that are not finite, as float32
@@ -473,14 +623,14 @@ __global__ __launch_bounds__(stream_waves(NB) * kWave, 2) void k_score_stream(
         }
       for (int ct = 0; ct < CT; ++ct) {
         const float4* blk = reinterpret_cast<const float4*>(buf[st & 1]);
-        if (ct + 1 < CT) fetch(st + 1);
+        if (ct + 1 < CT) fetch(st + 1, w0);
         __builtin_amdgcn_sched_barrier(0);
         f32x16 z;
         logits_phase<D>(blk, xh, xl, z, lane);
         softmax_tile<true>(blk + SplitBlock<D, 3>::kWUnits, blk + SplitBlock<D, 3>::kWUnits + SplitBlock<D, 3>::kTabUnits, z, unscale, ea_lo, ea_hi,
                      ssum, ssum_hi, m2, m2_rest, ct, C, g, lane, valid, dump_row, logits_out, best_z, best_c, dump, split);
         if (ct + 1 < CT) {
-          park(st + 1);
+          park(st + 1, w0);
           __syncthreads();
         }
         ++st;

@@ -1013,6 +1013,44 @@ def test_heads_of_the_streaming_kernel(gpu, shape):
     full_parity(gpu, w, max_rounds=10, ea_tol=2e-3 if dtype == wl.BF16 else None)
 
 
+@pytest.mark.parametrize("dtype,d,C", [(wl.F32, 160, 32), (wl.F32, 161, 33), (wl.F32, 195, 64), (wl.F32, 225, 65), (wl.F32, 260, 128), (wl.F32, 1003, 5),
+                                       (wl.BF16, 320, 64), (wl.BF16, 321, 100), (wl.BF16, 391, 32), (wl.BF16, 455, 33), (wl.BF16, 512, 128)])
+def test_rows_shared_by_two_teams(gpu, dtype, d, C):
+    """Five to thirty-two slices of a row, even and odd numbers, whole and partial last ones, taken by one team of wavefronts (windows of more
+    tiles than compute units, or of five slices) or two: the same requests in a long window and in short ones, logits, labels and
+    rows that bring their largest value in either team's share."""
+    torch, binding = gpu
+    tiles = torch.cuda.get_device_properties(0).multi_processor_count
+    n, few = tiles * 128 + 1, 389
+    w = wl.tiny(seed=8250 + d, n=few, classes=(C, 3), models=(5, 16), feat_dim=d, feat_dtype=dtype, fractions=(0.7, 0.3))
+    x = w.requests.x
+    if dtype == wl.F32:
+        x[0::5, :40] *= np.float32(30.0)
+        # (a product is held to 2^-22, so 32 of about 20 * 0.1 leave 3e-6 of a logit; at a thousand times a feature's usual size it is 1e-4, beyond
+        # the tolerance, in any float32 sum)
+        x[1::5, 32:64] *= np.float32(20.0)
+        x[2::5, d - 1] = np.float32(50.0)
+        x[3::5, 32:] = 0.0
+    ref_ea, ref_key = orc.score_requests(w.profile, w.requests)
+    tol = 2e-3 if dtype == wl.BF16 else TOL
+    ctx = binding.Context(w.profile, n, policy=wl.Policy(split_groups=1))
+    short = binding.to_device(w.requests)
+    long = [torch.cat([t.repeat(*([n // few + 1] + [1] * (t.dim() - 1)))[: n - few], t]) for t in short]
+    got = []
+    for args, m in ((short, few), (long, n), ([t[: n - 1] for t in long], n - 1)):
+        ea, key = torch.zeros((m, ctx.m_max), device="cuda:0"), torch.zeros(m, device="cuda:0")
+        logits = torch.zeros((m, C), device="cuda:0")
+        ctx.sp_score(*args, ea_out=ea, key_out=key)
+        ctx.sp_debug_dump(binding.SP_DUMP_LOGITS, logits, x=args[0])
+        got.append([v[:few].cpu().numpy() for v in (ea, key, logits)])
+    ctx.close()
+    for ea, key, logits in got:
+        parity.assert_close("EA", ea, ref_ea, tol)
+        parity.assert_close("key", key, ref_key, tol, floor=1e-30)
+        # sums of up to 1,003 products of 22 bits and more, in another order
+        parity.assert_close("logits", logits, got[1][2], 1e-5, floor=float(np.abs(logits).max()))
+
+
 @pytest.mark.parametrize("hidden", [0, 24])
 def test_streamed_rows_of_any_scale(gpu, hidden):
     """float32 rows are scaled by a running maximum: rows whose large values come first, last, or not at all, rows of zeros,
