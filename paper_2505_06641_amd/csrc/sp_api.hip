@@ -704,6 +704,12 @@ void launch_score_stream(sp_ctx* c, hipStream_t s, const void* x, const int32_t*
       return;
     }
   }
+  if constexpr (MLP && sizeof(T) == 2) {
+    if (c->stream_nb == 2 && ((int64_t)c->n + tile - 1) / tile <= 2 * c->cus) {      // (see stream_turns)
+      hipLaunchKernelGGL((k_score_stream<T, 2, MLP, false, 1, true>), grid, blk, 0, s, c->tb, c->w, (const T*)x, ids, dw, sortkey, c->stream, logits);
+      return;
+    }
+  }
 #define SP_LAUNCH_ST(NB) \
   hipLaunchKernelGGL((k_score_stream<T, NB, MLP, COLS>), grid, blk, 0, s, c->tb, c->w, (const T*)x, ids, dw, sortkey, c->stream, logits)
   switch (c->stream_nb) {

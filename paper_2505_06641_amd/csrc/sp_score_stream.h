@@ -59,9 +59,14 @@ constexpr int kTeamSlices = 6;
 // with it 8 lines, and the turn takes four LDS writes and four reads.  us per call, as it lies in memory / turned: 10 classes, rows of 700 floats,
 // 100,000 115.5 / 97.6, 30,000 39.9 / 37.8; 60 classes 108.7 / 99.7, 40.8 / 38.9; bfloat16 hidden layers of 64 and 128, 384 features, 30,000
 // 32.6 / 30.7, 34.6 / 33.4.  Not where registers run out: 100 classes of floats 54.9 / 58.0 (60,000 rows of 512); nor for hidden layers on floats,
-// which take fewer wavefronts per SIMD then: 100,000 of 100-32-10 46.0 / 48.9, of 128-64-10 49.7 / 50.2.
+// which take fewer wavefronts per SIMD then: 100,000 of 100-32-10 46.0 / 48.9, of 128-64-10 49.7 / 50.2.  bfloat16 hidden layers of 33 to 64
+// units turn rows while a window has at most two tiles per compute unit, the two wavefronts per SIMD that are left of three: 200,000 of
+// 384-64-50 88.7 / 94.1.
 template <typename T, int NB, bool MLP, int KS>
-constexpr bool stream_turns() { return sizeof(T) == 4 ? !MLP && NB <= 2 : NB <= 2 || (NB == 4 && (MLP || KS == 2)); }
+constexpr bool stream_turns() {
+  if (sizeof(T) == 4) return !MLP && NB <= 2;
+  return NB == 1 || (NB == 2 && !MLP) || (NB == 4 && (MLP || KS == 2));
+}
 
 template <typename T>
 struct StreamIn {
@@ -182,7 +187,7 @@ static __device__ f32x4 stream_zeros;            // what lies behind a row's end
 // 16 bytes of a feature row: rows start at any multiple of the element size
 typedef f32x4 f32x4_any __attribute__((aligned(2)));
 
-template <typename T, int NB, bool MLP, bool COLS = false, int KS = 1>
+template <typename T, int NB, bool MLP, bool COLS = false, int KS = 1, bool TURN = stream_turns<T, NB, MLP, KS>()>
 __global__ __launch_bounds__(KS * stream_waves(NB) * kWave, 2) void k_score_stream(
     Tables tb, Window w, const T* __restrict__ x, const int32_t* __restrict__ ids, const float2* __restrict__ dw_g,
     uint32_t* __restrict__ sortkey, StreamHeads hd, float* __restrict__ logits_out) {
@@ -240,7 +245,7 @@ __global__ __launch_bounds__(KS * stream_waves(NB) * kWave, 2) void k_score_stre
 
   // ---- features: this lane's 64 bytes of a step, 16 at a time.  kTurn: read in whole lines, eight lanes a row, and turned in LDS (a
   // wavefront its own rows), where piece p of row r lies in place p ^ (r % 8) of the row: no bank conflicts on either side ----
-  constexpr bool kTurn = stream_turns<T, NB, MLP, KS>();
+  constexpr bool kTurn = TURN;
   __shared__ f32x4 turn[KS * stream_waves(NB)][kTurn || KS == 2 ? 32 * 8 : 1];
   constexpr int kRows = kTurn ? 4 : 1;
   const unsigned char* rows[kRows];
