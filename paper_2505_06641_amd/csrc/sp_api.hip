@@ -1407,11 +1407,16 @@ sp_status sp_score(sp_ctx* c, int32_t n, const void* x_dev, const int32_t* app_d
     if (tm) SP_HIP(c, hipEventRecord(c->ev[2], s));
     const uint32_t* labels = order_requests(c, s, n, sortkey, c->bufK[1]);
     if (c->tb.pol_split) {
-      hipLaunchKernelGGL(k_slot_ranges, dim3((c->n_slots + 255) / 256), dim3(256), 0, s, c->n_slots,
-                         (const int32_t*)c->slot_app, (const int32_t*)c->slot_base, (const int32_t*)w.seg,
-                         labels, c->slot_beg, c->slot_end);
-      hipLaunchKernelGGL(k_groups_compact, dim3(1), dim3(1024), 0, s, c->n_slots, (const int32_t*)c->slot_app,
-                         (const int32_t*)c->slot_beg, (const int32_t*)c->slot_end, w, c->h_grp_n_dev);
+      if (c->n_slots <= kFewSlots) {
+        hipLaunchKernelGGL(k_groups_few, dim3(1), dim3(kFewSlots), 0, s, c->n_slots, (const int32_t*)c->slot_app, (const int32_t*)c->slot_base,
+                           (const int32_t*)w.seg, labels, w, c->h_grp_n_dev);
+      } else {
+        hipLaunchKernelGGL(k_slot_ranges, dim3((c->n_slots + 255) / 256), dim3(256), 0, s, c->n_slots,
+                           (const int32_t*)c->slot_app, (const int32_t*)c->slot_base, (const int32_t*)w.seg,
+                           labels, c->slot_beg, c->slot_end);
+        hipLaunchKernelGGL(k_groups_compact, dim3(1), dim3(1024), 0, s, c->n_slots, (const int32_t*)c->slot_app,
+                           (const int32_t*)c->slot_beg, (const int32_t*)c->slot_end, w, c->h_grp_n_dev);
+      }
     }
     if (tms) SP_HIP(c, hipEventRecord(c->ev[3], s));
     if (tm) c->timed_score = true;

@@ -1208,6 +1208,61 @@ __global__ __launch_bounds__(1024) void k_groups_compact(int n_slots, const int3
   }
 }
 
+// Both in one workgroup, for up to kFewSlots slots: a slot ends where the next one begins, so one search is enough, four ways at a time
+// (both kernels wait for one dependent trip to memory after the other).  Eight applications of 101 slots, 65,536 requests: 6.5 + 7.2 us
+// -> 7.6.
+constexpr int kFewSlots = 1024;
+__global__ __launch_bounds__(kFewSlots) void k_groups_few(int n_slots, const int32_t* __restrict__ slot_app, const int32_t* __restrict__ slot_base,
+                                                          const int32_t* __restrict__ seg, const uint32_t* __restrict__ sub_sorted, Window w,
+                                                          int32_t* __restrict__ grp_n_host /*pinned [2]*/) {
+  __shared__ int wave_cnt[kFewSlots / kWave], beg_s[kFewSlots], of_app[kFewSlots];
+  __shared__ int max_run;
+  const int s = threadIdx.x, lane = s & 63, wave = s >> 6;
+  of_app[s] = 0;
+  if (s == 0) max_run = 0;
+  const int a = slot_app[min(s, n_slots - 1)];
+  const int base = slot_base[a], b0 = seg[a], e0 = seg[a + 1];
+  const bool last = s + 1 >= n_slots || slot_app[s + 1] != a;    // (of its application)
+  const uint32_t code = (uint32_t)(s - base);
+  int lo = b0, hi = s < n_slots ? e0 : b0;                        // first position with at least this code
+  while (lo < hi) {
+    const int step = (hi - lo) / 4, p0 = lo + step, p1 = p0 + step, p2 = p1 + step;    // lo <= p0 <= p1 <= p2 < hi
+    const uint32_t c0 = sub_sorted[p0], c1 = sub_sorted[p1], c2 = sub_sorted[p2];
+    if (c2 < code) lo = p2 + 1;
+    else if (c1 < code) { lo = p1 + 1; hi = p2; }
+    else if (c0 < code) { lo = p0 + 1; hi = p1; }
+    else hi = p0;
+  }
+  beg_s[s] = lo;
+  __syncthreads();
+  const int end = last ? e0 : beg_s[s + 1];
+  const bool full = s < n_slots && end > lo;
+  const unsigned long long bal = __ballot(full);
+  if (lane == 0) wave_cnt[wave] = __popcll(bal);
+  if (full) atomicAdd(&of_app[a], 1);                             // (every application has a slot, so there are no more of them than slots)
+  __syncthreads();
+  int before = 0, total = 0;
+  for (int i = 0; i < kFewSlots / kWave; ++i) {
+    before += i < wave ? wave_cnt[i] : 0;
+    total += wave_cnt[i];
+  }
+  if (of_app[s] > 0) atomicMax(&max_run, of_app[s]);
+  if (full) {
+    const int j = before + __popcll(bal & ((1ull << lane) - 1ull));
+    if (j < w.gcap) {
+      w.grp_app[j] = a;
+      w.grp_end[j] = end;
+      w.head[j] = lo;
+      w.head[w.gcap + j] = lo;
+    }
+  }
+  __syncthreads();
+  if (s == 0) {
+    grp_n_host[0] = w.grp_n[0] = min(total, w.gcap);
+    grp_n_host[1] = w.grp_n[1] = max_run;
+  }
+}
+
 // The same two numbers of an empty window for the host, in the order of the stream: an earlier window's k_groups_compact may
 // still be on its way there.
 __global__ void k_groups_publish(Window w, int32_t* __restrict__ grp_n_host /*pinned [2]*/) {

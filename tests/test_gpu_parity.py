@@ -1186,6 +1186,18 @@ def test_ordering_by_subgroup_and_key(gpu, n):
         assert np.array_equal(got[keep], want)
 
 
+@pytest.mark.parametrize("classes", [(2,), (1000, 22), (1000, 23), (40, 3, 500)])
+def test_subgroups_up_to_the_slots_of_one_workgroup_and_beyond(gpu, classes):
+    """Groups formed from 3 possible pairs of application and label, from 1,024 (one thread each) and from 1,025: their ranges, their number
+    and what the rounds make of them."""
+    A = len(classes)
+    w = wl.tiny(seed=9300 + classes[-1], n=500, classes=classes, models=(3, 2, 4)[:A], max_batch=6, feat_dim=16, deadline=(6.0, 150.0),
+                fractions=(0.6, 0.3, 0.1) if A == 3 else (0.7, 0.3)[:A] if A == 2 else (1.0,))
+    for a in range(A):
+        w.profile.W1[a] *= np.float32(8.0)               # (decided heads: most requests have a label)
+    full_parity(gpu, w, max_rounds=12, want_cube=True, policy=wl.Policy(split_groups=1))
+
+
 @pytest.mark.parametrize("n", [1023, 1024, 1025, 3100])
 @pytest.mark.parametrize("rounds", [1, 3])
 def test_outputs_of_unserved_requests_at_the_fill_edges(gpu, n, rounds):
