@@ -45,6 +45,8 @@ struct sp_ctx {
   int32_t* bufV[3] = {nullptr, nullptr, nullptr};
   // grouping: every tile's counts per application, or (more than 255 applications) the radix passes' digit totals and
   // per-tile published counts
+  unsigned long long* group_words = nullptr;   // see GroupWords
+  uint32_t* group_launch = nullptr;
   uint32_t* group_counts = nullptr;  // [tiles, 256]
   uint32_t* dtot_app = nullptr;      // [2 passes, 1 row, 256] passes over the application ids (one segment)
   uint32_t* dtot_key = nullptr;      // [kMaxSortPasses, tiles_cap, 256] passes inside the applications' ranges
@@ -475,8 +477,15 @@ sp_status build_ctx(sp_ctx* c, const sp_profile* p) {
   }
   if ((s = dev_alloc(c, &c->dtot_app, 2 * 256)) != SP_OK) return s;
   if (N > (size_t)kMergeMax && (s = dev_alloc(c, &c->dtot_key, (size_t)kMaxSortPasses * c->tiles_cap * 256)) != SP_OK) return s;
-  if ((s = dev_alloc(c, &c->sort_state, (size_t)c->tiles_cap * 256)) != SP_OK) return s;
-  SP_HIP(c, hipMemset(c->sort_state, 0, (size_t)c->tiles_cap * 256 * sizeof(unsigned long long)));
+  {
+    // what starts at zero: the passes' words, the grouping's words and its two numbers, the rounds' workgroups that have left
+    const size_t sort_words = (size_t)c->tiles_cap * 256, words = sort_words + (size_t)kGroupDirect * kGroupWords;
+    if ((s = dev_alloc(c, &c->sort_state, words + 2)) != SP_OK) return s;
+    SP_HIP(c, hipMemset(c->sort_state, 0, (words + 2) * sizeof(unsigned long long)));
+    c->group_words = c->sort_state + sort_words;
+    c->group_launch = reinterpret_cast<uint32_t*>(c->sort_state + words);
+    c->ps.left = reinterpret_cast<uint32_t*>(c->sort_state + words + 1);
+  }
   if ((s = dev_alloc(c, &c->sort_desc, std::max(std::min(N, (size_t)kRankMax) / kRanks, N / kRun) + A + kXcds)) != SP_OK) return s;
   if ((s = dev_alloc(c, &c->seg1, 2)) != SP_OK) return s;
   for (int i = 0; i < (app_passes(A) > 1 ? 2 : 1); ++i)
@@ -782,8 +791,6 @@ sp_status setup_persist(sp_ctx* c, const sp_profile* p) {
   if ((s = dev_alloc(c, &ps.ring, ring)) != SP_OK) return s;
   if ((s = dev_alloc(c, &ps.dec, kPersistRounds)) != SP_OK) return s;
   if ((s = dev_alloc(c, &ps.decision, 8)) != SP_OK) return s;
-  if ((s = dev_alloc(c, &ps.left, 1)) != SP_OK) return s;
-  SP_HIP(c, hipMemset(ps.left, 0, sizeof(uint32_t)));
   SP_HIP(c, hipMemset(ps.decision, 0, 8 * 8));
   if ((s = dev_alloc(c, &ps.ticks, kPersistRounds + 1)) != SP_OK) return s;
   SP_HIP(c, hipMemset(ps.slots, 0, 8 * n_pairs * 8));
@@ -1111,11 +1118,21 @@ int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev,
     if (n <= kGroupSelf && A <= kGroupSelfApps) {
 #define SP_GROUP(QUADS)                                                                                                 \
       hipLaunchKernelGGL((k_group_place<2, QUADS>), place_grid, dim3(kGroupThreads), 0, s, n, A, nbits, app_dev, deadline_ms_dev, \
-                         weight_dev, (const uint32_t*)nullptr, tiles, c->bufV[0], c->dw_g[0], seg_args, w, w.st)
+                         weight_dev, (const uint32_t*)nullptr, tiles, c->bufV[0], c->dw_g[0], seg_args, w, w.st, GroupWords{})
       if (n <= 2048) SP_GROUP(1);
       else if (n <= 8192) SP_GROUP(4);
       else if (n <= 16384) SP_GROUP(8);
       else SP_GROUP(16);
+#undef SP_GROUP
+      return c->bufV[0];
+    }
+    if (tiles <= kGroupDirect && A <= kGroupOneApps) {
+      const GroupWords gw{c->group_words, c->group_launch, c->spin_limit == kSpinLimit ? kGroupSpins : 0};
+#define SP_GROUP(ITEMS)                                                                                                 \
+      hipLaunchKernelGGL((k_group_place<ITEMS, -1>), place_grid, dim3(kGroupThreads), 0, s, n, A, nbits, app_dev, deadline_ms_dev, \
+                         weight_dev, (const uint32_t*)nullptr, tiles, c->bufV[0], c->dw_g[0], seg_args, w, w.st, gw)
+      if (tile == 1024) SP_GROUP(2);
+      else SP_GROUP(4);
 #undef SP_GROUP
       return c->bufV[0];
     }
@@ -1127,7 +1144,7 @@ int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev,
         hipLaunchKernelGGL(k_group_scan, dim3(A + 1), dim3(1024), 0, s, c->group_counts, tiles);                        \
       hipLaunchKernelGGL(k_group_place<ITEMS>, place_grid, dim3(kGroupThreads), 0, s, n, A, nbits, app_dev,             \
                          deadline_ms_dev, weight_dev, (const uint32_t*)c->group_counts, tiles, c->bufV[0], c->dw_g[0],  \
-                         seg_args, w, w.st);                                                                            \
+                         seg_args, w, w.st, GroupWords{});                                                              \
     } while (0)
     if (tile == 1024) SP_GROUP(2);
     else SP_GROUP(4);

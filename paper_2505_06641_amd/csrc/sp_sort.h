@@ -2,8 +2,9 @@
 // priority"; eq. (12); Sec. 5.3.2 with subgroups).
 //
 // Grouping by application.  Short windows of up to seven applications: one kernel, in which every workgroup counts the whole
-// window.  Else up to 255 applications: one kernel counts the applications of every tile of the queue
-// (k_group_count), a second one places the requests (k_group_place): a tile reads the counts of all tiles, which are few
+// window.  Else windows of up to 262,144 requests of up to 31 applications: one kernel too, whose tiles hand each other their counts, and
+// count for themselves what does not come (GroupWords).  Else up to 255 applications: one kernel counts the applications of every tile of
+// the queue (k_group_count), a second one places the requests (k_group_place): a tile reads the counts of all tiles, which are few
 // (tiles times applications words), so no tile waits for another.  More applications: two or three stable radix passes
 // over the ids (k_digit_totals, k_radix_pass), whose tiles learn the digit counts of the tiles before them by looking back
 // through published words.
@@ -672,6 +673,110 @@ __device__ __forceinline__ void group_sums_self(const int32_t* __restrict__ app,
   __syncthreads();
 }
 
+// Windows of up to kGroupDirect tiles that are not counted in that way: every workgroup counts its tile, hands the counts to the others and
+// waits for theirs, which spares a launch.  A word carries two counts and the number of the launch, which the launch before has left in
+// memory (not an argument: a recorded launch may be played again), and is valid exactly when that number is the launch's.  A wait that
+// runs out (the grid did not fit on the device beside other work) is no error: what has not come is counted from the ids.  Kernels, 65,536
+// requests: 3.4 to 4.6 + 5.1 to 6.2 us -> 7.4 to 8.9.  us per scoring call (16 features), two launches / one: eight applications of 4,000
+// requests 21.3 / 19.3, 32,768 25.9 / 23.6, 65,536 28.7 / 26.8, 100,000 36.1 / 34.9, 200,000 62.2 / 60.3; thirty-one of 65,536 27.8 / 26.4,
+// 262,144 67.9 / 65.8; one of 65,536 38.7 / 37.9, seven of 131,072 (128 tiles, where the polls are most) 49.7 / 49.8.
+constexpr int kGroupOneApps = 31;                      // (sixteen words a tile; a workgroup reads all tiles' words)
+constexpr int kGroupWords = (kGroupOneApps + 2) / 2;
+constexpr int kGroupSpins = 64;                        // polls of about half a microsecond
+struct GroupWords {
+  unsigned long long* words;                           // [kGroupDirect][kGroupWords]
+  uint32_t* launch;                                    // workgroups that have their sums; launches so far
+  int32_t spins;
+};
+
+// A tile's counts (of up to 2,048 requests) to the other workgroups.
+__device__ __forceinline__ void publish_counts(const GroupWords& gw, uint32_t launch, int tile, int A, const uint32_t* count) {
+  const int tid = threadIdx.x;
+  if (2 * tid > A) return;
+  const uint32_t two = count[2 * tid] | (2 * tid + 1 <= A ? count[2 * tid + 1] << 16 : 0u);
+  __hip_atomic_store(gw.words + tile * kGroupWords + tid, ((unsigned long long)(launch + 1u) << 32) | two, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// What group_sums gives, from the words of all tiles.
+__device__ __forceinline__ void group_sums_handed(const GroupWords& gw, uint32_t launch, const int32_t* __restrict__ app, int n, int n_tiles, int tile,
+                                                  int tile_size, int A, uint32_t* before, uint32_t* total, uint32_t (*red)[2][64]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_words = A / 2 + 1;
+  int bits = 0;
+  while ((1 << bits) < n_words) ++bits;
+  const int nw = 1 << bits, parts = kGroupThreads >> bits, word = tid & (nw - 1);
+  constexpr int kMost = kGroupDirect * kGroupWords / kGroupThreads;
+  static_assert((kGroupWords & (kGroupWords - 1)) == 0 && kGroupWords <= 16 && kGroupDirect * kGroupWords % kGroupThreads == 0, "shares of a thread");
+  unsigned long long v[kMost];
+  bool there = false;
+  for (int spin = 0; spin < gw.spins && !there; ++spin) {
+    there = true;
+#pragma unroll
+    for (int k = 0; k < kMost; ++k) {
+      const int q = (tid >> bits) + k * parts;
+      if (q < n_tiles && word < n_words) v[k] = __hip_atomic_load(gw.words + q * kGroupWords + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int k = 0; k < kMost; ++k) {
+      const int q = (tid >> bits) + k * parts;
+      there = there && (q >= n_tiles || word >= n_words || (uint32_t)(v[k] >> 32) == launch + 1u);
+    }
+  }
+  uint32_t sum[2][2] = {{0u, 0u}, {0u, 0u}};           // before, total; even and odd application
+#pragma unroll
+  for (int k = 0; k < kMost; ++k) {
+    const int q = (tid >> bits) + k * parts;
+    if (q >= n_tiles || word >= n_words) continue;
+    uint32_t c[2];
+    if (there) {
+      c[0] = (uint32_t)v[k] & 0xffffu;
+      c[1] = (uint32_t)v[k] >> 16;
+    } else {
+      c[0] = c[1] = 0u;
+      for (int i = q * tile_size; i < min((q + 1) * tile_size, n); ++i) {
+        const uint32_t key = min((uint32_t)app[i], (uint32_t)A);
+        c[0] += key == (uint32_t)(2 * word) ? 1u : 0u;
+        c[1] += key == (uint32_t)(2 * word + 1) ? 1u : 0u;
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      sum[1][h] += c[h];
+      sum[0][h] += q < tile ? c[h] : 0u;
+    }
+  }
+  for (int o = nw; o < kWave; o <<= 1)
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) sum[e][h] += __shfl_xor(sum[e][h], o);
+  if (lane < nw) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) red[wave][e][2 * lane + h] = sum[e][h];
+  }
+  __syncthreads();
+  if (tid < 256) {
+    uint32_t sb = 0, stt = 0;
+    if (tid <= A) {
+#pragma unroll
+      for (int u = 0; u < kGroupWaves; ++u) {
+        sb += red[u][0][tid];
+        stt += red[u][1][tid];
+      }
+    }
+    before[tid] = sb;
+    total[tid] = stt;
+  }
+  // (all words read: the last workgroup to come here makes the launch's number the next one's)
+  if (tid == 0 && atomicAdd(gw.launch, 1u) == (uint32_t)n_tiles) {
+    __hip_atomic_store(gw.launch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(gw.launch + 1, launch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+}
+
 // The segments from the number of requests of every application (and of invalid ids, total[A]), at most 255 of them: one thread
 // per application, tables in LDS, three barriers (k_group_place takes 4.0 us for 256 requests where tables in memory took 4.8), two
 // more where tiles differ in cost.
@@ -743,13 +848,14 @@ __device__ __forceinline__ void segments_from_totals(const SegArgs& g, const Win
 // and weight (the scoring kernel then reads them in order instead of gathering by request id, 4 useful bytes per 64-byte
 // line).  One extra workgroup turns the counts into segment starts and descriptors.  Bound by three or four dependent
 // trips to memory (2 us each), not by its 28 bytes per request.
-// SELF > 0: the first kernel of a short window; it counts 2,048 SELF ids itself and resets the window's state.
+// SELF > 0: the first kernel of a short window; it counts 2,048 SELF ids itself and resets the window's state.  SELF < 0: the first kernel
+// too; its workgroups hand each other their counts (GroupWords).
 template <int ITEMS, int SELF = 0>
 __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int nbits, const int32_t* __restrict__ app,
                                                                const float* __restrict__ D, const float* __restrict__ weight,
                                                                const uint32_t* __restrict__ counts, int n_tiles,
                                                                int32_t* __restrict__ ids_out, float2* __restrict__ dw_out,
-                                                               SegArgs sg, Window sw, State* st) {
+                                                               SegArgs sg, Window sw, State* st, GroupWords gw) {
   constexpr int kTile = kGroupThreads * ITEMS;
   __shared__ uint32_t before[256];
   __shared__ __align__(16) uint32_t total[256];        // (read four words at a time: wave_digit_bases)
@@ -761,6 +867,9 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
     if constexpr (SELF > 0) {
       if (tid == 0) reset_state(st);
       group_sums_self<SELF>(app, n, 0, kTile, A, before, total, red);
+    } else if constexpr (SELF < 0) {
+      if (tid == 0) reset_state(st);
+      group_sums_handed(gw, gw.launch[1], app, n, n_tiles, 0, kTile, A, before, total, red);
     } else {
       group_sums(counts, n_tiles, 0, A, nbits, before, total, red);
     }
@@ -780,6 +889,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
   __shared__ uint8_t skey[kTile];
   for (int i = tid; i < kGroupWaves * 256; i += kGroupThreads) cnt[0][i] = 0u;
   const int beg = tile * kTile;
+  const uint32_t launch = SELF < 0 ? gw.launch[1] : 0u;
   uint32_t key[ITEMS];
   float2 pay[ITEMS];
   bool bad = false;
@@ -791,7 +901,8 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
   }
   // (the barriers in here cover the cleared counts)
   if constexpr (SELF > 0) group_sums_self<SELF>(app, n, tile, kTile, A, before, total, red);
-  else group_sums(counts, n_tiles, tile, A, nbits, before, total, red);
+  else if constexpr (SELF == 0) group_sums(counts, n_tiles, tile, A, nbits, before, total, red);
+  else __syncthreads();
   // rank inside the wavefront: lanes with my application ahead of me in this chunk, plus the wavefront's earlier chunks
   const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   uint32_t rank[ITEMS];
@@ -814,6 +925,12 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(int n, int A, int
       cnt[v][tid] = mine;
       mine += c;
     }
+  }
+  if constexpr (SELF < 0) {
+    if (tid < 256) lstart[tid] = mine;
+    __syncthreads();
+    publish_counts(gw, launch, tile, A, lstart);
+    group_sums_handed(gw, launch, app, n, n_tiles, tile, kTile, A, before, total, red);
   }
   const uint32_t ls = scan256_excl<kGroupWaves>(tid < 256 ? mine : 0u, wave_tot);
   const uint32_t gs = scan256_excl<kGroupWaves>(tid < 256 ? total[tid] : 0u, wave_tot);

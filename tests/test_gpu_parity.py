@@ -1122,6 +1122,57 @@ def test_short_windows_counted_and_placed_in_one_launch(gpu, n, A):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,A", [(1, 8), (1023, 8), (1025, 31), (2049, 32), (32769, 7), (40000, 1), (131072, 31), (131073, 30), (262144, 9)])
+def test_windows_whose_tiles_hand_each_other_their_counts(gpu, n, A):
+    """One tile to 128, one application more than are counted in this way: windows one after the other with other ids and lengths, waits that run
+    out at once (every tile counted from the ids), and a recorded window played again with ids changed in place.  Whole numbers."""
+    torch, binding = gpu
+    rng = np.random.default_rng(9100 + n + A)
+    w = wl.tiny(seed=9100 + A, n=n, classes=(2,) * A, models=(1,) * A, max_batch=2, feat_dim=8)
+    x, app, D, wt = binding.to_device(w.requests)
+    key = torch.zeros(n, device="cuda:0")
+    order = torch.zeros(n, dtype=torch.int32, device="cuda:0")
+    seg = torch.zeros(A + 1, dtype=torch.int32, device="cuda:0")
+    ctx = binding.Context(w.profile, n)
+
+    def draw(m):
+        p = rng.random(A) ** 3 + 1e-3
+        ids = rng.choice(A, m, p=p / p.sum()).astype(np.int32)
+        app[:m].copy_(torch.from_numpy(ids))
+        return ids
+
+    def check(ids):
+        ctx.sp_debug_dump(binding.SP_DUMP_SEGMENTS, seg)
+        assert np.array_equal(seg.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(ids, minlength=A))]))
+        ctx.sp_debug_dump(binding.SP_DUMP_ORDER, order)
+        m = ids.size
+        assert np.array_equal(order[:m].cpu().numpy(), np.lexsort((np.arange(m), -key[:m].cpu().numpy().astype(np.float64), ids)))
+
+    for m in (n, max(1, n // 2), n):
+        ids = draw(m)
+        ctx.sp_score(x[:m], app[:m], D[:m], wt[:m], key_out=key)
+        check(ids)
+    ctx.sp_debug_set_spin_limit(1)
+    for _ in range(2):
+        ids = draw(n)
+        ctx.sp_score(x, app, D, wt, key_out=key)
+        check(ids)
+    ctx.sp_debug_set_spin_limit(0)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        ctx.sp_score(x, app, D, wt, key_out=key)
+    for _ in range(3):
+        ids = draw(n)
+        graph.replay()
+        torch.cuda.synchronize()
+        check(ids)
+        ids = draw(n)
+        ctx.sp_score(x, app, D, wt, key_out=key)
+        check(ids)
+    ctx.close()
+
+
 @pytest.mark.parametrize("policy", ["sneakpeek", "lo_edf"])
 @pytest.mark.parametrize("n,A,ties", [
     (1, 1, 0), (255, 2, 0), (1023, 1, 0), (1024, 1, 0), (1025, 1, 0), (3000, 1, 3), (4097, 3, 0), (16384, 1, 0), (16385, 1, 2),
