@@ -25,10 +25,10 @@
 // registers and walk the class tiles like the bfloat16 kernel; class blocks follow the slices through the same two
 // buffers.
 //
-// Measured (rocprofv3, median us, before -> now): 32,768 rows of 768 floats, 100 classes 1543 -> 38.7 (2.6 TB/s of rows);
-// 65,536 rows of 512 bfloat16, 100 classes 1273 -> 26.2 (2.6 TB/s); 100,000 requests of 128-64-10/7/2 float32 heads 185 -> 27.0
-// (1.9 TB/s), all three from the generic kernel; 30,011 of 384-128-100/37/10 bfloat16 heads 29 -> 20.6 (1.1 TB/s), from the
-// kernel that pads the hidden layer to 256.  A large copy reaches 5.2 TB/s on this card (read and written).
+// Measured (rocprofv3, median us): 32,768 rows of 768 floats, 100 classes 32.9 (3.1 TB/s of rows; 38.1 without the second team, 1543 in the
+// generic kernel); 65,536 rows of 512 bfloat16, 100 classes 24.5 (2.7 TB/s); 100,000 requests of 128-64-10/7/2 float32 heads 25.5
+// (2.0 TB/s); 30,011 of 384-128-100/37/10 bfloat16 heads 17.4 (1.3 TB/s; 19.9 with rows read as they lie).  A large copy reaches 5.2 TB/s on
+// this card (read and written).
 #pragma once
 #include "sp_common.h"
 #include "sp_score_split.h"
