@@ -17,7 +17,8 @@
 // Bound by dependent trips to memory (descriptor, keys, records; of longer applications one for the positions collected) and by the counting and
 // comparing, of which every workgroup of an application does all.  Kernel, us, where runs and merges took as many launches as given before:
 // 65,536 requests of eight applications 9.3 (three: 18.2), 4,096 of three 5.7 (two: 12.7).  A workgroup of 8,192 keys of its application: sample
-// in registers 1.4, counted 1.9, all keys tested and the range collected 2.0, counted again 1.1, in place 1.2; each 8,192 more 1.5.
+// in registers 1.4, counted 1.9, all keys tested and the range collected 2.0, counted again 1.1, in place 1.2; each 8,192 more 1.35 (1.5 when every
+// turn asked for its own places in LDS: one application of 65,536 requests 38.0 -> 36.8 us per call, three of 100,000 38.7 -> 38.2).
 #pragma once
 #include "sp_sort.h"
 
@@ -392,17 +393,26 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
           ++at;
         }
     } else {
+      // (places in LDS are asked for four turns at a time, a bit for each key: every wavefront waits for its answer)
+      uint32_t in = 0u;
+      int turns = 0;
       const auto take = [&](const Keys& k, int base) {
-        uint32_t in = 0u;
-        test_any(k, base, in);
+        uint32_t bits = 0u;
+        test_any(k, base, bits);
+        in |= bits << (kRankItems * turns);
+        ++turns;
+      };
+      const auto put = [&](int first) {                          // first: of the turns' keys
         uint32_t at = room_for(in);
         while (in != 0u) {
-          const int e = __ffs((int)in) - 1;
+          const int e = __ffs((int)in) - 1, turn = e / kRankItems;
           in &= in - 1u;
-          if (at < (uint32_t)kRankCap) held[at] = (Ranked)(uint32_t)(piece_at(base, e >> 2) + (e & 3));
+          if (at < (uint32_t)kRankCap) held[at] = (Ranked)(uint32_t)(piece_at(first + turn * kRankHeld, (e % kRankItems) >> 2) + (e & 3));
           ++at;
         }
+        turns = 0;
       };
+      static_assert(4 * kRankItems == 32, "four turns' keys in a word");
       Keys u;
       const auto fetch = [&](Keys& k, int base) {
 #pragma unroll
@@ -415,6 +425,7 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
         take(v, base);
         fetch(v, base + 2 * kRankHeld);
         if (base + kRankHeld < size) take(u, base + kRankHeld);
+        if (turns >= 3 || base + 2 * kRankHeld >= size) put(base + (turns > 2 ? -2 * kRankHeld : 0));
       }
     }
     before = wave_scan_incl(before);
