@@ -1084,10 +1084,11 @@ void radix_pass(sp_ctx* c, hipStream_t s, const SortPlan& plan, int tiles, const
 
 // Whether a window is ordered in one launch (k_order).  Its workgroups each read all keys of their application, so its time grows with
 // the largest one; runs and merges take one to four launches.  us per scoring call (16 features, 10 classes), runs and merges / one launch: one
-// application of 256 requests 13.6 / 14.5, 768 16.5 / 15.6, 4,096 22.4 / 19.0, 16,384 28.3 / 23.7, 65,536 39.5 / 36.8, 100,000 50.0 / 52.7 (before k_order asked for places four turns at a time); three
-// (0.5, 0.3, 0.2) of 16,384 25.0 / 22.9, 65,536 37.0 / 33.0, 100,000 45.8 / 41.9; eight of 16,384 25.8 / 20.6, 65,536 33.9 / 26.6, 100,000
-// 45.4 / 35.0, 131,072 (more workgroups than compute units) 49.2 / 48.8.  Deadlines as keys are often few different ones, and then it is the
-// slower way: of three deadlines one application of 16,384 27.6 / 37.2, 65,536 42.8 / 58.0, eight of 65,536 33.8 / 37.3.
+// application of 256 requests 13.6 / 14.5, 768 16.5 / 15.6, 4,096 22.4 / 19.0, 16,384 28.3 / 23.7, 65,536 39.5 / 36.8, 100,000 50.0 / 52.7
+// (before k_order asked for places four turns at a time); three (0.5, 0.3, 0.2) of 16,384 25.0 / 22.9, 65,536 37.0 / 33.0, 100,000 45.8 /
+// 41.9; eight of 16,384 25.8 / 20.6, 65,536 33.9 / 26.6, 100,000 45.4 / 35.0, 131,072 (more workgroups than compute units) 49.2 / 48.8.
+// Deadlines as keys are often few different ones, and then it is the slower way: of three deadlines one application of 16,384 27.6 / 37.2,
+// 65,536 42.8 / 58.0, eight of 65,536 33.8 / 37.3.
 bool one_launch_order(const sp_ctx* c, int n) {
   return n > kRankMin && n <= (c->A <= 2 ? kRankMaxFew : kRankMax) && !c->tb.pol_edf && !(c->tb.pol_split && c->Cmax >= kRankLabels);
 }
