@@ -131,7 +131,8 @@ struct RankDivision {
 
 template <bool SPLIT>
 __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint32_t* __restrict__ keys, const int32_t* __restrict__ labels,
-                                                        uint32_t* __restrict__ label_out, int n, Window w, int edf) {
+                                                        const int32_t* __restrict__ n_classes, uint32_t* __restrict__ label_out, int n, Window w,
+                                                        int edf) {
   __shared__ __align__(16) uint32_t bins[kRankBins + 4];
   __shared__ uint32_t bin_low[kRankBins], bin_high[kRankBins];
   __shared__ __align__(16) Ranked held[kRankCap];
@@ -167,6 +168,7 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
   const uint32_t r0 = (uint32_t)(__builtin_amdgcn_readfirstlane(desc.y) - s0), r1 = min(r0 + (uint32_t)kRanks, (uint32_t)size);
   keys += s0;
   if (SPLIT) labels += s0;
+  const uint32_t most_labels = SPLIT ? (uint32_t)n_classes[__builtin_amdgcn_readfirstlane(desc.w)] : 0u;   // (0: of no class's subgroup)
   // Keys are read in pieces of 256, four neighbours a lane; positions past the end give the last request again.
   typedef uint32_t quad __attribute__((ext_vector_type(4), aligned(4)));
   struct Keys { uint32_t key[kRankItems], label[SPLIT ? kRankItems : 1]; };
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
       }
   };
   rest();
-  uint32_t key_low, key_high, label_high = 0u;                  // the sample's
+  uint32_t key_low, key_high, label_high = 0u;                  // the sample's keys; the application's labels
   {
     uint32_t lo = 0u, hi = 0u, top = 0u;                        // lo: of the inverted keys
     each_sampled([&](uint32_t lb, uint32_t k, int, bool) {
@@ -239,7 +241,8 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
     __syncthreads();                                            // (also covers the cleared bins)
     key_low = ~wave_max_u32(lane < kRankWaves ? wave_low[lane] : 0u);
     key_high = wave_max_u32(lane < kRankWaves ? wave_high[lane] : 0u);
-    if (SPLIT) label_high = wave_max_u32(lane < kRankWaves ? wave_label[lane] : 0u);
+    // (a request that is not sampled may have any label: one above the greatest would share a bin with that one's requests)
+    if (SPLIT) label_high = all_held ? wave_max_u32(lane < kRankWaves ? wave_label[lane] : 0u) : most_labels;
   }
   RankBins<SPLIT> bin_of;
   bin_of.over(key_low, key_high, 0u, label_high);

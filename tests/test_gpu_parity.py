@@ -2016,3 +2016,50 @@ def test_ordering_by_subgroup_in_one_launch(gpu, n, C, shape):
         keep = np.isin(got, ids[clear])
         want = ids[clear][np.lexsort((ids[clear], -key[ids[clear]].astype(np.float64), label[clear]))]
         assert np.array_equal(got[keep], want)
+
+
+def _rare_labels_window(n, C, rare, shape):
+    """One application whose requests' classes are set by hand: all but the `rare` greatest in turn, and one to three requests of each of
+    those, early, in the middle and late among the requests that the ordering does not sample."""
+    rng = np.random.default_rng(n + C)
+    w = wl.tiny(seed=8950 + C, n=n, classes=(C,), models=(1,), max_batch=2, feat_dim=16)
+    w.profile.W1[0] = np.zeros((16, C), np.float32)
+    w.profile.W1[0][np.arange(C), np.arange(C)] = 40.0
+    w.profile.b1[0] = np.zeros(C, np.float32)
+    label = rng.integers(0, C - rare, n)
+    free = np.setdiff1d(np.arange(n), _sampled_positions(n))
+    for k in range(rare):
+        some = rng.choice(free, 1 + (C + k) % 3, replace=False)
+        label[some] = C - 1 - k
+        free = np.setdiff1d(free, some)
+    w.requests.x[:] = np.eye(16, dtype=np.float32)[label]
+    w.requests.deadline_rel_ms[:] = 10.0
+    if shape == "two deadlines":
+        w.requests.weight[:] = 1.0
+        w.requests.deadline_rel_ms[:] = rng.choice([10.0, 25.0], n)
+    else:
+        w.requests.weight[:] = np.where(rng.random(n) < 0.4, 0.0, rng.random(n)) if shape == "zeros" else rng.integers(1, 4, n) * 0.25
+    return w, label
+
+
+@pytest.mark.parametrize("shape", ["zeros", "three", "two deadlines"])
+@pytest.mark.parametrize("n,C,rare", [(8700, 2, 1), (20000, 2, 1), (20000, 3, 1), (20000, 12, 2), (60000, 2, 1), (60000, 4, 1), (60000, 8, 1), (60000, 12, 2),
+                                      (60000, 5, 3)])
+def test_ordering_by_subgroup_with_labels_that_are_not_sampled(gpu, n, C, rare, shape):
+    """The greatest subgroups consist of a few requests outside the ordering's sample.  Whole numbers, no tolerance."""
+    torch, binding = gpu
+    w, label = _rare_labels_window(n, C, rare, shape)
+    ctx = binding.Context(w.profile, n, policy=wl.Policy(split_groups=1))
+    key = torch.zeros(n, device="cuda:0")
+    order = torch.zeros(n, dtype=torch.int32, device="cuda:0")
+    x, app, D, wt = binding.to_device(w.requests)
+    ctx.sp_score(x, app, D, wt, key_out=key)
+    ctx.sp_debug_dump(binding.SP_DUMP_ORDER, order)
+    key = key.cpu().numpy().astype(np.float64)
+    assert np.array_equal(order.cpu().numpy(), np.lexsort((np.arange(n), -key, label)))
+    ctx.close()
+
+
+def test_rounds_over_subgroups_with_labels_that_are_not_sampled(gpu):
+    w, _ = _rare_labels_window(20000, 2, 1, "two deadlines")
+    full_parity(gpu, w, 4, policy=wl.Policy(split_groups=1))
