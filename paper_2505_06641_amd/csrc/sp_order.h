@@ -41,7 +41,7 @@ constexpr int kRankMaxFew = 65536;              // ... of one or two application
 constexpr int kRankPosBits = 17;                // label, key and position inside the application are one word
 constexpr int kRankLabels = 1 << (32 - kRankPosBits);     // subgroup labels
 static_assert(kRankBins == 4 * kRankThreads && kRankCap <= 2 * kRankBins && kRankHeld <= 2 * kRankBins, "shares of a thread; bins of a division");
-static_assert(kRankMax <= 1 << kRankPosBits, "positions");
+static_assert(kRankMax < 1 << kRankPosBits, "positions, and the one behind the last");
 
 // A request as one word: label (with subgroups), key, position in the application.
 typedef unsigned long long Ranked;
@@ -314,12 +314,12 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
 
   // ---- all keys: those before the range are counted, those inside it collected (of longer applications the positions alone) ----
   {
-    // the first number for which a condition that stays true once it is holds, sixty-four ways at a time
+    // the first number for which a condition that stays true once it is holds, sixty-four ways at a time; there has to be one
     const auto first_true = [&](int top_shift, auto holds) {
       uint32_t base = 0u;
       for (int shift = top_shift;; shift = max(shift - 6, 0)) {
         const uint32_t k = base + ((uint32_t)lane << shift);
-        const int n_false = __popcll(__ballot(!holds(k)));      // (a prefix of the lanes)
+        const int n_false = __popcll(__ballot(k >= base && !holds(k)));        // (a prefix of the lanes; of the last ones k may start over)
         if (shift == 0) return base + (uint32_t)n_false;
         if (n_false > 0) base += (uint32_t)(n_false - 1) << shift;
       }
@@ -329,18 +329,23 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
     uint32_t k0 = 0u, k_width = ~0u;
     Ranked low = 0ull, high = ~0ull;                            // (the first one behind it)
     if (!SPLIT && divided) {
-      const auto end_of = [&](uint32_t b, uint32_t d) {         // the first request of bin b with at least d in the second counting
-        if (bin_low[b] != bin_high[b]) return ranked(0u, first_true(26, [&](uint32_t k) {
-          const uint32_t at = bin_of(0u, k);
-          return at > b || (at == b && div(b, k, 0) >= d);
-        }), 0);
-        return ranked(0u, bin_low[b], (int)first_true(12, [&](uint32_t p) { return div(b, bin_low[b], (int)p) >= d; }));
+      // the first request of bin b with at least d in the second counting; behind all keys, or all of bin b's one key, where there is none
+      const auto end_of = [&](uint32_t b, uint32_t d) {
+        if (bin_low[b] != bin_high[b]) {
+          const auto holds = [&](uint32_t k) {
+            const uint32_t at = bin_of(0u, k);
+            return at > b || (at == b && div(b, k, 0) >= d);
+          };
+          return holds(~0u) ? ranked(0u, first_true(26, holds), 0) : ~0ull;
+        }
+        return ranked(0u, bin_low[b], (int)first_true(12, [&](uint32_t p) { return p >= (uint32_t)size || div(b, bin_low[b], (int)p) >= d; }));
       };
       if (d0 > 0u) low = end_of(b0, d0);
       if (d1 != ~0u) high = end_of(b1, d1 + 1u);
     } else if (!SPLIT && !all_held) {
       k0 = b0 > 0u ? first_key(b0) : 0u;
-      k_width = (b1 < kRankBins - 1u ? first_key(b1 + 1u) - 1u : ~0u) - k0;
+      // (of bins of few keys the last one's may be the greatest there is)
+      k_width = (b1 < kRankBins - 1u && bin_of(0u, ~0u) > b1 ? first_key(b1 + 1u) - 1u : ~0u) - k0;
     }
     uint32_t before = 0u;
     const auto test = [&](const Keys& k, int base, uint32_t& in, auto where) {       // (-1: before the range, 0: inside)

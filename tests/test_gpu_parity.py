@@ -2063,3 +2063,24 @@ def test_ordering_by_subgroup_with_labels_that_are_not_sampled(gpu, n, C, rare, 
 def test_rounds_over_subgroups_with_labels_that_are_not_sampled(gpu):
     w, _ = _rare_labels_window(20000, 2, 1, "two deadlines")
     full_parity(gpu, w, 4, policy=wl.Policy(split_groups=1))
+
+
+def test_ordering_of_equal_keys_finds_its_range(gpu):
+    """Where all keys are equal no workgroup of the one-launch ordering has to find its places digit by digit, which takes ten times as
+    long as all of the rest: the device time of the ordering is of the same order as for keys that are spread (bound: four times)."""
+    torch, binding = gpu
+    n, took = 65536, {}
+    for shape in ("spread", "equal"):
+        w = wl.tiny(seed=8990, n=n, classes=(2,), models=(1,), max_batch=2, feat_dim=8)
+        w.requests.deadline_rel_ms[:] = 10.0
+        w.requests.weight[:] = _weights(shape, n, np.random.default_rng(1)).astype(np.float32)
+        ctx = binding.Context(w.profile, n)
+        ctx.sp_set_timing(1)
+        data = binding.to_device(w.requests)
+        times = []
+        for _ in range(20):
+            ctx.sp_score(*data)
+            times.append(ctx.sp_get_timing()["order_ms"])
+        ctx.close()
+        took[shape] = min(times)
+    assert took["equal"] < 4 * took["spread"], took
