@@ -73,9 +73,11 @@ struct RankBins {
     if constexpr (SPLIT) return fmaf((float)(max(label, label0) - label0), per_label, fminf(v, fmaxf(per_label - 0.001f, 0.f)));
     else return v;
   }
-  __device__ __forceinline__ uint32_t operator()(uint32_t label, uint32_t key) const { return min((uint32_t)at(label, key), (uint32_t)kRankBins - 1u); }
+  __device__ __forceinline__ uint32_t operator()(uint32_t label, uint32_t key) const { return whole(at(label, key)); }
+  // (ends first: a number outside of what an integer holds has no integer)
+  static __device__ __forceinline__ uint32_t whole(float v) { return (uint32_t)__builtin_amdgcn_fmed3f(v, 0.f, (float)(kRankBins - 1)); }
   __device__ __forceinline__ uint32_t fine(Ranked e) const {
-    return min((uint32_t)((at(ranked_label(e), ranked_key(e)) - first) * finer), (uint32_t)kRankBins - 1u);
+    return whole((at(ranked_label(e), ranked_key(e)) - first) * finer);
   }
 };
 
