@@ -56,12 +56,11 @@ __device__ __forceinline__ uint32_t ranked_label(Ranked e) { return (uint32_t)(e
 // the ends.  With subgroups the labels, and inside each the keys; while there are bins for all labels, none has requests of two.
 template <bool SPLIT>
 struct RankBins {
-  uint32_t least, label0;
+  uint32_t least;
   float scale, per_label, first, finer;         // (then bins from `first` on, `finer` of them for one)
-  __device__ __forceinline__ void over(uint32_t low, uint32_t high, uint32_t label_low, uint32_t label_high) {
+  __device__ __forceinline__ void over(uint32_t low, uint32_t high, uint32_t label_high) {
     least = low;
-    label0 = label_low;
-    const float labels = (float)(label_high - label_low + 1u);
+    const float labels = (float)(label_high + 1u);
     per_label = labels > (float)kRankBins ? (float)kRankBins / labels : floorf((float)kRankBins / labels);
     scale = (SPLIT ? per_label : (float)kRankBins) / ((float)(high - low) + 1.0f);
     first = 0.f;
@@ -70,7 +69,7 @@ struct RankBins {
   __device__ __forceinline__ float at(uint32_t label, uint32_t key) const {
     const float v = (float)(max(key, least) - least) * scale;
     // (a label's last bins end a thousandth early: the sum is never rounded to the next label's first)
-    if constexpr (SPLIT) return fmaf((float)(max(label, label0) - label0), per_label, fminf(v, fmaxf(per_label - 0.001f, 0.f)));
+    if constexpr (SPLIT) return fmaf((float)label, per_label, fminf(v, fmaxf(per_label - 0.001f, 0.f)));
     else return v;
   }
   __device__ __forceinline__ uint32_t operator()(uint32_t label, uint32_t key) const { return whole(at(label, key)); }
@@ -133,8 +132,7 @@ struct RankDivision {
 
 template <bool SPLIT>
 __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint32_t* __restrict__ keys, const int32_t* __restrict__ labels,
-                                                        const int32_t* __restrict__ n_classes, uint32_t* __restrict__ label_out, int n, Window w,
-                                                        int edf) {
+                                                        const int32_t* __restrict__ n_classes, uint32_t* __restrict__ label_out, int n, Window w) {
   __shared__ __align__(16) uint32_t bins[kRankBins + 4];
   __shared__ uint32_t bin_low[kRankBins], bin_high[kRankBins];
   __shared__ __align__(16) Ranked held[kRankCap];
@@ -247,7 +245,7 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
     if (SPLIT) label_high = all_held ? wave_max_u32(lane < kRankWaves ? wave_label[lane] : 0u) : most_labels;
   }
   RankBins<SPLIT> bin_of;
-  bin_of.over(key_low, key_high, 0u, label_high);
+  bin_of.over(key_low, key_high, label_high);
   uint32_t b0 = 0u, b1 = kRankBins - 1u;                        // the range in bins, and
   uint32_t d0 = 0u, d1 = ~0u;                                   // (divided) in those of the second counting
   bool divided = false;
@@ -448,7 +446,7 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
     if (rank < r0 || rank >= r1) return;
     const int at = s0 + (int)rank;
     if constexpr (SPLIT) label_out[at] = ranked_label(e);
-    finish_position(w, at, ranked_key(e), s0 + ranked_pos(e), edf);
+    finish_position(w, at, ranked_key(e), s0 + ranked_pos(e), SPLIT ? 1 : 0);
   };
   if (count <= kRankCap && from <= r0 && r1 <= from + (uint32_t)count) {
     // ---- in finer bins over the range: counted, then put bin by bin, a bin's start counting up to its end ----
