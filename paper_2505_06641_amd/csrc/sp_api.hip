@@ -1082,15 +1082,22 @@ void radix_pass(sp_ctx* c, hipStream_t s, const SortPlan& plan, int tiles, const
                        c->sort_state, gen, c->sort_spin_limit, keys_out, vals_out, c->w.st, SortCarry{});
 }
 
-// Whether a window is ordered in one launch (k_order).  Its workgroups each read all keys of their application, so its time grows with
-// the largest one; runs and merges take one to four launches.  us per scoring call (16 features, 10 classes), runs and merges / one launch: one
-// application of 256 requests 13.6 / 14.5, 768 16.5 / 15.6, 4,096 22.4 / 19.0, 16,384 28.3 / 23.7, 65,536 39.5 / 36.8, 100,000 50.0 / 52.7
-// (before k_order asked for places four turns at a time); three (0.5, 0.3, 0.2) of 16,384 25.0 / 22.9, 65,536 37.0 / 33.0, 100,000 45.8 /
-// 41.9; eight of 16,384 25.8 / 20.6, 65,536 33.9 / 26.6, 100,000 45.4 / 35.0, 131,072 (more workgroups than compute units) 49.2 / 48.8.
-// Deadlines as keys are often few different ones, and then it is the slower way: of three deadlines one application of 16,384 27.6 / 37.2,
-// 65,536 42.8 / 58.0, eight of 65,536 33.8 / 37.3.
+// Whether a window is ordered in one launch (k_order).  us per scoring call (16 features, 10 classes, keys that are spread, both ways in turn),
+// runs and merges / one launch:
+// * Up to kRun requests runs take one launch too, and the shorter an application the sooner: 513 requests of one application 17.2 / 16.8,
+//   1,024 17.4 / 16.6; of two 16.1 / 16.3 and 16.5 / 16.7, of three 16.1 / 16.6 and 17.4 / 16.5, of five 15.2 / 16.8 and 15.6 / 16.7.  From 1,025
+//   on they take two: 21.8 / 17.3 of one, 18.0 / 17.0 of five, 20.8 / 19.9 of eight.  Up to 300 requests of one application 15.8 / 15.9.
+// * k_order's workgroups each read all keys of their application, so its time follows the largest one, which is not known here.  One of
+//   65,536 39.9 / 36.3, 80,000 42.0 / 42.0, 100,352 49.8 / 50.2; three (0.5, 0.3, 0.2) of 65,536 37.2 / 32.3, 100,000 45.6 / 40.7; eight of
+//   65,536 34.3 / 25.8, 100,000 45.4 / 34.5.  Windows of three and more go by what most divisions give: of 106,496 three 46.4 / 41.3, eight
+//   46.2 / 34.6; with 98% in one of three 50.8 / 51.2 (102,400 50.3 / 50.0), 93% in one of eight 50.3 / 51.3 (102,400 51.8 / 49.5).  Longer
+//   windows would find such applications far slower (at 120,000 what a workgroup of one application collects outgrows its LDS: 51.9 / 216).
+// * Keys of few values are the slower way: of those as spread as priorities are, one application of 16,384 28.4 / 24.1, but with 40% of the
+//   weights zero 28.3 / 37.1 and all keys equal 22.1 / 40.8; eight of 65,536 34.3 / 26.0, 34.1 / 37.4 and 28.9 / 39.4.  Deadlines as keys
+//   are often such (three deadlines, one of 16,384 27.6 / 37.2), so they take runs and merges.
 bool one_launch_order(const sp_ctx* c, int n) {
-  return n > kRankMin && n <= (c->A <= 2 ? kRankMaxFew : kRankMax) && !c->tb.pol_edf && !(c->tb.pol_split && c->Cmax >= kRankLabels);
+  return (n > kRun || (c->A == 1 && n > kRanks)) && n <= (c->A <= 2 ? kRankMaxFew : kRankMax) && !c->tb.pol_edf &&
+         !(c->tb.pol_split && c->Cmax >= kRankLabels);
 }
 // Requests of a sort run, for the descriptors.
 int sort_unit(const sp_ctx* c, int n) { return one_launch_order(c, n) ? kRanks : n <= kMergeMax ? kRun : kSortTile; }

@@ -35,8 +35,7 @@ constexpr int kRankCap = 7168;                  // requests collected in LDS
 constexpr int kRankOwn = kRankCap / kRankThreads;
 constexpr int kRankMates = 64;                  // fullest bin whose requests are compared one by one ...
 constexpr int kRankMatesLast = 512;             // ... after a division (few are as full: places next to another key's)
-constexpr int kRankMin = 512;                   // windows of up to this many: one run (k_sort_runs)
-constexpr int kRankMax = 106496;                // longest window
+constexpr int kRankMax = 106496;                // longest window (see one_launch_order)
 constexpr int kRankMaxFew = 65536;              // ... of one or two applications
 constexpr int kRankPosBits = 17;                // label, key and position inside the application are one word
 constexpr int kRankLabels = 1 << (32 - kRankPosBits);     // subgroup labels

@@ -1961,7 +1961,7 @@ def _weights(shape, n, rng):
 
 
 @pytest.mark.parametrize("shape", ["spread", "equal", "three", "zeros", "two scales", "rising", "almost equal", "sample apart"])
-@pytest.mark.parametrize("n,A", [(512, 1), (513, 1), (1025, 1), (4096, 1), (4097, 1), (8192, 1), (8193, 1), (20011, 1), (65536, 1), (65537, 1), (65536, 2),
+@pytest.mark.parametrize("n,A", [(512, 1), (513, 1), (1024, 2), (1025, 2), (1025, 5), (1025, 1), (4096, 1), (4097, 1), (8192, 1), (8193, 1), (20011, 1), (65536, 1), (65537, 1), (65536, 2),
                                  (65536, 8), (106496, 3), (106497, 3)])
 def test_ordering_in_one_launch(gpu, n, A, shape):
     """Window lengths around the steps of the one-launch ordering, keys that are evenly spread, equal, clustered, sorted or unlike
