@@ -81,7 +81,7 @@ struct sp_ctx {
   unsigned long long* h_ended = nullptr;       // pinned, behind h_state: the last launch that has told the host of its end (see tell_host_ended)
   unsigned long long* h_ended_dev = nullptr;   // its device-visible address
   unsigned long long launches = 0;   // launches that were to tell it so far
-  hipEvent_t ev_ended = nullptr;     // recorded behind such a launch of sp_schedule (see fetch_state)
+  hipEvent_t ev_ended = nullptr;     // recorded behind such a launch (see fetch_state)
   bool single_ok = false;            // a round by itself may run in one workgroup
   uint32_t gen_base = 0;             // slot generations handed out so far
   int32_t spin_limit = kSpinLimit;   // polls before a wait between resident workgroups is given up
@@ -1309,21 +1309,22 @@ sp_status wait_ended(sp_ctx* c, hipStream_t s) {
 }
 
 // Where the window's state comes from: copied behind what is on the stream, or written into the pinned copy by a round kernel's commits;
-// then the last launch on the stream may be one that tells the host.  kToldMarked: an event goes behind it while it runs.  The runtime
-// would do that itself when the program waits for the stream next, and the program for it (12 us instead of 4; 3 after
-// hipStreamSynchronize); it costs a microsecond and a half of the next window where the program does not wait.  us per window of 256
-// requests, without and with a wait behind it: hipStreamSynchronize 31.3 and 34.3, told 28.2 and 38.1, told and marked 30.5 and 30.9;
-// sp_score and eight calls of sp_greedy_round: 193.5 and 195.6, 162.0 and 192.9, 168.2 and 194.7.
-enum class Fetch { kCopied, kMirrored, kTold, kToldMarked };
+// kTold: by the last launch on the stream, which tells the host.  An event goes behind that launch while it runs.  The runtime would do that
+// itself when the program waits for the stream next, and the program for it; it costs a microsecond and a half of the next window where the
+// program does not wait.  us, without and with a wait for the stream behind it, hipStreamSynchronize / told without an event / with one: window of 256
+// requests 31.8 and 34.6 / 28.9 and 39.4 / 28.7 and 31.9; sp_score and one call of sp_greedy_round 49.9 and 52.6 / 45.4 and 56.4 / 45.3 and
+// 48.0; eight calls 201 and 204 / 158 and 190 / 165 and 192; thirty-two 357 and 360 / 277 and 309 / 287 and 319.  (Some 27 us of what
+// several calls in a row leave out the program meets when it next waits, once, however many they were.)
+enum class Fetch { kCopied, kMirrored, kTold };
 // Requests up to which sp_schedule waits in that way.  In hipStreamSynchronize the runtime also puts away what it has kept of a
 // context's first launches, 20 to 30 us beside a window that runs longer than that, which a program that synchronises then waits for:
 // 65,536 requests, first pass with a wait behind it 226 (told: 243), repeated ones 195 (189); 16,384 requests 101 to 106 (104 to 107) and 87 (83).
 constexpr int kToldRequests = 16384;
 
 sp_status fetch_state(sp_ctx* c, hipStream_t s, Fetch how) {
-  if (how == Fetch::kTold || how == Fetch::kToldMarked) {
+  if (how == Fetch::kTold) {
     SP_HIP(c, hipGetLastError());
-    if (how == Fetch::kToldMarked) SP_HIP(c, hipEventRecord(c->ev_ended, s));
+    SP_HIP(c, hipEventRecord(c->ev_ended, s));
     const sp_status st = wait_ended(c, s);
     if (st != SP_OK) return st;
   } else {
@@ -1578,7 +1579,7 @@ sp_status sp_schedule(sp_ctx* c, int32_t max_rounds, void* stream, int32_t* mode
       }
     }
     outputs_copied = want_outputs;
-    st = fetch_state(c, s, told ? Fetch::kToldMarked : Fetch::kMirrored);    // tells how far the device got and whether the queue ran dry
+    st = fetch_state(c, s, told ? Fetch::kTold : Fetch::kMirrored);    // tells how far the device got and whether the queue ran dry
     fetched = true;
     if (st != SP_OK) return st;
     if (persist && (int32_t)c->log.size() == before) {
