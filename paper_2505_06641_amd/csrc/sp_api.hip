@@ -1316,10 +1316,12 @@ sp_status wait_ended(sp_ctx* c, hipStream_t s) {
 // 48.0; eight calls 201 and 204 / 158 and 190 / 165 and 192; thirty-two 357 and 360 / 277 and 309 / 287 and 319.  (Some 27 us of what
 // several calls in a row leave out the program meets when it next waits, once, however many they were.)
 enum class Fetch { kCopied, kMirrored, kTold };
-// Requests up to which sp_schedule waits in that way.  In hipStreamSynchronize the runtime also puts away what it has kept of a
-// context's first launches, 20 to 30 us beside a window that runs longer than that, which a program that synchronises then waits for:
-// 65,536 requests, first pass with a wait behind it 226 (told: 243), repeated ones 195 (189); 16,384 requests 101 to 106 (104 to 107) and 87 (83).
-constexpr int kToldRequests = 16384;
+// Requests up to which sp_schedule waits in that way.  Behind longer windows a context's first pass is the slower one for a program that waits for
+// the stream behind it (the runtime then puts away there what it has kept of the first launches).  us, hipStreamSynchronize / told, first pass of a
+// context with a wait, repeated passes without and with one: 4,096 requests 187 / 184, 131.6 and 134.5 / 128.8 and 133.0; 16,384 110 / 109,
+// 79.1 and 81.9 / 76.3 and 79.6; 24,000 (64 batches) 176 / 176, 119.4 and 122.3 / 115.4 and 119.7; 32,000 (bfloat16) first pass 218 / 224;
+// 65,536 231 / 247, 177.5 and 180.2 / 175.1 and 178.1.
+constexpr int kToldRequests = 24576;
 
 sp_status fetch_state(sp_ctx* c, hipStream_t s, Fetch how) {
   if (how == Fetch::kTold) {
