@@ -1324,9 +1324,8 @@ enum class Fetch { kCopied, kMirrored, kTold };
 constexpr int kToldRequests = 24576;
 
 sp_status fetch_state(sp_ctx* c, hipStream_t s, Fetch how) {
-  if (how == Fetch::kTold) {
-    SP_HIP(c, hipGetLastError());
-    SP_HIP(c, hipEventRecord(c->ev_ended, s));
+  // (an error of this launch, or of the program before it, is reported behind the wait, whatever runs having ended)
+  if (how == Fetch::kTold && hipPeekAtLastError() == hipSuccess && hipEventRecord(c->ev_ended, s) == hipSuccess) {
     const sp_status st = wait_ended(c, s);
     if (st != SP_OK) return st;
   } else {

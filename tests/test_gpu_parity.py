@@ -2084,3 +2084,26 @@ def test_ordering_of_equal_keys_finds_its_range(gpu):
         ctx.close()
         took[shape] = min(times)
     assert took["equal"] < 4 * took["spread"], took
+
+
+@pytest.mark.parametrize("call", ["round", "schedule"])
+def test_a_call_that_meets_an_error_of_the_program_still_waits(gpu, call):
+    """An earlier HIP call of the program has failed: a call reports that as it did before, and what it has launched has ended by then."""
+    import ctypes
+    torch, binding = gpu
+    n = 20000
+    w = wl.tiny(seed=9300, n=n, classes=(1000,), models=(2,), max_batch=4, feat_dim=256)
+    ctx = binding.Context(w.profile, n)
+    data = binding.to_device(w.requests)
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    torch.cuda.synchronize()
+    for _ in range(20):                                 # (more than a millisecond)
+        ctx.sp_score(*data)
+    assert hip.hipSetDevice(4096) != 0
+    with pytest.raises(binding.SneakPeekError) as e:
+        ctx.sp_greedy_round() if call == "round" else ctx.sp_schedule(1)
+    assert e.value.status == binding.SP_EDEVICE
+    assert torch.cuda.current_stream().query()
+    ctx.sp_score(*data)
+    assert ctx.sp_greedy_round()[0] == binding.SP_OK
+    ctx.close()
