@@ -106,10 +106,11 @@ __device__ __forceinline__ int pcid_batch(uint32_t c) { return (int)(c & 0xffu) 
 static_assert(kMaxModels <= 16 && kMaxBatch <= 256, "fields of a candidate id (groups: at most 65,536)");
 
 // A wait has run out.  The commit workgroup mirrors the state for the host when its own work ends, which may be before another
-// workgroup gives up: each of them tells the host itself.
+// workgroup gives up: each of them tells the host itself, past its die's L2 and before it counts itself among those that have left
+// (persist_leave), so that the host finds it when it is told that all have ended.
 __device__ __forceinline__ void raise_lost(State* st, const Persist& ps) {
   atomicOr(&st->err, kErrSync);
-  *ps.lost_host = 1;
+  __hip_atomic_store(ps.lost_host, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __device__ __forceinline__ void copy_output(int i, const Window& w, const Outputs& out) {
@@ -339,7 +340,7 @@ __device__ __forceinline__ int wave_window(const Window& w, int kind, int head, 
 }
 
 // A workgroup's work has ended: the last one of the grid tells the host.  The commit workgroup alone writes through its L2, which it
-// writes back first.
+// writes back first; what the others leave (raise_lost, first live positions) is written past it.
 __device__ __forceinline__ void persist_leave(const Window& w, const Persist& ps, bool committed = false) {
   if (w.ended_host == nullptr) return;
   stores_arrived();
