@@ -362,6 +362,8 @@ sp_status sp_debug_set_generation(sp_ctx* ctx, uint32_t generation);
  * that a test can take that path with every kernel still ending normally; 0 restores the default (2^20).  While a
  * bound is set, no round runs in one workgroup (see sp_rounds_in_one_workgroup): rounds that are calls of their own take two
  * kernels, sp_schedule with max_rounds 1 the resident workgroups that the bound is for.
+ * Requests of up to 31 applications are grouped by workgroups that hand each other counts and count for themselves what does not
+ * come: while a bound is set, they wait for none (polls 1), or every other one hands out nothing (polls > 1).
  * SP_EINVAL: ctx NULL or polls < 0.
  */
 sp_status sp_debug_set_spin_limit(sp_ctx* ctx, int32_t polls);

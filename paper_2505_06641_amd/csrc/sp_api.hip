@@ -1135,7 +1135,8 @@ int32_t* group_requests(sp_ctx* c, hipStream_t s, int n, const int32_t* app_dev,
       return c->bufV[0];
     }
     if (tiles <= kGroupDirect && A <= kGroupOneApps) {
-      const GroupWords gw{c->group_words, c->group_launch, c->spin_limit == kSpinLimit ? kGroupSpins : 0};
+      // (a bound on the polls of resident workgroups: no counts are waited for, or those of every other tile do not come)
+      const GroupWords gw{c->group_words, c->group_launch, c->spin_limit == 1 ? 0 : kGroupSpins, c->spin_limit == kSpinLimit ? 0 : 1};
 #define SP_GROUP(ITEMS)                                                                                                 \
       hipLaunchKernelGGL((k_group_place<ITEMS, -1>), place_grid, dim3(kGroupThreads), 0, s, n, A, nbits, app_dev, deadline_ms_dev, \
                          weight_dev, (const uint32_t*)nullptr, tiles, c->bufV[0], c->dw_g[0], seg_args, w, w.st, gw)

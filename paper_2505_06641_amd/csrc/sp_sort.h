@@ -677,9 +677,11 @@ __device__ __forceinline__ void group_sums_self(const int32_t* __restrict__ app,
 // waits for theirs, which spares a launch.  A word carries two counts and the number of the launch, which the launch before has left in
 // memory (not an argument: a recorded launch may be played again), and is valid exactly when that number is the launch's.  A wait that
 // runs out (the grid did not fit on the device beside other work) is no error: what has not come is counted from the ids.  Kernels, 65,536
-// requests: 3.4 to 4.6 + 5.1 to 6.2 us -> 7.4 to 8.9.  us per scoring call (16 features), two launches / one: eight applications of 4,000
-// requests 21.3 / 19.3, 32,768 25.9 / 23.6, 65,536 28.7 / 26.8, 100,000 36.1 / 34.9, 200,000 62.2 / 60.3; thirty-one of 65,536 27.8 / 26.4,
-// 262,144 67.9 / 65.8; one of 65,536 38.7 / 37.9, seven of 131,072 (128 tiles, where the polls are most) 49.7 / 49.8.
+// requests: 3.4 to 4.6 + 5.1 to 6.2 us -> 7.4 to 8.9.  us per scoring call (16 features, both ways in turn), two launches / one: eight applications
+// of 64 requests 16.0 / 15.8, 500 16.9 / 16.4, 2,000 21.7 / 20.2, 8,000 24.4 / 23.1, 33,000 31.2 / 30.0, 65,536 35.6 / 34.2, 131,072 49.0 /
+// 48.1, 262,144 75.7 / 74.1; thirty-one of 500 17.0 / 16.7, 4,000 21.8 / 21.0, 65,536 36.0 / 34.1, 262,144 67.6 / 66.0; one of 33,000 37.0 /
+// 35.7, 262,144 88.6 / 87.4; seven of 131,072 (128 tiles, where the polls are most) 48.6 / 48.4.  Where no count comes at all, behind some 30
+// us of polls: of 65,536 40 to 49, 262,144 127 to 167.
 constexpr int kGroupOneApps = 31;                      // (sixteen words a tile; a workgroup reads all tiles' words)
 constexpr int kGroupWords = (kGroupOneApps + 2) / 2;
 constexpr int kGroupSpins = 64;                        // polls of about half a microsecond
@@ -687,12 +689,13 @@ struct GroupWords {
   unsigned long long* words;                           // [kGroupDirect][kGroupWords]
   uint32_t* launch;                                    // workgroups that have their sums; launches so far
   int32_t spins;
+  int32_t silent;                                      // tiles whose number has these bits hand out nothing (0 but in a test)
 };
 
 // A tile's counts (of up to 2,048 requests) to the other workgroups.
 __device__ __forceinline__ void publish_counts(const GroupWords& gw, uint32_t launch, int tile, int A, const uint32_t* count) {
   const int tid = threadIdx.x;
-  if (2 * tid > A) return;
+  if (2 * tid > A || (tile & gw.silent) != 0) return;
   const uint32_t two = count[2 * tid] | (2 * tid + 1 <= A ? count[2 * tid + 1] << 16 : 0u);
   __hip_atomic_store(gw.words + tile * kGroupWords + tid, ((unsigned long long)(launch + 1u) << 32) | two, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -707,10 +710,14 @@ __device__ __forceinline__ void group_sums_handed(const GroupWords& gw, uint32_t
   const int nw = 1 << bits, parts = kGroupThreads >> bits, word = tid & (nw - 1);
   constexpr int kMost = kGroupDirect * kGroupWords / kGroupThreads;
   static_assert((kGroupWords & (kGroupWords - 1)) == 0 && kGroupWords <= 16 && kGroupDirect * kGroupWords % kGroupThreads == 0, "shares of a thread");
+  __shared__ uint32_t lost[kGroupDirect];              // the words of a tile that have not come, a bit each
+  __shared__ int any_lost;
+  if (tid < kGroupDirect) lost[tid] = 0u;
+  if (tid == 0) any_lost = 0;
   unsigned long long v[kMost];
-  bool there = false;
-  for (int spin = 0; spin < gw.spins && !there; ++spin) {
-    there = true;
+  uint32_t wanted = 0u;                                // of this thread's words, a bit each
+  for (int spin = 0; spin < gw.spins; ++spin) {
+    wanted = 0u;
 #pragma unroll
     for (int k = 0; k < kMost; ++k) {
       const int q = (tid >> bits) + k * parts;
@@ -719,26 +726,17 @@ __device__ __forceinline__ void group_sums_handed(const GroupWords& gw, uint32_t
 #pragma unroll
     for (int k = 0; k < kMost; ++k) {
       const int q = (tid >> bits) + k * parts;
-      there = there && (q >= n_tiles || word >= n_words || (uint32_t)(v[k] >> 32) == launch + 1u);
+      if (q < n_tiles && word < n_words && (uint32_t)(v[k] >> 32) != launch + 1u) wanted |= 1u << k;
     }
+    if (wanted == 0u) break;
   }
+  if (gw.spins == 0) wanted = ~0u;                     // (a test's: nothing has been read)
   uint32_t sum[2][2] = {{0u, 0u}, {0u, 0u}};           // before, total; even and odd application
 #pragma unroll
   for (int k = 0; k < kMost; ++k) {
     const int q = (tid >> bits) + k * parts;
-    if (q >= n_tiles || word >= n_words) continue;
-    uint32_t c[2];
-    if (there) {
-      c[0] = (uint32_t)v[k] & 0xffffu;
-      c[1] = (uint32_t)v[k] >> 16;
-    } else {
-      c[0] = c[1] = 0u;
-      for (int i = q * tile_size; i < min((q + 1) * tile_size, n); ++i) {
-        const uint32_t key = min((uint32_t)app[i], (uint32_t)A);
-        c[0] += key == (uint32_t)(2 * word) ? 1u : 0u;
-        c[1] += key == (uint32_t)(2 * word + 1) ? 1u : 0u;
-      }
-    }
+    if (q >= n_tiles || word >= n_words || (wanted >> k & 1u) != 0u) continue;
+    const uint32_t c[2] = {(uint32_t)v[k] & 0xffffu, (uint32_t)(v[k] >> 16) & 0xffffu};
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       sum[1][h] += c[h];
@@ -769,10 +767,44 @@ __device__ __forceinline__ void group_sums_handed(const GroupWords& gw, uint32_t
     before[tid] = sb;
     total[tid] = stt;
   }
+  if (wanted != 0u) {
+#pragma unroll
+    for (int k = 0; k < kMost; ++k) {
+      const int q = (tid >> bits) + k * parts;
+      if (q < n_tiles && word < n_words && (wanted >> k & 1u) != 0u) {
+        atomicOr(&lost[q], 1u << word);
+        any_lost = 1;
+      }
+    }
+  }
   // (all words read: the last workgroup to come here makes the launch's number the next one's)
   if (tid == 0 && atomicAdd(gw.launch, 1u) == (uint32_t)n_tiles) {
     __hip_atomic_store(gw.launch, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(gw.launch + 1, launch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (any_lost == 0) return;
+  // what has not come, from the ids: a wavefront takes every kGroupWaves-th tile, sixteen ids a lane at a time
+  constexpr int kAtATime = 16;
+  for (int q = wave; q < n_tiles; q += kGroupWaves) {
+    const uint32_t words = lost[q];
+    if (words == 0u) continue;                         // (uniform in the wavefront)
+    const int end = min((q + 1) * tile_size, n);
+    for (int i0 = q * tile_size + lane; i0 - lane < end; i0 += kAtATime * kWave) {
+      uint32_t id[kAtATime];
+#pragma unroll
+      for (int e = 0; e < kAtATime; ++e) id[e] = (uint32_t)app[min(i0 + e * kWave, n - 1)];
+#pragma unroll
+      for (int e = 0; e < kAtATime; ++e) {
+        const uint32_t key = min(id[e], (uint32_t)A);
+        // (those of the first lane's application at once: with few applications most are)
+        const bool in = i0 + e * kWave < end && (words >> (key >> 1) & 1u) != 0u, with_first = key == (uint32_t)__builtin_amdgcn_readfirstlane((int)key);
+        const uint32_t firsts = (uint32_t)__popcll(__ballot(in && with_first)), add = !with_first ? (in ? 1u : 0u) : lane == 0 ? firsts : 0u;
+        if (add == 0u) continue;
+        atomicAdd(&total[key], add);
+        if (q < tile) atomicAdd(&before[key], add);
+      }
+    }
   }
   __syncthreads();
 }
