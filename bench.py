@@ -315,23 +315,32 @@ def main():
         gbs_ = nbytes / (ms * 1e-3) / 1e9 if ms > 0 else None
         return {"name": name, "algorithmic_bytes": nbytes, "ms": ms, "gbs": gbs_,
                 "frac_of_hbm_peak": gbs_ / PEAK_HBM_GBS if gbs_ else None, "what": note}
-    # windows of up to 262,144 requests: runs of 1,024 sorted in LDS, then merged (up to sixteen runs a time); the last launch
-    # is counted as finish_order.  Longer ones: digit totals and four radix passes, then a gather.
-    launches = 1 + (0 if n <= 1024 else 1 if n <= 16384 else 2)
-    merged = n <= 262144
-    order_b = 16 * (launches - 1) if merged else 68
-    order_note = (f"{launches - 1} of the {launches} launches that sort and merge runs: (key, position) read (8 B) and written (8 B)" if merged
+    # Ordered in one launch, which is counted as finish_order: windows of up to 1,024 requests, and by priority keys of up to 65,536 of one or two
+    # applications and 106,496 of more.  Else up to 262,144 requests: runs of 1,024 sorted in LDS, then merged (up to sixteen runs a time), the last
+    # launch counted as finish_order.  Longer ones: digit totals and four radix passes, then a gather.
+    edf = policy is not None and policy.order == wl.ORDER_EDF
+    alone = n <= 1024 or (not edf and n <= (65536 if A <= 2 else 106496))
+    launches = 1 if alone else 2 if n <= 16384 else 3
+    order_b = 16 * (launches - 1) if n <= 262144 else 68
+    order_note = ("nothing: one launch orders and finishes" if alone else
+                  f"{launches - 1} of the {launches} launches that sort and merge runs: (key, position) read (8 B) and written (8 B)" if n <= 262144
                   else "digit totals of the keys (4 B) + four radix passes (8 B read, 8 B written each)")
+    finish_b = 53 if alone else 57
+    finish_note = ("key and 16-byte record" if alone else "position, 16-byte record and key") + \
+        " read; id, deadline, weight, key, pending flag written; outputs reset"
+    # grouped in one launch: up to 32,768 requests of up to seven applications, 262,144 of up to thirty-one
+    group_b, group_note = (24, "every request") if n <= 262144 and A <= 31 or n <= 32768 and A <= 7 else \
+        (28, "application counts per tile (4 B read per request), then every request")
     out["kernels"] = [
-        stream("group_by_app", 28 * N, g_ms, "application counts per tile (4 B read per request), then every request placed (id 4 B, deadline and weight 8 B read; position 4 B and deadline, weight 8 B written)"),
+        stream("group_by_app", group_b * N, g_ms, group_note + " placed (id 4 B, deadline and weight 8 B read; position 4 B and deadline, weight 8 B written)"),
         stream("order_by_key_passes", order_b * N, o_ms - f_ms, order_note),
-        stream("finish_order", 57 * N, f_ms, "position, 16-byte record and key read; id, deadline, weight, key, pending flag written; outputs reset"),
+        stream("finish_order", finish_b * N, f_ms, finish_note),
         stream("copy_outputs", 32 * N, c_ms, "four per-request outputs read and written"),
     ]
     out["hbm_copy_measured_gbs"] = binding.sp_debug_copy_rate(1 << 28)
     # the whole step against the scoring kernel's ceilings: its algorithmic flops and the algorithmic bytes of
     # every stage over the step's wall time (the rounds work on LDS-resident windows: no bytes counted for them)
-    step_bytes = k_bytes + (28 + order_b + 57 + 32) * N
+    step_bytes = k_bytes + (group_b + order_b + finish_b + 32) * N
     out["whole_step_roofline"] = {"algorithmic_flops": flops, "algorithmic_bytes": step_bytes,
                                   "tflops": flops / (ms_per_step * 1e-3) / 1e12,
                                   "frac_of_scoring_kernel_ceiling": flops / (ms_per_step * 1e-3) / 1e12 / peak_c,

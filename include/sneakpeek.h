@@ -137,7 +137,8 @@ typedef struct {
   int32_t n_rounds_timed;  /* rounds with an individual time (see sp_get_round_times)          */
   float finish_order_ms;   /* within order_ms: its last kernel, which gathers id, deadline, weight
                               and key per service position (windows of up to 262,144 requests:
-                              and sorts or merges)                                            */
+                              and sorts or merges; where one launch orders a window, which is
+                              most of up to 106,496 requests, it is the whole ordering)       */
   float copy_outputs_ms;   /* the kernel that copies the four per-request outputs to the
                               caller's arrays (first chunk of the last sp_schedule call; while
                               no stage is timed, short windows' outputs are written by the
@@ -188,9 +189,11 @@ sp_status sp_score(sp_ctx* ctx, int32_t n, const void* x_dev, const int32_t* app
  * below 1; for every application the first min(B, n_live) live requests in
  * service order form the candidate window; every (a, m, b) is scored and the
  * best one is committed (exact ties: smallest (a, m, b)); the clock advances
- * to its completion time.  Waits for the stream.  *out_host receives the
- * decision; req_ids_out_dev (NULL or [B]) the ids of its members in service
- * order.  Returns SP_DONE (and leaves *out_host untouched) when no request is
+ * to its completion time.  Waits until the round and all that was on the
+ * stream before it has ended, its results in memory for the host and for every
+ * stream (hipStreamQuery may take the stream for busy some microseconds
+ * longer).  *out_host receives the decision; req_ids_out_dev (NULL or [B]) the
+ * ids of its members in service order.  Returns SP_DONE (and leaves *out_host untouched) when no request is
  * live, SP_ESTATE before the first sp_score.                                   */
 sp_status sp_greedy_round(sp_ctx* ctx, void* stream, sp_decision* out_host, int32_t* req_ids_out_dev);
 
@@ -210,7 +213,8 @@ sp_status sp_greedy_round_static(sp_ctx* ctx, void* stream, sp_decision* out_hos
 
 /* Greedy rounds until nothing is live, or until max_rounds more rounds have
  * been committed (max_rounds <= 0: no limit).  Rounds run back to back on the
- * device; the call waits for the stream before returning.
+ * device; the call returns when they and all that was on the stream before
+ * them have ended (as sp_greedy_round does).
  *   model_out_dev / round_out_dev / order_out_dev / util_out_dev: each NULL
  *     or [n]; variant id (-1 = not served), round id (-1), global execution
  *     order starting at 1 (0 = not served, as s_ij = 0 in Sec. 3.1), utility.
