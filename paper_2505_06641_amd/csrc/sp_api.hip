@@ -1310,12 +1310,14 @@ sp_status wait_ended(sp_ctx* c, hipStream_t s) {
 }
 
 // Where the window's state comes from: copied behind what is on the stream, or written into the pinned copy by a round kernel's commits;
-// kTold: by the last launch on the stream, which tells the host.  An event goes behind that launch while it runs.  The runtime would do that
-// itself when the program waits for the stream next, and the program for it; it costs a microsecond and a half of the next window where the
-// program does not wait.  us, without and with a wait for the stream behind it, hipStreamSynchronize / told without an event / with one: window of 256
-// requests 31.8 and 34.6 / 28.9 and 39.4 / 28.7 and 31.9; sp_score and one call of sp_greedy_round 49.9 and 52.6 / 45.4 and 56.4 / 45.3 and
-// 48.0; eight calls 201 and 204 / 158 and 190 / 165 and 192; thirty-two 357 and 360 / 277 and 309 / 287 and 319.  (Some 27 us of what
-// several calls in a row leave out the program meets when it next waits, once, however many they were.)
+// kTold: by the last launch on the stream, which tells the host.  An event goes behind that launch while it runs: the runtime would do that
+// itself when the program waits for the stream next, and the program for it.  us, hipStreamSynchronize / told without an event / with one:
+// sp_score and one call of sp_greedy_round 47.5 / 43.0 / 42.9, three 86.9 / 72.0 / 71.9, eight 194 / 156 / 162; where the program waits for the
+// stream behind the last call 50.7 / 54.0 / 46.6, 90.6 / 82.1 / 93.4, 196 / 186 / 187; behind every call (three) 97.1 / 106.8 / 84.5, (eight) 218 /
+// 243 / 186; where it copies each call's ids to the host, eight 312 / 277 / 284.  A window of 256 requests 31.8 / 28.9 / 28.7, with a wait behind it
+// 34.6 / 39.4 / 31.9.  (Of what three and more calls in a row save, a program that then waits once meets some 25 us there, however many they
+// were: the runtime's wait takes another way beyond eight launches and events.  hipStreamSynchronize before there are that many makes eight
+// calls with one wait 170 and costs 14 to 30 us wherever the program waits in another way.)
 enum class Fetch { kCopied, kMirrored, kTold };
 // Requests up to which sp_schedule waits in that way.  Behind longer windows a context's first pass is the slower one for a program that waits for
 // the stream behind it (the runtime then puts away there what it has kept of the first launches).  us, hipStreamSynchronize / told, first pass of a
