@@ -1233,11 +1233,9 @@ const uint32_t* order_requests(sp_ctx* c, hipStream_t s, int n, uint32_t* sortke
     const dim3 grid((n / kRanks + A + kXcds - 1) / kXcds * kXcds);
     stage_event();
     if (split)
-      hipLaunchKernelGGL(k_order<true>, grid, dim3(kRankThreads), 0, s, plan, (const uint32_t*)sortkey, (const int32_t*)w.sub_g,
-                         c->tb.n_classes, c->bufL[0], n, w);
+      hipLaunchKernelGGL(k_order<true>, grid, dim3(kRankThreads), 0, s, plan, (const uint32_t*)sortkey, (const int32_t*)w.sub_g, c->bufL[0], n, w);
     else
-      hipLaunchKernelGGL(k_order<false>, grid, dim3(kRankThreads), 0, s, plan, (const uint32_t*)sortkey, (const int32_t*)nullptr,
-                         (const int32_t*)nullptr, (uint32_t*)nullptr, n, w);
+      hipLaunchKernelGGL(k_order<false>, grid, dim3(kRankThreads), 0, s, plan, (const uint32_t*)sortkey, (const int32_t*)nullptr, (uint32_t*)nullptr, n, w);
     return c->bufL[0];
   }
   const int grid = (n / kRun + A + kXcds - 1) / kXcds * kXcds;

@@ -52,15 +52,19 @@ __device__ __forceinline__ int ranked_pos(Ranked e) { return (int)((uint32_t)e &
 __device__ __forceinline__ uint32_t ranked_label(Ranked e) { return (uint32_t)(e >> (32 + kRankPosBits)); }
 
 // What a key is counted under: a number of bins in floating point, rounded on the way, which keeps the order; what lies outside goes to
-// the ends.  With subgroups the labels, and inside each the keys; while there are bins for all labels, none has requests of two.
+// the ends.  With subgroups the labels, and inside each the keys; while there are bins for all labels, none has requests of two.  The
+// labels are the sample's.  Requests of greater ones, which it may have missed, have bins behind all of its labels' (at least the last one, and
+// there whatever their labels are).
 template <bool SPLIT>
 struct RankBins {
-  uint32_t least;
+  uint32_t least, label_high;
   float scale, per_label, first, finer;         // (then bins from `first` on, `finer` of them for one)
-  __device__ __forceinline__ void over(uint32_t low, uint32_t high, uint32_t label_high) {
+  __device__ __forceinline__ void over(uint32_t low, uint32_t high, uint32_t top_label) {
     least = low;
-    const float labels = (float)(label_high + 1u);
-    per_label = labels > (float)kRankBins ? (float)kRankBins / labels : floorf((float)kRankBins / labels);
+    label_high = top_label;
+    constexpr float kMost = (float)(kRankBins - 1);
+    const float labels = (float)(top_label + 1u);
+    per_label = labels > kMost ? kMost / labels : floorf(kMost / labels);
     scale = (SPLIT ? per_label : (float)kRankBins) / ((float)(high - low) + 1.0f);
     first = 0.f;
     finer = 1.f;
@@ -71,6 +75,7 @@ struct RankBins {
     if constexpr (SPLIT) return fmaf((float)label, per_label, fminf(v, fmaxf(per_label - 0.001f, 0.f)));
     else return v;
   }
+  __device__ __forceinline__ bool beyond(uint32_t label) const { return SPLIT && label > label_high; }
   __device__ __forceinline__ uint32_t operator()(uint32_t label, uint32_t key) const { return whole(at(label, key)); }
   // (ends first: a number outside of what an integer holds has no integer)
   static __device__ __forceinline__ uint32_t whole(float v) { return (uint32_t)__builtin_amdgcn_fmed3f(v, 0.f, (float)(kRankBins - 1)); }
@@ -131,7 +136,7 @@ struct RankDivision {
 
 template <bool SPLIT>
 __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint32_t* __restrict__ keys, const int32_t* __restrict__ labels,
-                                                        const int32_t* __restrict__ n_classes, uint32_t* __restrict__ label_out, int n, Window w) {
+                                                        uint32_t* __restrict__ label_out, int n, Window w) {
   __shared__ __align__(16) uint32_t bins[kRankBins + 4];
   __shared__ uint32_t bin_low[kRankBins], bin_high[kRankBins];
   __shared__ __align__(16) Ranked held[kRankCap];
@@ -167,7 +172,6 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
   const uint32_t r0 = (uint32_t)(__builtin_amdgcn_readfirstlane(desc.y) - s0), r1 = min(r0 + (uint32_t)kRanks, (uint32_t)size);
   keys += s0;
   if (SPLIT) labels += s0;
-  const uint32_t most_labels = SPLIT ? (uint32_t)n_classes[__builtin_amdgcn_readfirstlane(desc.w)] : 0u;   // (0: of no class's subgroup)
   // Keys are read in pieces of 256, four neighbours a lane; positions past the end give the last request again.
   typedef uint32_t quad __attribute__((ext_vector_type(4), aligned(4)));
   struct Keys { uint32_t key[kRankItems], label[SPLIT ? kRankItems : 1]; };
@@ -221,7 +225,7 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
       }
   };
   rest();
-  uint32_t key_low, key_high, label_high = 0u;                  // the sample's keys; the application's labels
+  uint32_t key_low, key_high, label_high = 0u;                  // the sample's
   {
     uint32_t lo = 0u, hi = 0u, top = 0u;                        // lo: of the inverted keys
     each_sampled([&](uint32_t lb, uint32_t k, int, bool) {
@@ -240,15 +244,14 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
     __syncthreads();                                            // (also covers the cleared bins)
     key_low = ~wave_max_u32(lane < kRankWaves ? wave_low[lane] : 0u);
     key_high = wave_max_u32(lane < kRankWaves ? wave_high[lane] : 0u);
-    // (a request that is not sampled may have any label: one above the greatest would share a bin with that one's requests)
-    if (SPLIT) label_high = all_held ? wave_max_u32(lane < kRankWaves ? wave_label[lane] : 0u) : most_labels;
+    if (SPLIT) label_high = wave_max_u32(lane < kRankWaves ? wave_label[lane] : 0u);
   }
   RankBins<SPLIT> bin_of;
   bin_of.over(key_low, key_high, label_high);
   uint32_t b0 = 0u, b1 = kRankBins - 1u;                        // the range in bins, and
   uint32_t d0 = 0u, d1 = ~0u;                                   // (divided) in those of the second counting
   bool divided = false;
-  const bool divisible = !SPLIT || label_high < (uint32_t)kRankBins;     // (a bin has requests of one label)
+  const bool divisible = !SPLIT || label_high + 1u < (uint32_t)kRankBins;     // (a bin has requests of one label, or of none of the sample's)
   uint32_t cnt[4], beg[4];
   RankDivision div{bins, bin_low, bin_high, 1.0f / (float)size, 0};
   const auto prepare_division = [&] {
@@ -501,10 +504,14 @@ __global__ __launch_bounds__(kRankThreads) void k_order(SortPlan sp, const uint3
         if (tid + h * kRankThreads < count) to_division(bin_of.fine(own[h]), ranked_key(own[h]));
       __syncthreads();
       div.half = count > kRankBins ? 1 : 0;
-      uint32_t sub[kRankOwn];
+      uint32_t sub[kRankOwn] = {};
 #pragma unroll
       for (int h = 0; h < kRankOwn; ++h)
-        sub[h] = tid + h * kRankThreads < count ? div(bin_of.fine(own[h]), ranked_key(own[h]), ranked_pos(own[h])) : 0u;
+        if (tid + h * kRankThreads < count) {
+          const uint32_t b = bin_of.fine(own[h]);
+          // (a bin of labels beyond the sample's may have several of them, and is not divided by keys)
+          sub[h] = bin_of.beyond(ranked_label(own[h])) ? bins[b] >> div.half : div(b, ranked_key(own[h]), ranked_pos(own[h]));
+        }
       __syncthreads();
       clear_bins(bins);
       __syncthreads();

@@ -38,7 +38,7 @@ struct SortPlan {
   const int32_t* seg;          // [nseg+1] segment starts
   const int32_t* unit_start;   // [nseg+1] prefix of runs per segment
   int32_t nseg;
-  const int4* desc;            // per run or tile: (start of the segment, first element, end of the segment, segment); null = one segment
+  const int4* desc;            // per run or tile: (start of the segment, first element, end of the segment, 0); null = one segment
 };
 
 // mask of lanes whose 8-bit digit equals mine
@@ -164,9 +164,9 @@ __device__ __forceinline__ void write_descriptors(const SegArgs& g, bool in_turn
     }
     g.tile_desc[wg] = d;
   }
-  for (int u = tid; u < s_unit[g.A]; u += threads) {                // (start of the application, first element, end, application)
+  for (int u = tid; u < s_unit[g.A]; u += threads) {                // (start of the application, first element, end, 0)
     const int a = range_of(s_unit, g.A, u);
-    g.sort_desc[u] = make_int4(s_seg[a], s_seg[a] + (u - s_unit[a]) * g.unit, s_seg[a + 1], a);
+    g.sort_desc[u] = make_int4(s_seg[a], s_seg[a] + (u - s_unit[a]) * g.unit, s_seg[a + 1], 0);
   }
 }
 
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(256) void k_segments(SegArgs g, Window w) {
       const int c = app_at(k), cb = seg[c], ce = seg[c + 1], nt = tiles_of(c);
       const int sb = seg[k], se = seg[k + 1], nu = (se - sb + unit - 1) / unit;
       for (int t = 0; t < nt; ++t) g.tile_desc[workgroup_of(in_turn, ts + t, run_t[255])] = make_int4(c, cb + t * tile, ce, 0);
-      for (int u = 0; u < nu; ++u) g.sort_desc[us + u] = make_int4(sb, sb + u * unit, se, k);
+      for (int u = 0; u < nu; ++u) g.sort_desc[us + u] = make_int4(sb, sb + u * unit, se, 0);
       ts += nt;
       us += nu;
     }

@@ -2019,9 +2019,9 @@ def test_ordering_by_subgroup_in_one_launch(gpu, n, C, shape):
         assert np.array_equal(got[keep], want)
 
 
-def _rare_labels_window(n, C, rare, shape):
-    """One application whose requests' classes are set by hand: all but the `rare` greatest in turn, and one to three requests of each of
-    those, early, in the middle and late among the requests that the ordering does not sample."""
+def _rare_labels_window(n, C, rare, shape, many=False):
+    """One application whose requests' classes are set by hand: all but the `rare` greatest at random, and one to three requests of each of
+    those (many: 300), early, in the middle and late among the requests that the ordering does not sample."""
     rng = np.random.default_rng(n + C)
     w = wl.tiny(seed=8950 + C, n=n, classes=(C,), models=(1,), max_batch=2, feat_dim=16)
     w.profile.W1[0] = np.zeros((16, C), np.float32)
@@ -2030,7 +2030,7 @@ def _rare_labels_window(n, C, rare, shape):
     label = rng.integers(0, C - rare, n)
     free = np.setdiff1d(np.arange(n), _sampled_positions(n))
     for k in range(rare):
-        some = rng.choice(free, 1 + (C + k) % 3, replace=False)
+        some = rng.choice(free, 300 if many else 1 + (C + k) % 3, replace=False)
         label[some] = C - 1 - k
         free = np.setdiff1d(free, some)
     w.requests.x[:] = np.eye(16, dtype=np.float32)[label]
@@ -2047,9 +2047,14 @@ def _rare_labels_window(n, C, rare, shape):
 @pytest.mark.parametrize("n,C,rare", [(8700, 2, 1), (20000, 2, 1), (20000, 3, 1), (20000, 12, 2), (60000, 2, 1), (60000, 4, 1), (60000, 8, 1), (60000, 12, 2),
                                       (60000, 5, 3)])
 def test_ordering_by_subgroup_with_labels_that_are_not_sampled(gpu, n, C, rare, shape):
-    """The greatest subgroups consist of a few requests outside the ordering's sample.  Whole numbers, no tolerance."""
+    """The greatest subgroups consist of a few requests outside the ordering's sample, of 60,000 also of hundreds.  Whole numbers, no tolerance."""
+    for many in (False, True) if n == 60000 else (False,):
+        _check_rare_labels(gpu, n, C, rare, shape, many)
+
+
+def _check_rare_labels(gpu, n, C, rare, shape, many):
     torch, binding = gpu
-    w, label = _rare_labels_window(n, C, rare, shape)
+    w, label = _rare_labels_window(n, C, rare, shape, many)
     ctx = binding.Context(w.profile, n, policy=wl.Policy(split_groups=1))
     key = torch.zeros(n, device="cuda:0")
     order = torch.zeros(n, dtype=torch.int32, device="cuda:0")
